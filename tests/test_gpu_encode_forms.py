@@ -1,0 +1,80 @@
+"""Key encoding over the forms its kernels distinguish: every padded sub-vector length, few and
+many keys, near ties, magnitudes at which the fp16 terms of the ranking product overflow, vanish or become subnormal.
+Codes are compared bit for bit with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lk():
+    import paper_2601_10155_amd as pkg
+    pkg.load_library()
+    return pkg
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _keys_with_near_ties(rng, cb, B, N, dtype):
+    """Every other key's sub-vectors lie between two centroids, a little off the middle (by 0 to 1e-3 of their distance)."""
+    H, m, _, d_sub = cb.shape
+    keys = rng.standard_normal((B, H, N, m, d_sub)) * np.abs(cb).max()
+    for h in range(H):
+        for i in range(m):
+            a, c = rng.integers(0, 256, (2, B, N))
+            off = 0.5 + rng.choice([0.0, 1e-8, -1e-8, 1e-6, -1e-6, 1e-3], (B, N, 1))
+            near = cb[h, i][a] * off + cb[h, i][c] * (1.0 - off)
+            keys[:, h, 1::2, i] = near[:, 1::2]
+    return keys.reshape(B, H, N, m * d_sub).astype(dtype)
+
+
+# (d_k, m): sub-vectors of 1 to 72 coordinates, with and without an instance of their own
+_LENGTHS = [(8, 8), (64, 32), (24, 8), (16, 4), (80, 16), (48, 8), (64, 8), (80, 8), (96, 8), (64, 4), (96, 4), (112, 4),
+            (64, 2), (80, 2), (128, 2), (72, 1)]
+
+
+@pytest.mark.parametrize("d_k,m", _LENGTHS)
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+@pytest.mark.parametrize("B,N", [(3, 1), (5, 33), (2, 500)])   # under 64 keys per head; ragged blocks; several pairs of blocks
+def test_encode_every_sub_vector_length(lk, d_k, m, dtype, B, N):
+    rng = np.random.default_rng(100 * d_k + m + N)
+    cb = rng.standard_normal((2, m, 256, d_k // m)).astype(np.float32)
+    keys = _keys_with_near_ties(rng, cb, B, N, dtype)
+    ref = oracle.encode_keys(keys, cb)
+    got = lk.lookat_encode_keys(dev(keys), dev(cb)).cpu().numpy()
+    assert np.array_equal(got, ref), f"{(got != ref).sum()} of {ref.size} codes differ"
+
+
+@pytest.mark.parametrize("d_k,m", [(16, 4), (32, 4), (64, 4), (64, 2), (128, 2)])
+@pytest.mark.parametrize("dtype,book,ratio", [
+    ("float32", 1.0, 1.0), ("float32", 2.0 ** -70, 1.0), ("float32", 2.0 ** -45, 1.0), ("float32", 2.0 ** 50, 1.0),
+    ("float32", 2.0 ** 74, 1.0), ("float32", 1.0, 3e4), ("float32", 1.0, 1e-6), ("float32", 1.0, 200.0),
+    ("float16", 1.0, 1e-6), ("float16", 2.0 ** -20, 1.0), ("float16", 2.0 ** -20, 1e9), ("float16", 2.0 ** 14, 0.5)])
+def test_encode_magnitudes(lk, d_k, m, dtype, book, ratio):
+    """Codebook magnitude and keys' magnitude relative to it: scales beyond the filter's range, keys whose scaled value does
+    not fit fp16, keys that are subnormal in fp16 or drown in the codebook."""
+    rng = np.random.default_rng(d_k + m)
+    cb = (rng.standard_normal((2, m, 256, d_k // m)) * book).astype(np.float32)
+    cb[1] *= rng.choice([1.0, 1e-3, 1e-6], (m, 256, 1)).astype(np.float32)   # norms over many orders of magnitude
+    keys = (_keys_with_near_ties(rng, cb, 2, 150, np.float64) * ratio).astype(dtype)
+    ref = oracle.encode_keys(keys, cb)
+    got = lk.lookat_encode_keys(dev(keys), dev(cb)).cpu().numpy()
+    assert np.array_equal(got, ref), f"{(got != ref).sum()} of {ref.size} codes differ"
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+def test_encode_keys_that_are_not_finite(lk, bad, dtype):
+    rng = np.random.default_rng(3)
+    cb = rng.standard_normal((2, 4, 256, 16)).astype(np.float32)
+    keys = rng.standard_normal((2, 2, 100, 64)).astype(dtype)
+    keys[0, 0, 5, 7] = bad
+    keys[1, 1, 99, 63] = bad
+    ref = oracle.encode_keys(keys, cb)
+    assert np.array_equal(lk.lookat_encode_keys(dev(keys), dev(cb)).cpu().numpy(), ref)
