@@ -80,41 +80,6 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const KT *__restric
         codes[bh * code_stride_bh + n * m + i] = (uint8_t)best_c;
 }
 
-// Any d_sub: the key sub-vector is re-read from memory per centroid (slow, small shapes only).
-template <typename KT>
-__global__ __launch_bounds__(kEncThreads) void encode_generic_kernel(const KT *__restrict__ keys,
-                                                                     const float *__restrict__ codebooks,
-                                                                     uint8_t *__restrict__ codes,
-                                                                     int64_t code_stride_bh, int B, int H, int64_t N,
-                                                                     int d_k, int m)
-{
-    const int d_sub = d_k / m;
-    const int i = blockIdx.y;
-    const int h = blockIdx.z;
-    const int64_t r = (int64_t)blockIdx.x * kEncThreads + threadIdx.x;
-    if (r >= (int64_t)B * N)
-        return;
-    const int64_t b = r / N, n = r % N;
-    const int64_t bh = b * H + h;
-    const KT *src = keys + (bh * N + n) * d_k + (int64_t)i * d_sub;
-    const float *cb = codebooks + ((int64_t)h * m + i) * kCentroids * d_sub;
-    double best = 0.0;
-    int best_c = 0;
-    for (int c = 0; c < kCentroids; ++c) {
-        double acc = 0.0;
-        for (int j = 0; j < d_sub; ++j) {
-            double diff = widen<KT>(src[j]) - (double)cb[(int64_t)c * d_sub + j];
-            double sq = diff * diff;
-            acc = acc + sq;
-        }
-        if (c == 0 || acc < best) {
-            best = acc;
-            best_c = c;
-        }
-    }
-    codes[bh * code_stride_bh + n * m + i] = (uint8_t)best_c;
-}
-
 // ---- few keys per head (decode-time append) -------------------------------------------
 // With a handful of keys per head the thread-per-key kernel above leaves the chip empty and
 // each thread walks all 256 centroids serially.  Here the centroids are spread over the
@@ -122,6 +87,46 @@ __global__ __launch_bounds__(kEncThreads) void encode_generic_kernel(const KT *_
 // holds centroid c in registers as fp64, evaluates its distance to every key of the block
 // (same arithmetic, same order) and the block takes the argmin over (distance, index).
 constexpr int kEncFewKeys = 8;
+
+// Per key the minimum over the wavefront's 64 centroids (cross-lane moves on the vector ALU, the eight chains
+// interleaved), the lowest lane that holds it (the serial scan's choice among exact ties), and the same over the
+// block's wavefronts.
+__device__ __forceinline__ void encode_few_finish(const double (&dv)[kEncFewKeys], double (&dm)[kEncFewKeys],
+                                                  double (&red_d)[kEncFewKeys][kCentroids / kWave],
+                                                  int (&red_c)[kEncFewKeys][kCentroids / kWave], uint8_t *codes,
+                                                  int64_t code_stride_bh, int B, int H, int64_t N, int m, int i, int h,
+                                                  int64_t r0, int lane, int wave)
+{
+    dmin_wave<kEncFewKeys>(dm);
+#pragma unroll
+    for (int k = 0; k < kEncFewKeys; ++k) {
+        const uint64_t holders = __ballot(dv[k] == dm[k]);
+        if (lane == 0) {
+            red_d[k][wave] = dm[k];
+            red_c[k][wave] = wave * kWave + (int)__builtin_ctzll(holders);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kEncFewKeys) {
+        const int k = threadIdx.x;
+        const int64_t r = r0 + k;
+        if (r < (int64_t)B * N) {
+            // wavefronts hold ascending centroid ranges: strict '<' keeps the lowest index on ties
+            double bd = red_d[k][0];
+            int best = red_c[k][0];
+#pragma unroll
+            for (int w = 1; w < kCentroids / kWave; ++w) {
+                const double d = red_d[k][w];
+                const int cw = red_c[k][w];
+                const bool better = d < bd;
+                bd = better ? d : bd;
+                best = better ? cw : best;
+            }
+            const int64_t b = r / N, n = r % N;
+            codes[(b * H + h) * code_stride_bh + n * m + i] = (uint8_t)best;
+        }
+    }
+}
 
 template <typename KT, int DSUB>
 __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__restrict__ keys,
@@ -158,9 +163,7 @@ __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__rest
     }
     __syncthreads();
 
-    // Distances of centroid c to the block's keys, then per key the minimum over the wavefront's 64
-    // centroids (cross-lane moves on the vector ALU, the eight chains interleaved) and the lowest
-    // lane that holds it: the serial scan's choice among exact ties.
+    // Distances of centroid c to the block's keys.
     double dv[kEncFewKeys], dm[kEncFewKeys];
 #pragma unroll
     for (int k = 0; k < kEncFewKeys; ++k) {
@@ -174,35 +177,73 @@ __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__rest
         dv[k] = argmin_value(acc, c);
         dm[k] = dv[k];
     }
-    dmin_wave<kEncFewKeys>(dm);
-#pragma unroll
-    for (int k = 0; k < kEncFewKeys; ++k) {
-        const uint64_t holders = __ballot(dv[k] == dm[k]);
-        if (lane == 0) {
-            red_d[k][wave] = dm[k];
-            red_c[k][wave] = wave * kWave + (int)__builtin_ctzll(holders);
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < kEncFewKeys) {
-        const int k = threadIdx.x;
-        const int64_t r = r0 + k;
-        if (r < rows) {
-            // wavefronts hold ascending centroid ranges: strict '<' keeps the lowest index on ties
-            double bd = red_d[k][0];
-            int best = red_c[k][0];
-#pragma unroll
-            for (int w = 1; w < kCentroids / kWave; ++w) {
-                const double d = red_d[k][w];
-                const int cw = red_c[k][w];
-                const bool better = d < bd;
-                bd = better ? d : bd;
-                best = better ? cw : best;
+    encode_few_finish(dv, dm, red_d, red_c, codes, code_stride_bh, B, H, N, m, i, h, r0, lane, wave);
+}
+
+// Any sub-vector length: the same with the centroid's coordinates read as they are needed (each serves the block's
+// eight keys) instead of kept in registers.  The keys' sub-vectors sit in dynamic LDS.
+template <typename KT>
+__global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__restrict__ keys,
+                                                                    const float *__restrict__ codebooks,
+                                                                    uint8_t *__restrict__ codes, int64_t code_stride_bh,
+                                                                    int B, int H, int64_t N, int d_k, int m)
+{
+    extern __shared__ __align__(16) double xs[];   // [d_sub][kEncFewKeys]
+    __shared__ double red_d[kEncFewKeys][kCentroids / kWave];
+    __shared__ int red_c[kEncFewKeys][kCentroids / kWave];
+    const int d_sub = d_k / m;
+    const int i = blockIdx.y;
+    const int h = blockIdx.z;
+    const int c = threadIdx.x;
+    const int lane = c & (kWave - 1), wave = c / kWave;
+    const int64_t rows = (int64_t)B * N;
+    const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * d_sub;
+    for (int64_t r0 = (int64_t)blockIdx.x * kEncFewKeys; r0 < rows; r0 += (int64_t)gridDim.x * kEncFewKeys) {
+        for (int e = c; e < kEncFewKeys * d_sub; e += kCentroids) {
+            const int k = e / d_sub, j = e % d_sub;
+            const int64_t r = r0 + k;
+            double v = 0.0;
+            if (r < rows) {
+                const int64_t b = r / N, n = r % N;
+                v = widen<KT>(keys[((b * H + h) * N + n) * d_k + (int64_t)i * d_sub + j]);
             }
-            const int64_t b = r / N, n = r % N;
-            codes[(b * H + h) * code_stride_bh + n * m + i] = (uint8_t)best;
+            xs[j * kEncFewKeys + k] = v;
         }
+        __syncthreads();
+        double dv[kEncFewKeys], dm[kEncFewKeys];
+#pragma unroll
+        for (int k = 0; k < kEncFewKeys; ++k)
+            dv[k] = 0.0;
+#pragma unroll 4
+        for (int j = 0; j < d_sub; ++j) {
+            const double y = (double)src[j];
+#pragma unroll
+            for (int k = 0; k < kEncFewKeys; ++k) {
+                double diff = xs[j * kEncFewKeys + k] - y;
+                double sq = diff * diff;
+                dv[k] = dv[k] + sq;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kEncFewKeys; ++k) {
+            dv[k] = argmin_value(dv[k], c);
+            dm[k] = dv[k];
+        }
+        encode_few_finish(dv, dm, red_d, red_c, codes, code_stride_bh, B, H, N, m, i, h, r0, lane, wave);
+        __syncthreads();   // the next keys overwrite the staged ones
     }
+}
+
+// (also the exact scan of sub-vector lengths without an encode_kernel instance, however many keys)
+template <typename KT>
+static void launch_encode_few_any(const lookat_shape *s, int64_t N, const void *keys, const float *codebooks,
+                                  uint8_t *codes, int64_t code_stride_bh, hipStream_t st)
+{
+    const int64_t rows = (int64_t)s->B * N;
+    const int64_t blocks = (rows + kEncFewKeys - 1) / kEncFewKeys;
+    const dim3 grid((unsigned)(blocks < 65536 ? blocks : 65536), (unsigned)s->m, (unsigned)s->H);
+    hipLaunchKernelGGL((encode_few_any_kernel<KT>), grid, dim3(kCentroids), (size_t)kEncFewKeys * (s->d_k / s->m) * sizeof(double),
+                       st, static_cast<const KT *>(keys), codebooks, codes, code_stride_bh, s->B, s->H, N, s->d_k, s->m);
 }
 
 template <typename KT>
@@ -227,7 +268,8 @@ static bool launch_encode_few(const lookat_shape *s, int64_t N, const void *keys
         LOOKAT_ENCF_CASE(16)
         LOOKAT_ENCF_CASE(32)
     default:
-        return false;   // no centroid-parallel variant for this sub-vector length
+        launch_encode_few_any<KT>(s, N, keys, codebooks, codes, code_stride_bh, st);
+        return true;
     }
 #undef LOOKAT_ENCF_CASE
 }
@@ -255,8 +297,7 @@ static void launch_encode(const lookat_shape *s, int64_t N, const void *keys, co
         LOOKAT_ENC_CASE(32)
         LOOKAT_ENC_CASE(64)
     default:
-        hipLaunchKernelGGL((encode_generic_kernel<KT>), grid, block, 0, st, k, codebooks, codes, code_stride_bh,
-                           s->B, s->H, N, s->d_k, s->m);
+        launch_encode_few_any<KT>(s, N, keys, codebooks, codes, code_stride_bh, st);
         break;
     }
 #undef LOOKAT_ENC_CASE
