@@ -1,6 +1,6 @@
-"""Key encoding over the forms its kernels distinguish: every padded sub-vector length, few and
+"""Key encoding and codebook learning over the forms their kernels distinguish: every padded sub-vector length, few and
 many keys, near ties, magnitudes at which the fp16 terms of the ranking product overflow, vanish or become subnormal.
-Codes are compared bit for bit with the oracle."""
+Codes and codebooks are compared bit for bit with the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -78,3 +78,17 @@ def test_encode_keys_that_are_not_finite(lk, bad, dtype):
     keys[1, 1, 99, 63] = bad
     ref = oracle.encode_keys(keys, cb)
     assert np.array_equal(lk.lookat_encode_keys(dev(keys), dev(cb)).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("d_k,m", [(24, 8), (32, 4), (80, 2), (128, 2)])   # single coordinates, 2, 10 and 16 pieces of four
+@pytest.mark.parametrize("Nc", [1, 63, 1025, 16384, 16448, 40000])         # one chunk of keys, exactly one, several
+def test_learn_matches_oracle(lk, d_k, m, Nc):
+    """Members are added in ascending key order across wavefronts, chunks and workgroups; one cluster holds half the keys."""
+    rng = np.random.default_rng(d_k + Nc)
+    cb = rng.standard_normal((1, m, 256, d_k // m)).astype(np.float32)
+    calib = rng.standard_normal((1, Nc, d_k)).astype(np.float32)
+    calib[0, ::2] = (cb[0, :, 17].reshape(-1) + 0.01 * calib[0, ::2]).astype(np.float32)
+    ref, _ = oracle.kmeans_step(calib, cb)
+    got, assign = lk.lookat_kmeans_step(dev(calib), dev(cb))
+    assert np.array_equal(assign.cpu().numpy(), oracle.encode_keys(calib[None], cb)[0])
+    assert np.array_equal(got.cpu().numpy(), ref)
