@@ -60,14 +60,27 @@ struct KeyCodes {
     }
 };
 
-// Runtime m: byte loads (used for m = 1 and m = 32 and any m without a vector load).
-__device__ __forceinline__ float score_bytes(const float *lut_s, __amdgpu_buffer_rsrc_t rc, uint32_t byte_off, int m)
-{
-    float s = 0.f;
-    for (int i = 0; i < m; ++i)
-        s += lut_s[i * kCentroids + __builtin_amdgcn_raw_buffer_load_b8(rc, byte_off + i, 0, 0)];
-    return s;
-}
+// Any m up to 32 without a vector load of its own: one byte per register, all of a key's bytes requested together.
+struct KeyCodesAny {
+    static constexpr int kMax = 32;
+    uint32_t c[kMax];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rc, uint32_t byte_off, int m)
+    {
+#pragma unroll
+        for (int i = 0; i < kMax; ++i)
+            if (i < m)
+                c[i] = __builtin_amdgcn_raw_buffer_load_b8(rc, byte_off + i, 0, 0);
+    }
+    __device__ __forceinline__ float score(const float *lut_s, int m) const
+    {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < kMax; ++i)
+            if (i < m)
+                s += lut_s[i * kCentroids + c[i]];
+        return s;
+    }
+};
 
 __device__ __forceinline__ void fma_row(float (&acc)[8], float p, const v4u &v)
 {
@@ -102,19 +115,30 @@ __device__ __forceinline__ void fma_rows(float (&acc)[8], float p, const v4u (&v
 }
 
 // Loads CH consecutive wave-wide row groups of the tile starting at key kb, from group g0.
+// Non-temporal (aux bit 1): the rows are read once and should not displace tables, codebooks and
+// queries from the caches; measured 11.94 -> 11.29 us per fused launch at batch 32 x 12 heads x 1024
+// keys (the same hint on the code loads as well: 11.39).
+constexpr int kStreamOnce = 2;
 template <int DK, int CH>
 __device__ __forceinline__ void load_rows(v4u (&v)[CH], __amdgpu_buffer_rsrc_t rv, uint32_t kb, int g0, int lane)
 {
     // lane (rowin, sub) reads 16 bytes at row*DK*2 + sub*16 = (row0*DK*2) + lane*16: 1 KB per load
     constexpr uint32_t kGroupBytes = kWave * 16;
-    // Non-temporal (aux bit 1): the rows are read once and should not displace tables, codebooks and
-    // queries from the caches; measured 11.94 -> 11.29 us per fused launch at batch 32 x 12 heads x 1024
-    // keys (the same hint on the code loads as well: 11.39).
-    constexpr int kStreamOnce = 2;
 #pragma unroll
     for (int j = 0; j < CH; ++j)
         v[j] = __builtin_amdgcn_raw_buffer_load_b128(rv, kb * (DK * 2) + (g0 + j) * kGroupBytes + lane * 16, 0,
                                                      kStreamOnce);
+}
+// The same for rows of row_bytes < 2 * DK: lane (rowin, sub) reads at lane_off = rowin * row_bytes + sub * 16 of a row group,
+// lanes past the end of a row repeat its last 16 bytes.
+template <int DK, int CH>
+__device__ __forceinline__ void load_rows_padded(v4u (&v)[CH], __amdgpu_buffer_rsrc_t rv, uint32_t kb, int g0, uint32_t lane_off,
+                                                 uint32_t row_bytes)
+{
+    constexpr uint32_t RPL = kWave / (DK / 8);
+#pragma unroll
+    for (int j = 0; j < CH; ++j)
+        v[j] = __builtin_amdgcn_raw_buffer_load_b128(rv, (kb + (g0 + j) * RPL) * row_bytes + lane_off, 0, kStreamOnce);
 }
 
 // Online-softmax state of one wavefront (base-2 exponent domain), for each of the G query heads
