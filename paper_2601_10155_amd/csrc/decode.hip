@@ -790,25 +790,53 @@ __global__ __launch_bounds__(kDecThreads) void decode_combine_kernel(const float
 
 static int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
 
-// Ranges per (b,h) when the caller leaves the choice to the library.  One range as long as the
-// (b,h) count alone fills the 256 compute units: the merge kernel is a second launch and costs more
-// than it buys on short contexts.  With fewer (b,h) pairs the sequence is cut so that about
-// `workgroups` workgroups exist, but never into ranges shorter than `min_range` keys.
-static int auto_splits(const lookat_shape *s, int64_t L, int workgroups = 256, int min_range = 2048)
+// Ranges per (b,h) when the caller leaves the choice to the library: the count with the least predicted time.
+// A workgroup streams its range at 62 KB/us while few share the memory, 62 - 0.11 n with n workgroups, and no faster than
+// its part of 7.4 n / (n + 16) MB/us.  Workgroups are dealt evenly to the 256 compute units, which get equal shares of the memory: if some
+// compute units hold one workgroup more than the rest, all finish the common part together and those few then stream
+// their last range alone, at no more than one compute unit's rate.  Each round of workgroups costs its table or codebook
+// (about 0.9 us at d_k = 128), and more than one range costs the merge launch (2.6 us).
+// Measured (us per fused call at 1 / 2 / 4 / 8 / 16 ranges; the count taken in brackets; before: one range from 129 (b,h)
+// pairs on, at most 256 workgroups and ranges of 2048 keys below):
+//   d_k = 128, m = 8:  12 (b,h) x 4096 keys 24.4 / 18.0 / 13.3 / 11.8 / 11.9 [8];  32 x 2048 16.8 / 14.1 / 12.6 / 13.1 / 13.7
+//   [4];  32 x 8192 43.4 / 28.7 / 20.0 / 18.6 / 20.4 [8];  128 x 4096 29.8 / 31.4 / 31.3 / 34.3 / 48.7 [1];  264 x 8192
+//   124 / 112 / 111 / 108 / 116 [8];  384 x 8192 137 / 139 / 145 / 149 / 161 [1]
+//   d_k = 64, m = 4:  264 x 4096 33.6 / 31.8 / 30.3 / 35.4 / 54.8 [4];  264 x 32768 235 / 201 / 182 / 173 / 169 [16]
+static int auto_splits(const lookat_shape *s, int64_t L)
 {
-    // Ungrouped kernels: one workgroup per compute unit and ranges of at least 2048 keys, measured
-    // at d_k = 128, m = 8 (us per call, 2/4/8/16 ranges): 32 (b,h) x 32768 keys: -/55/54/60;
-    // 64 x 32768: 103/95/99/107; 128 x 32768: 183/183/190/-; 32 x 8192: 25.8/18.7/20.4/24.6.
     const int64_t BH = (int64_t)s->B * s->H;
-    int64_t want = workgroups / BH;
-    const int64_t cap = (L + min_range - 1) / min_range;
-    if (want > cap)
-        want = cap;
-    if (want < 1)
-        want = 1;
-    if (want > 256)
-        want = 256;
-    return (int)want;
+    if (BH > 128 && BH <= 256)
+        return 1;                      // one workgroup per compute unit, and too few for a second round
+    const double bytes = (double)L * (2.0 * s->d_k + s->m);   // of one (b,h)
+    constexpr double kPeak = 7.4e6, kChip = kPeak * 256 / (256 + 16), kOne = 62e3, kStart = 7.0, kMerge = 2.6;
+    const double round_cost = 0.9 * s->d_k / 128.0;
+    static const int counts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
+    int best = 1;
+    double best_cost = 0.0;
+    for (int S : counts) {
+        if (S > 1 && (L < (int64_t)S * 256 || BH * S > 4096))
+            break;
+        const int64_t wgs = BH * S;
+        const int64_t rounds = (wgs + 255) / 256;
+        const double last = (double)(wgs - 256 * (rounds - 1));   // compute units that hold `rounds` workgroups
+        const double range = bytes / S;
+        const double share = kPeak / (last + 16.0);
+        const double rate = kOne - 110.0 * last < share ? kOne - 110.0 * last : share;
+        const double cost = kStart + (rounds - 1) * (range * 256.0 / kChip + round_cost) + range / rate + (S > 1 ? kMerge : 0.0);
+        if (S == 1 || cost < (best == 1 ? 0.97 * best_cost - 1.0 : best_cost)) {   // (a second launch has to be worth it)
+            best = S;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+// A caller that left the choice to the library and brings less workspace than that count needs gets one range where the
+// library once took one (it asked for no workspace there).
+static int fit_splits(const lookat_shape *s, int64_t L, int S, size_t workspace_bytes)
+{
+    const int64_t BH = (int64_t)s->B * s->H;
+    const bool one = BH > 128 || L <= 2048;
+    return one && (size_t)BH * S * (s->d_k + 2) * sizeof(float) > workspace_bytes ? 1 : S;
 }
 // Grouped queries: from group 4 on one 512-thread workgroup per compute unit (see gqa_waves), at
 // group 2 two 256-thread ones.  Measured at 8 x 32 query heads x 32768 keys, d_k = 128, m = 8 (us per
@@ -816,7 +844,12 @@ static int auto_splits(const lookat_shape *s, int64_t L, int workgroups = 256, i
 // group 2: 283 / 187 / 186 / 200.
 static int auto_splits_gqa(const lookat_shape *s, int group, int64_t L)
 {
-    return group >= 4 ? auto_splits(s, L, 256, 1024) : auto_splits(s, L, 512, 1024);
+    if (group == 1)
+        return auto_splits(s, L);
+    int64_t want = (group >= 4 ? 256 : 512) / ((int64_t)s->B * s->H);
+    const int64_t cap = (L + 1023) / 1024;      // ranges of at least 1024 keys
+    want = want < cap ? want : cap;
+    return (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
 }
 
 static bool tuned_dk(int d_k) { return d_k == 32 || d_k == 64 || d_k == 128 || d_k == 256; }
@@ -1239,7 +1272,7 @@ extern "C" int lookat_decode_step_split(const lookat_shape *shape, int64_t L, co
         return rc;
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
-    const int S = num_splits ? num_splits : (L > 0 ? auto_splits(shape, L) : 1);
+    const int S = num_splits ? num_splits : (L > 0 ? fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0) : 1);
     return decode_step_impl("lookat_decode_step_split", shape, 1, L, q, k_new, qk_dtype, codebooks, codes, code_stride_bh,
                             values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }
@@ -1264,8 +1297,7 @@ extern "C" int lookat_decode_step_gqa(const lookat_shape *shape, int32_t group, 
         return fail(LOOKAT_ERR_UNSUPPORTED, "lookat_decode_step_gqa handles group in {1,2,4,8}; got %d", group);
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
-    const int S = num_splits ? num_splits
-                             : (L > 0 ? (group == 1 ? auto_splits(shape, L) : auto_splits_gqa(shape, group, L)) : 1);
+    const int S = num_splits ? num_splits : (L > 0 ? auto_splits_gqa(shape, group, L) : 1);
     return decode_step_impl("lookat_decode_step_gqa", shape, group, L, q, k_new, qk_dtype, codebooks, codes,
                             code_stride_bh, values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }
@@ -1343,7 +1375,7 @@ static int attend_decode_impl(const lookat_shape *shape, int64_t L, const float 
     if ((L + 2048) * (int64_t)shape->d_k * 2 > 0xffffffffLL)
         return fail(LOOKAT_ERR_UNSUPPORTED, "L=%lld: one (b,h) value slab must stay below 4 GiB", (long long)L);
     const int64_t BH = (int64_t)shape->B * shape->H;
-    const int S = num_splits ? num_splits : auto_splits(shape, L);
+    const int S = num_splits ? num_splits : fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0);
     const size_t need = (S == 1) ? 0 : (size_t)BH * S * (shape->d_k + 2) * sizeof(float);
     if (need) {
         if (!workspace || workspace_bytes < need)
@@ -1477,6 +1509,11 @@ extern "C" int lookat_attend_decode_noalloc(const lookat_shape *shape, int64_t L
         return fail(LOOKAT_ERR_SHAPE, "L=%lld must be positive", (long long)L);
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
+    if (num_splits == 0) {   // the library's choice, as far as the scratch memory holds it
+        num_splits = auto_splits(shape, L);
+        while (num_splits > 1 && lookat_attend_decode_workspace_bytes(shape, L, num_splits) > (size_t)LOOKAT_NOALLOC_SCRATCH_BYTES)
+            num_splits /= 2;
+    }
     const size_t need = lookat_attend_decode_workspace_bytes(shape, L, num_splits);
     if (need > (size_t)LOOKAT_NOALLOC_SCRATCH_BYTES)
         return fail(LOOKAT_ERR_WORKSPACE,

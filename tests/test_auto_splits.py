@@ -1,0 +1,63 @@
+"""The library's choice of ranges per (b,h): what it promises about workspaces and callers that bring none."""
+import ctypes
+import math
+
+import numpy as np
+import pytest
+
+
+def _lk():
+    import paper_2601_10155_amd as pkg
+    pkg.load_library()
+    return pkg
+
+
+def test_auto_splits_invariants():
+    lk = _lk()
+    for d_k, m in ((32, 4), (64, 4), (96, 8), (128, 8), (256, 16)):
+        for BH in (1, 7, 12, 32, 64, 100, 128, 129, 200, 256, 257, 264, 300, 384, 520, 1000, 5000):
+            for L in (1, 64, 300, 1024, 2048, 3000, 8192, 32768):
+                S = lk.attend_decode_auto_splits(1, BH, d_k, m, L)
+                assert 1 <= S <= 256 and (S == 1 or L >= 256 * S) and BH * S <= max(BH, 4096)
+                if 128 < BH <= 256 or L < 512:
+                    assert S == 1
+                assert lk.attend_decode_workspace_bytes(1, BH, d_k, m, L) == (0 if S == 1 else BH * S * (d_k + 2) * 4)
+                assert lk.attend_decode_gqa_workspace_bytes(1, BH, 1, d_k, m, L) == lk.attend_decode_workspace_bytes(1, BH, d_k, m, L)
+    # long contexts of few pairs are cut, a little over one workgroup per compute unit too
+    assert lk.attend_decode_auto_splits(1, 32, 128, 8, 8192) == 8
+    assert lk.attend_decode_auto_splits(1, 264, 128, 8, 8192) > 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,L", [(1, 3, 2048), (11, 24, 4133)])
+def test_auto_splits_without_a_workspace(B, H, L):
+    """Where one range needed no workspace, a call that brings none is still taken (with one range), and the library's
+    choice gives the same result to the bar of the split count tests."""
+    import torch
+    from paper_2601_10155_amd.binding import _Shape, load_library
+    lk = _lk()
+    lib = load_library()
+    d_k, m = 128, 8
+    assert lk.attend_decode_auto_splits(B, H, d_k, m, L) > 1
+    g = torch.Generator(device="cuda").manual_seed(B * L)
+    lut = torch.randn((B, H, m, 256), generator=g, device="cuda")
+    codes = torch.randint(0, 256, (B, H, L, m), generator=g, device="cuda", dtype=torch.uint8)
+    v = torch.randn((B, H, L, d_k), generator=g, device="cuda").half()
+    scale = 1.0 / math.sqrt(d_k)
+    ref = lk.lookat_attend_decode(lut, codes, v, scale, num_splits=1)
+    assert float((lk.lookat_attend_decode(lut, codes, v, scale) - ref).abs().max()) <= 2e-5
+    out = torch.empty_like(ref)
+    shape = _Shape(B, H, d_k, m, 256)
+    rc = lib.lookat_attend_decode(ctypes.byref(shape), L, lut.data_ptr(), codes.data_ptr(), L * m, v.data_ptr(), L * d_k, scale, 0,
+                                  None, 0, out.data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and torch.equal(out, ref)
+    lk.lookat_attend_decode_noalloc(lut, codes, v, scale, out)
+    assert torch.equal(out, lk.lookat_attend_decode(lut, codes, v, scale))
+
+    cb = torch.randn((H, m, 256, d_k // m), generator=g, device="cuda")
+    q, k = torch.randn((B, H, d_k), generator=g, device="cuda"), torch.randn((B, H, d_k), generator=g, device="cuda")
+    one = lk.lookat_decode_step(q, k, cb, codes, v, scale)
+    assert float((lk.lookat_decode_step_split(q, k, cb, codes, v, scale) - one).abs().max()) <= 2e-5
+    rc = lib.lookat_decode_step_split(ctypes.byref(shape), L, q.data_ptr(), k.data_ptr(), 2, cb.data_ptr(), codes.data_ptr(), L * m,
+                                      v.data_ptr(), L * d_k, scale, 0, None, 0, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and torch.equal(out, one)
