@@ -373,6 +373,10 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
     // bytes apart), so that the pair reads the head's codebook once instead of twice.
     static_assert(NB == 1 || (NB == 2 && G == 1 && M % 2 == 0), "paired batch entries: ungrouped, even m");
     constexpr int DSUB = DK / M;
+    // A range without the new key skips the distances (they are half of the arithmetic; 32 (b,h) x 8003 keys in 8 ranges,
+    // d_k = 128, m = 8: 17.8 -> 14.2 us of kernel) -- except with 16 subspaces of 4, where the branch costs registers that
+    // the 128 do not hold.
+    constexpr bool kAlways = G == 1 && DK == 64 && M == 16;
     constexpr int MS = M / NB;            // subspaces this builder group covers
     // rows held at once: 64 registers; paired entries keep two entries' distances alive, so there short rows
     // (d_sub < 16) are taken 16 registers at a time and, at d_k = 128 (twice the tile registers), longer ones 32
@@ -428,15 +432,12 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
                         e = fmaf(uniform_elem<FT>(qg[nb], hq * DK + i * DSUB + j), frow[g][j], e);
                     lut_nb[(hq * M + i) * kCentroids + tid] = e;
                 }
-                if (G == 1 || encode) {
+                if (kAlways || encode) {
                     dv[g] = argmin_value(step_sq_dist<FT, DSUB>(kg[nb], i * DSUB, frow[g]), tid);
                     dm[g] = dv[g];
                 }
             }
-            // Ungrouped, the distances are evaluated in every range and published only where the new key is
-            // scored: the branch would cost more than the arithmetic.  With grouped queries the ranges that
-            // do not hold the new key skip them (eight heads' tables already keep those wavefronts busy).
-            if (G == 1 || encode) {
+            if (kAlways || encode) {
                 dmin_wave<GS>(dm);
 #pragma unroll
                 for (int g = 0; g < GS; ++g) {
@@ -465,9 +466,13 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
 // thing shared is the codebook, of which each half's table builders fetch half the subspaces and compute
 // both entries' table rows and distances.  The head's codebook then crosses from L2 to the compute units
 // once per pair instead of once per (b,h).  Both halves execute the same barriers (same L, same ranges).
+// LONE (ungrouped fused step, d_k = 128): for launches that leave every workgroup a compute unit of its own, where two
+// wavefronts share a SIMD and have 256 registers each: a tile's 16 KB are requested in one round instead of two, and the
+// next tile is in flight while one is consumed.
 // PAD (tables given, ungrouped): the head size is a.d_k < DK, a multiple of 8; lanes past the end of a row repeat its last
 // 16 bytes and their sums are not written.
-template <int DK, int M, int WAVES, int OCC, typename FT = void, int G = 1, int PF = 1, int NB = 1, bool PAD = false>
+template <int DK, int M, int WAVES, int OCC, typename FT = void, int G = 1, int PF = 1, int NB = 1, bool PAD = false,
+          bool LONE = false>
 __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOOKAT_DECODE_HEAD_PARAMS,
                                                                              const DecodeLate late)
 {
@@ -484,6 +489,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     // tile requests queued ahead of its table arithmetic starts that arithmetic microseconds late.
     static_assert(G == 1 || M != 0, "grouped queries: compile-time m");
     static_assert(!PAD || (!FUSED && G == 1), "padded head sizes: tables given, ungrouped");
+    static_assert(!LONE || (FUSED && G == 1 && NB == 1 && PF == 2 && DK == 128), "lone workgroups: ungrouped fused step, d_k = 128");
     const int dk = PAD ? a.d_k : DK;
     constexpr int LPR = DK / 8;            // lanes per value row (16 bytes per lane)
     constexpr int RPL = kWave / LPR;       // value rows covered by one wave-wide load
@@ -492,7 +498,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     // loads kept in flight together: 8 KB of a tile; the whole 16 KB tile where the matrix cores take the value sum
     // (its accumulators are half the size, and a second request round in the middle of a tile is a second
     // exposed round trip at two wavefronts per SIMD)
-    constexpr int CH = MM ? NLD : (NLD < 8 ? NLD : 8);
+    constexpr int CH = (MM || LONE) ? NLD : (NLD < 8 ? NLD : 8);
     constexpr int NT = WAVES * kWave;
 
     extern __shared__ __align__(16) float smem_all[];
@@ -644,25 +650,42 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     if (kb < k1) {
         consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm, pstage,
                                              lane_off, row_bytes);
+        if constexpr (LONE) {
+            // the next tile is in flight while this one is consumed (a wait for it waits for nothing else)
+            for (kb += NT; kb < k1; kb += NT) {
+                kc = kcs[1];
 #pragma unroll
-        for (int t = 1; t < PF; ++t) {   // the other tiles requested at the start
-            kb += NT;
-            if (kb < k1)
-                consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kcs[t], vs[t], lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm,
-                                                      pstage, lane_off, row_bytes);
-        }
-        for (kb += NT; kb < k1; kb += NT) {
-            if constexpr (M != 0)
-                kc.load(rc, (kb + kofs) * M);
-            else
-                kc.load(rc, (kb + kofs) * m, m);
-            __builtin_amdgcn_sched_barrier(0);   // request order = need order: codes before value rows
-            if constexpr (PAD)
-                load_rows_padded<DK, CH>(v, rv, kb, 0, lane_off, row_bytes);
-            else
-                load_rows<DK, CH>(v, rv, kb, 0, lane);
-            consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm, pstage,
-                                             lane_off, row_bytes);
+                for (int j = 0; j < CH; ++j)
+                    v[j] = vs[1][j];
+                if (kb + NT < k1) {
+                    kcs[1].load(rc, (kb + NT + kofs) * M);
+                    load_rows<DK, CH>(vs[1], rv, kb + NT, 0, lane);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm,
+                                                           pstage, lane_off, row_bytes);
+            }
+        } else {
+#pragma unroll
+            for (int t = 1; t < PF; ++t) {   // the other tiles requested at the start
+                kb += NT;
+                if (kb < k1)
+                    consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kcs[t], vs[t], lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm,
+                                                          pstage, lane_off, row_bytes);
+            }
+            for (kb += NT; kb < k1; kb += NT) {
+                if constexpr (M != 0)
+                    kc.load(rc, (kb + kofs) * M);
+                else
+                    kc.load(rc, (kb + kofs) * m, m);
+                __builtin_amdgcn_sched_barrier(0);   // request order = need order: codes before value rows
+                if constexpr (PAD)
+                    load_rows_padded<DK, CH>(v, rv, kb, 0, lane_off, row_bytes);
+                else
+                    load_rows<DK, CH>(v, rv, kb, 0, lane);
+                consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm, pstage,
+                                                 lane_off, row_bytes);
+            }
         }
     }
 
@@ -902,12 +925,34 @@ static int pick_waves(int d_k, int m, int64_t keys_per_split)
 // the streamers' tile requests instead of interleaved with them).
 constexpr int kStepPrefetch = 2;
 constexpr int kStepWaves = 2 * kDecWaves;   // four wavefronts build the table, four start streaming at once
+// d_k = 128, up to 256 workgroups: every one has a compute unit to itself (LONE).  Kernel time in us, LONE / otherwise: 256
+// (b,h) x 1024 keys, m = 8: 14.2 / 15.8; x 2048: 26.0 / 29.3; x 4096, m = 4: 46.4 / 48.5; 64 x 4096 in 4 ranges, m = 16:
+// 15.1 / 16.9; 32 x 32768 in 8: 44.0 / 46.7; 32 (b,h) in one range: equal.  At d_k = 64, where a tile is one round of requests
+// anyway, it is 1-2% slower and not taken.
 template <int DK, typename FT>
 static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
 {
     dim3 block(kStepWaves * kWave);
     const size_t lds = ((size_t)a.m * kCentroids + (size_t)kStepWaves * (DK + 2)) * sizeof(float) +
                        (size_t)a.m * kDecWaves * (sizeof(double) + sizeof(int));
+    if constexpr (DK == 128) {
+        if ((int64_t)a.BH * a.splits <= 256) {
+#define LOOKAT_STEP_LONE(M_)                                                                                              \
+    case M_:                                                                                                              \
+        hipLaunchKernelGGL((decode_split_kernel<DK, M_, kStepWaves, 2, FT, 1, 2, 1, false, true>), grid, block, lds, st,  \
+                           LOOKAT_DECODE_HEAD_ARGS(a, true), late_of(a));                                                 \
+        return true;
+            switch (a.m) {
+                LOOKAT_STEP_LONE(2)
+                LOOKAT_STEP_LONE(4)
+                LOOKAT_STEP_LONE(8)
+                LOOKAT_STEP_LONE(16)
+            default:
+                return false;
+            }
+#undef LOOKAT_STEP_LONE
+        }
+    }
     switch (a.m) {
     case 2:
         hipLaunchKernelGGL((decode_split_kernel<DK, 2, kStepWaves, 4, FT, 1, kStepPrefetch>), grid, block, lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true),

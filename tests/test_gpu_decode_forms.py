@@ -44,3 +44,22 @@ def test_decode_padded_head_sizes(lk, d_k, m, L, splits):
     assert_out_close(out.cpu().numpy(), ref, "attend_decode, padded head sizes", s_ref, scale)
     assert_scores_close(scores.cpu().numpy(), lut, codes[:, :, :L], s_ref)
     assert bool((guard[:256] == 7.0).all()) and bool((guard[256 + n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("m", [2, 4, 8, 16])
+@pytest.mark.parametrize("L,dtype", [(1, "float16"), (64, "float16"), (513, "float32"), (1100, "float16"), (2065, "float32")])
+def test_fused_step_lone_workgroups(lk, m, L, dtype):
+    """d_k = 128: up to 256 (b,h) take the instance for workgroups that have a compute unit to themselves (whole tiles
+    requested, the next one in flight), 257 the other; both add in the same order, so equal inputs give equal bits."""
+    H, d_k = 257, 128
+    assert lk.decode_step_entries_per_workgroup(1, H, d_k, m, L) == 1
+    g = torch.Generator(device="cuda").manual_seed(m * 10000 + L)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    cb, q, k = rnd(H, m, 256, d_k // m), rnd(1, H, d_k).to(getattr(torch, dtype)), rnd(1, H, d_k).to(getattr(torch, dtype))
+    codes = torch.randint(0, 256, (1, H, L + 3, m), generator=g, device="cuda", dtype=torch.uint8)
+    v = rnd(1, H, L + 3, d_k).half()
+    c1, c2 = codes.clone(), codes.clone()
+    many = lk.lookat_decode_step(q, k, cb, c1[:, :, :L], v[:, :, :L], 0.3)
+    lone = lk.lookat_decode_step(q[:, :256].contiguous(), k[:, :256].contiguous(), cb[:256], c2[:, :256, :L], v[:, :256, :L], 0.3)
+    assert torch.equal(many[:, :256], lone)
+    assert torch.equal(c1[:, :256], c2[:, :256]) and torch.equal(c2[:, 256], codes[:, 256])
