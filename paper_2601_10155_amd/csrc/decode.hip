@@ -180,9 +180,10 @@ __device__ __forceinline__ double step_sq_dist(UniformWords x, int x0, const flo
 //     remainder (p - fp16(p)) * 2^11 rounded to fp16, so that hi + lo * 2^-11 carries 22 bits of p; the
 //     weights go from the scoring lanes (one key per lane, all heads) to the operand layout (one column per
 //     lane, four keys) through 2 KB of LDS per wavefront, rows XOR-swizzled so that neither side conflicts;
-//   * the accumulators (8 instructions x 4 registers) are rescaled only in tiles where a running maximum
-//     moved; hi and lo columns are combined once, after the last tile.
+//   * the accumulators (8 instructions x 4 registers) are rescaled only in tiles where the reference
+//     moves; hi and lo columns are combined once, after the last tile.
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+constexpr float kLag = 8.f;          // log2 units: weights stay below 2^8, inside fp16 and far from fp32's limits
 constexpr float kLoScale = 2048.f;   // 2^11: lifts the remainder of a weight into fp16's normal range
 
 template <int M>
@@ -234,9 +235,8 @@ __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G
         }
     }
     // one score per query head of the group: the same codes index that head's tables
-    float p[G];
-    float corr_n = 1.f;      // MM: the correction of the query head whose column this lane accumulates
-    bool moved = false;      // MM: some head's running maximum changed in this tile (wave-uniform)
+    float sc[G], p[G];
+    bool above = false;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         float raw;
@@ -244,34 +244,47 @@ __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G
             raw = kc.score(lut_s + g * (M * kCentroids));
         else
             raw = kc.score(lut_s + g * (m * kCentroids), m);
-        float s = -INFINITY;
+        sc[g] = -INFINITY;
         if (key < k1) {
             if (a.scores_out)
                 a.scores_out[((int64_t)bh * G + g) * a.L + key] = raw;
-            s = raw * a.scale_log2e;
+            sc[g] = raw * a.scale_log2e;
         }
-        const float m_new = fmaxf(st.m_run[g], wave_max(s));
-        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        const float corr = fast_exp2(st.m_run[g] - m_use);
-        p[g] = fast_exp2(s - m_use);
-        st.z[g] = st.z[g] * corr + p[g];
-        if constexpr (MM) {
-            corr_n = ((lane & (G - 1)) == g) ? corr : corr_n;
-            moved = moved || (m_new != st.m_run[g]);
-        } else {
-#pragma unroll
-            for (int d = 0; d < 8; ++d)
-                st.acc[g][d] *= corr;
-        }
-        st.m_run[g] = m_new;
+        above |= sc[g] > st.m_run[g] + kLag;
     }
-    if constexpr (MM) {
-        static_assert(DK == 128 && CH % 4 == 0 && G >= 4 && G <= 8, "matrix-core value sum: d_k = 128, 4 or 8 query heads");
-        if (__builtin_amdgcn_readfirstlane((int)moved)) {
+    // The weights' reference need not be the running maximum, only near it: it moves (and the sums are rescaled) when a score
+    // exceeds it by more than kLag, so most tiles do without the reduction over the wavefront.
+    if (__builtin_amdgcn_ballot_w64(above)) {
+        float corr_n = 1.f;      // MM: the correction of the query head whose column this lane accumulates
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float m_new = fmaxf(st.m_run[g], wave_max(sc[g]));
+            const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+            const float corr = fast_exp2(st.m_run[g] - m_use);
+            st.z[g] *= corr;
+            if constexpr (MM) {
+                corr_n = ((lane & (G - 1)) == g) ? corr : corr_n;
+            } else {
+#pragma unroll
+                for (int d = 0; d < 8; ++d)
+                    st.acc[g][d] *= corr;
+            }
+            st.m_run[g] = m_new;
+        }
+        if constexpr (MM) {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 accm[e] *= corr_n;
         }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        // (all scores so far -inf: weights 0)
+        p[g] = fast_exp2(sc[g] - ((st.m_run[g] == -INFINITY) ? 0.f : st.m_run[g]));
+        st.z[g] += p[g];
+    }
+    if constexpr (MM) {
+        static_assert(DK == 128 && CH % 4 == 0 && G >= 4 && G <= 8, "matrix-core value sum: d_k = 128, 4 or 8 query heads");
         // weights to the staging rows: this lane scored key 16*(sub/4) + 4*(sub%4) + rowin of the tile
         const uint32_t sub_ = (uint32_t)lane & 15u, rowin_ = (uint32_t)lane >> 4;
         const uint32_t r_w = (sub_ & ~3u) + rowin_;                 // staging row (step, rowin)
