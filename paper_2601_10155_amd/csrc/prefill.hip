@@ -475,7 +475,11 @@ static int dispatch_prefill(const lookat_shape *s, const PrefillArgs &a, hipStre
 bool launch_prefill_dense(const lookat_shape *s, int T, int64_t L, const void *q, bool q_fp32, const float *codebooks,
                           const uint8_t *codes, int64_t code_stride_bh, float *scores, hipStream_t st);
 
-// From this many queries per (b,h) on, blocks of queries are scored on the matrix cores.  Its workgroups
+// prefill_short.hip: the same contraction with the codebook in LDS, for the short blocks where that is the fastest way.
+bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q, bool q_fp32, const float *codebooks,
+                          const uint8_t *codes, int64_t code_stride_bh, float *scores, hipStream_t st, int *rc);
+
+// From this many queries per (b,h) on, blocks of queries that prefill_short.hip leaves are scored on the matrix cores.  Its workgroups
 // spend their first microseconds fetching centroids, which a short block does not repay: measured at 4 x 32
 // heads, 4096 keys, d_k 128, m 16 (us per call, matrix cores / lookup-and-sum): T = 8: 40 / 22, 16: 40 / 34,
 // 24: 40 / 46, 32: 41 / 57, 64: 52 / 67, 256: 135 / 236.
@@ -519,6 +523,10 @@ static int score_prefill_impl(const lookat_shape *shape, int32_t T, int64_t L, c
     a.groups = 0;
     a.vec4 = (L % 4 == 0) && aligned16(scores);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    int rc = LOOKAT_OK;
+    if (allow_dense &&
+        launch_prefill_short(shape, T, L, q, q_dtype == LOOKAT_F32, codebooks, codes, code_stride_bh, scores, st, &rc))
+        return rc;
     if (allow_dense && T >= kPfDenseMinT &&
         launch_prefill_dense(shape, T, L, q, q_dtype == LOOKAT_F32, codebooks, codes, code_stride_bh, scores, st))
         return check_launch("lookat_score_prefill");

@@ -1,0 +1,385 @@
+// Causal scoring of a short block of queries against coded keys (paper Sec. 3.5, "Lookup and Sum", applied to every
+// query position), the same scores as prefill.hip and prefill_dense.hip:
+//     scores[b,h,t,l] = sum_i q_t^(i) . C_i[codes[b,h,l,i]]   for l <= t + (L - T),  else -inf.
+//
+// As in prefill_dense.hip the sum over subspaces is taken as a dense contraction of the queries with the keys' centroids
+// on the matrix cores.  With few queries there is nothing to hide the fetch of the centroids behind: every key needs
+// 2 d_k bytes of centroids whatever the number of queries, in pieces of 2 d_sub bytes, and fetched from L2 these random
+// pieces are the whole time (41 us for 4 x 32 heads x 4096 keys at d_k = 128, m = 16).  So here a head's codebook moves
+// into LDS first, once per workgroup, already scaled and split into two fp16 terms (d_k KB in all), and the keys gather
+// their matrix operands from there, 16 bytes per read, ready to use.
+//
+// Shape of the computation
+//   * one workgroup of 16 wavefronts per compute unit (two at d_k = 64) looks after one head: its share of the head's
+//     (batch entry, 32-key block) list, NG groups of 16 queries at a time.  A wavefront's share is contiguous; the queries
+//     of a batch entry are its stationary operand, reloaded when the batch entry changes;
+//   * A = keys, B = queries on v_mfma_f32_16x16x32_f16: lane (n, kg) holds 8 coordinates of key n (one 16-byte gather for each
+//     of the two terms; two 8-byte ones at d_sub = 4) and the same coordinates of query n of every group.  The result has
+//     four consecutive keys of one query in a lane: 16-byte stores, 64 contiguous bytes of a score row;
+//   * blocks that no query of the tile may see are filled with -inf without a gather.
+// Arithmetic as in prefill_dense.hip (its error bound holds): centroids scaled by one power of two per head (largest entry
+// near 2^13), hi + lo 2^-11 carries 22 bits of every entry down to 2^-27 of the largest; fp32 queries are scaled and split
+// per query row, the product of the two small terms is dropped; fp32 accumulation over all d_k coordinates.
+// What bounds it: LDS.  Per 64 keys 4 d_k / 16 reads of 1 KB at random 16-byte addresses (about 12 clocks each), then the set-up
+// of a workgroup (d_k KB of fp32 codebook through one compute unit, about 3 us).  Figures: see short_block.
+#include <type_traits>
+
+#include "common.h"
+
+namespace lookat {
+
+typedef _Float16 ps_v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 ps_v4h __attribute__((ext_vector_type(4)));
+typedef float ps_v4f __attribute__((ext_vector_type(4)));
+typedef unsigned int ps_v2u __attribute__((ext_vector_type(2)));
+typedef unsigned int ps_v4u __attribute__((ext_vector_type(4)));
+
+constexpr int kPsThreads = 1024;
+constexpr int kPsWaves = kPsThreads / kWave;
+constexpr float kPsLoScale = 2048.f;
+
+struct PrefillShortArgs {
+    const void *q;            // [BH, T, d_k] fp16 or fp32
+    const float *codebooks;   // [H, m, 256, d_sub]
+    const uint8_t *codes;     // (bh, l, i) at bh*code_stride + l*m + i
+    float *scores;            // [BH, T, L]
+    int64_t code_stride;
+    int64_t L;
+    int T;
+    int H;
+    int tiles;                // query tiles of 16 NG
+    int shares;               // workgroups per (head, query tile)
+    int blocks_per_bh;        // 32-key blocks
+    int blocks;               // of a head: B times as many
+    int vec4;                 // L % 4 == 0 and scores 16-byte aligned
+};
+
+// A power of two that brings the largest magnitude near 2^13, and its inverse.
+__device__ __forceinline__ void ps_scale(float largest, float &scale, float &inverse)
+{
+    int se = 13 - ((int)((__float_as_uint(largest) >> 23) & 0xffu) - 127);
+    if (largest == 0.f)
+        se = 13;
+    se = se > 100 ? 100 : (se < -100 ? -100 : se);
+    scale = __uint_as_float((uint32_t)(se + 127) << 23);
+    inverse = __uint_as_float((uint32_t)(127 - se) << 23);
+}
+
+template <typename QT, int DK, int M, int NG>
+__global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(const PrefillShortArgs a)
+{
+    constexpr bool Q32 = std::is_same<QT, float>::value;
+    constexpr int DSUB = DK / M;
+    constexpr int KW = 32;                            // coordinates per instruction
+    constexpr int KS = DK / KW;                       // instructions per term and group
+    constexpr uint32_t kTerm = DK * kCentroids * 2;   // bytes of one term's table
+    static_assert(DSUB % 4 == 0, "an operand's coordinates come from one or two subspaces");
+    extern __shared__ __align__(16) unsigned char smem[];   // [hi, lo][M][256][DSUB] fp16
+    __shared__ float max_s[kPsWaves];
+
+    // all workgroups of a head on one die, whose L2 then holds its codebook, codes and queries
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int per_head = a.tiles * a.shares;
+    const int h = (slot / per_head) * 8 + xcd;
+    if (h >= a.H)
+        return;
+    const int tile = (slot % per_head) / a.shares, share = slot % a.shares;
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int n = lane & 15, kg = lane >> 4;
+    const int64_t off = a.L - a.T;
+    const int t0 = tile * 16 * NG;
+    const int64_t seen = (t0 + 16 * NG < a.T ? t0 + 16 * NG : a.T) + off;    // keys from here on: -inf for every query of the tile
+
+    // ---- this wavefront's blocks, and the codes of the next one (key n of each half, in every lane group) ----
+    const int64_t parts = (int64_t)a.shares * kPsWaves, part = (int64_t)share * kPsWaves + wave;
+    const int blk0 = (int)(part * a.blocks / parts), blk1 = (int)((part + 1) * a.blocks / parts);
+    int b = blk0 / a.blocks_per_bh, lb = blk0 - b * a.blocks_per_bh;       // the block's batch entry and number within it
+    constexpr int kCodeWords = (M + 3) / 4;
+    uint32_t ahead[2][kCodeWords];
+    auto load_codes = [&](int b_, int lb_) {
+        const uint8_t *base = a.codes + ((int64_t)b_ * a.H + h) * a.code_stride;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int64_t l = (int64_t)lb_ * 32 + 16 * half + n;
+            const uint8_t *cp = base + (l < a.L ? l : a.L - 1) * M;         // past the end: a repeat, not stored
+            if constexpr (M == 2) {
+                ahead[half][0] = *reinterpret_cast<const uint16_t *>(cp);
+            } else if constexpr (M == 4) {
+                ahead[half][0] = *reinterpret_cast<const uint32_t *>(cp);
+            } else if constexpr (M == 8) {
+                const ps_v2u t = *reinterpret_cast<const ps_v2u *>(cp);
+                ahead[half][0] = t.x;
+                ahead[half][1] = t.y;
+            } else {
+                const ps_v4u t = *reinterpret_cast<const ps_v4u *>(cp);
+                ahead[half][0] = t.x;
+                ahead[half][1] = t.y;
+                ahead[half][2] = t.z;
+                ahead[half][3] = t.w;
+            }
+        }
+    };
+    if (blk0 < blk1)
+        load_codes(b, lb);
+
+    // ---- codebook: registers -> largest magnitude -> LDS, scaled and split ----
+    constexpr int NV = DK * kCentroids / 4 / kPsThreads;
+    const ps_v4f *cb = reinterpret_cast<const ps_v4f *>(a.codebooks + (int64_t)h * M * kCentroids * DSUB);
+    ps_v4f cv[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+        cv[k] = cb[tid + k * kPsThreads];
+    float cmax = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            cmax = fmaxf(cmax, fabsf(cv[k][e]));
+    cmax = wave_max(cmax);
+    if (lane == 0)
+        max_s[wave] = cmax;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kPsWaves; ++w)
+        cmax = fmaxf(cmax, max_s[w]);
+    float scale, inv;
+    ps_scale(cmax, scale, inv);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        ps_v4h hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float w = scale * cv[k][e];                          // exact: a power of two
+            hi[e] = (_Float16)w;
+            lo[e] = (_Float16)((w - (float)hi[e]) * kPsLoScale);       // exact difference and scaling, one rounding
+        }
+        *reinterpret_cast<ps_v4h *>(smem + (uint32_t)(tid + k * kPsThreads) * 8u) = hi;
+        *reinterpret_cast<ps_v4h *>(smem + kTerm + (uint32_t)(tid + k * kPsThreads) * 8u) = lo;
+    }
+    __syncthreads();
+
+    ps_v8h qh[NG][KS], ql[Q32 ? NG : 1][Q32 ? KS : 1];     // the batch entry's queries: operand B
+    float qinv[NG];
+    float *row[NG];                                          // this lane's query of every group (past the end: a repeat, not stored)
+    int b_loaded = -1;
+    for (int blk = blk0; blk < blk1; ++blk) {
+        if (b != b_loaded) {
+            b_loaded = b;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int t = t0 + 16 * g + n < a.T ? t0 + 16 * g + n : a.T - 1;
+                const int64_t qrow = ((int64_t)b * a.H + h) * a.T + t;
+                const QT *q = static_cast<const QT *>(a.q) + qrow * DK + 8 * kg;
+                row[g] = a.scores + qrow * a.L;
+                qinv[g] = inv;
+                if constexpr (!Q32) {
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+                        qh[g][s] = *reinterpret_cast<const ps_v8h *>(q + KW * s);
+                } else {
+                    ps_v4f v[KS][2];
+                    float qmax = 0.f, qs, qi, x, y;
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p)
+                            v[s][p] = *reinterpret_cast<const ps_v4f *>(q + KW * s + 4 * p);
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            qmax = fmaxf(qmax, fabsf(v[s][e / 4][e % 4]));
+                    lanes_xor16(qmax, x, y);
+                    qmax = fmaxf(x, y);
+                    lanes_xor32(qmax, x, y);
+                    ps_scale(fmaxf(x, y), qs, qi);
+                    qinv[g] *= qi;
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const float w = qs * v[s][e / 4][e % 4];
+                            qh[g][s][e] = (_Float16)w;
+                            ql[g][s][e] = (_Float16)((w - (float)qh[g][s][e]) * kPsLoScale);
+                        }
+                }
+            }
+        }
+        const int64_t l0 = (int64_t)lb * 32;
+        uint32_t now[2][kCodeWords];
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int w = 0; w < kCodeWords; ++w)
+                now[half][w] = ahead[half][w];
+        if (++lb == a.blocks_per_bh) {
+            lb = 0;
+            ++b;
+        }
+        if (blk + 1 < blk1)
+            load_codes(b, lb);                               // the next block's codes arrive while this one is scored
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int64_t lh = l0 + 16 * half;
+            const uint32_t(&cw)[kCodeWords] = now[half];
+            ps_v4f acc_h[NG], acc_l[NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                acc_h[g] = ps_v4f{0.f, 0.f, 0.f, 0.f};
+                acc_l[g] = ps_v4f{0.f, 0.f, 0.f, 0.f};
+            }
+            if (lh < seen) {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    // coordinates 32 s + 8 kg .. + 7 of the key
+                    ps_v8h kh, kl;
+                    if constexpr (DSUB >= 8) {
+                        uint32_t code, base;
+                        if constexpr (DSUB >= KW) {                        // one subspace for all lanes
+                            constexpr int per = DSUB / KW;
+                            const int i = s / per;
+                            code = (cw[i / 4] >> (8 * (i % 4))) & 0xffu;
+                            base = (uint32_t)(i * kCentroids * DSUB + (s % per) * KW + 8 * kg) * 2u;
+                        } else {                                           // lane groups in 2 or 4 consecutive subspaces
+                            constexpr int IPS = KW / DSUB;
+                            const int isub = kg / (DSUB / 8);
+                            code = (cw[(s * IPS) / 4] >> (8 * ((s * IPS) % 4 + isub))) & 0xffu;
+                            base = (uint32_t)((s * IPS + isub) * kCentroids * DSUB + (8 * kg) % DSUB) * 2u;
+                        }
+                        const unsigned char *p = smem + base + code * (DSUB * 2);
+                        kh = *reinterpret_cast<const ps_v8h *>(p);
+                        kl = *reinterpret_cast<const ps_v8h *>(p + kTerm);
+                    } else {                                               // d_sub = 4: two subspaces per lane
+                        const int i0 = s * 8 + 2 * kg;
+                        const uint32_t word_lo = cw[2 * s], word_hi = cw[2 * s + 1];
+                        const uint32_t two = ((kg >= 2 ? word_hi : word_lo) >> (16 * (kg & 1))) & 0xffffu;
+                        const unsigned char *p0 = smem + (uint32_t)(i0 * kCentroids + (two & 0xffu)) * 8u;
+                        const unsigned char *p1 = smem + (uint32_t)((i0 + 1) * kCentroids + (two >> 8)) * 8u;
+                        const ps_v4h h0 = *reinterpret_cast<const ps_v4h *>(p0), h1 = *reinterpret_cast<const ps_v4h *>(p1);
+                        const ps_v4h g0 = *reinterpret_cast<const ps_v4h *>(p0 + kTerm), g1 = *reinterpret_cast<const ps_v4h *>(p1 + kTerm);
+                        kh = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
+                        kl = __builtin_shufflevector(g0, g1, 0, 1, 2, 3, 4, 5, 6, 7);
+                    }
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) {
+                        acc_h[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[g][s], acc_h[g], 0, 0, 0);
+                        acc_l[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[g][s], acc_l[g], 0, 0, 0);
+                        if constexpr (Q32)
+                            acc_l[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, ql[g][s], acc_l[g], 0, 0, 0);
+                    }
+                }
+            }
+            // result register r of lane (n, kg): key lh + 4 kg + r of query n of the group
+            const int64_t l = lh + 4 * kg;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int t = t0 + 16 * g + n;
+                if (t < a.T) {
+                    ps_v4f o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        o[e] = l + e <= t + off ? fmaf(acc_l[g][e], 1.f / kPsLoScale, acc_h[g][e]) * qinv[g] : -INFINITY;
+                    if (a.vec4) {
+                        if (l < a.L)
+                            *reinterpret_cast<ps_v4f *>(row[g] + l) = o;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (l + e < a.L)
+                                row[g][l + e] = o[e];
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <typename QT, int DK, int M, int NG>
+static int launch_prefill_short_case(const PrefillShortArgs &a, hipStream_t st)
+{
+    const size_t lds = (size_t)DK * kCentroids * 4;
+    auto kern = score_prefill_short_kernel<QT, DK, M, NG>;
+    if (lds > 48 * 1024) {   // (64 KB with the static part)
+        // allow more than 64 KB of LDS: idempotent, so every call makes it (no flag shared between host threads)
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess)
+            return fail(LOOKAT_ERR_HIP, "lookat_score_prefill: cannot reserve %zu bytes of LDS: %s", lds, hipGetErrorString(e));
+    }
+    const int64_t wgs = (int64_t)((a.H + 7) / 8 * 8) * a.tiles * a.shares;
+    hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(kPsThreads), lds, st, a);
+    return check_launch("lookat_score_prefill");
+}
+
+// Which blocks come here.  The alternatives are the lookup-and-sum kernel (blocks under 24 queries; its reads of LDS grow
+// with m ceil(T / 4), and it has one workgroup per (b,h)) and the dense kernel that fetches centroids from L2 (its cost grows
+// with the number of keys of all (b,h), hardly with T).  us per call, here / there:
+//   d_k = 128, fp16 queries: 4 x 32 heads x 4096 keys, m = 16: T = 2 13.5 / 15.9, 8 14.7 / 22.2, 16 16.6 / 34.7, 24 20.9 / 45.2,
+//   32 24.0 / 46.0, 48 50.9 / 53.3;  8 x 40 x 2000, m = 4: 2 16.8 / 21.7, 8 18.3 / 26.8, 32 36.5 / 59.4;  2 x 32 x 4096, m = 8:
+//   24 15.1 / 23.2;  1 x 32 x 4096, m = 8: 8 8.4 / 16.1, 24 14.1 / 12.7;  1 x 8 x 2000, m = 2: 2 10.3 / 9.4
+//   d_k = 128, fp32 queries (split like the centroids: 1.1e-7 off 64 bits against 0.93e-7 by lookup, so not below 24, where the
+//   lookup kernel is the other one): 4 x 32 x 4096, m = 16: 24 25.6 / 55.2, 64 59.7 / 76.1
+//   d_k = 64: 4 x 32 x 4096, m = 8: 2 9.9 / 8.1, 8 11.6 / 12.4, 16 13.9 / 19.4;  16 x 12 x 2000, m = 4: 16 12.9 / 11.8;
+//   2 x 8 x 8000, m = 16: 2 7.9 / 16.7
+static bool short_block(const lookat_shape *s, int T, int64_t L, bool q_fp32)
+{
+    const int64_t BH = (int64_t)s->B * s->H;
+    if (T >= 24)
+        return s->d_k == 128 && T <= (q_fp32 ? 64 : 32) && BH * L >= 200000;
+    const int reads = s->m * ((T + 3) / 4);
+    return !q_fp32 && (s->d_k == 128 ? reads >= 4 : (reads >= 16 && BH <= 128));
+}
+
+// d_k in {64, 128}, m in {2, 4, 8, 16}: launches (status in *rc) and returns true; otherwise returns false.
+bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q, bool q_fp32, const float *codebooks,
+                          const uint8_t *codes, int64_t code_stride_bh, float *scores, hipStream_t st, int *rc)
+{
+    if (!short_block(s, T, L, q_fp32))
+        return false;
+    PrefillShortArgs a;
+    a.q = q;
+    a.codebooks = codebooks;
+    a.codes = codes;
+    a.scores = scores;
+    a.code_stride = code_stride_bh;
+    a.L = L;
+    a.T = T;
+    a.H = s->H;
+    const int64_t blocks_per_bh = (L + 31) / 32;
+    const int ng = (q_fp32 || T <= 16) ? 1 : 2;   // (two groups of split fp32 queries do not fit 128 registers)
+    a.tiles = (T + 16 * ng - 1) / (16 * ng);
+    // workgroups per head and tile: one per compute unit (two at d_k = 64, whose codebook takes half the LDS), and at least
+    // two blocks for a wavefront
+    int64_t shares = (s->d_k == 64 ? 512 : 256) / ((int64_t)(s->H + 7) / 8 * 8 * a.tiles);
+    const int64_t most = (s->B * blocks_per_bh + 2 * kPsWaves - 1) / (2 * kPsWaves);
+    shares = shares < most ? shares : most;
+    a.shares = (int)(shares < 1 ? 1 : shares);
+    a.vec4 = (L % 4 == 0) && aligned16(scores);
+    if ((int64_t)((s->H + 7) / 8 * 8) * a.tiles * a.shares > 0x3fffff || s->B * blocks_per_bh > 0x7fffffff)   // (a grid of 2^32 threads)
+        return false;
+    a.blocks_per_bh = (int)blocks_per_bh;
+    a.blocks = (int)(s->B * blocks_per_bh);
+#define LOOKAT_PS_CASE(DK_, M_)                                                                              \
+    if (s->d_k == DK_ && s->m == M_) {                                                                       \
+        if (q_fp32)                                                                                          \
+            *rc = launch_prefill_short_case<float, DK_, M_, 1>(a, st);                                       \
+        else if (ng == 1)                                                                                    \
+            *rc = launch_prefill_short_case<__half, DK_, M_, 1>(a, st);                                      \
+        else                                                                                                 \
+            *rc = launch_prefill_short_case<__half, DK_, M_, 2>(a, st);                                      \
+        return true;                                                                                         \
+    }
+    LOOKAT_PS_CASE(64, 2)
+    LOOKAT_PS_CASE(64, 4)
+    LOOKAT_PS_CASE(64, 8)
+    LOOKAT_PS_CASE(64, 16)
+    LOOKAT_PS_CASE(128, 2)
+    LOOKAT_PS_CASE(128, 4)
+    LOOKAT_PS_CASE(128, 8)
+    LOOKAT_PS_CASE(128, 16)
+#undef LOOKAT_PS_CASE
+    return false;
+}
+
+}  // namespace lookat
