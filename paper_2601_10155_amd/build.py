@@ -1,4 +1,5 @@
-"""Builds liblookat.so (HIP, gfx950) in-tree with hipcc.  `python -m paper_2601_10155_amd.build`."""
+"""Builds liblookat.so (HIP, gfx950; hipcc) and _marshal.so (the binding's native marshalling; g++ against torch's headers)
+in-tree.  `python -m paper_2601_10155_amd.build`."""
 from __future__ import annotations
 
 import os
@@ -10,6 +11,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblookat.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
 # -packed-fp32-ops off: keeps the compiler from forming packed fp32 instructions.
@@ -33,6 +35,21 @@ def sources() -> list[str]:
     return sorted(f for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
+def marshal_command() -> list[str]:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_path("include")]
+    for d in include_paths():
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL]
+    for d in library_paths():
+        cmd += ["-L", d]
+    return cmd + ["-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(verbose: bool = True, force: bool = True) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     cc = hipcc()
@@ -50,12 +67,18 @@ def build(verbose: bool = True, force: bool = True) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    deps = [os.path.join(CSRC, "marshal.cpp"), os.path.join(ROOT, "include", "lookat.h")]
+    if force or not (os.path.exists(MARSHAL) and all(os.path.getmtime(MARSHAL) >= os.path.getmtime(d) for d in deps)):
+        cmd = marshal_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append(("marshal.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         # hipcc's host pass does not know the packed-fp32 feature name and says so: harmless
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            raise RuntimeError(f"the compiler failed on {src}:\n{out}")
         if verbose and out.strip():
             print(out, flush=True)
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
