@@ -18,16 +18,20 @@ namespace lookat {
 // equal codes find each other with eight ballots (one per code bit), a lane's slot is the pair's
 // running offset plus the number of equal-code lanes below it, and the lowest of them advances
 // the offset.  (LDS operations of one wavefront execute in program order.)
-// What bounds it: latency.  The sums are serial chains behind scattered reads of V * 4 bytes (the workgroups of
-// a head's other subspaces read the rest of a key's row), so a thread requests kKmBatch members' pieces before it adds
-// the first, and a sub-vector longer than 16 coordinates is shared by several workgroups, each with its own lists
-// (cheap beside the reads).  With 256 threads, four single floats in flight per thread and every thread
-// taking d_sub chains in turn the update took 305 us at 32 heads x 16384 keys x 128 coordinates, m = 8; now 108 us.
+// What bounds it: scattered reads.  The sums are serial chains behind reads of V * 4 bytes, 4 d_sub of a row, so a thread
+// requests kKmBatch members' pieces before it adds the first, and a sub-vector longer than 16 coordinates is shared by
+// several workgroups, each with its own lists (cheap beside the reads).  Half of every 128-byte line belongs to another
+// subspace at d_sub = 16: the workgroups of a head run side by side on one die and take the same chunk of keys at about
+// the same time, so that its L2 serves the other half.  32 heads x 16384 keys x 128 coordinates, m = 8: 305 us with 256 threads,
+// four single floats in flight and every thread taking d_sub chains in turn; 113 us with 1024 threads, 16-byte pieces
+// and eight in flight; 86 us with the subspaces of a head on one die and chunks of 4096 keys (2048: 93, 8192: 93, 16384: 103;
+// 12 or 16 pieces in flight: no change; the lists alone: 29).
 //   LDS: first[257] | run[16][256] | list [kKmChunk] uint16
-//   grid = (m, H, pieces of a sub-vector / pieces per workgroup), 1024 threads
+//   grid = (8 heads x m x groups of a sub-vector's pieces, ceil(H / 8)), 1024 threads; consecutive workgroups go to the
+//   eight dies in turn
 constexpr int kKmThreads = 1024;
 constexpr int kKmWaves = kKmThreads / kWave;
-constexpr int kKmChunk = 16384;
+constexpr int kKmChunk = 4096;
 constexpr int kKmRounds = kKmChunk / kKmThreads;     // 64-key rounds of a wavefront in a full chunk
 constexpr int kKmPieces = kKmThreads / kCentroids;   // one (centroid, piece) per thread
 constexpr int kKmBatch = 8;
@@ -37,7 +41,7 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_update_kernel(const float *
                                                                    const uint8_t *__restrict__ assign,
                                                                    const float *__restrict__ cb_in,
                                                                    float *__restrict__ cb_out, int64_t Nc, int d_k,
-                                                                   int m, int pieces_per_wg)
+                                                                   int H, int m, int groups, int pieces_per_wg)
 {
     __shared__ uint32_t first_s[kCentroids + 1];
     __shared__ uint32_t run_s[kKmWaves][kCentroids];
@@ -45,11 +49,15 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_update_kernel(const float *
     __shared__ uint32_t wave_tot[kCentroids / kWave];
 
     const int d_sub = d_k / m;
-    const int i = blockIdx.x;
-    const int h = blockIdx.y;
+    // all workgroups of a head side by side on one die
+    const int h = (int)blockIdx.y * 8 + blockIdx.x % 8;
+    if (h >= H)
+        return;
+    const int slot = blockIdx.x / 8;
+    const int i = slot / groups;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
-    const int p0 = blockIdx.z * pieces_per_wg;
+    const int p0 = slot % groups * pieces_per_wg;
     const int np = (d_sub / V - p0) < pieces_per_wg ? (d_sub / V - p0) : pieces_per_wg;
     const bool sums = tid < kCentroids * np;         // this thread owns a (centroid, piece)
     const int c = sums ? tid / np : 0;
@@ -199,13 +207,14 @@ extern "C" int lookat_kmeans_step(const lookat_shape *shape, int64_t Nc, const f
     int per = kKmPieces < pieces ? kKmPieces : pieces;
     while (per > 1 && (int64_t)shape->m * shape->H * ((pieces + per - 1) / per) < 256)
         per /= 2;
-    const dim3 grid((unsigned)shape->m, (unsigned)shape->H, (unsigned)((pieces + per - 1) / per));
+    const int groups = (pieces + per - 1) / per;      // workgroups per (head, subspace)
+    const dim3 grid((unsigned)(8 * shape->m * groups), (unsigned)(((int64_t)shape->H + 7) / 8));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (V == 4)
         hipLaunchKernelGGL(kmeans_update_kernel<4>, grid, dim3(kKmThreads), 0, st, calib, assign, codebooks_in, codebooks_out,
-                           Nc, shape->d_k, shape->m, per);
+                           Nc, shape->d_k, shape->H, shape->m, groups, per);
     else
         hipLaunchKernelGGL(kmeans_update_kernel<1>, grid, dim3(kKmThreads), 0, st, calib, assign, codebooks_in, codebooks_out,
-                           Nc, shape->d_k, shape->m, per);
+                           Nc, shape->d_k, shape->H, shape->m, groups, per);
     return check_launch("lookat_kmeans_step (update kernel)");
 }

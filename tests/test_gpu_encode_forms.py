@@ -81,7 +81,7 @@ def test_encode_keys_that_are_not_finite(lk, bad, dtype):
 
 
 @pytest.mark.parametrize("d_k,m", [(24, 8), (32, 4), (80, 2), (128, 2)])   # single coordinates, 2, 10 and 16 pieces of four
-@pytest.mark.parametrize("Nc", [1, 63, 1025, 16384, 16448, 40000])         # one chunk of keys, exactly one, several
+@pytest.mark.parametrize("Nc", [1, 63, 1025, 4096, 4097, 40000])           # one chunk of keys, exactly one, several
 def test_learn_matches_oracle(lk, d_k, m, Nc):
     """Members are added in ascending key order across wavefronts, chunks and workgroups; one cluster holds half the keys."""
     rng = np.random.default_rng(d_k + Nc)
@@ -91,4 +91,14 @@ def test_learn_matches_oracle(lk, d_k, m, Nc):
     ref, _ = oracle.kmeans_step(calib, cb)
     got, assign = lk.lookat_kmeans_step(dev(calib), dev(cb))
     assert np.array_equal(assign.cpu().numpy(), oracle.encode_keys(calib[None], cb)[0])
+    assert np.array_equal(got.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("H", [8, 9, 17])
+def test_learn_heads_beyond_one_row_of_dies(lk, H):
+    rng = np.random.default_rng(H)
+    cb = rng.standard_normal((H, 4, 256, 8)).astype(np.float32)
+    calib = rng.standard_normal((H, 700, 32)).astype(np.float32)
+    ref, _ = oracle.kmeans_step(calib, cb)
+    got, _ = lk.lookat_kmeans_step(dev(calib), dev(cb))
     assert np.array_equal(got.cpu().numpy(), ref)
