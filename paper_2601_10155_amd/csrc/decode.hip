@@ -883,7 +883,10 @@ static int auto_splits_gqa(const lookat_shape *s, int group, int64_t L)
     if (group == 1)
         return auto_splits(s, L);
     int64_t want = (group >= 4 ? 256 : 512) / ((int64_t)s->B * s->H);
-    const int64_t cap = (L + 1023) / 1024;      // ranges of at least 1024 keys
+    // Ranges of at least 512 keys from 2048 keys on, of 1024 below (us per fused step, ranges of 1024 / 512 keys; d_k = 128, m = 8: group 8,
+    // 32 key/value heads x 2048 keys 19.6 / 19.0, 8 x 8192 19.3 / 19.5; group 2, 64 x 2048 15.0 / 14.0; d_k = 64: group 4, 32 x
+    // 2500, m = 4 11.4 / 11.2; group 2, 16 x 3000, m = 16 13.3 / 12.4; but group 4, 32 x 1024 in one range 16.0, in two 17.1).
+    const int64_t cap = L >= 2048 ? (L + 511) / 512 : (L + 1023) / 1024;
     want = want < cap ? want : cap;
     return (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
 }
@@ -1355,7 +1358,9 @@ extern "C" int lookat_decode_step_gqa(const lookat_shape *shape, int32_t group, 
         return fail(LOOKAT_ERR_UNSUPPORTED, "lookat_decode_step_gqa handles group in {1,2,4,8}; got %d", group);
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
-    const int S = num_splits ? num_splits : (L > 0 ? auto_splits_gqa(shape, group, L) : 1);
+    int S = num_splits ? num_splits : (L > 0 ? auto_splits_gqa(shape, group, L) : 1);
+    if (!num_splits && group == 1 && L > 0)
+        S = fit_splits(shape, L, S, workspace ? workspace_bytes : 0);
     return decode_step_impl("lookat_decode_step_gqa", shape, group, L, q, k_new, qk_dtype, codebooks, codes,
                             code_stride_bh, values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }

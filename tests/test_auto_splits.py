@@ -23,6 +23,11 @@ def test_auto_splits_invariants():
                     assert S == 1
                 assert lk.attend_decode_workspace_bytes(1, BH, d_k, m, L) == (0 if S == 1 else BH * S * (d_k + 2) * 4)
                 assert lk.attend_decode_gqa_workspace_bytes(1, BH, 1, d_k, m, L) == lk.attend_decode_workspace_bytes(1, BH, d_k, m, L)
+    for group, fill in ((2, 512), (4, 256), (8, 256)):        # grouped queries: ranges of 512 keys, none cut under 1025 keys
+        for BH in (1, 3, 32, 64, 200, 300, 600):
+            for L, most in ((1, 1), (1024, 1), (1025, 2), (2047, 2), (2048, 4), (2049, 5), (4096, 8), (200000, 256)):
+                S = min(most, max(1, fill // BH))
+                assert lk.attend_decode_gqa_workspace_bytes(1, BH, group, 64, 4, L) == (0 if S == 1 else BH * group * S * 66 * 4)
     # long contexts of few pairs are cut, a little over one workgroup per compute unit too
     assert lk.attend_decode_auto_splits(1, 32, 128, 8, 8192) == 8
     assert lk.attend_decode_auto_splits(1, 264, 128, 8, 8192) > 1
@@ -60,4 +65,8 @@ def test_auto_splits_without_a_workspace(B, H, L):
     assert float((lk.lookat_decode_step_split(q, k, cb, codes, v, scale) - one).abs().max()) <= 2e-5
     rc = lib.lookat_decode_step_split(ctypes.byref(shape), L, q.data_ptr(), k.data_ptr(), 2, cb.data_ptr(), codes.data_ptr(), L * m,
                                       v.data_ptr(), L * d_k, scale, 0, None, 0, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and torch.equal(out, one)
+    out.zero_()
+    rc = lib.lookat_decode_step_gqa(ctypes.byref(shape), 1, L, q.data_ptr(), k.data_ptr(), 2, cb.data_ptr(), codes.data_ptr(), L * m,
+                                    v.data_ptr(), L * d_k, scale, 0, None, 0, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
     assert rc == 0 and torch.equal(out, one)
