@@ -90,122 +90,122 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_generic_kernel(const QT
 
 // ---- many queries per head: the table build is a dense contraction -> matrix cores ------
 // Per (head h, subspace i):  LUT[r][c] = sum_j Q[r][j] * C[c][j]  with r over the B*T queries
-// of the head, c over the 256 centroids, j over d_sub: an [R x d_sub] . [d_sub x 256] product.
-// One wavefront owns 32-query tiles and keeps the whole [d_sub x 256] codebook slice in
-// registers as MFMA B-fragments; per tile it issues 8 column blocks x d_sub/2 steps of
-// v_mfma_f32_32x32x2_f32 (fp32 in, fp32 accumulate: same accuracy class as the vector kernel)
-// and streams the 32 x 256 fp32 results out through an LDS transpose, 16 bytes per lane and 512
-// contiguous bytes per half-wavefront.  The kernel is bound by that output stream (d_sub*2 flops per 4 bytes
-// written), not by the matrix cores.  NTS = 1 writes the tables with non-temporal stores: a table set far
-// larger than the last-level cache is read back from HBM by its consumer whatever the stores do, and
-// stores that do not allocate cache lines reach 5.7-5.8 TB/s where plain ones reach 5.0-5.1 (workload
-// of 4.3 GB of tables); small table sets keep plain stores so that the consumer finds them in cache.
+// of the head, c over the 256 centroids, j over d_sub: an [R x d_sub] . [d_sub x 256] product on
+// v_mfma_f32_32x32x2_f32 (fp32 in, fp32 accumulate: same accuracy class as the vector kernel).
+// What bounds it: the output stream (d_sub*2 flops per 4 bytes written), and that stream depends on the order in which it
+// is written.  One workgroup makes 32 queries x 256 centroids of one subspace, 32 KB, and ends; the subspaces of the same
+// queries, then the next queries, are made by the workgroups that follow, so what the chip writes at one time is
+// one compact piece of the tables.  A launch that only stores writes 1.07 GB in this order in 155 us, 182-218 us with the
+// 256 KB strips of 256 queries of one subspace that a workgroup made before (its codebook slice kept in registers).
+// us per call before / now: 4 x 32 x 512 queries, m = 16 (1.07 GB) 194 / 175; 32 x 12 x 128, m = 4 86 / 53; 12 x 1000, m = 4, fp32
+// 27.8 / 15.8; 256 x 32 x 1, m = 8 31.2 / 19.6; 3 x 7 x 333, m = 8 30.6 / 16.4.  The LDS holds four workgroups per compute unit;
+// three: 176 us, two: 198.
+// Each wavefront makes 64 of the 256 centroids: two 32-column blocks of the MFMA, whose results cross LDS so that they leave
+// as 1 KB table rows, 16 bytes per lane (stored straight from the accumulators, a store instruction would write 4 bytes
+// per lane in two 128-byte pieces).  NTS = 1 writes with non-temporal stores: a table set far larger than
+// the last-level cache is read back from HBM by its consumer whatever the stores do, and stores that do not
+// allocate cache lines are faster; small table sets keep plain stores so that the consumer finds them in cache.
 //   fragment layout of the 32x32x2 MFMA: A[row = lane%32][k = lane/32], B[k = lane/32][col = lane%32],
 //   D[row = 8*(r/4) + 4*(lane/32) + r%4][col = lane%32] for accumulator register r = 0..15.
 typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr int kMfmaWaves = 4;
+constexpr int kMfmaRows = 32;            // queries per workgroup
 
 typedef float lut_v4f __attribute__((ext_vector_type(4)));
+
+
+// DSUB consecutive elements, loaded in pieces of up to 16 bytes (aligned to their size)
+template <typename T, int DSUB>
+__device__ __forceinline__ void lut_load_row(const T *src, T (&v)[DSUB])
+{
+    constexpr int kBytes = DSUB * (int)sizeof(T) < 16 ? DSUB * (int)sizeof(T) : 16;
+    typedef uint32_t piece_t __attribute__((ext_vector_type(kBytes / 4)));
+    constexpr int kPieces = DSUB * (int)sizeof(T) / kBytes;
+    piece_t p[kPieces];
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k)
+        p[k] = reinterpret_cast<const piece_t *>(src)[k];
+    __builtin_memcpy(v, p, sizeof(p));
+}
 
 template <typename QT, int DSUB, int NTS>
 __global__ __launch_bounds__(kMfmaWaves *kWave) void build_lut_mfma_kernel(const QT *__restrict__ q,
                                                                            const float *__restrict__ codebooks,
                                                                            float *__restrict__ lut, int B, int H,
-                                                                           int T, int d_k, int m, int tiles_per_wave)
+                                                                           int T, int d_k, int m, uint32_t run)
 {
     constexpr int KS = DSUB / 2;
-    const int i = blockIdx.y;
-    const int h = blockIdx.z;
+    constexpr int kBlocks = kCentroids / 32 / kMfmaWaves;     // 32-column blocks per wavefront
+    constexpr int kStageStride = kCentroids + 4;              // floats per staged table row (pad: rows 4 apart on distinct banks)
+    __shared__ __align__(16) float stage_s[kMfmaRows * kStageStride];
+    // subspaces fastest, then `run` query tiles (a batch entry's), then heads, then the next tiles
+    const uint32_t w0 = blockIdx.x, w1 = w0 / (uint32_t)m, w2 = w1 / run, w3 = w2 / (uint32_t)H;
+    const int i = (int)(w0 - w1 * (uint32_t)m);
+    const int h = (int)(w2 - w3 * (uint32_t)H);
+    const int64_t nq = (int64_t)B * T;
+    const int64_t r0 = ((int64_t)w3 * run + (w1 - w2 * run)) * kMfmaRows;
+    if (r0 >= nq)
+        return;
+    const int b0 = (int)((uint32_t)r0 / (uint32_t)T);         // (B*T < 2^31)
+    const int t0 = (int)((uint32_t)r0 - (uint32_t)b0 * (uint32_t)T);
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int n = lane & 31;
     const int kh = lane >> 5;
-    const int64_t nq = (int64_t)B * T;
-    const int64_t ntiles = (nq + 31) / 32;
-    constexpr int kStageStride = 128;       // floats per staged query row: 4 wavefronts x 16 KB = the 64 KB of static LDS
-    __shared__ __align__(16) float stage_s[kMfmaWaves][32 * kStageStride];
-    float *stage = stage_s[wave];
 
-    float bfrag[8][KS];
+    float a[KS], c[kBlocks][KS];
     {
-        const float *cb = codebooks + ((int64_t)h * m + i) * kCentroids * DSUB;
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                bfrag[nt][s] = cb[(nt * 32 + n) * DSUB + 2 * s + kh];
-    }
-
-    // Tiles are taken four at a time: the query fragments of the four are loaded together, then the
-    // four are computed and stored.  Loads and stores share one in-order counter on this chip, so
-    // every wait for a load also waits for all stores issued before it (32 KB of table rows per tile
-    // and wavefront): with one load phase per four tiles that drain is paid a quarter as often.
-    constexpr int kChunk = 4;
-    const int64_t tile0 = ((int64_t)blockIdx.x * kMfmaWaves + wave) * tiles_per_wave;
-    for (int it0 = 0; it0 < tiles_per_wave && tile0 + it0 < ntiles; it0 += kChunk) {
-      float afr[kChunk][KS];
-#pragma unroll
-      for (int c = 0; c < kChunk; ++c) {
-          const int64_t r = (tile0 + it0 + c) * 32 + n;
-          const bool live = (it0 + c < tiles_per_wave) && (r < nq);
-          const int64_t b = live ? r / T : 0, t = live ? r % T : 0;
-          const QT *src = q + ((b * H + h) * T + t) * d_k + (int64_t)i * DSUB + kh;
-#pragma unroll
-          for (int s = 0; s < KS; ++s)
-              afr[c][s] = live ? to_f32<QT>(src[2 * s]) : 0.f;
-      }
-#pragma unroll
-      for (int c = 0; c < kChunk; ++c) {
-        const int64_t tile = tile0 + it0 + c;
-        if (it0 + c >= tiles_per_wave || tile >= ntiles)
-            break;
-        const float(&afrag)[KS] = afr[c];
-        // The accumulator layout gives a lane one column (centroid) and 16 rows (queries): stored
-        // directly, every store instruction would write 4 bytes per lane (two 128-byte pieces per
-        // wavefront), and the kernel is then limited by store-instruction issue, not by HBM.  So the
-        // results cross LDS: four column blocks (128 centroids) of the 32 queries are written as
-        // [query][128] and read back 16 bytes per lane, 512 contiguous bytes of a table row per
-        // half-wavefront, and stored with 16-byte stores.
-        const int64_t r0 = tile * 32;
-        const int64_t b0 = r0 / T;
-        const int t0 = (int)(r0 % T);
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const int nt = 4 * half + nb;
-                v16f acc;
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr)
-                    acc[rr] = 0.f;
-#pragma unroll
-                for (int s = 0; s < KS; ++s)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(afrag[s], bfrag[nt][s], acc, 0, 0, 0);
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr)
-                    stage[(8 * (rr / 4) + 4 * kh + (rr % 4)) * kStageStride + nb * 32 + n] = acc[rr];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int rp = 0; rp < 16; ++rp) {
-                const int row = 2 * rp + kh;                  // lanes 0..31: one query, lanes 32..63: the next
-                const lut_v4f v = *reinterpret_cast<const lut_v4f *>(stage + row * kStageStride + 4 * n);
-                const int rr = t0 + row;                      // position of the query within its batch entry, unwrapped
-                const int64_t bq = b0 + rr / T;
-                const int tq = rr % T;
-                if (r0 + row < nq) {
-                    float *dst = lut + ((((bq * H + h) * T + tq) * m) + i) * kCentroids + half * 128 + 4 * n;
-                    if (NTS)
-                        __builtin_nontemporal_store(v, reinterpret_cast<lut_v4f *>(dst));
-                    else
-                        *reinterpret_cast<lut_v4f *>(dst) = v;
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            __builtin_amdgcn_wave_barrier();              // the next half overwrites the staging area
+        int b = b0, t = r0 + n < nq ? t0 + n : t0;            // past the end: any query of the tile (not stored)
+        if (t >= T) {
+            b += t / T;
+            t %= T;
         }
-      }
+        QT qv[DSUB];
+        lut_load_row<QT, DSUB>(q + (((int64_t)b * H + h) * T + t) * d_k + (int64_t)i * DSUB, qv);
+        const float *cb = codebooks + (((int64_t)h * m + i) * kCentroids + wave * (32 * kBlocks) + n) * DSUB;
+        float cv[kBlocks][DSUB];
+#pragma unroll
+        for (int nb = 0; nb < kBlocks; ++nb)
+            lut_load_row<float, DSUB>(cb + nb * 32 * DSUB, cv[nb]);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            a[s] = kh ? to_f32<QT>(qv[2 * s + 1]) : to_f32<QT>(qv[2 * s]);
+#pragma unroll
+            for (int nb = 0; nb < kBlocks; ++nb)
+                c[nb][s] = kh ? cv[nb][2 * s + 1] : cv[nb][2 * s];
+        }
+    }
+#pragma unroll
+    for (int nb = 0; nb < kBlocks; ++nb) {
+        v16f acc;
+#pragma unroll
+        for (int rr = 0; rr < 16; ++rr)
+            acc[rr] = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], c[nb][s], acc, 0, 0, 0);
+#pragma unroll
+        for (int rr = 0; rr < 16; ++rr)
+            stage_s[(8 * (rr / 4) + 4 * kh + (rr % 4)) * kStageStride + (wave * kBlocks + nb) * 32 + n] = acc[rr];
+    }
+    __syncthreads();
+    // a wavefront stores whole table rows, one per instruction
+#pragma unroll
+    for (int k = 0; k < kMfmaRows / kMfmaWaves; ++k) {
+        const int row = k * kMfmaWaves + wave;
+        if (r0 + row >= nq)
+            break;
+        int b = b0, t = t0 + row;
+        if (t >= T) {
+            b += t / T;
+            t %= T;
+        }
+        const lut_v4f v = *reinterpret_cast<const lut_v4f *>(stage_s + row * kStageStride + 4 * lane);
+        lut_v4f *dst = reinterpret_cast<lut_v4f *>(lut + ((((int64_t)b * H + h) * T + t) * m + i) * kCentroids) + lane;
+        if (NTS)
+            __builtin_nontemporal_store(v, dst);
+        else
+            *dst = v;
     }
 }
 
@@ -215,27 +215,25 @@ static bool launch_build_lut_mfma(const lookat_shape *s, int T, const void *q, c
 {
     const int d_sub = s->d_k / s->m;
     const int64_t nq = (int64_t)s->B * T;
-    const int64_t ntiles = (nq + 31) / 32;
-    // tiles per wave: reuse the codebook fragments, but keep at least four thousand workgroups
-    int tpw = 1;
-    while (tpw < 16 && (ntiles / (kMfmaWaves * tpw * 2)) * s->m * s->H >= 4096)
-        tpw *= 2;
-    const int64_t gx = (ntiles + (int64_t)kMfmaWaves * tpw - 1) / ((int64_t)kMfmaWaves * tpw);
-    if (gx > 0x7fffffffLL)
+    const int64_t ntiles = (nq + kMfmaRows - 1) / kMfmaRows;
+    const int64_t run = T >= kMfmaRows ? T / kMfmaRows : 1;
+    const int64_t wgs = (ntiles + run - 1) / run * run * s->H * s->m;
+    if (wgs > 0xffffffLL)          // (a grid of 2^32 threads; 550 GB of tables)
         return false;
-    dim3 grid((unsigned)gx, (unsigned)s->m, (unsigned)s->H);
+    dim3 grid((unsigned)wgs);
     dim3 block(kMfmaWaves * kWave);
     const QT *qp = static_cast<const QT *>(q);
-    // tables beyond the last-level cache (256 MB) bypass it on the way out
-    const bool nts = (int64_t)nq * s->H * s->m * kCentroids * (int64_t)sizeof(float) > (int64_t)256 << 20;
+    // tables that fill the last-level cache (256 MB) bypass it on the way out (us to build / to read once by a
+    // reduction, plain and non-temporal stores: 192 MB 49 / 47 and 48 / 67; 256 MB 59 / 77 and 46 / 84)
+    const bool nts = (int64_t)nq * s->H * s->m * kCentroids * (int64_t)sizeof(float) >= (int64_t)256 << 20;
 #define LOOKAT_LUTM_CASE(D)                                                                                       \
     case D:                                                                                                       \
         if (nts)                                                                                                  \
             hipLaunchKernelGGL((build_lut_mfma_kernel<QT, D, 1>), grid, block, 0, st, qp, codebooks, lut, s->B,   \
-                               s->H, T, s->d_k, s->m, tpw);                                                       \
+                               s->H, T, s->d_k, s->m, (uint32_t)run);                                             \
         else                                                                                                      \
             hipLaunchKernelGGL((build_lut_mfma_kernel<QT, D, 0>), grid, block, 0, st, qp, codebooks, lut, s->B,   \
-                               s->H, T, s->d_k, s->m, tpw);                                                       \
+                               s->H, T, s->d_k, s->m, (uint32_t)run);                                             \
         return true;
     switch (d_sub) {
         LOOKAT_LUTM_CASE(2)
@@ -243,7 +241,7 @@ static bool launch_build_lut_mfma(const lookat_shape *s, int T, const void *q, c
         LOOKAT_LUTM_CASE(8)
         LOOKAT_LUTM_CASE(16)
     default:
-        return false;   // fragments would not fit the register file: vector kernel
+        return false;   // longer sub-vectors: vector kernel
     }
 #undef LOOKAT_LUTM_CASE
 }
