@@ -883,10 +883,9 @@ static int auto_splits_gqa(const lookat_shape *s, int group, int64_t L)
     if (group == 1)
         return auto_splits(s, L);
     int64_t want = (group >= 4 ? 256 : 512) / ((int64_t)s->B * s->H);
-    // Ranges of at least 512 keys from 2048 keys on, of 1024 below (us per fused step, ranges of 1024 / 512 keys; d_k = 128, m = 8: group 8,
-    // 32 key/value heads x 2048 keys 19.6 / 19.0, 8 x 8192 19.3 / 19.5; group 2, 64 x 2048 15.0 / 14.0; d_k = 64: group 4, 32 x
-    // 2500, m = 4 11.4 / 11.2; group 2, 16 x 3000, m = 16 13.3 / 12.4; but group 4, 32 x 1024 in one range 16.0, in two 17.1).
-    const int64_t cap = L >= 2048 ? (L + 511) / 512 : (L + 1023) / 1024;
+    // Ranges of at least 1024 keys.  With 512 (us per fused step, ranges of 1024 / 512 keys): group 2, 64 key/value heads x 2048 keys
+    // 15.0 / 14.0, but 80 x 2686 14.1 / 15.3, and group 4, 6 x 31374 keys 21.0 / 31.7 (more ranges to merge).
+    const int64_t cap = (L + 1023) / 1024;
     want = want < cap ? want : cap;
     return (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
 }

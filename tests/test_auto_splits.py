@@ -23,9 +23,9 @@ def test_auto_splits_invariants():
                     assert S == 1
                 assert lk.attend_decode_workspace_bytes(1, BH, d_k, m, L) == (0 if S == 1 else BH * S * (d_k + 2) * 4)
                 assert lk.attend_decode_gqa_workspace_bytes(1, BH, 1, d_k, m, L) == lk.attend_decode_workspace_bytes(1, BH, d_k, m, L)
-    for group, fill in ((2, 512), (4, 256), (8, 256)):        # grouped queries: ranges of 512 keys, none cut under 1025 keys
+    for group, fill in ((2, 512), (4, 256), (8, 256)):        # grouped queries: ranges of at least 1024 keys
         for BH in (1, 3, 32, 64, 200, 300, 600):
-            for L, most in ((1, 1), (1024, 1), (1025, 2), (2047, 2), (2048, 4), (2049, 5), (4096, 8), (200000, 256)):
+            for L, most in ((1, 1), (1024, 1), (1025, 2), (2047, 2), (2048, 2), (2049, 3), (4096, 4), (300000, 256)):
                 S = min(most, max(1, fill // BH))
                 assert lk.attend_decode_gqa_workspace_bytes(1, BH, group, 64, 4, L) == (0 if S == 1 else BH * group * S * 66 * 4)
     # long contexts of few pairs are cut, a little over one workgroup per compute unit too
