@@ -17,9 +17,13 @@
 //     of the two terms; two 8-byte ones at d_sub = 4) and the same coordinates of query n of every group.  The result has
 //     four consecutive keys of one query in a lane: 16-byte stores, 64 contiguous bytes of a score row;
 //   * blocks that no query of the tile may see are filled with -inf without a gather.
-// Arithmetic as in prefill_dense.hip (its error bound holds): centroids scaled by one power of two per head (largest entry
-// near 2^13), hi + lo 2^-11 carries 22 bits of every entry down to 2^-27 of the largest; fp32 queries are scaled and split
-// per query row, the product of the two small terms is dropped; fp32 accumulation over all d_k coordinates.
+// Arithmetic as in prefill_dense.hip where one power of two serves all centroids of the head (largest entry near 2^13):
+// hi + lo 2^-11 carries 22 bits of every entry down to 2^-27 of the largest and 19 down to 2^-29; fp32 queries are scaled
+// and split per query row, the product of the two small terms is dropped; fp32 accumulation over all d_k coordinates.
+// Codebooks whose entries lie further apart (or are not finite: a filler for centroids that shall never be chosen, an outlier):
+// the power of two is the one that serves most of them; the four coordinates around an entry that it does not serve are
+// stored as NaN, and 16 keys of which one meets such a NaN (or an infinite query) are scored again from the fp32 codebook in
+// plain fp32, on the fp32 matrix instruction, which takes operands and results in the same lanes.
 // What bounds it: LDS.  Per 64 keys 4 d_k / 16 reads of 1 KB at random 16-byte addresses (about 12 clocks each), then the set-up
 // of a workgroup (d_k KB of fp32 codebook through one compute unit, about 3 us).  Figures: see short_block.
 #include <type_traits>
@@ -54,15 +58,57 @@ struct PrefillShortArgs {
     int vec4;                 // L % 4 == 0 and scores 16-byte aligned
 };
 
-// A power of two that brings the largest magnitude near 2^13, and its inverse.
-__device__ __forceinline__ void ps_scale(float largest, float &scale, float &inverse)
+// A power of two that brings magnitudes of this (biased) exponent near 2^13, and its inverse.
+__device__ __forceinline__ void ps_scale(int exponent, float &scale, float &inverse)
 {
-    int se = 13 - ((int)((__float_as_uint(largest) >> 23) & 0xffu) - 127);
-    if (largest == 0.f)
-        se = 13;
+    int se = 13 - (exponent - 127);
     se = se > 100 ? 100 : (se < -100 ? -100 : se);
     scale = __uint_as_float((uint32_t)(se + 127) << 23);
     inverse = __uint_as_float((uint32_t)(127 - se) << 23);
+}
+constexpr int kPsSpan = 30;                          // exponents that one scale serves
+constexpr int kPsLowest = 40, kPsHighest = 240;      // exponents that ps_scale does not clamp
+
+__device__ __forceinline__ uint32_t ps_wave_max(uint32_t v)
+{
+    auto other = [](uint32_t a, float b) { return max(a, __float_as_uint(b)); };
+    v = other(v, dpp_mov<0xB1>(__uint_as_float(v), __uint_as_float(v)));
+    v = other(v, dpp_mov<0x4E>(__uint_as_float(v), __uint_as_float(v)));
+    v = other(v, dpp_mov<0x141>(__uint_as_float(v), __uint_as_float(v)));
+    v = other(v, dpp_mov<0x140>(__uint_as_float(v), __uint_as_float(v)));
+    float a, b;
+    lanes_xor16(__uint_as_float(v), a, b);
+    v = max(__float_as_uint(a), __float_as_uint(b));
+    lanes_xor32(__uint_as_float(v), a, b);
+    return max(__float_as_uint(a), __float_as_uint(b));
+}
+
+// Scores of 16 keys against 16 queries in plain fp32, in the lanes of the other path: lane (n, kg) brings coordinates
+// 32 s + 8 kg .. + 7 of key n (codes at cp) and of query n (q: its row, from coordinate 8 kg on); any order of the coordinates
+// serves as contraction index as long as both sides use the same one.
+template <typename QT, int DK, int M>
+__device__ __forceinline__ ps_v4f ps_plain(const float *cb_h, const uint8_t *cp, const QT *q, int kg)
+{
+    constexpr int DSUB = DK / M;
+    ps_v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int s = 0; s < DK / 32; ++s) {
+        float x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int d = 32 * s + 8 * kg + 4 * u, i = d / DSUB;
+            const ps_v4f v = *reinterpret_cast<const ps_v4f *>(cb_h + ((int64_t)i * kCentroids + cp[i]) * DSUB + d % DSUB);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[4 * u + e] = v[e];
+                y[4 * u + e] = (float)q[32 * s + 4 * u + e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], acc, 0, 0, 0);
+    }
+    return acc;
 }
 
 template <typename QT, int DK, int M, int NG>
@@ -75,7 +121,7 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
     constexpr uint32_t kTerm = DK * kCentroids * 2;   // bytes of one term's table
     static_assert(DSUB % 4 == 0, "an operand's coordinates come from one or two subspaces");
     extern __shared__ __align__(16) unsigned char smem[];   // [hi, lo][M][256][DSUB] fp16
-    __shared__ float max_s[kPsWaves];
+    __shared__ uint32_t range_s[2][kPsWaves];
 
     // all workgroups of a head on one die, whose L2 then holds its codebook, codes and queries
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
@@ -131,30 +177,80 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
 #pragma unroll
     for (int k = 0; k < NV; ++k)
         cv[k] = cb[tid + k * kPsThreads];
-    float cmax = 0.f;
+    // bits of the largest magnitude, and of the smallest that is not zero (less one; zero wraps to the top)
+    uint32_t top = 0u, low = ~0u;
 #pragma unroll
     for (int k = 0; k < NV; ++k)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            cmax = fmaxf(cmax, fabsf(cv[k][e]));
-    cmax = wave_max(cmax);
-    if (lane == 0)
-        max_s[wave] = cmax;
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t bits = __float_as_uint(cv[k][e]) & 0x7fffffffu;
+            top = max(top, bits);
+            low = min(low, bits - 1u);
+        }
+    top = ps_wave_max(top);
+    low = ~ps_wave_max(~low);
+    if (lane == 0) {
+        range_s[0][wave] = top;
+        range_s[1][wave] = low;
+    }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kPsWaves; ++w)
-        cmax = fmaxf(cmax, max_s[w]);
+    for (int w = 0; w < kPsWaves; ++w) {
+        top = max(top, range_s[0][w]);
+        low = min(low, range_s[1][w]);
+    }
+    int exponent = (int)(top >> 23);
+    // does one scale serve every entry?  (uniform over the workgroup)
+    const bool wide = top != 0u && (exponent > kPsHighest || exponent < kPsLowest || exponent - (int)((low + 1u) >> 23) >= kPsSpan);
+    if (wide) {
+        // the kPsSpan exponents that hold the largest entry of most 16-byte pieces, their lowest end as high as possible
+        uint32_t *count = reinterpret_cast<uint32_t *>(smem);      // per exponent; [256]: (pieces, 255 - top of the span)
+        if (tid <= 256)
+            count[tid] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            uint32_t bits = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                bits = max(bits, __float_as_uint(cv[k][e]) & 0x7fffffffu);
+            const int mine = (int)(bits >> 23);
+            uint64_t rest = __ballot(bits != 0u && mine < 255);
+            while (rest) {                                         // one addition per exponent and wavefront
+                const int first = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(rest));
+                const int x = __builtin_amdgcn_readlane(mine, first);
+                const uint64_t same = __ballot(mine == x) & rest;
+                if (lane == 0)
+                    atomicAdd(&count[x], (uint32_t)__popcll(same));
+                rest &= ~same;
+            }
+        }
+        __syncthreads();
+        if (tid < 255) {
+            uint32_t pieces = 0u;
+            for (int x = tid >= kPsSpan ? tid - kPsSpan + 1 : 0; x <= tid; ++x)
+                pieces += count[x];
+            atomicMax(&count[256], pieces << 8 | (uint32_t)(255 - tid));
+        }
+        __syncthreads();
+        exponent = 255 - (int)(count[256] & 255u);
+        __syncthreads();                                           // (the operands overwrite the counts)
+    }
     float scale, inv;
-    ps_scale(cmax, scale, inv);
+    ps_scale(exponent, scale, inv);
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         ps_v4h hi, lo;
+        bool served = true;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float w = scale * cv[k][e];                          // exact: a power of two
+            const float w = scale * cv[k][e];                          // exact (a power of two) where the scale serves
             hi[e] = (_Float16)w;
             lo[e] = (_Float16)((w - (float)hi[e]) * kPsLoScale);       // exact difference and scaling, one rounding
+            served = served && fabsf(w) < 0x1p14f && (cv[k][e] == 0.f || fabsf(w) >= 0x1p-17f);
         }
+        if (wide && !served)
+            hi = ps_v4h{(_Float16)NAN, (_Float16)NAN, (_Float16)NAN, (_Float16)NAN};
         *reinterpret_cast<ps_v4h *>(smem + (uint32_t)(tid + k * kPsThreads) * 8u) = hi;
         *reinterpret_cast<ps_v4h *>(smem + kTerm + (uint32_t)(tid + k * kPsThreads) * 8u) = lo;
     }
@@ -194,7 +290,7 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
                     lanes_xor16(qmax, x, y);
                     qmax = fmaxf(x, y);
                     lanes_xor32(qmax, x, y);
-                    ps_scale(fmaxf(x, y), qs, qi);
+                    ps_scale((int)(__float_as_uint(fmaxf(x, y)) >> 23), qs, qi);
                     qinv[g] *= qi;
 #pragma unroll
                     for (int s = 0; s < KS; ++s)
@@ -273,6 +369,26 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
             }
             // result register r of lane (n, kg): key lh + 4 kg + r of query n of the group
             const int64_t l = lh + 4 * kg;
+            ps_v4f sc[NG];
+            bool redo = false;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    sc[g][e] = fmaf(acc_l[g][e], 1.f / kPsLoScale, acc_h[g][e]) * qinv[g];
+                redo |= !(fabsf((sc[g][0] + sc[g][1]) + (sc[g][2] + sc[g][3])) < INFINITY);
+            }
+            if (__ballot(redo)) {   // a NaN that stands for an entry outside the scale's reach, an infinite input, or a score near the end of fp32
+                const float *cb_h = a.codebooks + (int64_t)h * M * kCentroids * DSUB;
+                const int64_t lk = lh + n < a.L ? lh + n : a.L - 1;
+                const uint8_t *cp = a.codes + ((int64_t)b_loaded * a.H + h) * a.code_stride + lk * M;
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    const int t = t0 + 16 * g + n < a.T ? t0 + 16 * g + n : a.T - 1;
+                    const QT *q = static_cast<const QT *>(a.q) + (((int64_t)b_loaded * a.H + h) * a.T + t) * DK + 8 * kg;
+                    sc[g] = ps_plain<QT, DK, M>(cb_h, cp, q, kg);
+                }
+            }
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
                 const int t = t0 + 16 * g + n;
@@ -280,7 +396,7 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
                     ps_v4f o;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        o[e] = l + e <= t + off ? fmaf(acc_l[g][e], 1.f / kPsLoScale, acc_h[g][e]) * qinv[g] : -INFINITY;
+                        o[e] = l + e <= t + off ? sc[g][e] : -INFINITY;
                     if (a.vec4) {
                         if (l < a.L)
                             *reinterpret_cast<ps_v4f *>(row[g] + l) = o;

@@ -43,3 +43,50 @@ def test_short_blocks(lk, d_k, m, dtype, B, H, T, L):
             got = out[b, h].double()
             assert bool((torch.isinf(got) & (got < 0) == unseen).all())
             assert bool(((got - ref).abs() <= bar)[~unseen].all())
+
+
+def _books(kind, rnd, H, m, d_sub):
+    """Codebooks whose entries one power of two cannot bring into two fp16 terms; centroid 7 is used by no key."""
+    cb = rnd(H, m, 256, d_sub)
+    if kind.startswith("unused "):
+        cb[:, :, 7] = float(kind.split()[1])
+    elif kind == "used 1e30":
+        cb[:, 0, 9, 0], cb[:, m - 1, 200, d_sub - 1] = 1e30, -1e30
+    elif kind == "subspaces 2^40 apart":
+        cb[:, ::2] *= 2.0 ** 40
+    elif kind == "one subspace of 1e-30":
+        cb[:, 1] *= 1e-30
+    else:
+        cb *= float(kind.split()[1])         # "all 1e30", "all 1e-30": far from 1, but together
+    return cb
+
+
+# error bar: the split keeps 2^-19 of an entry or better, fp32 sums of d_k products add d_k 2^-24 of the summed magnitudes
+@pytest.mark.parametrize("kind", ["unused 1e12", "unused 1e30", "unused inf", "unused nan", "used 1e30", "subspaces 2^40 apart",
+                                  "one subspace of 1e-30", "all 1e30", "all 1e-30"])
+@pytest.mark.parametrize("d_k,m,dtype,B,H,T,L", [(128, 16, "float16", 2, 16, 2, 3001), (128, 8, "float16", 2, 16, 8, 3000),
+                                                 (128, 2, "float16", 2, 16, 16, 3000), (64, 16, "float16", 2, 16, 16, 3000),
+                                                 (128, 16, "float16", 2, 16, 32, 7000), (128, 4, "float32", 2, 16, 24, 7000),
+                                                 (128, 16, "float32", 2, 16, 64, 7000)])
+def test_wide_codebooks(lk, kind, d_k, m, dtype, B, H, T, L):
+    g = torch.Generator(device="cuda").manual_seed(d_k + m + T)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    cb = _books(kind, rnd, H, m, d_k // m)
+    q = (rnd(B, H, T, d_k) / 8).to(getattr(torch, dtype)).view(B, H, T, m, d_k // m)
+    if "subspace" in kind:                   # every other query meets nothing but the small entries
+        large = slice(0, None, 2) if kind.startswith("subspaces") else [i for i in range(m) if i != 1]
+        q[:, :, ::2, large] = 0
+    q = q.view(B, H, T, d_k)
+    codes = torch.randint(0, 255, (B, H, L, m), generator=g, device="cuda", dtype=torch.uint8)
+    codes += (codes >= 7).to(torch.uint8)
+    out = lk.lookat_score_prefill(q, cb, codes)
+    sub = torch.arange(m, device="cuda")
+    unseen = torch.arange(L, device="cuda")[None, :] > torch.arange(L - T, L, device="cuda")[:, None]
+    for b in range(B):
+        for h in range(0, H, 5):
+            keys = cb[h][sub, codes[b, h].long()].reshape(L, d_k).double()
+            ref = q[b, h].double() @ keys.t()
+            bar = (2.0 ** -19 + d_k * 2.0 ** -24) * (q[b, h].double().abs() @ keys.abs().t())
+            got = out[b, h].double()
+            assert bool((torch.isinf(got) & (got < 0) == unseen).all())
+            assert bool(((got - ref).abs() <= bar)[~unseen].all()), float(((got - ref).abs() / bar)[~unseen].max())
