@@ -18,11 +18,11 @@
 //     four consecutive keys of one query in a lane: 16-byte stores, 64 contiguous bytes of a score row;
 //   * blocks that no query of the tile may see are filled with -inf without a gather.
 // Arithmetic as in prefill_dense.hip where one power of two serves all centroids of the head (largest entry near 2^13):
-// hi + lo 2^-11 carries 22 bits of every entry down to 2^-27 of the largest and 19 down to 2^-29; fp32 queries are scaled
+// hi + lo 2^-11 carries 22 bits of every entry down to 2^-27 of the largest and 16 down to 2^-33; fp32 queries are scaled
 // and split per query row, the product of the two small terms is dropped; fp32 accumulation over all d_k coordinates.
 // Codebooks whose entries lie further apart (or are not finite: a filler for centroids that shall never be chosen, an outlier):
 // the power of two is the one that serves most of them; the four coordinates around an entry that it does not serve are
-// stored as NaN, and 16 keys of which one meets such a NaN (or an infinite query) are scored again from the fp32 codebook in
+// stored as NaN, and 32 keys of which one meets such a NaN (or an infinite query) are scored again from the fp32 codebook in
 // plain fp32, on the fp32 matrix instruction, which takes operands and results in the same lanes.
 // What bounds it: LDS.  Per 64 keys 4 d_k / 16 reads of 1 KB at random 16-byte addresses (about 12 clocks each), then the set-up
 // of a workgroup (d_k KB of fp32 codebook through one compute unit, about 3 us).  Figures: see short_block.
@@ -66,21 +66,27 @@ __device__ __forceinline__ void ps_scale(int exponent, float &scale, float &inve
     scale = __uint_as_float((uint32_t)(se + 127) << 23);
     inverse = __uint_as_float((uint32_t)(127 - se) << 23);
 }
-constexpr int kPsSpan = 30;                          // exponents that one scale serves
+constexpr int kPsSpan = 34;                          // exponents that one scale serves
 constexpr int kPsLowest = 40, kPsHighest = 240;      // exponents that ps_scale does not clamp
 
-__device__ __forceinline__ uint32_t ps_wave_max(uint32_t v)
+// Largest value of each of the two halves over the wavefront.
+typedef unsigned short ps_v2s __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t ps_max2(uint32_t a, uint32_t b)
 {
-    auto other = [](uint32_t a, float b) { return max(a, __float_as_uint(b)); };
-    v = other(v, dpp_mov<0xB1>(__uint_as_float(v), __uint_as_float(v)));
-    v = other(v, dpp_mov<0x4E>(__uint_as_float(v), __uint_as_float(v)));
-    v = other(v, dpp_mov<0x141>(__uint_as_float(v), __uint_as_float(v)));
-    v = other(v, dpp_mov<0x140>(__uint_as_float(v), __uint_as_float(v)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ps_v2s, a), __builtin_bit_cast(ps_v2s, b)));
+}
+__device__ __forceinline__ uint32_t ps_wave_max2(uint32_t v)
+{
+    auto with = [&](float other) { v = ps_max2(v, __float_as_uint(other)); };
+    with(dpp_mov<0xB1>(__uint_as_float(v), __uint_as_float(v)));
+    with(dpp_mov<0x4E>(__uint_as_float(v), __uint_as_float(v)));
+    with(dpp_mov<0x141>(__uint_as_float(v), __uint_as_float(v)));
+    with(dpp_mov<0x140>(__uint_as_float(v), __uint_as_float(v)));
     float a, b;
     lanes_xor16(__uint_as_float(v), a, b);
-    v = max(__float_as_uint(a), __float_as_uint(b));
+    v = ps_max2(__float_as_uint(a), __float_as_uint(b));
     lanes_xor32(__uint_as_float(v), a, b);
-    return max(__float_as_uint(a), __float_as_uint(b));
+    return ps_max2(__float_as_uint(a), __float_as_uint(b));
 }
 
 // Scores of 16 keys against 16 queries in plain fp32, in the lanes of the other path: lane (n, kg) brings coordinates
@@ -91,7 +97,8 @@ __device__ __forceinline__ ps_v4f ps_plain(const float *cb_h, const uint8_t *cp,
 {
     constexpr int DSUB = DK / M;
     ps_v4f acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
+    constexpr int kUnroll = DK == 128 ? 2 : 1;      // (registers)
+#pragma unroll kUnroll
     for (int s = 0; s < DK / 32; ++s) {
         float x[8], y[8];
 #pragma unroll
@@ -121,7 +128,7 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
     constexpr uint32_t kTerm = DK * kCentroids * 2;   // bytes of one term's table
     static_assert(DSUB % 4 == 0, "an operand's coordinates come from one or two subspaces");
     extern __shared__ __align__(16) unsigned char smem[];   // [hi, lo][M][256][DSUB] fp16
-    __shared__ uint32_t range_s[2][kPsWaves];
+    __shared__ uint32_t range_s[kPsWaves];
 
     // all workgroups of a head on one die, whose L2 then holds its codebook, codes and queries
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
@@ -177,59 +184,47 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
 #pragma unroll
     for (int k = 0; k < NV; ++k)
         cv[k] = cb[tid + k * kPsThreads];
-    // bits of the largest magnitude, and of the smallest that is not zero (less one; zero wraps to the top)
-    uint32_t top = 0u, low = ~0u;
+    // largest magnitude, and twice the bits of the smallest that is not zero (less one: zero wraps to the top)
+    float top = 0.f;
+    uint32_t low = ~0u;
 #pragma unroll
     for (int k = 0; k < NV; ++k)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const uint32_t bits = __float_as_uint(cv[k][e]) & 0x7fffffffu;
-            top = max(top, bits);
-            low = min(low, bits - 1u);
+            top = fmaxf(top, fabsf(cv[k][e]));
+            low = min(low, (__float_as_uint(cv[k][e]) << 1) - 1u);
         }
-    top = ps_wave_max(top);
-    low = ~ps_wave_max(~low);
-    if (lane == 0) {
-        range_s[0][wave] = top;
-        range_s[1][wave] = low;
-    }
+    // exponents of both, the smallest's counted from the top
+    uint32_t range = ps_wave_max2((__float_as_uint(top) >> 23) << 16 | (255u - (low >> 24)));
+    if (lane == 0)
+        range_s[wave] = range;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kPsWaves; ++w) {
-        top = max(top, range_s[0][w]);
-        low = min(low, range_s[1][w]);
-    }
-    int exponent = (int)(top >> 23);
-    // does one scale serve every entry?  (uniform over the workgroup)
-    const bool wide = top != 0u && (exponent > kPsHighest || exponent < kPsLowest || exponent - (int)((low + 1u) >> 23) >= kPsSpan);
+    for (int w = 0; w < kPsWaves; ++w)
+        range = ps_max2(range, range_s[w]);
+    int exponent = (int)(range >> 16);
+    // Are there entries that one scale does not serve?  (Uniform over the workgroup.  NaN entries need no search, they stay NaN.)
+    const bool wide = exponent > kPsHighest || (exponent && exponent < kPsLowest) || exponent - (255 - (int)(range & 0xffffu)) >= kPsSpan;
     if (wide) {
-        // the kPsSpan exponents that hold the largest entry of most 16-byte pieces, their lowest end as high as possible
-        uint32_t *count = reinterpret_cast<uint32_t *>(smem);      // per exponent; [256]: (pieces, 255 - top of the span)
-        if (tid <= 256)
-            count[tid] = 0u;
+        // the kPsSpan exponents that hold the largest entry of most 16-byte pieces (an eighth of them is looked at, from all
+        // subspaces), their top end as low as possible
+        uint32_t *count = reinterpret_cast<uint32_t *>(smem) + kPsSpan;   // per exponent, zeros in front; [256]: (pieces, 255 - top of the span)
+        if (tid <= 256 + kPsSpan)
+            count[tid - kPsSpan] = 0u;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            uint32_t bits = 0u;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                bits = max(bits, __float_as_uint(cv[k][e]) & 0x7fffffffu);
-            const int mine = (int)(bits >> 23);
-            uint64_t rest = __ballot(bits != 0u && mine < 255);
-            while (rest) {                                         // one addition per exponent and wavefront
-                const int first = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(rest));
-                const int x = __builtin_amdgcn_readlane(mine, first);
-                const uint64_t same = __ballot(mine == x) & rest;
-                if (lane == 0)
-                    atomicAdd(&count[x], (uint32_t)__popcll(same));
-                rest &= ~same;
+        for (int k = 0; k < NV; ++k)
+            if (k == wave % NV) {
+                const float x = fmaxf(fmaxf(fabsf(cv[k][0]), fabsf(cv[k][1])), fmaxf(fabsf(cv[k][2]), fabsf(cv[k][3])));
+                if (x > 0.f && x < INFINITY)
+                    atomicAdd(&count[__float_as_uint(x) >> 23], 1u);
             }
-        }
         __syncthreads();
         if (tid < 255) {
             uint32_t pieces = 0u;
-            for (int x = tid >= kPsSpan ? tid - kPsSpan + 1 : 0; x <= tid; ++x)
-                pieces += count[x];
+#pragma unroll
+            for (int x = 0; x < kPsSpan; ++x)
+                pieces += count[tid - x];
             atomicMax(&count[256], pieces << 8 | (uint32_t)(255 - tid));
         }
         __syncthreads();
@@ -241,18 +236,28 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         ps_v4h hi, lo;
-        bool served = true;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float w = scale * cv[k][e];                          // exact (a power of two) where the scale serves
             hi[e] = (_Float16)w;
             lo[e] = (_Float16)((w - (float)hi[e]) * kPsLoScale);       // exact difference and scaling, one rounding
-            served = served && fabsf(w) < 0x1p14f && (cv[k][e] == 0.f || fabsf(w) >= 0x1p-17f);
         }
-        if (wide && !served)
-            hi = ps_v4h{(_Float16)NAN, (_Float16)NAN, (_Float16)NAN, (_Float16)NAN};
         *reinterpret_cast<ps_v4h *>(smem + (uint32_t)(tid + k * kPsThreads) * 8u) = hi;
         *reinterpret_cast<ps_v4h *>(smem + kTerm + (uint32_t)(tid + k * kPsThreads) * 8u) = lo;
+    }
+    if (wide) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            bool served = true;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float w = fabsf(scale * cv[k][e]);
+                served = served && w <= 65504.f && (w >= 0x1p-20f || cv[k][e] == 0.f);
+            }
+            if (!served)
+                *reinterpret_cast<ps_v4h *>(smem + (uint32_t)(tid + k * kPsThreads) * 8u) =
+                    ps_v4h{(_Float16)NAN, (_Float16)NAN, (_Float16)NAN, (_Float16)NAN};
+        }
     }
     __syncthreads();
 
@@ -316,95 +321,107 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
         }
         if (blk + 1 < blk1)
             load_codes(b, lb);                               // the next block's codes arrive while this one is scored
+        // result register r of lane (n, kg): key lh + 4 kg + r of query n of the group
+        // (both halves before the check, so that the second one's gathers do not wait behind it, except where that
+        // costs more registers than there are: 128, or 64 for two workgroups per compute unit at d_k = 64)
+        constexpr int HJ = NG == 1 && DK == 128 ? 2 : 1;
+        ps_v4f sc[2][NG];
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int64_t lh = l0 + 16 * half;
-            const uint32_t(&cw)[kCodeWords] = now[half];
-            ps_v4f acc_h[NG], acc_l[NG];
-#pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                acc_h[g] = ps_v4f{0.f, 0.f, 0.f, 0.f};
-                acc_l[g] = ps_v4f{0.f, 0.f, 0.f, 0.f};
-            }
-            if (lh < seen) {
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    // coordinates 32 s + 8 kg .. + 7 of the key
-                    ps_v8h kh, kl;
-                    if constexpr (DSUB >= 8) {
-                        uint32_t code, base;
-                        if constexpr (DSUB >= KW) {                        // one subspace for all lanes
-                            constexpr int per = DSUB / KW;
-                            const int i = s / per;
-                            code = (cw[i / 4] >> (8 * (i % 4))) & 0xffu;
-                            base = (uint32_t)(i * kCentroids * DSUB + (s % per) * KW + 8 * kg) * 2u;
-                        } else {                                           // lane groups in 2 or 4 consecutive subspaces
-                            constexpr int IPS = KW / DSUB;
-                            const int isub = kg / (DSUB / 8);
-                            code = (cw[(s * IPS) / 4] >> (8 * ((s * IPS) % 4 + isub))) & 0xffu;
-                            base = (uint32_t)((s * IPS + isub) * kCentroids * DSUB + (8 * kg) % DSUB) * 2u;
-                        }
-                        const unsigned char *p = smem + base + code * (DSUB * 2);
-                        kh = *reinterpret_cast<const ps_v8h *>(p);
-                        kl = *reinterpret_cast<const ps_v8h *>(p + kTerm);
-                    } else {                                               // d_sub = 4: two subspaces per lane
-                        const int i0 = s * 8 + 2 * kg;
-                        const uint32_t word_lo = cw[2 * s], word_hi = cw[2 * s + 1];
-                        const uint32_t two = ((kg >= 2 ? word_hi : word_lo) >> (16 * (kg & 1))) & 0xffffu;
-                        const unsigned char *p0 = smem + (uint32_t)(i0 * kCentroids + (two & 0xffu)) * 8u;
-                        const unsigned char *p1 = smem + (uint32_t)((i0 + 1) * kCentroids + (two >> 8)) * 8u;
-                        const ps_v4h h0 = *reinterpret_cast<const ps_v4h *>(p0), h1 = *reinterpret_cast<const ps_v4h *>(p1);
-                        const ps_v4h g0 = *reinterpret_cast<const ps_v4h *>(p0 + kTerm), g1 = *reinterpret_cast<const ps_v4h *>(p1 + kTerm);
-                        kh = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
-                        kl = __builtin_shufflevector(g0, g1, 0, 1, 2, 3, 4, 5, 6, 7);
-                    }
-#pragma unroll
-                    for (int g = 0; g < NG; ++g) {
-                        acc_h[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[g][s], acc_h[g], 0, 0, 0);
-                        acc_l[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[g][s], acc_l[g], 0, 0, 0);
-                        if constexpr (Q32)
-                            acc_l[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, ql[g][s], acc_l[g], 0, 0, 0);
-                    }
-                }
-            }
-            // result register r of lane (n, kg): key lh + 4 kg + r of query n of the group
-            const int64_t l = lh + 4 * kg;
-            ps_v4f sc[NG];
+        for (int half0 = 0; half0 < 2; half0 += HJ) {
             bool redo = false;
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
+            for (int half = half0; half < half0 + HJ; ++half) {
+                const int64_t lh = l0 + 16 * half;
+                const uint32_t(&cw)[kCodeWords] = now[half];
+                ps_v4f acc_h[NG], acc_l[NG];
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    sc[g][e] = fmaf(acc_l[g][e], 1.f / kPsLoScale, acc_h[g][e]) * qinv[g];
-                redo |= !(fabsf((sc[g][0] + sc[g][1]) + (sc[g][2] + sc[g][3])) < INFINITY);
+                for (int g = 0; g < NG; ++g) {
+                    acc_h[g] = ps_v4f{0.f, 0.f, 0.f, 0.f};
+                    acc_l[g] = ps_v4f{0.f, 0.f, 0.f, 0.f};
+                }
+                if (lh < seen) {
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) {
+                        // coordinates 32 s + 8 kg .. + 7 of the key
+                        ps_v8h kh, kl;
+                        if constexpr (DSUB >= 8) {
+                            uint32_t code, base;
+                            if constexpr (DSUB >= KW) {                        // one subspace for all lanes
+                                constexpr int per = DSUB / KW;
+                                const int i = s / per;
+                                code = (cw[i / 4] >> (8 * (i % 4))) & 0xffu;
+                                base = (uint32_t)(i * kCentroids * DSUB + (s % per) * KW + 8 * kg) * 2u;
+                            } else {                                           // lane groups in 2 or 4 consecutive subspaces
+                                constexpr int IPS = KW / DSUB;
+                                const int isub = kg / (DSUB / 8);
+                                code = (cw[(s * IPS) / 4] >> (8 * ((s * IPS) % 4 + isub))) & 0xffu;
+                                base = (uint32_t)((s * IPS + isub) * kCentroids * DSUB + (8 * kg) % DSUB) * 2u;
+                            }
+                            const unsigned char *p = smem + base + code * (DSUB * 2);
+                            kh = *reinterpret_cast<const ps_v8h *>(p);
+                            kl = *reinterpret_cast<const ps_v8h *>(p + kTerm);
+                        } else {                                               // d_sub = 4: two subspaces per lane
+                            const int i0 = s * 8 + 2 * kg;
+                            const uint32_t word_lo = cw[2 * s], word_hi = cw[2 * s + 1];
+                            const uint32_t two = ((kg >= 2 ? word_hi : word_lo) >> (16 * (kg & 1))) & 0xffffu;
+                            const unsigned char *p0 = smem + (uint32_t)(i0 * kCentroids + (two & 0xffu)) * 8u;
+                            const unsigned char *p1 = smem + (uint32_t)((i0 + 1) * kCentroids + (two >> 8)) * 8u;
+                            const ps_v4h h0 = *reinterpret_cast<const ps_v4h *>(p0), h1 = *reinterpret_cast<const ps_v4h *>(p1);
+                            const ps_v4h g0 = *reinterpret_cast<const ps_v4h *>(p0 + kTerm), g1 = *reinterpret_cast<const ps_v4h *>(p1 + kTerm);
+                            kh = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
+                            kl = __builtin_shufflevector(g0, g1, 0, 1, 2, 3, 4, 5, 6, 7);
+                        }
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) {
+                            acc_h[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[g][s], acc_h[g], 0, 0, 0);
+                            acc_l[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[g][s], acc_l[g], 0, 0, 0);
+                            if constexpr (Q32)
+                                acc_l[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, ql[g][s], acc_l[g], 0, 0, 0);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        sc[half][g][e] = fmaf(acc_l[g][e], 1.f / kPsLoScale, acc_h[g][e]) * qinv[g];
+                    redo |= !(fabsf((sc[half][g][0] + sc[half][g][1]) + (sc[half][g][2] + sc[half][g][3])) < INFINITY);
+                }
             }
             if (__ballot(redo)) {   // a NaN that stands for an entry outside the scale's reach, an infinite input, or a score near the end of fp32
                 const float *cb_h = a.codebooks + (int64_t)h * M * kCentroids * DSUB;
-                const int64_t lk = lh + n < a.L ? lh + n : a.L - 1;
-                const uint8_t *cp = a.codes + ((int64_t)b_loaded * a.H + h) * a.code_stride + lk * M;
+                const uint8_t *codes_b = a.codes + ((int64_t)b_loaded * a.H + h) * a.code_stride;
 #pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    const int t = t0 + 16 * g + n < a.T ? t0 + 16 * g + n : a.T - 1;
-                    const QT *q = static_cast<const QT *>(a.q) + (((int64_t)b_loaded * a.H + h) * a.T + t) * DK + 8 * kg;
-                    sc[g] = ps_plain<QT, DK, M>(cb_h, cp, q, kg);
+                for (int half = half0; half < half0 + HJ; ++half) {
+                    const int64_t lk = l0 + 16 * half + n < a.L ? l0 + 16 * half + n : a.L - 1;
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) {
+                        const int t = t0 + 16 * g + n < a.T ? t0 + 16 * g + n : a.T - 1;
+                        const QT *q = static_cast<const QT *>(a.q) + (((int64_t)b_loaded * a.H + h) * a.T + t) * DK + 8 * kg;
+                        sc[half][g] = ps_plain<QT, DK, M>(cb_h, codes_b + lk * M, q, kg);
+                    }
                 }
             }
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                const int t = t0 + 16 * g + n;
-                if (t < a.T) {
-                    ps_v4f o;
+            for (int half = half0; half < half0 + HJ; ++half) {
+                const int64_t l = l0 + 16 * half + 4 * kg;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        o[e] = l + e <= t + off ? sc[g][e] : -INFINITY;
-                    if (a.vec4) {
-                        if (l < a.L)
-                            *reinterpret_cast<ps_v4f *>(row[g] + l) = o;
-                    } else {
+                for (int g = 0; g < NG; ++g) {
+                    const int t = t0 + 16 * g + n;
+                    if (t < a.T) {
+                        ps_v4f o;
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
-                            if (l + e < a.L)
-                                row[g][l + e] = o[e];
+                            o[e] = l + e <= t + off ? sc[half][g][e] : -INFINITY;
+                        if (a.vec4) {
+                            if (l < a.L)
+                                *reinterpret_cast<ps_v4f *>(row[g] + l) = o;
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (l + e < a.L)
+                                    row[g][l + e] = o[e];
+                        }
                     }
                 }
             }
