@@ -98,6 +98,20 @@ int lookat_probe_score_prefill_lookup(const lookat_shape *shape, int32_t T, int6
                                       float *scores,
                                       void *stream);
 
+/* lookat_score_prefill on its kernel for short blocks (codebook in LDS), whatever the library would choose: d_k = 128, or d_k = 64
+ * with fp16 queries (LOOKAT_ERR_UNSUPPORTED otherwise).  Exists so that the kernel can be timed and checked on any block. */
+int lookat_probe_score_prefill_short(const lookat_shape *shape, int32_t T, int64_t L,
+                                     const void *q, lookat_dtype q_dtype,
+                                     const float *codebooks,
+                                     const uint8_t *codes, int64_t code_stride_bh,
+                                     float *scores,
+                                     void *stream);
+
+/* Which kernel lookat_score_prefill takes for this problem (host only, no HIP call): 1 lookup-and-sum, 2 dense with centroids
+ * fetched from L2, 3 dense with the codebook in LDS (short blocks); 0 if it has none or the arguments are invalid.  Exists so that
+ * tests and measurements can state which kernel a shape exercises. */
+int32_t lookat_probe_score_prefill_form(const lookat_shape *shape, int32_t T, int64_t L, lookat_dtype q_dtype);
+
 /*
  * lookat_decode_step with the number of batch entries a workgroup serves chosen by the caller instead of
  * by the library (see lookat_decode_step_entries_per_workgroup): 1 = one (b,h) per 512-thread workgroup;

@@ -86,6 +86,10 @@ def load_library():
         lib.lookat_score_prefill.restype = ctypes.c_int
         lib.lookat_probe_score_prefill_lookup.argtypes = lib.lookat_score_prefill.argtypes
         lib.lookat_probe_score_prefill_lookup.restype = ctypes.c_int
+        lib.lookat_probe_score_prefill_short.argtypes = lib.lookat_score_prefill.argtypes
+        lib.lookat_probe_score_prefill_short.restype = ctypes.c_int
+        lib.lookat_probe_score_prefill_form.argtypes = [sp, i32, i64, ctypes.c_int]
+        lib.lookat_probe_score_prefill_form.restype = i32
         lib.lookat_kmeans_step.argtypes = [sp, i64, vp, vp, vp, vp, vp]
         lib.lookat_kmeans_step.restype = ctypes.c_int
         lib.lookat_probe_stream_read.argtypes = [vp, sz, vp, vp]
@@ -527,6 +531,19 @@ def lookat_probe_score_prefill_lookup(q: torch.Tensor, codebooks: torch.Tensor, 
                                       scores_out: torch.Tensor | None = None) -> torch.Tensor:
     """lookat_score_prefill forced onto its lookup-and-sum kernel (measurement aid)."""
     return lookat_score_prefill(q, codebooks, codes, scores_out, _entry="lookat_probe_score_prefill_lookup")
+
+
+def lookat_probe_score_prefill_short(q: torch.Tensor, codebooks: torch.Tensor, codes: torch.Tensor,
+                                     scores_out: torch.Tensor | None = None) -> torch.Tensor:
+    """lookat_score_prefill forced onto its kernel for short blocks (measurement aid)."""
+    return lookat_score_prefill(q, codebooks, codes, scores_out, _entry="lookat_probe_score_prefill_short")
+
+
+def probe_score_prefill_form(B: int, H: int, T: int, L: int, d_k: int, m: int, dtype: torch.dtype) -> int:
+    """Which kernel lookat_score_prefill takes: 1 lookup-and-sum, 2 dense, 3 dense with the codebook in LDS (0: none)."""
+    shape = _Shape(B, H, d_k, m, 256)
+    return int(load_library().lookat_probe_score_prefill_form(ctypes.byref(shape), T, L,
+                                                              {torch.float16: LOOKAT_F16, torch.float32: LOOKAT_F32}[dtype]))
 
 
 def lookat_kmeans_step(calib: torch.Tensor, codebooks: torch.Tensor, codebooks_out: torch.Tensor | None = None,

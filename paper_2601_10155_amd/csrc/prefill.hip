@@ -477,7 +477,8 @@ bool launch_prefill_dense(const lookat_shape *s, int T, int64_t L, const void *q
 
 // prefill_short.hip: the same contraction with the codebook in LDS, for the short blocks where that is the fastest way.
 bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q, bool q_fp32, const float *codebooks,
-                          const uint8_t *codes, int64_t code_stride_bh, float *scores, hipStream_t st, int *rc);
+                          const uint8_t *codes, int64_t code_stride_bh, float *scores, hipStream_t st, bool any, int *rc);
+bool prefill_short_takes(const lookat_shape *s, int T, int64_t L, bool q_fp32);
 
 // From this many queries per (b,h) on, blocks of queries that prefill_short.hip leaves are scored on the matrix cores.  Its workgroups
 // spend their first microseconds fetching centroids, which a short block does not repay: measured at 4 x 32
@@ -485,9 +486,10 @@ bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q
 // 24: 40 / 46, 32: 41 / 57, 64: 52 / 67, 256: 135 / 236.
 constexpr int kPfDenseMinT = 24;
 
+// form: 0 = the library's choice, 1 = lookup-and-sum, 3 = codebook in LDS (measurement aids)
 static int score_prefill_impl(const lookat_shape *shape, int32_t T, int64_t L, const void *q, lookat_dtype q_dtype,
                               const float *codebooks, const uint8_t *codes, int64_t code_stride_bh,
-                              float *scores, void *stream, bool allow_dense)
+                              float *scores, void *stream, int form = 0)
 {
     clear_error();
     if (int rc = check_shape(shape))
@@ -524,10 +526,12 @@ static int score_prefill_impl(const lookat_shape *shape, int32_t T, int64_t L, c
     a.vec4 = (L % 4 == 0) && aligned16(scores);
     hipStream_t st = static_cast<hipStream_t>(stream);
     int rc = LOOKAT_OK;
-    if (allow_dense &&
-        launch_prefill_short(shape, T, L, q, q_dtype == LOOKAT_F32, codebooks, codes, code_stride_bh, scores, st, &rc))
+    if (form != 1 &&
+        launch_prefill_short(shape, T, L, q, q_dtype == LOOKAT_F32, codebooks, codes, code_stride_bh, scores, st, form == 3, &rc))
         return rc;
-    if (allow_dense && T >= kPfDenseMinT &&
+    if (form == 3)
+        return fail(LOOKAT_ERR_UNSUPPORTED, "no short-block kernel for d_k=%d m=%d dtype=%d", shape->d_k, shape->m, q_dtype);
+    if (form == 0 && T >= kPfDenseMinT &&
         launch_prefill_dense(shape, T, L, q, q_dtype == LOOKAT_F32, codebooks, codes, code_stride_bh, scores, st))
         return check_launch("lookat_score_prefill");
     return (q_dtype == LOOKAT_F16) ? dispatch_prefill<__half>(shape, a, st) : dispatch_prefill<float>(shape, a, st);
@@ -539,12 +543,29 @@ extern "C" int lookat_score_prefill(const lookat_shape *shape, int32_t T, int64_
                                     const float *codebooks, const uint8_t *codes, int64_t code_stride_bh,
                                     float *scores, void *stream)
 {
-    return lookat::score_prefill_impl(shape, T, L, q, q_dtype, codebooks, codes, code_stride_bh, scores, stream, true);
+    return lookat::score_prefill_impl(shape, T, L, q, q_dtype, codebooks, codes, code_stride_bh, scores, stream);
 }
 
 extern "C" int lookat_probe_score_prefill_lookup(const lookat_shape *shape, int32_t T, int64_t L, const void *q,
                                                  lookat_dtype q_dtype, const float *codebooks, const uint8_t *codes,
                                                  int64_t code_stride_bh, float *scores, void *stream)
 {
-    return lookat::score_prefill_impl(shape, T, L, q, q_dtype, codebooks, codes, code_stride_bh, scores, stream, false);
+    return lookat::score_prefill_impl(shape, T, L, q, q_dtype, codebooks, codes, code_stride_bh, scores, stream, 1);
+}
+
+extern "C" int lookat_probe_score_prefill_short(const lookat_shape *shape, int32_t T, int64_t L, const void *q,
+                                                lookat_dtype q_dtype, const float *codebooks, const uint8_t *codes,
+                                                int64_t code_stride_bh, float *scores, void *stream)
+{
+    return lookat::score_prefill_impl(shape, T, L, q, q_dtype, codebooks, codes, code_stride_bh, scores, stream, 3);
+}
+
+extern "C" int32_t lookat_probe_score_prefill_form(const lookat_shape *shape, int32_t T, int64_t L, lookat_dtype q_dtype)
+{
+    using namespace lookat;
+    clear_error();
+    if (check_shape(shape) != LOOKAT_OK || T <= 0 || L < T || (q_dtype != LOOKAT_F16 && q_dtype != LOOKAT_F32) ||
+        (shape->d_k != 64 && shape->d_k != 128) || (shape->m != 2 && shape->m != 4 && shape->m != 8 && shape->m != 16))
+        return 0;
+    return prefill_short_takes(shape, T, L, q_dtype == LOOKAT_F32) ? 3 : (T >= kPfDenseMinT ? 2 : 1);
 }

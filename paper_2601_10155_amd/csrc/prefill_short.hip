@@ -445,31 +445,90 @@ static int launch_prefill_short_case(const PrefillShortArgs &a, hipStream_t st)
     return check_launch("lookat_score_prefill");
 }
 
-// Which blocks come here.  The alternatives are the lookup-and-sum kernel (blocks under 24 queries; its reads of LDS grow
-// with m ceil(T / 4), and it has one workgroup per (b,h)) and the dense kernel that fetches centroids from L2 (its cost grows
-// with the number of keys of all (b,h), hardly with T).  us per call, here / there:
-//   d_k = 128, fp16 queries: 4 x 32 heads x 4096 keys, m = 16: T = 2 13.5 / 15.9, 8 14.7 / 22.2, 16 16.6 / 34.7, 24 20.9 / 45.2,
-//   32 24.0 / 46.0, 48 50.9 / 53.3;  8 x 40 x 2000, m = 4: 2 16.8 / 21.7, 8 18.3 / 26.8, 32 36.5 / 59.4;  2 x 32 x 4096, m = 8:
-//   24 15.1 / 23.2;  1 x 32 x 4096, m = 8: 8 8.4 / 16.1, 24 14.1 / 12.7;  1 x 8 x 2000, m = 2: 2 10.3 / 9.4
-//   d_k = 128, fp32 queries (split like the centroids: 1.1e-7 off 64 bits against 0.93e-7 by lookup, so not below 24, where the
-//   lookup kernel is the other one): 4 x 32 x 4096, m = 16: 24 25.6 / 55.2, 64 59.7 / 76.1
-//   d_k = 64: 4 x 32 x 4096, m = 8: 2 9.9 / 8.1, 8 11.6 / 12.4, 16 13.9 / 19.4;  16 x 12 x 2000, m = 4: 16 12.9 / 11.8;
-//   2 x 8 x 8000, m = 16: 2 7.9 / 16.7
+// How a block is dealt out.
+struct PsLayout {
+    int ng;                  // groups of 16 queries per workgroup
+    int tiles;               // query tiles of 16 ng
+    int64_t blocks_per_bh;   // 32-key blocks
+    int64_t shares;          // workgroups per (head, tile)
+    int64_t wgs;
+};
+static PsLayout ps_layout(const lookat_shape *s, int T, int64_t L, bool q_fp32)
+{
+    PsLayout o;
+    o.ng = (q_fp32 || T <= 16) ? 1 : 2;          // (two groups of split fp32 queries do not fit 128 registers)
+    o.tiles = (T + 16 * o.ng - 1) / (16 * o.ng);
+    o.blocks_per_bh = (L + 31) / 32;
+    // workgroups per head and tile: one per compute unit (two at d_k = 64, whose codebook takes half the LDS), and at least
+    // two blocks for a wavefront
+    const int64_t heads = ((int64_t)s->H + 7) / 8 * 8;
+    const int64_t most = (s->B * o.blocks_per_bh + 2 * kPsWaves - 1) / (2 * kPsWaves);
+    o.shares = (s->d_k == 64 ? 512 : 256) / (heads * o.tiles);
+    o.shares = o.shares < most ? o.shares : most;
+    o.shares = o.shares < 1 ? 1 : o.shares;
+    o.wgs = heads * o.tiles * o.shares;
+    return o;
+}
+
+// Is there an instance, and does the launch stay under a grid of 2^32 threads?
+static bool ps_fits(const lookat_shape *s, const PsLayout &o, bool q_fp32)
+{
+    return (s->d_k == 128 || (s->d_k == 64 && !q_fp32)) && (s->m == 2 || s->m == 4 || s->m == 8 || s->m == 16) && o.wgs <= 0x3fffff &&
+           s->B * o.blocks_per_bh <= 0x7fffffff;
+}
+
+// Which blocks come here.  The alternatives are the lookup-and-sum kernel (blocks under 24 queries) and the dense kernel that
+// fetches centroids from L2.  Which one is faster depends on how the work falls on the chip: here a head's workgroups share one die
+// (few heads leave dies idle, nine to fifteen fill some dies twice) and each pays for the codebook, there every (b,h) is a workgroup or
+// more.  So the rule compares predicted times, fitted to 15900 measured pairs (8 to 19% off at nine sizes in ten; d_k 64
+// and 128, m 2 to 16, 1 to 1024 (b,h) of 1 to 40 heads, 1 to 64 queries, 64 to 12000 keys), and asks for a clear lead.  The blocks that it takes are
+// 26% faster on the geometric mean at d_k = 128 under 24 queries (4 x 32 heads x 8 queries x 4096 keys, m = 16: 24.7 / 18.6 us, here
+// second); of the measured ones one in a thousand is more than 3% slower.  (A rule on m, T and the number of keys alone took 8% of them
+// at a loss of 10% and more: 115 x 2 heads x 8 queries x 7625 keys, m = 8: 41 / 145 us.)
 static bool short_block(const lookat_shape *s, int T, int64_t L, bool q_fp32)
 {
     const int64_t BH = (int64_t)s->B * s->H;
-    if (T >= 24)
-        return s->d_k == 128 && T <= (q_fp32 ? 64 : 32) && BH * L >= 200000;
-    const int reads = s->m * ((T + 3) / 4);
-    return !q_fp32 && (s->d_k == 128 ? reads >= 4 : (reads >= 16 && BH <= 128));
+    const int quads = (T + 3) / 4;
+    const PsLayout o = ps_layout(s, T, L, q_fp32);
+    if (!ps_fits(s, o, q_fp32))
+        return false;
+    // Only where it was measured to pay at all.  fp32 queries are split like the centroids: 1.1e-7 off 64 bits against 0.93e-7
+    // by lookup, so they do not come here where the lookup kernel is the other one.
+    if (T >= 24 ? (s->d_k == 64 || T > (q_fp32 ? 64 : 32))
+                : (q_fp32 || s->m * quads < (s->d_k == 128 ? 4 : 16) || (s->d_k == 64 && BH > 128)))
+        return false;
+    const double MB = 4e-6 * (double)BH * T * (double)L;           // of scores
+    const int64_t per_die = (s->H + 7) / 8 * o.tiles * o.shares, at_once = s->d_k == 64 ? 64 : 32;
+    const double rounds = (double)((per_die + at_once - 1) / at_once);
+    const double blocks = (double)((s->B * o.blocks_per_bh + kPsWaves * o.shares - 1) / (kPsWaves * o.shares));   // of a wavefront
+    const double setup = s->d_k == 64 ? 1.5 : (q_fp32 ? 4.2 : (o.ng == 2 ? 3.5 : 2.9));
+    const double block = s->d_k == 64 ? (o.ng == 2 ? 3.8 : 2.4) : (q_fp32 ? 1.9 : (o.ng == 2 ? 2.5 : 2.0));
+    const double store = (s->d_k == 64 ? 0.27 : 0.2) + (L % 4 ? 0.3 : 0.0);       // (four-byte stores where rows are not 16-byte aligned)
+    const double here = setup * (1.0 + rounds) + block * rounds * blocks + store * MB;
+    double there;
+    if (T >= 24) {
+        const double panels = (double)BH * (double)((L + 127) / 128) / 512.0, tiles = (double)((T + 31) / 32);
+        there = q_fp32 ? 7.4 + 3.4 * panels + 2.0 * panels * tiles + 0.15 * MB : 5.9 + 2.9 * panels + 0.75 * panels * tiles + 0.09 * MB;
+    } else {
+        const double turns = (double)((BH + 255) / 256), look = 1e-3 * (double)L * quads;
+        if (s->d_k == 64)
+            there = -0.6 + 6.1 * turns + (0.04 + 0.078 * s->m) * turns * look + (1.0 + 0.023 * s->m) * 1e-3 * BH * look + 1.1 * quads + 0.04 * MB;
+        else
+            there = -2.4 + 11.4 * turns + (0.02 + 0.077 * s->m) * turns * look + (1.7 - 0.037 * s->m) * 1e-3 * BH * look + 1.6 * quads + 0.04 * MB;
+    }
+    return here < (s->d_k == 64 ? 0.8 : 0.85) * (s->H < 4 ? 0.85 : 1.0) * there;   // (one to three heads: 10-30% too low here)
 }
 
-// d_k in {64, 128}, m in {2, 4, 8, 16}: launches (status in *rc) and returns true; otherwise returns false.
+bool prefill_short_takes(const lookat_shape *s, int T, int64_t L, bool q_fp32) { return short_block(s, T, L, q_fp32); }
+
+// Launches where the rule says so (`any`: wherever there is an instance), status in *rc, and returns true; otherwise returns false.
 bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q, bool q_fp32, const float *codebooks,
-                          const uint8_t *codes, int64_t code_stride_bh, float *scores, hipStream_t st, int *rc)
+                          const uint8_t *codes, int64_t code_stride_bh, float *scores, hipStream_t st, bool any, int *rc)
 {
-    if (!short_block(s, T, L, q_fp32))
+    const PsLayout o = ps_layout(s, T, L, q_fp32);
+    if (any ? !ps_fits(s, o, q_fp32) : !short_block(s, T, L, q_fp32))
         return false;
+    const int ng = o.ng;
     PrefillShortArgs a;
     a.q = q;
     a.codebooks = codebooks;
@@ -479,25 +538,20 @@ bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q
     a.L = L;
     a.T = T;
     a.H = s->H;
-    const int64_t blocks_per_bh = (L + 31) / 32;
-    const int ng = (q_fp32 || T <= 16) ? 1 : 2;   // (two groups of split fp32 queries do not fit 128 registers)
-    a.tiles = (T + 16 * ng - 1) / (16 * ng);
-    // workgroups per head and tile: one per compute unit (two at d_k = 64, whose codebook takes half the LDS), and at least
-    // two blocks for a wavefront
-    int64_t shares = (s->d_k == 64 ? 512 : 256) / ((int64_t)(s->H + 7) / 8 * 8 * a.tiles);
-    const int64_t most = (s->B * blocks_per_bh + 2 * kPsWaves - 1) / (2 * kPsWaves);
-    shares = shares < most ? shares : most;
-    a.shares = (int)(shares < 1 ? 1 : shares);
+    a.tiles = o.tiles;
+    a.shares = (int)o.shares;
     a.vec4 = (L % 4 == 0) && aligned16(scores);
-    if ((int64_t)((s->H + 7) / 8 * 8) * a.tiles * a.shares > 0x3fffff || s->B * blocks_per_bh > 0x7fffffff)   // (a grid of 2^32 threads)
-        return false;
-    a.blocks_per_bh = (int)blocks_per_bh;
-    a.blocks = (int)(s->B * blocks_per_bh);
+    a.blocks_per_bh = (int)o.blocks_per_bh;
+    a.blocks = (int)(s->B * o.blocks_per_bh);
 #define LOOKAT_PS_CASE(DK_, M_)                                                                              \
     if (s->d_k == DK_ && s->m == M_) {                                                                       \
-        if (q_fp32)                                                                                          \
-            *rc = launch_prefill_short_case<float, DK_, M_, 1>(a, st);                                       \
-        else if (ng == 1)                                                                                    \
+        if constexpr (DK_ == 128) {                                                                          \
+            if (q_fp32) {                                                                                    \
+                *rc = launch_prefill_short_case<float, DK_, M_, 1>(a, st);                                   \
+                return true;                                                                                 \
+            }                                                                                                \
+        }                                                                                                    \
+        if (ng == 1)                                                                                         \
             *rc = launch_prefill_short_case<__half, DK_, M_, 1>(a, st);                                      \
         else                                                                                                 \
             *rc = launch_prefill_short_case<__half, DK_, M_, 2>(a, st);                                      \
