@@ -303,7 +303,7 @@ static void launch_encode(const lookat_shape *s, int64_t N, const void *keys, co
 #undef LOOKAT_ENC_CASE
 }
 
-// encode_filter.hip: matrix-core filter in front of the exact rule (d_sub up to 64)
+// encode_filter.hip: matrix-core filter in front of the exact rule (d_sub 2 to 64)
 bool launch_encode_filter(const lookat_shape *s, int64_t N, const void *keys, int key_dtype, const float *codebooks,
                           uint8_t *codes, int64_t code_stride_bh, hipStream_t st);
 
