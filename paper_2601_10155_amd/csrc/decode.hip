@@ -374,9 +374,13 @@ __device__ __forceinline__ void load_centroid_rows(float (&row)[GS][DSUB], const
 // all rows of a group requested together.
 // `encode`: this workgroup's range holds position L-1 (with several ranges per (b,h) only the last one
 // scores the new key and appends its codes; the others build the table alone).
+// SKIP: a workgroup that does not encode skips the distances, half of the arithmetic (32 (b,h) x 8003 keys in 8 ranges, d_k =
+// 128, m = 8: 17.8 -> 14.2 us of kernel).  The branch keeps the table's and the distances' arithmetic apart, which costs a
+// workgroup that does encode 1 us at d_k = 64, m = 8 and, at d_k = 128, m = 16, the registers of a third workgroup per
+// compute unit (77 -> 106; 640 (b,h) x 104 keys 17.6 -> 23.6 us), so one range per (b,h) goes without.
 // G > 1 (grouped queries): bh is the key/value head; the G query heads bh*G .. bh*G+G-1 each get their
 // table (lut_s[g][i][c]) from the one pass over the key/value head's codebook rows.
-template <typename FT, int DK, int M, int G = 1, int NB = 1>
+template <typename FT, int DK, int M, int G, int NB, bool SKIP>
 __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int part, int tid, int lane, int wave,
                                               float *lut_s, double *enc_d, int *enc_c, int lds_stride, bool encode)
 {
@@ -386,10 +390,6 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
     // bytes apart), so that the pair reads the head's codebook once instead of twice.
     static_assert(NB == 1 || (NB == 2 && G == 1 && M % 2 == 0), "paired batch entries: ungrouped, even m");
     constexpr int DSUB = DK / M;
-    // A range without the new key skips the distances (they are half of the arithmetic; 32 (b,h) x 8003 keys in 8 ranges,
-    // d_k = 128, m = 8: 17.8 -> 14.2 us of kernel) -- except with 16 subspaces of 4, where the branch costs registers that
-    // the 128 do not hold.
-    constexpr bool kAlways = G == 1 && DK == 64 && M == 16;
     constexpr int MS = M / NB;            // subspaces this builder group covers
     // rows held at once: 64 registers; paired entries keep two entries' distances alive, so there short rows
     // (d_sub < 16) are taken 16 registers at a time and, at d_k = 128 (twice the tile registers), longer ones 32
@@ -445,12 +445,12 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
                         e = fmaf(uniform_elem<FT>(qg[nb], hq * DK + i * DSUB + j), frow[g][j], e);
                     lut_nb[(hq * M + i) * kCentroids + tid] = e;
                 }
-                if (kAlways || encode) {
+                if (!SKIP || encode) {
                     dv[g] = argmin_value(step_sq_dist<FT, DSUB>(kg[nb], i * DSUB, frow[g]), tid);
                     dm[g] = dv[g];
                 }
             }
-            if (kAlways || encode) {
+            if (!SKIP || encode) {
                 dmin_wave<GS>(dm);
 #pragma unroll
                 for (int g = 0; g < GS; ++g) {
@@ -485,7 +485,7 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
 // PAD (tables given, ungrouped): the head size is a.d_k < DK, a multiple of 8; lanes past the end of a row repeat its last
 // 16 bytes and their sums are not written.
 template <int DK, int M, int WAVES, int OCC, typename FT = void, int G = 1, int PF = 1, int NB = 1, bool PAD = false,
-          bool LONE = false>
+          bool LONE = false, bool SKIP = (G > 1)>
 __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOOKAT_DECODE_HEAD_PARAMS,
                                                                              const DecodeLate late)
 {
@@ -608,7 +608,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
             // compute unit's memory queue before the tile requests fill it
             __builtin_amdgcn_s_setprio(3);
             // (paired entries: the LDS blocks and the (b,h) index are handed over as entry 0's)
-            step_prologue<FT, DK, M, G, NB>(a, bh - hf * a.H, hf, tid, lane, wave,
+            step_prologue<FT, DK, M, G, NB, SKIP>(a, bh - hf * a.H, hf, tid, lane, wave,
                                             reinterpret_cast<float *>(reinterpret_cast<char *>(lut_s) - hf * kHalfBytes),
                                             reinterpret_cast<double *>(reinterpret_cast<char *>(enc_d) - hf * kHalfBytes),
                                             reinterpret_cast<int *>(reinterpret_cast<char *>(enc_c) - hf * kHalfBytes),
@@ -950,44 +950,37 @@ static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
     dim3 block(kStepWaves * kWave);
     const size_t lds = ((size_t)a.m * kCentroids + (size_t)kStepWaves * (DK + 2)) * sizeof(float) +
                        (size_t)a.m * kDecWaves * (sizeof(double) + sizeof(int));
-    if constexpr (DK == 128) {
-        if ((int64_t)a.BH * a.splits <= 256) {
-#define LOOKAT_STEP_LONE(M_)                                                                                              \
+    const bool lone = DK == 128 && (int64_t)a.BH * a.splits <= 256;
+    const bool skip = a.splits > 1;
+#define LOOKAT_STEP_LAUNCH(M_, OCC_, PF_, LONE_, SKIP_)                                                                   \
+    hipLaunchKernelGGL((decode_split_kernel<DK, M_, kStepWaves, OCC_, FT, 1, PF_, 1, false, LONE_, SKIP_>), grid, block,  \
+                       lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true), late_of(a))
+#define LOOKAT_STEP_CASE(M_)                                                                                              \
     case M_:                                                                                                              \
-        hipLaunchKernelGGL((decode_split_kernel<DK, M_, kStepWaves, 2, FT, 1, 2, 1, false, true>), grid, block, lds, st,  \
-                           LOOKAT_DECODE_HEAD_ARGS(a, true), late_of(a));                                                 \
+        if constexpr (DK == 128) {                                                                                        \
+            if (lone) {                                                                                                   \
+                if (skip)                                                                                                 \
+                    LOOKAT_STEP_LAUNCH(M_, 2, 2, true, true);                                                             \
+                else                                                                                                      \
+                    LOOKAT_STEP_LAUNCH(M_, 2, 2, true, false);                                                            \
+                return true;                                                                                              \
+            }                                                                                                             \
+        }                                                                                                                 \
+        if (skip && !(DK == 64 && M_ == 16))   /* (there the branch costs registers that the 128 do not hold) */          \
+            LOOKAT_STEP_LAUNCH(M_, 4, (M_ == 16 ? 1 : kStepPrefetch), false, (DK != 64 || M_ != 16));                     \
+        else                                                                                                              \
+            LOOKAT_STEP_LAUNCH(M_, 4, (M_ == 16 ? 1 : kStepPrefetch), false, false);                                      \
         return true;
-            switch (a.m) {
-                LOOKAT_STEP_LONE(2)
-                LOOKAT_STEP_LONE(4)
-                LOOKAT_STEP_LONE(8)
-                LOOKAT_STEP_LONE(16)
-            default:
-                return false;
-            }
-#undef LOOKAT_STEP_LONE
-        }
-    }
     switch (a.m) {
-    case 2:
-        hipLaunchKernelGGL((decode_split_kernel<DK, 2, kStepWaves, 4, FT, 1, kStepPrefetch>), grid, block, lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true),
-                           late_of(a));
-        return true;
-    case 4:
-        hipLaunchKernelGGL((decode_split_kernel<DK, 4, kStepWaves, 4, FT, 1, kStepPrefetch>), grid, block, lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true),
-                           late_of(a));
-        return true;
-    case 8:
-        hipLaunchKernelGGL((decode_split_kernel<DK, 8, kStepWaves, 4, FT, 1, kStepPrefetch>), grid, block, lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true),
-                           late_of(a));
-        return true;
-    case 16:
-        hipLaunchKernelGGL((decode_split_kernel<DK, 16, kStepWaves, 4, FT, 1, 1>), grid, block, lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true),
-                           late_of(a));
-        return true;
+        LOOKAT_STEP_CASE(2)
+        LOOKAT_STEP_CASE(4)
+        LOOKAT_STEP_CASE(8)
+        LOOKAT_STEP_CASE(16)
     default:
         return false;
     }
+#undef LOOKAT_STEP_CASE
+#undef LOOKAT_STEP_LAUNCH
 }
 
 // Two batch entries of one head per workgroup (1024 threads): see decode_split_kernel, NB = 2.
