@@ -479,7 +479,7 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
 // thing shared is the codebook, of which each half's table builders fetch half the subspaces and compute
 // both entries' table rows and distances.  The head's codebook then crosses from L2 to the compute units
 // once per pair instead of once per (b,h).  Both halves execute the same barriers (same L, same ranges).
-// LONE (ungrouped fused step, d_k = 128): for launches that leave every workgroup a compute unit of its own, where two
+// LONE (ungrouped fused step, d_k = 128; see step_is_lone): for launches that leave every workgroup a compute unit of its own, where two
 // wavefronts share a SIMD and have 256 registers each: a tile's 16 KB are requested in one round instead of two, and the
 // next tile is in flight while one is consumed.
 // PAD (tables given, ungrouped): the head size is a.d_k < DK, a multiple of 8; lanes past the end of a row repeat its last
@@ -940,17 +940,24 @@ static int pick_waves(int d_k, int m, int64_t keys_per_split)
 // the streamers' tile requests instead of interleaved with them).
 constexpr int kStepPrefetch = 2;
 constexpr int kStepWaves = 2 * kDecWaves;   // four wavefronts build the table, four start streaming at once
-// d_k = 128, up to 256 workgroups: every one has a compute unit to itself (LONE).  Kernel time in us, LONE / otherwise: 256
-// (b,h) x 1024 keys, m = 8: 14.2 / 15.8; x 2048: 26.0 / 29.3; x 4096, m = 4: 46.4 / 48.5; 64 x 4096 in 4 ranges, m = 16:
-// 15.1 / 16.9; 32 x 32768 in 8: 44.0 / 46.7; 32 (b,h) in one range: equal.  At d_k = 64, where a tile is one round of requests
-// anyway, it is 1-2% slower and not taken.
+// LONE (d_k = 128): where every workgroup has a compute unit to itself, which takes at most 32 on a die (all ranges of a (b,h) run on
+// one), and its range is longer than the one tile per wavefront that both forms request first.  LONE / otherwise, fp16, geometric mean
+// over m = 2, 4, 8, 16, at 96..256 workgroups of 256 / 512 / 640 / 1024 / 2048 / 8192 keys: 1.05 / 1.02 / 0.99 / 0.96 / 0.96 / 0.98;
+// up to 64 workgroups of one range per (b,h): 1.07 / 1.05 / 1.00 / 0.98 / 1.01 / 1.01, not taken; of several: 1.05 / 1.03 / 0.99 /
+// 0.96 / 0.99 / 1.00.  256 (b,h) x 1024 keys, m = 8: 14.2 / 15.8 us.  At d_k = 64, where a tile is one round of requests anyway, it is
+// 1-2% slower and not taken.
+static bool step_is_lone(const DecodeArgs &a)
+{
+    const int64_t on_a_die = ((int64_t)a.BH + kXcds - 1) / kXcds * a.splits;
+    return a.d_k == 128 && on_a_die <= 32 && a.keys_per_split > kStepWaves * kTile && (a.splits > 1 || a.BH > 64);
+}
 template <int DK, typename FT>
 static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
 {
     dim3 block(kStepWaves * kWave);
     const size_t lds = ((size_t)a.m * kCentroids + (size_t)kStepWaves * (DK + 2)) * sizeof(float) +
                        (size_t)a.m * kDecWaves * (sizeof(double) + sizeof(int));
-    const bool lone = DK == 128 && (int64_t)a.BH * a.splits <= 256;
+    const bool lone = step_is_lone(a);
     const bool skip = a.splits > 1;
 #define LOOKAT_STEP_LAUNCH(M_, OCC_, PF_, LONE_, SKIP_)                                                                   \
     hipLaunchKernelGGL((decode_split_kernel<DK, M_, kStepWaves, OCC_, FT, 1, PF_, 1, false, LONE_, SKIP_>), grid, block,  \
