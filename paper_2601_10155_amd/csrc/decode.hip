@@ -189,7 +189,7 @@ constexpr float kLoScale = 2048.f;   // 2^11: lifts the remainder of a weight in
 template <int M>
 using CodesOf = typename std::conditional<M == 0, KeyCodesAny, KeyCodes<M ? M : 2>>::type;
 
-template <int DK, int M, int CH, bool FUSED = false, int G = 1, bool MM = false, bool PAD = false>
+template <int DK, int M, int CH, bool FUSED, int G, bool MM, bool PAD, bool FIRST = false>
 __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G> &st, const CodesOf<M> &kc_in,
                                              v4u (&v)[CH], const float *lut_s, __amdgpu_buffer_rsrc_t rc,
                                              __amdgpu_buffer_rsrc_t rv, int bh, uint32_t kb, uint32_t k1,
@@ -250,11 +250,16 @@ __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G
                 a.scores_out[((int64_t)bh * G + g) * a.L + key] = raw;
             sc[g] = raw * a.scale_log2e;
         }
-        above |= sc[g] > st.m_run[g] + kLag;
+        if constexpr (FIRST)
+            st.m_run[g] = wave_max(sc[g]);
+        else
+            above |= sc[g] > st.m_run[g] + kLag;
     }
     // The weights' reference need not be the running maximum, only near it: it moves (and the sums are rescaled) when a score
-    // exceeds it by more than kLag, so most tiles do without the reduction over the wavefront.
-    if (__builtin_amdgcn_ballot_w64(above)) {
+    // exceeds it by more than kLag, so most tiles do without the reduction over the wavefront.  A wavefront's first tile (FIRST)
+    // sets it and has no sums to rescale: contexts of one tile per wavefront would otherwise pay for the test as well (group 4, up
+    // to 512 keys, d_k = 128: 7.5 us a launch before there was a test, 7.9 with it in every tile, 7.5 now).
+    if (!FIRST && __builtin_amdgcn_ballot_w64(above)) {
         float corr_n = 1.f;      // MM: the correction of the query head whose column this lane accumulates
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -661,7 +666,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
         *reinterpret_cast<__attribute__((address_space(3))) v4f *>(pstage + (uint32_t)lane * 32u + 16u) = v4f{0.f, 0.f, 0.f, 0.f};
     }
     if (kb < k1) {
-        consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm, pstage,
+        consume_tile<DK, M, CH, FUSED, G, MM, PAD, true>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm, pstage,
                                              lane_off, row_bytes);
         if constexpr (LONE) {
             // the next tile is in flight while this one is consumed (a wait for it waits for nothing else)
