@@ -187,7 +187,23 @@ constexpr float kLag = 8.f;          // log2 units: weights stay below 2^8, insi
 constexpr float kLoScale = 2048.f;   // 2^11: lifts the remainder of a weight into fp16's normal range
 
 template <int M>
-using CodesOf = typename std::conditional<M == 0, KeyCodesAny, KeyCodes<M ? M : 2>>::type;
+struct CodesOfM {
+    typedef KeyCodes<M> type;
+};
+template <>
+struct CodesOfM<0> {
+    typedef KeyCodesAny type;
+};
+template <>
+struct CodesOfM<1> {
+    typedef KeyCodesBytes<1> type;
+};
+template <>
+struct CodesOfM<32> {
+    typedef KeyCodesBytes<32> type;
+};
+template <int M>
+using CodesOf = typename CodesOfM<M>::type;
 
 template <int DK, int M, int CH, bool FUSED, int G, bool MM, bool PAD, bool FIRST = false>
 __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G> &st, const CodesOf<M> &kc_in,
@@ -342,7 +358,7 @@ __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G
     }
 }
 
-// DK in {32, 64, 128, 256}; M in {2, 4, 8, 16} or 0 (= runtime m, one byte per load);
+// DK in {32, 64, 128, 256}; M in {1, 2, 4, 8, 16, 32} or 0 (= runtime m, padded head sizes; 0, 1 and 32 load a byte at a time);
 // WAVES wavefronts per workgroup, OCC = wavefronts per SIMD the register budget must allow.
 // Codebook rows of centroid `tid` for the GS subspaces i0 .. i0+GS-1 of one head.
 template <int DSUB, int GS>
@@ -917,10 +933,15 @@ static void launch_tuned(const DecodeArgs &a, dim3 grid, hipStream_t st)
         break;
     default:
         if constexpr (WAVES == kDecWaves) {   // (pick_waves: the large workgroup is taken with m = 2, 4 or 8)
+            // (32, 64, 128 and 256 coordinates have no other divisors up to 32)
             if (a.m == 16)
                 LOOKAT_TUNED_LAUNCH(16);
-            else
+            else if constexpr (PAD)
                 LOOKAT_TUNED_LAUNCH(0);
+            else if (a.m == 1)
+                LOOKAT_TUNED_LAUNCH(1);
+            else
+                LOOKAT_TUNED_LAUNCH(32);
         }
         break;
     }
