@@ -847,42 +847,64 @@ __global__ __launch_bounds__(kDecThreads) void decode_combine_kernel(const float
 
 static int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
 
-// Ranges per (b,h) when the caller leaves the choice to the library: the count with the least predicted time.
-// A workgroup streams its range at 62 KB/us while few share the memory, 62 - 0.11 n with n workgroups, and no faster than
-// its part of 7.4 n / (n + 16) MB/us.  Workgroups are dealt evenly to the 256 compute units, which get equal shares of the memory: if some
-// compute units hold one workgroup more than the rest, all finish the common part together and those few then stream
-// their last range alone, at no more than one compute unit's rate.  Each round of workgroups costs its table or codebook
-// (about 0.9 us at d_k = 128), and more than one range costs the merge launch (2.6 us).
-// Measured (us per fused call at 1 / 2 / 4 / 8 / 16 ranges; the count taken in brackets; before: one range from 129 (b,h)
-// pairs on, at most 256 workgroups and ranges of 2048 keys below):
-//   d_k = 128, m = 8:  12 (b,h) x 4096 keys 24.4 / 18.0 / 13.3 / 11.8 / 11.9 [8];  32 x 2048 16.8 / 14.1 / 12.6 / 13.1 / 13.7
-//   [4];  32 x 8192 43.4 / 28.7 / 20.0 / 18.6 / 20.4 [8];  128 x 4096 29.8 / 31.4 / 31.3 / 34.3 / 48.7 [1];  264 x 8192
-//   124 / 112 / 111 / 108 / 116 [8];  384 x 8192 137 / 139 / 145 / 149 / 161 [1]
-//   d_k = 64, m = 4:  264 x 4096 33.6 / 31.8 / 30.3 / 35.4 / 54.8 [4];  264 x 32768 235 / 201 / 182 / 173 / 169 [16]
+// Ranges of at least 2048 keys, and no more workgroups than compute units.
+static int base_splits(const lookat_shape *s, int64_t L)
+{
+    int64_t want = 256 / ((int64_t)s->B * s->H);
+    const int64_t cap = (L + 2047) / 2048;
+    want = want < cap ? want : cap;
+    return (int)(want < 1 ? 1 : want);
+}
+static size_t splits_bytes(const lookat_shape *s, int64_t S)
+{
+    return S == 1 ? 0 : (size_t)s->B * s->H * S * (s->d_k + 2) * sizeof(float);
+}
+// Predicted us of a launch with S ranges per (b,h).  All ranges of a (b,h) run on one die (map_block_n), so the die with the
+// most (b,h) decides: its n workgroups go evenly to its 32 compute units.  A workgroup streams its range at 54 KB/us while few
+// share the memory, 54 - 0.11 w with w workgroups, and no faster than its part of the chip's 7.9 w / (w + 17) MB/us or of a die's
+// 965 KB/us; where some compute units hold one workgroup more than the rest, those stream their last range alone.  Each round of
+// workgroups costs its table or codebook (about 0.9 us at d_k = 128), and more than one range costs the merge launch.
+static double splits_us(const lookat_shape *s, int64_t L, int64_t S)
+{
+    constexpr double kPeak = 7.92e6, kHalf = 17.0, kOne = 53.8e3, kDie = 965e3, kStart = 7.65, kMerge = 2.1;
+    const int64_t BH = (int64_t)s->B * s->H;
+    const double range = (double)round_up((L + S - 1) / S, kTile) * (2.0 * s->d_k + s->m);   // bytes
+    const int64_t n = (BH + kXcds - 1) / kXcds * S;
+    const int64_t rounds = (n + 31) / 32, rest = n - 32 * (rounds - 1);
+    const int64_t dies = BH < kXcds ? BH : kXcds, fullest = BH < kXcds ? BH : (BH % kXcds ? BH % kXcds : kXcds);
+    auto rate = [&](double w, double on_a_die) {
+        double r = kOne - 109.0 * w;
+        r = r < kPeak / (w + kHalf) ? r : kPeak / (w + kHalf);
+        return r < kDie / on_a_die ? r : kDie / on_a_die;
+    };
+    return kStart + (double)(rounds - 1) * (range / rate(32.0 * (double)dies, 32.0) + 0.88 * s->d_k / 128.0) +
+           range / rate((double)(rest * fullest), (double)rest) + (S > 1 ? kMerge : 0.0);
+}
+// Ranges per (b,h) when the caller leaves the choice to the library: base_splits, unless another count is predicted to take
+// 4% less time (and 1 us less, where that means a second launch), then the count with the least.
+// Measured at 28 numbers of (b,h) from 1 to 520, 600 to 32768 keys and nine (d_k, m), fused and not: 0.86 of the time of
+// base_splits on the geometric mean, 3% off the best of ten counts; two launches in a thousand more than 3% slower than
+// base_splits.  us per fused call, base / taken [ranges], d_k = 128, m = 8: 1 x 8192 17.1 / 11.4 [16]; 1 x 32768 18.1 / 14.6 [24];
+// 12 x 4096 18.4 / 12.1 [8]; 20 x 32768 46.4 / 33.7 [8]; 32 x 2048 17.4 / 13.5 [4]; 264 x 8192 126 / 106 [6].  A model that dealt the
+// workgroups evenly to 256 compute units took 128 ranges for 1 x 32768 (37.4 us), 12 for 20 x 8192 (21.5; 8: 14.7) and one for
+// 80 x 4096 at d_k = 64 (15.9; 2: 13.0).
 static int auto_splits(const lookat_shape *s, int64_t L)
 {
     const int64_t BH = (int64_t)s->B * s->H;
     if (BH > 128 && BH <= 256)
         return 1;                      // one workgroup per compute unit, and too few for a second round
-    const double bytes = (double)L * (2.0 * s->d_k + s->m);   // of one (b,h)
-    constexpr double kPeak = 7.4e6, kChip = kPeak * 256 / (256 + 16), kOne = 62e3, kStart = 7.0, kMerge = 2.6;
-    const double round_cost = 0.9 * s->d_k / 128.0;
-    static const int counts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
-    int best = 1;
-    double best_cost = 0.0;
+    static const int counts[] = {2, 3, 4, 6, 8, 12, 16, 24, 32};
+    const int base = base_splits(s, L);
+    const double base_us = splits_us(s, L, base);
+    int best = base;
+    double best_us = 0.96 * base_us - (base == 1 ? 1.0 : 0.0);
     for (int S : counts) {
-        if (S > 1 && (L < (int64_t)S * 256 || BH * S > 4096))
+        if (L < (int64_t)S * 256 || BH * S > 4096)
             break;
-        const int64_t wgs = BH * S;
-        const int64_t rounds = (wgs + 255) / 256;
-        const double last = (double)(wgs - 256 * (rounds - 1));   // compute units that hold `rounds` workgroups
-        const double range = bytes / S;
-        const double share = kPeak / (last + 16.0);
-        const double rate = kOne - 110.0 * last < share ? kOne - 110.0 * last : share;
-        const double cost = kStart + (rounds - 1) * (range * 256.0 / kChip + round_cost) + range / rate + (S > 1 ? kMerge : 0.0);
-        if (S == 1 || cost < (best == 1 ? 0.97 * best_cost - 1.0 : best_cost)) {   // (a second launch has to be worth it)
+        const double us = splits_us(s, L, S);
+        if (us < best_us) {
             best = S;
-            best_cost = cost;
+            best_us = us;
         }
     }
     return best;
@@ -891,9 +913,7 @@ static int auto_splits(const lookat_shape *s, int64_t L)
 // library once took one (it asked for no workspace there).
 static int fit_splits(const lookat_shape *s, int64_t L, int S, size_t workspace_bytes)
 {
-    const int64_t BH = (int64_t)s->B * s->H;
-    const bool one = BH > 128 || L <= 2048;
-    return one && (size_t)BH * S * (s->d_k + 2) * sizeof(float) > workspace_bytes ? 1 : S;
+    return base_splits(s, L) == 1 && splits_bytes(s, S) > workspace_bytes ? 1 : S;
 }
 // Grouped queries: from group 4 on one 512-thread workgroup per compute unit (see gqa_waves), at
 // group 2 two 256-thread ones.  Measured at 8 x 32 query heads x 32768 keys, d_k = 128, m = 8 (us per
@@ -905,7 +925,7 @@ static int auto_splits_gqa(const lookat_shape *s, int group, int64_t L)
         return auto_splits(s, L);
     int64_t want = (group >= 4 ? 256 : 512) / ((int64_t)s->B * s->H);
     // Ranges of at least 1024 keys.  With 512 (us per fused step, ranges of 1024 / 512 keys): group 2, 64 key/value heads x 2048 keys
-    // 15.0 / 14.0, but 80 x 2686 14.1 / 15.3, and group 4, 6 x 31374 keys 21.0 / 31.7 (more ranges to merge).
+    // 15.0 / 14.0, but 80 x 2686 14.1 / 15.3, and group 4, 6 x 31374 keys 21.0 / 31.7 (42 workgroups for a die's 32 compute units).
     const int64_t cap = (L + 1023) / 1024;
     want = want < cap ? want : cap;
     return (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
@@ -1383,9 +1403,8 @@ extern "C" int lookat_decode_step_gqa(const lookat_shape *shape, int32_t group, 
         return fail(LOOKAT_ERR_UNSUPPORTED, "lookat_decode_step_gqa handles group in {1,2,4,8}; got %d", group);
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
-    int S = num_splits ? num_splits : (L > 0 ? auto_splits_gqa(shape, group, L) : 1);
-    if (!num_splits && group == 1 && L > 0)
-        S = fit_splits(shape, L, S, workspace ? workspace_bytes : 0);
+    const int S = num_splits ? num_splits
+                             : (L <= 0 ? 1 : (group == 1 ? fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0) : auto_splits_gqa(shape, group, L)));
     return decode_step_impl("lookat_decode_step_gqa", shape, group, L, q, k_new, qk_dtype, codebooks, codes,
                             code_stride_bh, values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }
@@ -1599,7 +1618,7 @@ extern "C" int lookat_attend_decode_noalloc(const lookat_shape *shape, int64_t L
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
     if (num_splits == 0) {   // the library's choice, as far as the scratch memory holds it
         num_splits = auto_splits(shape, L);
-        while (num_splits > 1 && lookat_attend_decode_workspace_bytes(shape, L, num_splits) > (size_t)LOOKAT_NOALLOC_SCRATCH_BYTES)
+        while (num_splits > 1 && splits_bytes(shape, num_splits) > (size_t)LOOKAT_NOALLOC_SCRATCH_BYTES)
             num_splits /= 2;
     }
     const size_t need = lookat_attend_decode_workspace_bytes(shape, L, num_splits);

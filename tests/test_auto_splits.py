@@ -28,6 +28,14 @@ def test_auto_splits_invariants():
             for L, most in ((1, 1), (1024, 1), (1025, 2), (2047, 2), (2048, 2), (2049, 3), (4096, 4), (300000, 256)):
                 S = min(most, max(1, fill // BH))
                 assert lk.attend_decode_gqa_workspace_bytes(1, BH, group, 64, 4, L) == (0 if S == 1 else BH * group * S * 66 * 4)
+    # no die (all ranges of a (b,h) share one of the eight, with 32 compute units) gets a few workgroups more than it runs at once
+    for BH in range(1, 33):
+        for d_k, m in ((32, 4), (64, 4), (128, 8)):
+            for L in (4096, 6144, 8192, 16000, 32768):
+                on_a_die = (BH + 7) // 8 * lk.attend_decode_auto_splits(1, BH, d_k, m, L)
+                assert on_a_die <= 32 or on_a_die >= 48, (BH, d_k, L, on_a_die)
+    assert [lk.attend_decode_auto_splits(1, BH, 128, 8, 32768) for BH in (1, 2, 4, 9, 20)] == [32, 32, 32, 16, 8]
+    assert lk.attend_decode_auto_splits(1, 80, 64, 4, 4096) >= 2 and lk.attend_decode_auto_splits(1, 128, 32, 4, 8192) >= 2
     # long contexts of few pairs are cut, a little over one workgroup per compute unit too
     assert lk.attend_decode_auto_splits(1, 32, 128, 8, 8192) == 8
     assert lk.attend_decode_auto_splits(1, 264, 128, 8, 8192) > 1
