@@ -1062,6 +1062,17 @@ static bool step_pairs_entries(const lookat_shape *s, int group, int64_t L, int 
     return false;
 }
 
+// Ranges of the fused step when the caller leaves the choice to the library: as the unfused call, except where one range would be
+// served by paired batch entries.  Cutting them gives that up and pays only for long contexts of up to 320 (b,h).  us per call,
+// paired / cut: d_k = 128, m = 4: 264 (b,h) x 2048 keys 33.9 / 45.8, 320 x 5000 74 / 78, 264 x 12000 154 / 144, 384 x 8192 129 / 140;
+// m = 8: 288 x 2048 34 / 40, 264 x 5000 71 / 64, 384 x 12000 181 / 187; d_k = 64, m = 2: 288 x 3500 27 / 32, 320 x 5000 37 / 43,
+// 264 x 12000 82 / 76; m = 4: 264 x 3500 26.4 / 27.9, 264 x 8192 53 / 50, 384 x 32768 252 / 254.
+static int step_auto_splits(const lookat_shape *s, int64_t L, int unfused)
+{
+    const int64_t pays = s->d_k == 128 ? (s->m == 4 ? 10000 : 2500) : (s->m == 2 ? 10000 : 5000);
+    return step_pairs_entries(s, 1, L, 1) && ((int64_t)s->B * s->H > 320 || L < pays) ? 1 : unfused;
+}
+
 template <int DK, typename FT>
 static bool launch_step_pair(const DecodeArgs &a, dim3 grid, hipStream_t st)
 {
@@ -1378,7 +1389,7 @@ extern "C" int lookat_decode_step_split(const lookat_shape *shape, int64_t L, co
         return rc;
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
-    const int S = num_splits ? num_splits : (L > 0 ? fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0) : 1);
+    const int S = num_splits ? num_splits : (L > 0 ? step_auto_splits(shape, L, fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0)) : 1);
     return decode_step_impl("lookat_decode_step_split", shape, 1, L, q, k_new, qk_dtype, codebooks, codes, code_stride_bh,
                             values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }
@@ -1404,7 +1415,7 @@ extern "C" int lookat_decode_step_gqa(const lookat_shape *shape, int32_t group, 
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
     const int S = num_splits ? num_splits
-                             : (L <= 0 ? 1 : (group == 1 ? fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0) : auto_splits_gqa(shape, group, L)));
+                             : (L <= 0 ? 1 : (group == 1 ? step_auto_splits(shape, L, fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0)) : auto_splits_gqa(shape, group, L)));
     return decode_step_impl("lookat_decode_step_gqa", shape, group, L, q, k_new, qk_dtype, codebooks, codes,
                             code_stride_bh, values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }

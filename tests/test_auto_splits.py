@@ -78,3 +78,23 @@ def test_auto_splits_without_a_workspace(B, H, L):
     rc = lib.lookat_decode_step_gqa(ctypes.byref(shape), 1, L, q.data_ptr(), k.data_ptr(), 2, cb.data_ptr(), codes.data_ptr(), L * m,
                                     v.data_ptr(), L * d_k, scale, 0, None, 0, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
     assert rc == 0 and torch.equal(out, one)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d_k,m,B,H,L,cut", [(128, 4, 22, 12, 2048, False), (128, 8, 24, 12, 2100, False), (128, 4, 48, 8, 2500, False),
+                                             (64, 4, 22, 12, 3500, False), (128, 8, 22, 12, 2600, True), (128, 4, 23, 12, 2048, True)])
+def test_fused_step_keeps_paired_entries(d_k, m, B, H, L, cut):
+    """Where one range is served by paired batch entries the library cuts only what gains by it (odd batches have no pairs)."""
+    import torch
+    lk = _lk()
+    assert lk.attend_decode_auto_splits(B, H, d_k, m, L) > 1 or not cut
+    assert lk.decode_step_entries_per_workgroup(B, H, d_k, m, L) == (1 if B % 2 else 2)
+    g = torch.Generator(device="cuda").manual_seed(L)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    codes = torch.randint(0, 256, (B, H, L, m), generator=g, device="cuda", dtype=torch.uint8)
+    v, q, k, cb = rnd(B, H, L, d_k).half(), rnd(B, H, d_k), rnd(B, H, d_k), rnd(H, m, 256, d_k // m)
+    one = lk.lookat_decode_step(q, k, cb, codes, v, d_k ** -0.5)
+    ws = torch.zeros(max(16, lk.decode_step_split_workspace_bytes(B, H, d_k, m, L)), dtype=torch.uint8, device="cuda")
+    got = lk.lookat_decode_step_split(q, k, cb, codes, v, d_k ** -0.5, workspace=ws)
+    assert bool(ws.any()) == cut                      # (the ranges' partial results)
+    assert torch.equal(got, one) if not cut else float((got - one).abs().max()) <= 2e-5
