@@ -126,10 +126,14 @@ int lookat_build_lut(const lookat_shape *shape, int32_t T,
  *   values          fp16; element (b,h,l,j) at values[(b*H+h)*value_stride_bh + l*d_k + j];
  *                   base pointer 16-byte aligned, value_stride_bh >= L*d_k
  *   scale           softmax scale (Algorithm 1 uses 1/sqrt(d_k))
- *   num_splits      >= 1, or 0 to let the library choose from the shape
+ *   num_splits      >= 1, or 0 to let the library choose from the shape and the workspace
  *   workspace       device scratch of at least
  *                   lookat_attend_decode_workspace_bytes(shape, L, num_splits)
  *                   bytes, 16-byte aligned; may be NULL when that size is 0.
+ *                   With num_splits == 0 a smaller one (or NULL) makes the library
+ *                   choose among the counts that it holds, as long as it holds
+ *                   min(256 / (B*H), ceil(L / 2048)) ranges (one: nothing); below
+ *                   that, and with num_splits >= 1: LOOKAT_ERR_WORKSPACE.
  *                   Contents before and after the call are unspecified.  Two calls
  *                   in flight at once must not share a workspace.
  *   out             [B,H,d_k] fp32, 16-byte aligned
@@ -153,8 +157,9 @@ int lookat_attend_decode(const lookat_shape *shape, int64_t L,
  * per-range partial results live in LOOKAT_NOALLOC_SCRATCH_BYTES of device memory that is part of
  * the library's own image (every GPU the library runs on holds one copy until the process ends;
  * its address is looked up on the first call on a device).  The call allocates and frees nothing.
- *   - Problems that need more than that (B*H*ranges*(d_k+2) floats, see
- *     lookat_attend_decode_workspace_bytes): LOOKAT_ERR_WORKSPACE, nothing enqueued.
+ *   - num_splits >= 1 with more than that (B*H*ranges*(d_k+2) floats, see
+ *     lookat_attend_decode_workspace_bytes): LOOKAT_ERR_WORKSPACE, nothing enqueued; num_splits == 0 takes a
+ *     count that it holds.
  *   - All calls on one GPU share the memory: two calls whose kernels may overlap on one GPU
  *     (different streams, no ordering between them) race.  Calls on one stream do not.
  *   - Nothing in it needs a defined value before a call: every partial result that is read was
@@ -251,7 +256,8 @@ int32_t lookat_decode_step_entries_per_workgroup(const lookat_shape *shape, int6
  *   num_splits                 ranges per (b,h); 0 = the library's choice (as lookat_attend_decode)
  *   workspace, workspace_bytes device scratch of at least
  *                              lookat_decode_step_split_workspace_bytes(shape, L, num_splits) bytes,
- *                              16-byte aligned, caller-owned; may be NULL when that is 0
+ *                              16-byte aligned, caller-owned; may be NULL when that is 0 (num_splits 0 and a smaller
+ *                              one: as lookat_attend_decode)
  * All other arguments, supported shapes and error behaviour as lookat_decode_step.
  */
 size_t lookat_decode_step_split_workspace_bytes(const lookat_shape *shape, int64_t L, int32_t num_splits);
@@ -295,12 +301,12 @@ int lookat_decode_step_gqa(const lookat_shape *shape, int32_t group, int64_t L,
                            float *out,
                            void *stream);
 
-/* The split count lookat_attend_decode uses when num_splits == 0 (host only,
- * no HIP call); 0 if the shape is invalid. */
+/* The split count lookat_attend_decode uses when num_splits == 0 and the workspace holds
+ * lookat_attend_decode_workspace_bytes() (host only, no HIP call); 0 if the shape is invalid. */
 int32_t lookat_attend_decode_auto_splits(const lookat_shape *shape, int64_t L);
 
 /* The launch shape lookat_attend_decode takes for this problem (host only, no HIP call):
- * *ranges = ranges per (b,h) (num_splits, or the library's choice when it is 0), *wavefronts =
+ * *ranges = ranges per (b,h) (num_splits, or the library's choice with a full workspace when it is 0), *wavefronts =
  * wavefronts per workgroup of the kernel instance that streams a range (4 for ranges under
  * 2048 keys and for shapes without a large-workgroup instance, 16 otherwise).  Either pointer
  * may be NULL.  Exists so that tests can state which instance a shape exercises.  Returns a

@@ -881,14 +881,15 @@ static double splits_us(const lookat_shape *s, int64_t L, int64_t S)
            range / rate((double)(rest * fullest), (double)rest) + (S > 1 ? kMerge : 0.0);
 }
 // Ranges per (b,h) when the caller leaves the choice to the library: base_splits, unless another count is predicted to take
-// 4% less time (and 1 us less, where that means a second launch), then the count with the least.
+// 4% less time (and 1 us less, where that means a second launch), then the count with the least; `workspace`: a caller that
+// brings less than that needs gets the best count that it holds, but no less than base_splits.
 // Measured at 28 numbers of (b,h) from 1 to 520, 600 to 32768 keys and nine (d_k, m), fused and not: 0.86 of the time of
 // base_splits on the geometric mean, 3% off the best of ten counts; two launches in a thousand more than 3% slower than
 // base_splits.  us per fused call, base / taken [ranges], d_k = 128, m = 8: 1 x 8192 17.1 / 11.4 [16]; 1 x 32768 18.1 / 14.6 [24];
 // 12 x 4096 18.4 / 12.1 [8]; 20 x 32768 46.4 / 33.7 [8]; 32 x 2048 17.4 / 13.5 [4]; 264 x 8192 126 / 106 [6].  A model that dealt the
 // workgroups evenly to 256 compute units took 128 ranges for 1 x 32768 (37.4 us), 12 for 20 x 8192 (21.5; 8: 14.7) and one for
 // 80 x 4096 at d_k = 64 (15.9; 2: 13.0).
-static int auto_splits(const lookat_shape *s, int64_t L)
+static int auto_splits(const lookat_shape *s, int64_t L, size_t workspace = SIZE_MAX)
 {
     const int64_t BH = (int64_t)s->B * s->H;
     if (BH > 128 && BH <= 256)
@@ -896,24 +897,24 @@ static int auto_splits(const lookat_shape *s, int64_t L)
     static const int counts[] = {2, 3, 4, 6, 8, 12, 16, 24, 32};
     const int base = base_splits(s, L);
     const double base_us = splits_us(s, L, base);
-    int best = base;
-    double best_us = 0.96 * base_us - (base == 1 ? 1.0 : 0.0);
-    for (int S : counts) {
-        if (L < (int64_t)S * 256 || BH * S > 4096)
-            break;
-        const double us = splits_us(s, L, S);
-        if (us < best_us) {
-            best = S;
-            best_us = us;
+    auto choose = [&](int low, size_t bytes) {
+        int best = base;
+        double best_us = 0.96 * base_us - (base == 1 ? 1.0 : 0.0);
+        for (int S : counts) {
+            if (L < (int64_t)S * 256 || BH * S > 4096)
+                break;
+            if (S < low || splits_bytes(s, S) > bytes)
+                continue;
+            const double us = splits_us(s, L, S);
+            if (us < best_us) {
+                best = S;
+                best_us = us;
+            }
         }
-    }
-    return best;
-}
-// A caller that left the choice to the library and brings less workspace than that count needs gets one range where the
-// library once took one (it asked for no workspace there).
-static int fit_splits(const lookat_shape *s, int64_t L, int S, size_t workspace_bytes)
-{
-    return base_splits(s, L) == 1 && splits_bytes(s, S) > workspace_bytes ? 1 : S;
+        return best;
+    };
+    const int S = choose(2, SIZE_MAX);
+    return splits_bytes(s, S) <= workspace || S < base ? S : choose(base, workspace);
 }
 // Grouped queries: from group 4 on one 512-thread workgroup per compute unit (see gqa_waves), at
 // group 2 two 256-thread ones.  Measured at 8 x 32 query heads x 32768 keys, d_k = 128, m = 8 (us per
@@ -1389,7 +1390,7 @@ extern "C" int lookat_decode_step_split(const lookat_shape *shape, int64_t L, co
         return rc;
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
-    const int S = num_splits ? num_splits : (L > 0 ? step_auto_splits(shape, L, fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0)) : 1);
+    const int S = num_splits ? num_splits : (L > 0 ? step_auto_splits(shape, L, auto_splits(shape, L, workspace ? workspace_bytes : 0)) : 1);
     return decode_step_impl("lookat_decode_step_split", shape, 1, L, q, k_new, qk_dtype, codebooks, codes, code_stride_bh,
                             values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }
@@ -1415,7 +1416,7 @@ extern "C" int lookat_decode_step_gqa(const lookat_shape *shape, int32_t group, 
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
     const int S = num_splits ? num_splits
-                             : (L <= 0 ? 1 : (group == 1 ? step_auto_splits(shape, L, fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0)) : auto_splits_gqa(shape, group, L)));
+                             : (L <= 0 ? 1 : (group == 1 ? step_auto_splits(shape, L, auto_splits(shape, L, workspace ? workspace_bytes : 0)) : auto_splits_gqa(shape, group, L)));
     return decode_step_impl("lookat_decode_step_gqa", shape, group, L, q, k_new, qk_dtype, codebooks, codes,
                             code_stride_bh, values, value_stride_bh, scale, S, workspace, workspace_bytes, out, stream);
 }
@@ -1493,7 +1494,7 @@ static int attend_decode_impl(const lookat_shape *shape, int64_t L, const float 
     if ((L + 2048) * (int64_t)shape->d_k * 2 > 0xffffffffLL)
         return fail(LOOKAT_ERR_UNSUPPORTED, "L=%lld: one (b,h) value slab must stay below 4 GiB", (long long)L);
     const int64_t BH = (int64_t)shape->B * shape->H;
-    const int S = num_splits ? num_splits : fit_splits(shape, L, auto_splits(shape, L), workspace ? workspace_bytes : 0);
+    const int S = num_splits ? num_splits : auto_splits(shape, L, workspace ? workspace_bytes : 0);
     const size_t need = (S == 1) ? 0 : (size_t)BH * S * (shape->d_k + 2) * sizeof(float);
     if (need) {
         if (!workspace || workspace_bytes < need)
@@ -1627,11 +1628,8 @@ extern "C" int lookat_attend_decode_noalloc(const lookat_shape *shape, int64_t L
         return fail(LOOKAT_ERR_SHAPE, "L=%lld must be positive", (long long)L);
     if (num_splits < 0 || num_splits > 65535)
         return fail(LOOKAT_ERR_SHAPE, "num_splits=%d out of range [0,65535]", num_splits);
-    if (num_splits == 0) {   // the library's choice, as far as the scratch memory holds it
-        num_splits = auto_splits(shape, L);
-        while (num_splits > 1 && splits_bytes(shape, num_splits) > (size_t)LOOKAT_NOALLOC_SCRATCH_BYTES)
-            num_splits /= 2;
-    }
+    if (num_splits == 0)   // the library's choice, as far as the scratch memory holds it
+        num_splits = auto_splits(shape, L, (size_t)LOOKAT_NOALLOC_SCRATCH_BYTES);
     const size_t need = lookat_attend_decode_workspace_bytes(shape, L, num_splits);
     if (need > (size_t)LOOKAT_NOALLOC_SCRATCH_BYTES)
         return fail(LOOKAT_ERR_WORKSPACE,

@@ -139,8 +139,9 @@ const at::Tensor *codebooks_of(PyObject *o)
     return cb && cb->dim() == 4 && cb->size(2) == 256 ? cb : nullptr;
 }
 
-// (workspace object, bytes needed) -> pointer and size as binding.py would pass them; false: one has to be allocated
-bool workspace_of(PyObject *o, size_t need, void *&ptr, size_t &bytes)
+// (workspace object, bytes needed) -> pointer and size as binding.py would pass them; false: one has to be allocated.
+// `fits`: the library takes fewer ranges where a given workspace does not hold its choice (or refuses, see answer()).
+bool workspace_of(PyObject *o, size_t need, bool fits, void *&ptr, size_t &bytes)
 {
     ptr = nullptr;
     bytes = 0;
@@ -151,7 +152,14 @@ bool workspace_of(PyObject *o, size_t need, void *&ptr, size_t &bytes)
         return false;
     ptr = w->data_ptr();
     bytes = (size_t)w->numel() * w->element_size();
-    return bytes >= need;
+    return fits || bytes >= need;
+}
+// A workspace that the library refuses is too small even for that: one has to be allocated.
+PyObject *answer(int rc)
+{
+    if (rc == LOOKAT_ERR_WORKSPACE)
+        GIVE_UP;
+    return status(rc);
 }
 
 // q, k_new, codebooks, codes, values, scale, [num_splits, workspace,] out: kind 0 decode_step, 1 split, 2 gqa
@@ -191,7 +199,7 @@ PyObject *step(PyObject *const *args, Py_ssize_t n, int kind)
     if (kind) {
         const size_t need = kind == 1 ? entry.decode_step_split_workspace_bytes(&s, L, (int32_t)splits)
                                       : entry.decode_step_gqa_workspace_bytes(&s, (int32_t)group, L, (int32_t)splits);
-        if (!workspace_of(args[7], need, ws, ws_bytes))
+        if (!workspace_of(args[7], need, splits == 0 && group == 1, ws, ws_bytes))
             GIVE_UP;
     }
     if (!current_stream(*values, stream))
@@ -204,7 +212,7 @@ PyObject *step(PyObject *const *args, Py_ssize_t n, int kind)
              : kind == 1 ? entry.decode_step_split(&s, L, qp, kp, qt, cbp, cp, cs, vp, vs, scale, (int32_t)splits, ws, ws_bytes, op, stream)
                          : entry.decode_step_gqa(&s, (int32_t)group, L, qp, kp, qt, cbp, cp, cs, vp, vs, scale, (int32_t)splits, ws,
                                                  ws_bytes, op, stream));
-    return status(rc);
+    return answer(rc);
 }
 
 // lut, codes, values, scale, num_splits, workspace, out, scores_out
@@ -227,12 +235,12 @@ PyObject *attend(PyObject *const *args, Py_ssize_t n)
         GIVE_UP;
     void *ws, *stream;
     size_t ws_bytes;
-    if (!workspace_of(args[5], entry.attend_decode_workspace_bytes(&s, L, (int32_t)splits), ws, ws_bytes) || !current_stream(*values, stream))
+    if (!workspace_of(args[5], entry.attend_decode_workspace_bytes(&s, L, (int32_t)splits), splits == 0, ws, ws_bytes) || !current_stream(*values, stream))
         GIVE_UP;
     CALL(rc, entry.attend_decode(&s, L, static_cast<const float *>(lut->data_ptr()), static_cast<const uint8_t *>(codes->data_ptr()), cs,
                                  values->data_ptr(), vs, scale, (int32_t)splits, ws, ws_bytes, static_cast<float *>(out->data_ptr()),
                                  scores ? static_cast<float *>(scores->data_ptr()) : nullptr, stream));
-    return status(rc);
+    return answer(rc);
 }
 
 // keys, codebooks, codes_out | None, cache | None, position

@@ -98,3 +98,39 @@ def test_fused_step_keeps_paired_entries(d_k, m, B, H, L, cut):
     got = lk.lookat_decode_step_split(q, k, cb, codes, v, d_k ** -0.5, workspace=ws)
     assert bool(ws.any()) == cut                      # (the ranges' partial results)
     assert torch.equal(got, one) if not cut else float((got - one).abs().max()) <= 2e-5
+
+
+@pytest.mark.gpu
+def test_auto_splits_with_a_smaller_workspace():
+    """The library's choice adapts to the workspace it is given, down to the count it asked for before it chose by predicted times."""
+    import torch
+    from paper_2601_10155_amd.binding import _Shape, load_library
+    lk, lib = _lk(), load_library()
+    d_k, m = 128, 8
+    for B, H, L in ((1, 12, 4096), (1, 32, 8192), (1, 3, 2048), (11, 24, 4133)):
+        shape = _Shape(B, H, d_k, m, 256)
+        per = B * H * (d_k + 2) * 4
+        auto = lk.attend_decode_auto_splits(B, H, d_k, m, L)
+        base = max(1, min(256 // (B * H), -(-L // 2048)))
+        assert auto > base
+        g = torch.Generator(device="cuda").manual_seed(L)
+        lut = torch.randn((B, H, m, 256), generator=g, device="cuda")
+        codes = torch.randint(0, 256, (B, H, L, m), generator=g, device="cuda", dtype=torch.uint8)
+        v = torch.randn((B, H, L, d_k), generator=g, device="cuda").half()
+        ref = lk.lookat_attend_decode(lut, codes, v, d_k ** -0.5, num_splits=1)
+        for held in range(0, auto + 1):
+            need = 0 if held <= 1 else held * per
+            ws = torch.zeros(auto * per + 16, dtype=torch.uint8, device="cuda")
+            out = torch.zeros_like(ref)
+            rc = lib.lookat_attend_decode(ctypes.byref(shape), L, lut.data_ptr(), codes.data_ptr(), L * m, v.data_ptr(), L * d_k,
+                                          d_k ** -0.5, 0, ws.data_ptr(), need, out.data_ptr(), None,
+                                          torch.cuda.current_stream().cuda_stream)
+            if base > 1 and held < base:
+                assert rc == -5                      # as it always was
+            else:
+                assert rc == 0 and float((out - ref).abs().max()) <= 2e-5
+                assert not bool(ws[need:].any())     # nothing beyond what was given
+            # and through the package: a workspace that is too small for any choice is replaced, a smaller one is used
+            got = lk.lookat_attend_decode(lut, codes, v, d_k ** -0.5, workspace=ws[:max(need, 16)], out=torch.empty_like(ref))
+            assert float((got - ref).abs().max()) <= 2e-5
+            assert not bool(ws[max(need, 16):].any())
