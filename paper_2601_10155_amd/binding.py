@@ -6,13 +6,14 @@ the method runs in the library's kernels.  If the library is missing the calls r
 
 The calls of a decode step and of a prompt block are marshalled by csrc/marshal.cpp where their
 arguments need no work (no copy, no allocation, nothing to refuse); it answers None where they do,
-and the Python code below takes the call.  One user's step (12 heads x 1024 keys, 12 layers, one call each): 107 us in
+and the Python code below takes the call, as it takes all of them where that module cannot be loaded.  One user's step (12 heads x 1024 keys, 12 layers, one call each): 107 us in
 Python, host-bound at 8.7 us a call; 80 us now, the time of the kernels.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -30,6 +31,14 @@ class LookatError(RuntimeError):
     def __init__(self, status: int, message: str):
         super().__init__(f"lookat status {status}: {message}")
         self.status = status
+
+
+class _PythonOnly:
+    """In the place of the native marshalling where it cannot be loaded: leaves every call to the Python code below."""
+    @staticmethod
+    def _leave(*args):
+        return None
+    encode_keys = build_lut = attend_decode = decode_step = decode_step_split = decode_step_gqa = score_prefill = _leave
 
 
 class _Shape(ctypes.Structure):
@@ -109,12 +118,14 @@ def load_library():
         lib.lookat_version.restype = ctypes.c_int
         try:
             from . import _marshal as native
-        except ImportError as e:
-            raise LookatError(-100, f"_marshal.so is not built ({e}); run `python -m paper_2601_10155_amd.build`") from e
-        native.bind(torch._C._cuda_getCurrentRawStream, *(
-            ctypes.cast(getattr(lib, "lookat_" + name), vp).value for name in (
-                "encode_keys", "build_lut", "attend_decode", "attend_decode_workspace_bytes", "decode_step", "decode_step_split",
-                "decode_step_split_workspace_bytes", "decode_step_gqa", "decode_step_gqa_workspace_bytes", "score_prefill")))
+            native.bind(torch._C._cuda_getCurrentRawStream, *(
+                ctypes.cast(getattr(lib, "lookat_" + name), vp).value for name in (
+                    "encode_keys", "build_lut", "attend_decode", "attend_decode_workspace_bytes", "decode_step", "decode_step_split",
+                    "decode_step_split_workspace_bytes", "decode_step_gqa", "decode_step_gqa_workspace_bytes", "score_prefill")))
+        except (ImportError, AttributeError, TypeError) as e:
+            # (not built, or for another torch: the same library calls are made, 2 to 6 us later each)
+            warnings.warn(f"the native marshalling is not available ({e}); run `python -m paper_2601_10155_amd.build`", RuntimeWarning)
+            native = _PythonOnly()
         globals()["_marshal"] = native
         _lib = lib
     return _lib

@@ -55,6 +55,7 @@ def build(verbose: bool = True, force: bool = True) -> str:
     cc = hipcc()
     objs = []
     procs = []
+    failed = None
     for src in sources():
         obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
         objs.append(obj)
@@ -72,19 +73,28 @@ def build(verbose: bool = True, force: bool = True) -> str:
         cmd = marshal_command()
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append(("marshal.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)
+        try:
+            procs.append(("marshal.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+        except OSError as e:
+            failed = str(e)
     for src, p in procs:
         out, _ = p.communicate()
         # hipcc's host pass does not know the packed-fp32 feature name and says so: harmless
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError(f"the compiler failed on {src}:\n{out}")
+            if src != "marshal.cpp":
+                raise RuntimeError(f"the compiler failed on {src}:\n{out}")
+            failed = out        # (the library works without it: linked first)
         if verbose and out.strip():
             print(out, flush=True)
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    if failed:
+        raise RuntimeError(f"the compiler failed on marshal.cpp (the library is built, and loads without it):\n{failed}")
     return LIB
 
 

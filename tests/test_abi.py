@@ -267,3 +267,30 @@ def test_attend_decode_gqa_argument_errors(lib):
     assert ws(ctypes.byref(s), 4, L, 1) == 0
     assert f(*args(splits=3)) == E_WS
     assert f(*args(splits=3, ws=FAKE, wsb=need - 1)) == E_WS
+
+
+def test_package_loads_without_the_native_marshalling():
+    """_marshal.so missing or built for another torch: a warning, the library itself, and the Python path for every call."""
+    import subprocess
+    import sys
+    code = """
+import sys, warnings
+sys.modules["paper_2601_10155_amd._marshal"] = None          # import raises ImportError
+import torch
+import paper_2601_10155_amd as lk
+from paper_2601_10155_amd import binding
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    binding.load_library()
+assert any("native marshalling" in str(x.message) for x in w)
+assert lk.version() >= 100 and lk.attend_decode_auto_splits(1, 32, 128, 8, 8192) == 8
+native = binding._native()
+names = ("encode_keys", "build_lut", "attend_decode", "decode_step", "decode_step_split", "decode_step_gqa", "score_prefill")
+assert all(getattr(native, n)(1, 2, 3) is None for n in names)
+try:
+    lk.lookat_encode_keys(torch.zeros((1, 1, 4, 64)), torch.zeros((1, 4, 256, 16)))
+except ValueError:                                            # the Python path's own refusal of host tensors
+    print("fine")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip() == "fine", r.stderr
