@@ -480,10 +480,10 @@ static bool ps_fits(const lookat_shape *s, const PsLayout &o, bool q_fp32)
 // Which blocks come here.  The alternatives are the lookup-and-sum kernel (blocks under 24 queries) and the dense kernel that
 // fetches centroids from L2.  Which one is faster depends on how the work falls on the chip: here a head's workgroups share one die
 // (few heads leave dies idle, nine to fifteen fill some dies twice) and each pays for the codebook, there every (b,h) is a workgroup or
-// more.  So the rule compares predicted times, fitted to 15900 measured pairs (8 to 19% off at nine sizes in ten; d_k 64
-// and 128, m 2 to 16, 1 to 1024 (b,h) of 1 to 40 heads, 1 to 64 queries, 64 to 12000 keys), and asks for a clear lead.  The blocks that it takes are
+// more.  So the rule compares predicted times, fitted to 15900 measured pairs (13 to 20% off at nine sizes in ten; d_k 64
+// and 128, m 2 to 16, 1 to 1024 (b,h) of 1 to 40 heads, 1 to 64 queries, 64 to 12000 keys).  The blocks that it takes are
 // 26% faster on the geometric mean at d_k = 128 under 24 queries (4 x 32 heads x 8 queries x 4096 keys, m = 16: 24.7 / 18.6 us, here
-// second); of the measured ones one in a thousand is more than 3% slower.  (A rule on m, T and the number of keys alone took 8% of them
+// second); of the measured ones five in a thousand are more than 3% slower.  (A rule on m, T and the number of keys alone took 8% of them
 // at a loss of 10% and more: 115 x 2 heads x 8 queries x 7625 keys, m = 8: 41 / 145 us.)
 static bool short_block(const lookat_shape *s, int T, int64_t L, bool q_fp32)
 {
@@ -500,23 +500,28 @@ static bool short_block(const lookat_shape *s, int T, int64_t L, bool q_fp32)
     const double MB = 4e-6 * (double)BH * T * (double)L;           // of scores
     const int64_t per_die = (s->H + 7) / 8 * o.tiles * o.shares, at_once = s->d_k == 64 ? 64 : 32;
     const double rounds = (double)((per_die + at_once - 1) / at_once);
-    const double blocks = (double)((s->B * o.blocks_per_bh + kPsWaves * o.shares - 1) / (kPsWaves * o.shares));   // of a wavefront
-    const double setup = s->d_k == 64 ? 1.5 : (q_fp32 ? 4.2 : (o.ng == 2 ? 3.5 : 2.9));
-    const double block = s->d_k == 64 ? (o.ng == 2 ? 3.8 : 2.4) : (q_fp32 ? 1.9 : (o.ng == 2 ? 2.5 : 2.0));
-    const double store = (s->d_k == 64 ? 0.27 : 0.2) + (L % 4 ? 0.3 : 0.0);       // (four-byte stores where rows are not 16-byte aligned)
+    // blocks of a wavefront (of the most loaded one, at d_k = 64, where a compute unit holds two workgroups)
+    const double blocks = s->d_k == 64 ? (double)((s->B * o.blocks_per_bh + kPsWaves * o.shares - 1) / (kPsWaves * o.shares))
+                                       : (double)(s->B * o.blocks_per_bh) / (double)(kPsWaves * o.shares);
+    const double setup = s->d_k == 64 ? 1.8 : (q_fp32 ? 4.7 : (o.ng == 2 ? 4.0 : 3.3));
+    const double block = s->d_k == 64 ? (o.ng == 2 ? 3.6 : 2.1) : (o.ng == 2 ? 2.5 : 1.8);
+    const double odd = L % 4 ? 1.0 : 0.0;                                         // (rows not 16-byte aligned: four-byte stores)
+    const double store = ((s->d_k == 64 ? 0.29 : 0.2) + 0.3 * odd) * (s->H < 4 ? 4.0 / s->H : 1.0);   // (one to three dies do not write faster)
     const double here = setup * (1.0 + rounds) + block * rounds * blocks + store * MB;
     double there;
     if (T >= 24) {
         const double panels = (double)BH * (double)((L + 127) / 128) / 512.0, tiles = (double)((T + 31) / 32);
-        there = q_fp32 ? 7.4 + 3.4 * panels + 2.0 * panels * tiles + 0.15 * MB : 5.9 + 2.9 * panels + 0.75 * panels * tiles + 0.09 * MB;
+        there = (q_fp32 ? 7.4 + 3.4 * panels + 2.0 * panels * tiles + 0.15 * MB : 5.9 + 2.9 * panels + 0.75 * panels * tiles + 0.09 * MB) +
+                0.2 * odd * MB;
     } else {
         const double turns = (double)((BH + 255) / 256), look = 1e-3 * (double)L * quads;
         if (s->d_k == 64)
-            there = -0.6 + 6.1 * turns + (0.04 + 0.078 * s->m) * turns * look + (1.0 + 0.023 * s->m) * 1e-3 * BH * look + 1.1 * quads + 0.04 * MB;
+            there = -0.6 + 6.1 * turns + (0.04 + 0.078 * s->m) * turns * look + (1.0 + 0.023 * s->m) * 1e-3 * BH * look + (0.9 + 0.046 * s->m) * quads;
         else
-            there = -2.4 + 11.4 * turns + (0.02 + 0.077 * s->m) * turns * look + (1.7 - 0.037 * s->m) * 1e-3 * BH * look + 1.6 * quads + 0.04 * MB;
+            there = -2.4 + 11.4 * turns + (0.02 + 0.077 * s->m) * turns * look + (1.7 - 0.037 * s->m) * 1e-3 * BH * look + (1.35 + 0.036 * s->m) * quads;
+        there += (0.04 + odd * (s->m <= 4 ? 0.35 : (s->m == 8 ? 0.15 : 0.0))) * MB;
     }
-    return here < (s->d_k == 64 ? 0.8 : 0.85) * (s->H < 4 ? 0.85 : 1.0) * there;   // (one to three heads: 10-30% too low here)
+    return here < (T >= 24 ? 0.92 : (s->d_k == 64 ? 0.97 : 1.0)) * there;
 }
 
 bool prefill_short_takes(const lookat_shape *s, int T, int64_t L, bool q_fp32) { return short_block(s, T, L, q_fp32); }

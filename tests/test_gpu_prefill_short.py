@@ -96,7 +96,7 @@ def test_which_kernel(form, B, H, T, L, d_k, m, dtype):
                                   "one subspace of 1e-30", "all 1e30", "all 1e-30"])
 @pytest.mark.parametrize("d_k,m,dtype,B,H,T,L", [(128, 16, "float16", 2, 16, 2, 3001), (128, 8, "float16", 2, 16, 8, 3000),
                                                  (128, 2, "float16", 2, 16, 16, 3000), (64, 16, "float16", 2, 16, 16, 3000),
-                                                 (128, 16, "float16", 2, 16, 32, 7000), (128, 4, "float32", 2, 16, 24, 7000),
+                                                 (128, 16, "float16", 4, 16, 32, 7000), (128, 4, "float32", 2, 16, 24, 7000),
                                                  (128, 16, "float32", 2, 16, 64, 7000)])
 def test_wide_codebooks(lk, kind, d_k, m, dtype, B, H, T, L):
     g = torch.Generator(device="cuda").manual_seed(d_k + m + T)
