@@ -398,7 +398,8 @@ __device__ __forceinline__ void load_centroid_rows(float (&row)[GS][DSUB], const
 // SKIP: a workgroup that does not encode skips the distances, half of the arithmetic (32 (b,h) x 8003 keys in 8 ranges, d_k =
 // 128, m = 8: 17.8 -> 14.2 us of kernel).  The branch keeps the table's and the distances' arithmetic apart, which costs a
 // workgroup that does encode 1 us at d_k = 64, m = 8 and, at d_k = 128, m = 16, the registers of a third workgroup per
-// compute unit (77 -> 106; 640 (b,h) x 104 keys 17.6 -> 23.6 us), so one range per (b,h) goes without.
+// compute unit (77 -> 106; 640 (b,h) x 104 keys 17.6 -> 23.6 us), so one range per (b,h) goes without -- except where paired
+// entries share the work: 32 x 12 (b,h) x 1024 keys, d_k = 64, m = 4 10.9 us with the branch, 11.3 without.
 // G > 1 (grouped queries): bh is the key/value head; the G query heads bh*G .. bh*G+G-1 each get their
 // table (lut_s[g][i][c]) from the one pass over the key/value head's codebook rows.
 template <typename FT, int DK, int M, int G, int NB, bool SKIP>
@@ -506,7 +507,7 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
 // PAD (tables given, ungrouped): the head size is a.d_k < DK, a multiple of 8; lanes past the end of a row repeat its last
 // 16 bytes and their sums are not written.
 template <int DK, int M, int WAVES, int OCC, typename FT = void, int G = 1, int PF = 1, int NB = 1, bool PAD = false,
-          bool LONE = false, bool SKIP = (G > 1)>
+          bool LONE = false, bool SKIP = (G > 1 || NB > 1)>
 __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOOKAT_DECODE_HEAD_PARAMS,
                                                                              const DecodeLate late)
 {
