@@ -288,6 +288,8 @@ def lookat_attend_decode(lut: torch.Tensor, codes: torch.Tensor, values: torch.T
     codes / values may be views of longer caches ([B,H,Lmax,*] sliced to L rows)."""
     rc = _native().attend_decode(lut, codes, values, scale, num_splits, workspace, out, scores_out)
     if rc is not None:
+        if out is None and rc.__class__ is not int:
+            return rc                # the output, allocated there
         if rc:
             _check(rc)
         return out
@@ -408,6 +410,8 @@ def lookat_decode_step_split(q: torch.Tensor, k_new: torch.Tensor, codebooks: to
     choice): for few (b,h) pairs and long contexts.  Arguments as lookat_decode_step."""
     rc = _native().decode_step_split(q, k_new, codebooks, codes, values, scale, num_splits, workspace, out)
     if rc is not None:
+        if out is None and rc.__class__ is not int:
+            return rc                # the output, allocated there
         if rc:
             _check(rc)
         return out
@@ -422,6 +426,8 @@ def lookat_decode_step_gqa(q: torch.Tensor, k_new: torch.Tensor, codebooks: torc
     H counts key/value heads, g = q.shape[1] // H."""
     rc = _native().decode_step_gqa(q, k_new, codebooks, codes, values, scale, num_splits, workspace, out)
     if rc is not None:
+        if out is None and rc.__class__ is not int:
+            return rc                # the output, allocated there
         if rc:
             _check(rc)
         return out

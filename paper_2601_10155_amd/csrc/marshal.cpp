@@ -1,8 +1,8 @@
 // Marshalling of the per-layer and per-block calls in native code.  The Python functions of binding.py read a dozen
 // attributes of every tensor, build a ctypes structure and convert a dozen arguments: 8.5 us a call, more than most decode
 // kernels take.  The functions here take the same objects, and where everything is as the call expects it (plain CUDA
-// tensors of the right type, shape and layout, output and workspace given) they make the library call and return its
-// status.  Anything else (a copy to make, a buffer to allocate, an argument to refuse) returns None and is left to the Python
+// tensors of the right type, shape and layout, output given) they make the library call and return its
+// status; where the library chooses the ranges they allocate a missing output and workspace too, and return the output.  Anything else (a copy to make, a buffer to allocate, an argument to refuse) returns None and is left to the Python
 // function, so what a call accepts, and with which error it refuses, is written down there alone.
 // The entry points are those of the library that binding.py has loaded, handed over as addresses.
 #define PY_SSIZE_T_CLEAN
@@ -139,14 +139,24 @@ const at::Tensor *codebooks_of(PyObject *o)
     return cb && cb->dim() == 4 && cb->size(2) == 256 ? cb : nullptr;
 }
 
-// (workspace object, bytes needed) -> pointer and size as binding.py would pass them; false: one has to be allocated.
+// (workspace object, bytes needed) -> pointer and size as binding.py would pass them; false: left to it.
+// `choice`: the ranges are the library's choice.  No workspace is then allocated here (`own`; on the current stream of that device, the
+// one the library is given, and returned to the allocator in its order): the Python path's allocation and second look
+// at the arguments cost as much as the ranges save (12 heads x 1024 keys, d_k = 128, attention without a workspace: 14.3 us a call;
+// 8.9 before the library cut such contexts; 7.3 now).
 // `fits`: the library takes fewer ranges where a given workspace does not hold its choice (or refuses, see answer()).
-bool workspace_of(PyObject *o, size_t need, bool fits, void *&ptr, size_t &bytes)
+bool workspace_of(PyObject *o, size_t need, bool choice, bool fits, const at::Tensor &like, at::Tensor &own, void *&ptr, size_t &bytes)
 {
     ptr = nullptr;
     bytes = 0;
-    if (o == Py_None)
-        return need == 0;
+    if (o == Py_None) {
+        if (need && choice) {
+            own = at::empty({(int64_t)need}, like.options().dtype(at::kByte));
+            ptr = own.data_ptr();
+            bytes = need;
+        }
+        return need == 0 || choice;
+    }
     const at::Tensor *w = plain(o);
     if (!w)
         return false;
@@ -162,6 +172,12 @@ PyObject *answer(int rc)
     return status(rc);
 }
 
+// The result of a call that was given no `out`: the tensor, or the status where that is not LOOKAT_OK.
+PyObject *answer(int rc, at::Tensor &made)
+{
+    return rc == LOOKAT_OK && made.defined() ? THPVariable_Wrap(std::move(made)) : answer(rc);
+}
+
 // q, k_new, codebooks, codes, values, scale, [num_splits, workspace,] out: kind 0 decode_step, 1 split, 2 gqa
 PyObject *step(PyObject *const *args, Py_ssize_t n, int kind)
 {
@@ -170,10 +186,15 @@ PyObject *step(PyObject *const *args, Py_ssize_t n, int kind)
     PyObject *out_o = args[n - 1];
     lookat_dtype qt, kt;
     const at::Tensor *q = dense_float(args[0], qt), *k = dense_float(args[1], kt), *cb = codebooks_of(args[2]);
-    const at::Tensor *codes = plain(args[3], at::kByte), *values = plain(args[4], at::kHalf), *out = dense(out_o, at::kFloat);
+    const at::Tensor *codes = plain(args[3], at::kByte), *values = plain(args[4], at::kHalf), *out = nullptr;
+    if (out_o != Py_None || !kind) {
+        out = dense(out_o, at::kFloat);
+        if (!out)
+            GIVE_UP;
+    }
     float scale;
     int64_t splits = 0, cs, vs;
-    if (!q || !k || !cb || !codes || !values || !out || qt != kt || codes->dim() != 4 || values->dim() != 4 || !number(args[5], scale) ||
+    if (!q || !k || !cb || !codes || !values || qt != kt || codes->dim() != 4 || values->dim() != 4 || !number(args[5], scale) ||
         (kind && !integer(args[6], 0, 0x7fffffff, splits)))
         GIVE_UP;
     const int64_t B = codes->size(0), H = codes->size(1), L = codes->size(2), m = codes->size(3), d_k = values->size(3);
@@ -192,27 +213,31 @@ PyObject *step(PyObject *const *args, Py_ssize_t n, int kind)
     } else if (q->numel() != B * H * d_k) {
         GIVE_UP;
     }
-    if (out->numel() != B * H * group * d_k)
+    if (out ? out->numel() != B * H * group * d_k : splits != 0)
         GIVE_UP;
     void *ws = nullptr, *stream;
     size_t ws_bytes = 0;
+    at::Tensor own;
     if (kind) {
         const size_t need = kind == 1 ? entry.decode_step_split_workspace_bytes(&s, L, (int32_t)splits)
                                       : entry.decode_step_gqa_workspace_bytes(&s, (int32_t)group, L, (int32_t)splits);
-        if (!workspace_of(args[7], need, splits == 0 && group == 1, ws, ws_bytes))
+        if (!workspace_of(args[7], need, splits == 0, splits == 0 && group == 1, *values, own, ws, ws_bytes))
             GIVE_UP;
     }
     if (!current_stream(*values, stream))
         GIVE_UP;
     const float *cbp = static_cast<const float *>(cb->data_ptr());
     uint8_t *cp = static_cast<uint8_t *>(codes->data_ptr());
-    float *op = static_cast<float *>(out->data_ptr());
+    at::Tensor made;
+    if (!out)
+        made = at::empty({B, H * group, d_k}, values->options().dtype(at::kFloat));
+    float *op = static_cast<float *>((out ? *out : made).data_ptr());
     const void *qp = q->data_ptr(), *kp = k->data_ptr(), *vp = values->data_ptr();
     CALL(rc, kind == 0   ? entry.decode_step(&s, L, qp, kp, qt, cbp, cp, cs, vp, vs, scale, op, stream)
              : kind == 1 ? entry.decode_step_split(&s, L, qp, kp, qt, cbp, cp, cs, vp, vs, scale, (int32_t)splits, ws, ws_bytes, op, stream)
                          : entry.decode_step_gqa(&s, (int32_t)group, L, qp, kp, qt, cbp, cp, cs, vp, vs, scale, (int32_t)splits, ws,
                                                  ws_bytes, op, stream));
-    return answer(rc);
+    return answer(rc, made);
 }
 
 // lut, codes, values, scale, num_splits, workspace, out, scores_out
@@ -221,26 +246,33 @@ PyObject *attend(PyObject *const *args, Py_ssize_t n)
     if (n != 8)
         GIVE_UP;
     const at::Tensor *lut = dense(args[0], at::kFloat), *codes = plain(args[1], at::kByte), *values = plain(args[2], at::kHalf);
-    const at::Tensor *out = dense(args[6], at::kFloat), *scores = args[7] == Py_None ? nullptr : dense(args[7], at::kFloat);
+    const at::Tensor *out = args[6] == Py_None ? nullptr : dense(args[6], at::kFloat), *scores = args[7] == Py_None ? nullptr : dense(args[7], at::kFloat);
     float scale;
     int64_t splits, cs, vs;
-    if (!lut || !codes || !values || !out || (args[7] != Py_None && !scores) || codes->dim() != 4 || values->dim() != 4 ||
+    if (!lut || !codes || !values || (args[6] != Py_None && !out) || (args[7] != Py_None && !scores) || codes->dim() != 4 || values->dim() != 4 ||
         !number(args[3], scale) || !integer(args[4], 0, 0x7fffffff, splits))
         GIVE_UP;
     const int64_t B = codes->size(0), H = codes->size(1), L = codes->size(2), m = codes->size(3), d_k = values->size(3);
     lookat_shape s;
     if (!shape_of(B, H, d_k, m, s) || values->size(0) != B || values->size(1) != H || values->size(2) != L ||
-        lut->numel() != B * H * m * 256 || out->numel() != B * H * d_k || (scores && scores->numel() != B * H * L) ||
+        lut->numel() != B * H * m * 256 || (out ? out->numel() != B * H * d_k : splits != 0) || (scores && scores->numel() != B * H * L) ||
         !bh_stride(*codes, cs) || !bh_stride(*values, vs))
         GIVE_UP;
     void *ws, *stream;
     size_t ws_bytes;
-    if (!workspace_of(args[5], entry.attend_decode_workspace_bytes(&s, L, (int32_t)splits), splits == 0, ws, ws_bytes) || !current_stream(*values, stream))
+    at::Tensor own;
+    if (!workspace_of(args[5], entry.attend_decode_workspace_bytes(&s, L, (int32_t)splits), splits == 0, splits == 0, *values, own, ws,
+                      ws_bytes) ||
+        !current_stream(*values, stream))
         GIVE_UP;
+    at::Tensor made;
+    if (!out)
+        made = at::empty({B, H, d_k}, values->options().dtype(at::kFloat));
+    float *op = static_cast<float *>((out ? *out : made).data_ptr());
     CALL(rc, entry.attend_decode(&s, L, static_cast<const float *>(lut->data_ptr()), static_cast<const uint8_t *>(codes->data_ptr()), cs,
-                                 values->data_ptr(), vs, scale, (int32_t)splits, ws, ws_bytes, static_cast<float *>(out->data_ptr()),
+                                 values->data_ptr(), vs, scale, (int32_t)splits, ws, ws_bytes, op,
                                  scores ? static_cast<float *>(scores->data_ptr()) : nullptr, stream));
-    return answer(rc);
+    return answer(rc, made);
 }
 
 // keys, codebooks, codes_out | None, cache | None, position

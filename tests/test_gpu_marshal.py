@@ -111,3 +111,43 @@ def test_calls_that_are_left(lk, both):
     with pytest.raises(lk.LookatError):
         lk.lookat_decode_step_split(c["q"], c["k"], c["cb"], c["codes"], c["values"], sc, num_splits=70000,
                                     workspace=torch.empty(1 << 28, dtype=torch.uint8, device="cuda"), out=c["out"])
+
+
+def test_no_workspace_and_no_output_where_the_library_chooses(lk, both):
+    """The ranges are the library's choice: a missing workspace and a missing output are allocated by the native module, with the
+    Python path's result, shape and type; explicit counts are left to it."""
+    c, g = case(L=3000, d_k=128, m=8), case(L=3000, d_k=128, m=8, group=4)
+    sc = 128 ** -0.5
+    assert lk.attend_decode_auto_splits(2, 4, 128, 8, 3000) > 1
+    lut = lk.lookat_build_lut(c["q"].unsqueeze(2), c["cb"]).view(2, 4, 8, 256)
+    scores = torch.empty((2, 4, 3000), device="cuda")
+    step = (c["q"], c["k"], c["cb"], c["codes"], c["values"], sc)
+    gqa = (g["q"], g["k"], g["cb"], g["codes"], g["values"], sc)
+    small = torch.empty(16, dtype=torch.uint8, device="cuda")
+    for n, call in enumerate([lambda: lk.lookat_attend_decode(lut, c["codes"], c["values"], sc),
+                              lambda: lk.lookat_attend_decode(lut, c["codes"], c["values"], sc, out=c["out"], scores_out=scores),
+                              lambda: lk.lookat_decode_step_split(*step), lambda: lk.lookat_decode_step_split(*step, out=c["out"]),
+                              lambda: lk.lookat_decode_step_gqa(*gqa), lambda: lk.lookat_decode_step_gqa(*gqa, out=g["out"])]):
+        a, b, taken = both(call)
+        assert taken, f"call {n} was left to the Python path"
+        assert a.shape == b.shape and a.dtype == b.dtype and a.device == b.device and torch.equal(a, b), f"call {n}"
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        stream.wait_stream(torch.cuda.default_stream())
+        a, b, taken = both(lambda: lk.lookat_decode_step_split(*step))
+    stream.synchronize()
+    assert taken and torch.equal(a, b)
+    for call in (lambda: lk.lookat_attend_decode(lut, c["codes"], c["values"], sc, num_splits=2, out=c["out"]),
+                 lambda: lk.lookat_attend_decode(lut, c["codes"], c["values"], sc, num_splits=1),
+                 lambda: lk.lookat_decode_step_gqa(*gqa, workspace=small, out=g["out"])):
+        a, b, taken = both(lambda: call().clone())
+        assert not taken and torch.equal(a, b)
+    graph = torch.cuda.CUDAGraph()                     # recorded: workspace and output come from the graph's own pool
+    with torch.cuda.graph(graph):
+        out = lk.lookat_decode_step_split(*step)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        assert torch.equal(out, lk.lookat_decode_step_split(*step))
+    with pytest.raises(lk.LookatError):
+        lk.lookat_attend_decode(lut, c["codes"], torch.empty(c["values"].numel() + 1, dtype=torch.float16, device="cuda")[1:].view(2, 4, 3000, 128), sc)
