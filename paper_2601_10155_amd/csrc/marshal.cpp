@@ -143,7 +143,7 @@ const at::Tensor *codebooks_of(PyObject *o)
 // `choice`: the ranges are the library's choice.  No workspace is then allocated here (`own`; on the current stream of that device, the
 // one the library is given, and returned to the allocator in its order): the Python path's allocation and second look
 // at the arguments cost as much as the ranges save (12 heads x 1024 keys, d_k = 128, attention without a workspace: 14.3 us a call;
-// 8.9 before the library cut such contexts; 7.3 now).
+// 8.9 before the library cut such contexts; 6.9 now).
 // `fits`: the library takes fewer ranges where a given workspace does not hold its choice (or refuses, see answer()).
 bool workspace_of(PyObject *o, size_t need, bool choice, bool fits, const at::Tensor &like, at::Tensor &own, void *&ptr, size_t &bytes)
 {
