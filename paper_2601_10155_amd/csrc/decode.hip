@@ -1069,9 +1069,13 @@ static bool step_pairs_entries(const lookat_shape *s, int group, int64_t L, int 
 // paired / cut: d_k = 128, m = 4: 264 (b,h) x 2048 keys 33.9 / 45.8, 320 x 5000 74 / 78, 264 x 12000 154 / 144, 384 x 8192 129 / 140;
 // m = 8: 288 x 2048 34 / 40, 264 x 5000 71 / 64, 384 x 12000 181 / 187; d_k = 64, m = 2: 288 x 3500 27 / 32, 320 x 5000 37 / 43,
 // 264 x 12000 82 / 76; m = 4: 264 x 3500 26.4 / 27.9, 264 x 8192 53 / 50, 384 x 32768 252 / 254.
+// Up to 1024 keys, two tiles per wavefront, that are requested before the table is there, a cut gains nothing (d_k = 128, m = 8, one
+// range / four: 1 (b,h) 10.7 / 10.4, 12 11.7 / 11.9, 32 12.4 / 12.5) and costs a launch.
 static int step_auto_splits(const lookat_shape *s, int64_t L, int unfused)
 {
     const int64_t pays = s->d_k == 128 ? (s->m == 4 ? 10000 : 2500) : (s->m == 2 ? 10000 : 5000);
+    if (L <= 2 * kStepWaves * kTile)
+        return 1;
     return step_pairs_entries(s, 1, L, 1) && ((int64_t)s->B * s->H > 320 || L < pays) ? 1 : unfused;
 }
 

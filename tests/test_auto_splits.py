@@ -82,13 +82,14 @@ def test_auto_splits_without_a_workspace(B, H, L):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("d_k,m,B,H,L,cut", [(128, 4, 22, 12, 2048, False), (128, 8, 24, 12, 2100, False), (128, 4, 48, 8, 2500, False),
-                                             (64, 4, 22, 12, 3500, False), (128, 8, 22, 12, 2600, True), (128, 4, 23, 12, 2048, True)])
-def test_fused_step_keeps_paired_entries(d_k, m, B, H, L, cut):
-    """Where one range is served by paired batch entries the library cuts only what gains by it (odd batches have no pairs)."""
+                                             (64, 4, 22, 12, 3500, False), (128, 8, 22, 12, 2600, True), (128, 4, 23, 12, 2048, True),
+                                             (128, 8, 1, 12, 1024, False), (128, 8, 1, 12, 1400, True)])
+def test_fused_step_is_cut_where_it_gains(d_k, m, B, H, L, cut):
+    """Where one range is served by paired batch entries, or is two tiles per wavefront, the library cuts only what gains by it."""
     import torch
     lk = _lk()
     assert lk.attend_decode_auto_splits(B, H, d_k, m, L) > 1 or not cut
-    assert lk.decode_step_entries_per_workgroup(B, H, d_k, m, L) == (1 if B % 2 else 2)
+    assert lk.decode_step_entries_per_workgroup(B, H, d_k, m, L) == (1 if B % 2 else 2)      # (odd batches have no pairs)
     g = torch.Generator(device="cuda").manual_seed(L)
     rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
     codes = torch.randint(0, 256, (B, H, L, m), generator=g, device="cuda", dtype=torch.uint8)
