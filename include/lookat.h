@@ -54,7 +54,7 @@ typedef enum {
     LOOKAT_ERR_SHAPE = -2,       /* non-positive size, m does not divide d_k, stride too small ... */
     LOOKAT_ERR_DTYPE = -3,       /* dtype tag is not LOOKAT_F16 / LOOKAT_F32 */
     LOOKAT_ERR_ALIGN = -4,       /* a pointer or stride breaks the alignment stated below */
-    LOOKAT_ERR_WORKSPACE = -5,   /* workspace missing or smaller than *_workspace_bytes() */
+    LOOKAT_ERR_WORKSPACE = -5,   /* workspace missing or too small (see num_splits in lookat_attend_decode) */
     LOOKAT_ERR_UNSUPPORTED = -6, /* valid problem, but outside the shapes this build handles */
     LOOKAT_ERR_HIP = -7          /* the HIP runtime refused a launch; text in lookat_last_error() */
 } lookat_status;
@@ -327,7 +327,8 @@ int lookat_attend_decode_launch_shape(const lookat_shape *shape, int64_t L, int3
  *     in L2, or for short blocks from a copy in LDS) on the matrix cores; centroids, and fp32 queries, are
  *     scaled by a power of two and split into two fp16 terms (products exact; the product of two small terms,
  *     2^-22 of a product, is dropped), accumulation in fp32 over all d_k coordinates in the matrix
- *     unit's order;
+ *     unit's order; short blocks whose keys meet centroids that the head's power of two cannot serve (more
+ *     than 33 binary orders apart) are scored with fp32 operands instead;
  *   - otherwise: per-query tables built in LDS and summed by look-up (table entries accumulated in
  *     fp32, the coordinates j in ascending groups of four whose inner order depends on the
  *     centroid; entries then summed in ascending i).

@@ -107,9 +107,9 @@ __global__ __launch_bounds__(kPdThreads, 2) void score_prefill_dense_kernel(cons
 
     // workgroup ids go round-robin to the 8 dies; all panels of a (b,h) stay on one die (its queries are
     // re-read by every panel and stay in that die's L2) and run side by side there: the panels of a score
-    // row are then written at about the same time, which the memory system rewards (a launch that only
-    // writes -inf in this pattern: 371 us with the panels of a (b,h) side by side, 418 us with the same
-    // panel of many (b,h) side by side; 4 x 32 heads x 2048 x 2048 scores)
+    // row are then written at about the same time, which the memory system rewards (a launch that only writes -inf, 4 x 32
+    // heads x 2048 x 2048 scores: in whole panels 371 us with the panels of a (b,h) side by side, 418 us with the same
+    // panel of many (b,h) side by side; in strips of 256 rows, panels side by side, 345 us)
     const int xcd = blockIdx.x % 8;
     const int slot = blockIdx.x / 8;
     const int panel = slot % a.panels;
