@@ -398,8 +398,9 @@ __device__ __forceinline__ void load_centroid_rows(float (&row)[GS][DSUB], const
 // SKIP: a workgroup that does not encode skips the distances, half of the arithmetic (32 (b,h) x 8003 keys in 8 ranges, d_k =
 // 128, m = 8: 17.8 -> 14.2 us of kernel).  The branch keeps the table's and the distances' arithmetic apart, which costs a
 // workgroup that does encode 1 us at d_k = 64, m = 8 and, at d_k = 128, m = 16, the registers of a third workgroup per
-// compute unit (77 -> 106; 640 (b,h) x 104 keys 17.6 -> 23.6 us), so one range per (b,h) goes without -- except where paired
-// entries share the work: 32 x 12 (b,h) x 1024 keys, d_k = 64, m = 4 10.9 us with the branch, 11.3 without.
+// compute unit (77 -> 106; 640 (b,h) x 104 keys 17.6 -> 23.6 us), so one range per (b,h) goes without -- except where it measured
+// faster with it: paired entries (32 x 12 (b,h) x 1024 keys, d_k = 64, m = 4 10.9 us, 11.3 without), the lone instances (1-3%), m = 2
+// and 4 at d_k = 128 (over 256 (b,h) 1-5%) and m = 2 at d_k = 64 (1%).
 // G > 1 (grouped queries): bh is the key/value head; the G query heads bh*G .. bh*G+G-1 each get their
 // table (lut_s[g][i][c]) from the one pass over the key/value head's codebook rows.
 template <typename FT, int DK, int M, int G, int NB, bool SKIP>
@@ -990,14 +991,13 @@ constexpr int kStepPrefetch = 2;
 constexpr int kStepWaves = 2 * kDecWaves;   // four wavefronts build the table, four start streaming at once
 // LONE (d_k = 128): where every workgroup has a compute unit to itself, which takes at most 32 on a die (all ranges of a (b,h) run on
 // one), and its range is longer than the one tile per wavefront that both forms request first.  LONE / otherwise, fp16, geometric mean
-// over m = 2, 4, 8, 16, at 96..256 workgroups of 256 / 512 / 640 / 1024 / 2048 / 8192 keys: 1.05 / 1.02 / 0.99 / 0.96 / 0.96 / 0.98;
-// up to 64 workgroups of one range per (b,h): 1.07 / 1.05 / 1.00 / 0.98 / 1.01 / 1.01, not taken; of several: 1.05 / 1.03 / 0.99 /
-// 0.96 / 0.99 / 1.00.  256 (b,h) x 1024 keys, m = 8: 14.2 / 15.8 us.  At d_k = 64, where a tile is one round of requests anyway, it is
-// 1-2% slower and not taken.
+// over m = 2, 4, 8, 16, at 96..256 workgroups of 256 / 512 / 640 / 1024 / 2048 / 8192 keys: 1.05 / 1.02 / 0.99 / 0.96 / 0.96 / 0.98; up to
+// 64 workgroups: 1.06 / 1.04 / 1.00 / 0.97 / 1.00 / 1.00.  256 (b,h) x 1024 keys, m = 8: 14.2 / 15.8 us.  At d_k = 64, where a tile is one
+// round of requests anyway, it is 1-2% slower and not taken.
 static bool step_is_lone(const DecodeArgs &a)
 {
     const int64_t on_a_die = ((int64_t)a.BH + kXcds - 1) / kXcds * a.splits;
-    return a.d_k == 128 && on_a_die <= 32 && a.keys_per_split > kStepWaves * kTile && (a.splits > 1 || a.BH > 64);
+    return a.d_k == 128 && on_a_die <= 32 && a.keys_per_split > kStepWaves * kTile;
 }
 template <int DK, typename FT>
 static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
@@ -1006,26 +1006,28 @@ static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
     const size_t lds = ((size_t)a.m * kCentroids + (size_t)kStepWaves * (DK + 2)) * sizeof(float) +
                        (size_t)a.m * kDecWaves * (sizeof(double) + sizeof(int));
     const bool lone = step_is_lone(a);
-    const bool skip = a.splits > 1;
+    const bool cut = a.splits > 1;
 #define LOOKAT_STEP_LAUNCH(M_, OCC_, PF_, LONE_, SKIP_)                                                                   \
     hipLaunchKernelGGL((decode_split_kernel<DK, M_, kStepWaves, OCC_, FT, 1, PF_, 1, false, LONE_, SKIP_>), grid, block,  \
                        lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true), late_of(a))
+    // One range skips nothing, but the branch also separates the two jobs: with few subspaces, and in the lone instances, that is
+    // faster (see SKIP); with 16 subspaces of 4 it costs registers that the 128 do not hold.
 #define LOOKAT_STEP_CASE(M_)                                                                                              \
-    case M_:                                                                                                              \
+    case M_: {                                                                                                            \
+        constexpr bool kAlways = M_ <= (DK == 128 ? 4 : 2), kNever = DK == 64 && M_ == 16;                                 \
+        constexpr int kAhead = M_ == 16 ? 1 : kStepPrefetch;                                                              \
         if constexpr (DK == 128) {                                                                                        \
             if (lone) {                                                                                                   \
-                if (skip)                                                                                                 \
-                    LOOKAT_STEP_LAUNCH(M_, 2, 2, true, true);                                                             \
-                else                                                                                                      \
-                    LOOKAT_STEP_LAUNCH(M_, 2, 2, true, false);                                                            \
+                LOOKAT_STEP_LAUNCH(M_, 2, 2, true, true);                                                                 \
                 return true;                                                                                              \
             }                                                                                                             \
         }                                                                                                                 \
-        if (skip && !(DK == 64 && M_ == 16))   /* (there the branch costs registers that the 128 do not hold) */          \
-            LOOKAT_STEP_LAUNCH(M_, 4, (M_ == 16 ? 1 : kStepPrefetch), false, (DK != 64 || M_ != 16));                     \
+        if (cut || kAlways)                                                                                               \
+            LOOKAT_STEP_LAUNCH(M_, 4, kAhead, false, !kNever);                                                            \
         else                                                                                                              \
-            LOOKAT_STEP_LAUNCH(M_, 4, (M_ == 16 ? 1 : kStepPrefetch), false, false);                                      \
-        return true;
+            LOOKAT_STEP_LAUNCH(M_, 4, kAhead, false, kAlways);                                                            \
+        return true;                                                                                                      \
+    }
     switch (a.m) {
         LOOKAT_STEP_CASE(2)
         LOOKAT_STEP_CASE(4)
