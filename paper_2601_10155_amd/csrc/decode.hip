@@ -883,10 +883,10 @@ static double splits_us(const lookat_shape *s, int64_t L, int64_t S)
            range / rate((double)(rest * fullest), (double)rest) + (S > 1 ? kMerge : 0.0);
 }
 // Ranges per (b,h) when the caller leaves the choice to the library: base_splits, unless another count is predicted to take
-// less time (4% and 1 us less, where that means a second launch), then the count with the least; `workspace`: a caller that
+// 4% less time (and 1 us less, where that means a second launch), then the count with the least; `workspace`: a caller that
 // brings less than that needs gets the best count that it holds, but no less than base_splits.
 // Measured at 28 numbers of (b,h) from 1 to 520, 600 to 32768 keys and nine (d_k, m), fused and not: 0.86 of the time of
-// base_splits on the geometric mean, 3% off the best of ten counts; four launches in a thousand more than 3% slower than
+// base_splits on the geometric mean, 3% off the best of ten counts; two launches in a thousand more than 3% slower than
 // base_splits.  us per fused call, base / taken [ranges], d_k = 128, m = 8: 1 x 8192 17.1 / 11.4 [16]; 1 x 32768 18.1 / 14.6 [24];
 // 12 x 4096 18.4 / 12.1 [8]; 20 x 32768 46.4 / 33.7 [8]; 32 x 2048 17.4 / 13.5 [4]; 264 x 8192 126 / 106 [6].  A model that dealt the
 // workgroups evenly to 256 compute units took 128 ranges for 1 x 32768 (37.4 us), 12 for 20 x 8192 (21.5; 8: 14.7) and one for
@@ -901,7 +901,7 @@ static int auto_splits(const lookat_shape *s, int64_t L, size_t workspace = SIZE
     const double base_us = splits_us(s, L, base);
     auto choose = [&](int low, size_t bytes) {
         int best = base;
-        double best_us = base == 1 ? 0.96 * base_us - 1.0 : base_us;
+        double best_us = 0.96 * base_us - (base == 1 ? 1.0 : 0.0);
         for (int S : counts) {
             if (L < (int64_t)S * 256 || BH * S > 4096)
                 break;
