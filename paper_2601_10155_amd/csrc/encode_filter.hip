@@ -5,53 +5,56 @@
 // subtract / multiply / add, coordinates ascending, lowest index on ties.  Evaluating d for all 256
 // centroids costs 3 fp64 operations per coordinate and centroid.  Here the 256 candidates are
 // first ranked with
-//     a_c = |C[c]|^2 - 2 k.C[c]        ( = d_c - |k|^2 up to rounding )
-// computed on the matrix cores (rows = 32 centroids, columns = 32 keys, the norm as the
-// accumulator's initial value).  If the smallest and the second smallest a_c of a key are further
-// apart than twice a bound on |a_c - (exact d_c - |k|^2)|, the smallest one is the unique exact argmin
-// and nothing else is evaluated.  Otherwise (near ties, exact ties, NaN or infinite inputs: a few
-// sub-vectors in ten thousand on the workloads here) the wavefront evaluates the exact rule for that key
-// over all 256 centroids.  Either way the code is the one the exact scan produces, bit for bit.
+//     a_c = |C'[c]|^2 - 2 k'.C'[c]        ( = |k' - C'[c]|^2 - |k'|^2 up to rounding )
+// computed on the matrix cores (rows = 32 centroids, columns = 32 keys, the norm as the accumulator's initial value) from
+// operands k', C' that stand for the key and the centroids in fp16.  The candidates whose a_c lies within a bound tau of
+// the smallest are the only ones that the exact rule can choose.  If there is one, it is the code; otherwise (near ties,
+// exact ties, NaN or infinite inputs: one or two sub-vectors in a hundred on the workloads here) the exact rule is evaluated
+// over these candidates, two of 256 as a rule.  Either way the code is the one the exact scan produces, bit for bit.
 //
-// The product.  Codebook entries are scaled by a power of two s_c (largest entry near 2^13) and split into
-// two fp16 terms, -2 s_c C = hi + lo, |error| <= 2^-22 |2 s_c C|; products of fp16 terms are exact in fp32.
-//   * fp16 keys enter as they are (s_k = 1);
-//   * fp32 keys are scaled by s_k = s_c 2^-6 (a key as large as the largest centroid entry lands near 2^7,
-//     which leaves a factor of 256 to fp16's largest value; longer keys go to the exact rule) and split into
-//     two truncated fp16 terms, |error| <= 2^-20 |s_k k|.
-// v_mfma_f32_32x32x16_f16 contracts sixteen slots at a time: sub-vectors of up to 4 and up to 8 coordinates
-// put the terms of one centroid side by side in the slots of one instruction, longer ones take one
-// instruction per 16 coordinates and product of terms (hi.hi, lo.hi, and for fp32 keys hi.lo; lo.lo, below
-// 2^-20 of the product, is dropped there).  The scores are s_c s_k a_c.  The fp32 matrix
-// instruction is not used: it runs at a sixteenth of the rate and shares the vector ALU's datapath.
-// Sub-vector lengths of 2 to 64 without an instance of their own are padded with zeros to 4, 8, 16, 32 or 64.
+// The operands.  Codebook entries are scaled by a power of two s_c (largest entry near 2^13); fp32 keys by s_k = s_c 2^-6 (a
+// key as large as the largest centroid entry lands near 2^7, which leaves a factor of 500 to fp16's largest value; longer keys
+// go to the exact rule), fp16 keys enter as they are (s_k = 1).  v_mfma_f32_32x32x16_f16 contracts sixteen slots at a time:
+//   * sub-vectors of 16 and more coordinates enter as ONE fp16 term each, keys and centroids, one instruction per 16
+//     coordinates; the norms are those of the rounded centroids, so that a_c is a distance between rounded points;
+//   * sub-vectors of up to 8 have room for two terms of a centroid, -2 s_c C = hi + lo, |error| <= 2^-22 |2 s_c C|, beside
+//     one term of the key;
+//   * sub-vectors of up to 4 have room for both terms of both, and for the norm;
+//   * launches of a pair of key blocks or two per wavefront (FINE) take both terms of everything, in more instructions: there
+//     the undecided keys' round trip to memory would be a fifth of the launch.
 //
-// Smallest, second smallest and index.  What bounds the kernel is vector issue: 128 scores per lane and
-// block of 32 keys have to be looked at.  Keeping (smallest, second, index) candidate by candidate takes four
-// instructions each.  Here a candidate's index is written as digits (row tile t, quarter q, lane half h,
-// element e: index = 32 t + 8 q + 4 h + e) and only group minima are formed, over the candidates that share
-// (q, e) and over those that share t, three operands at a time (v_minimum3_f32): one instruction per
-// candidate for both.  The digit at which a digit's group minima are smallest is that digit of the argmin; and since
-// two different candidates differ in at least one digit, the smallest "second smallest group minimum" over
-// the digits is exactly the second smallest score.  A NaN anywhere makes the minima NaN (v_minimum3
-// propagates it) and sends the key to the exact rule.  Two blocks of 32 keys are finished together, one per
-// lane half.
-//   Measured (us per call, this kernel / the one that tracked candidate by candidate and ranked fp32 keys with the fp32
-//   matrix instruction): 4 x 32 heads x 2048 fp16 keys, 16 subspaces of 8: 88 / 181; 32 x 12 heads x 1024 fp32 keys, 4
-//   of 16: 63 / 167; 32 heads x 16384 fp32 keys, 8 of 16: 145 / 425.  Vector and matrix issue add up (counters: 71% and
-//   18% of the busy cycles of the first): the matrix instructions do not hide behind the minima, whatever the order.
-// A key that the filter cannot decide is only noted (one ballot per 64 keys in LDS); when its keys are through, the
-// workgroup's wavefronts share the noted ones out.  Looked at on the spot, one held up its wavefront for microseconds, and
-// the unluckiest wavefront the launch (32 of 88 us at the second size above).
+// Error bound.  Let delta be a bound on |k - k'| + max_c |C[c] - C'[c]| (exact differences, squared and summed in fp32, with
+// 1.002 for the rounding of the sums).  By the triangle inequality the exact argmin a and the smallest a_b satisfy
+//     |k' - C'[a]| <= |k - C[a]| + delta <= |k - C[b]| + delta <= |k' - C'[b]| + 2 delta,
+// so with d = |k' - C'[b]| = sqrt(a_b + |k'|^2) no candidate beyond a_b + 4 delta (d + delta) can be the argmin.  To this
+// comes the fp32 rounding of a_c: a sum of n terms (d_sub + 1; 2 d_sub + 1 and 4 d_sub + 1 with two terms of the centroids
+// and of both, whose dropped terms amount to at most 2, respectively 14, more 2^-23) whose magnitudes add up to at most
+// S = |k'|^2 + 2 max_c |C'[c]|^2 (since 2|k.C| <= |k|^2 + |C|^2) times 1 + 2^-9.  With at most 2^-23 relative error per
+// accumulation step (round-to-nearest would give 2^-24) and norms summed in fp64 the error is at most E = (n + 3) 2^-23 S (n + 15 with
+// fp32 keys in two terms).  tau = 2.25 E + 4.01 delta (d + delta): twice E for the two candidates, the rest for S, for the rounding of
+// tau and of the limit and for d (whose square takes tau instead of E); plus 1e-30 for flushed denormals.  An infinite or NaN limit, fp32
+// keys beyond fp16's range after scaling and a codebook whose scale would leave [2^-60, 2^60] make every centroid a candidate.
 //
-// Error bound.  a_c is an fp32 sum of n terms (2 d_sub + 1 for fp16 keys, 4 d_sub + 1 for fp32 keys, whose
-// split residuals and dropped terms amount to at most 14 2^-23 more) whose magnitudes add up to at most
-// S = |k|^2 + 2 max_c |C[c]|^2 (since 2|k.C| <= |k|^2 + |C|^2) times 1 + 2^-9.  With at most 2^-23 relative
-// error per accumulation step (round-to-nearest would give 2^-24) and the fp32 rounding of the norms,
-// |a_c - exact| <= (2 d_sub + 4) 2^-23 S, respectively (4 d_sub + 16) 2^-23 S.  The threshold used is
-// 2.25 times that (twice for the two candidates, the rest for S and for the threshold's own rounding), plus 1e-30 for flushed
-// denormals; an infinite or NaN S, a key beyond fp16's range after scaling and a codebook whose scale would
-// leave [2^-60, 2^60] go to the exact rule.
+// Which candidates.  128 scores per lane and block of 32 keys have to be looked at.  A candidate's index is written as
+// digits (row tile t, quarter q, lane half h, element e: index = 32 t + 8 q + 4 h + e) and only group minima are formed, over the
+// candidates that share (q, e) and over those that share t, three operands at a time (v_minimum3_f32): one instruction per candidate
+// for both.  A digit value whose group minimum exceeds the limit holds no candidate; the remaining values of 2q + h, e and t, as bits of
+// a word, give every combination that can be one.  One bit per digit: the key is decided, and the bits are its code.  A NaN anywhere
+// makes the minima NaN (v_minimum3 propagates it).  Two blocks of 32 keys are finished together, one per lane half.
+// An undecided key is noted with its word in LDS; when the pairs are through, eight lanes share a noted key's combinations.
+//
+// What bounds it: vector issue and power.  A pair of blocks costs 410 to 480 vector instructions, 256 of them the minima; matrix
+// instructions of one wavefront hide behind another's minima, but the chip lowers its clock for them (a loop like this one with
+// the three instructions per tile that two terms of both need runs at 1.5 GHz, with one at 1.85 GHz, and takes 823 and 514 ns per block and
+// SIMD), and reads of operands and norms from LDS count as well (66 ns of 514 for the norms).  Hence one term, norms (and operands, where they
+// fit) in registers, two wavefronts per SIMD, both blocks sharing what is still read; a spilled register in the loop costs far
+// more than it saves, since its reload waits for the key requests ahead of it.  Wavefronts take their pairs from a shared counter: the
+// SIMD favours its oldest wavefront, and with fixed shares the last one ran alone for a third of the time.
+//   Measured (us per call, this kernel / the one with two terms of everything, norms and operands from LDS, 256 centroids exactly for
+// every undecided key): 4 x 32 heads x 2048 fp16 keys, 16 subspaces of 8: 80 / 85; 32 x 12 heads x 1024 fp32 keys, 4 of 16: 44 / 62;
+// 32 heads x 16384 fp32 keys, 8 of 16: 95 / 135; 8 x 16 x 2048, d_k = 128: fp16 8 of 16 45 / 59, 4 of 32 35 / 54, 2 of 64 33 / 55;
+// fp32 16 of 8 81 / 110, 4 of 32 41 / 72, 2 of 64 43 / 80; fp16, d_k = 64, 16 of 4 74 / 78.  Small ones: 24 (b,h) x 100 keys, fp16
+// 8 of 16: 6.9 / 7.2 (with one term 8.5).
 //
 // This translation unit must be compiled with -ffp-contract=off (the exact rule).
 #include <cstdlib>
@@ -66,15 +69,14 @@ namespace lookat {
 typedef float ef_v16f __attribute__((ext_vector_type(16)));
 typedef float ef_v4f __attribute__((ext_vector_type(4)));
 typedef _Float16 ef_v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 ef_v4h __attribute__((ext_vector_type(4)));
 typedef _Float16 ef_v2h __attribute__((ext_vector_type(2)));
 typedef __fp16 ef_v2fp __attribute__((ext_vector_type(2)));
 
-constexpr int kEfThreads = 256;
-constexpr int kEfWaves = kEfThreads / kWave;
 constexpr int kEfTiles = kCentroids / 32;
-constexpr int kEfRounds = 256;         // pairs of key blocks a wavefront may take
-static_assert(kEfThreads == kCentroids, "thread c looks after centroid c while the codebook is set up");
+constexpr int kEfList = 512;           // undecided keys a wavefront can note before they are worked off
+constexpr int kEfShared = 48;           // candidates that eight lanes share; for a key with more the whole wavefront takes all centroids
+constexpr int kEfMore = 1 << 16;       // flag beside the number of noted keys: the wavefront has pairs left
+constexpr uint32_t kEfAll = 0xfffffu;  // every value of every digit: 2q + h in bits 0..7, e in 8..11, t in 12..19
 
 template <typename T>
 __device__ __forceinline__ float ef_to_f32(T v);
@@ -169,45 +171,113 @@ __device__ __forceinline__ int ef_exact_code(const KT *key_sub, const float *cb,
     return c;
 }
 
+// Squared distance by the exact rule: fp64, one rounding per subtract, multiply and add, coordinates ascending.
+template <typename KT, int DP, bool FULL>
+__device__ __forceinline__ double ef_exact_distance(const KT *key_sub, const float *row, int d_sub)
+{
+    constexpr int JB = DP < 16 ? DP : 16;
+    double acc = 0.0;
+#pragma unroll 1
+    for (int j0 = 0; j0 < DP; j0 += JB) {
+        KT x[JB];
+        float y[JB];
+#pragma unroll
+        for (int q = 0; q < JB; q += 4) {
+            KT x4[4];
+            float y4[4];
+            ef_load4<FULL, KT>(key_sub, j0 + q, d_sub, x4);
+            ef_load4<FULL, float>(row, j0 + q, d_sub, y4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[q + e] = x4[e];
+                y[q + e] = y4[e];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < JB; ++q)
+            if (FULL || j0 + q < d_sub) {
+                const double diff = (double)ef_to_f32<KT>(x[q]) - (double)y[q];
+                const double sq = diff * diff;
+                acc = acc + sq;
+            }
+    }
+    return acc;
+}
+
+// Index of the n-th set bit (n from 0, below the number of set bits) of an eight-bit word.
+__device__ __forceinline__ int ef_nth_bit(uint32_t bits, int n)
+{
+    int at = 0;
+#pragma unroll
+    for (int width = 4; width >= 1; width >>= 1) {
+        const uint32_t low = bits >> at & ((1u << width) - 1u);
+        const int c = __builtin_popcount(low);
+        const bool up = n >= c;
+        n = up ? n - c : n;
+        at = up ? at + width : at;
+    }
+    return at;
+}
+
+// (value, index) of the lane that the DPP control selects, taken where it is the smaller one (lowest index on ties).
+template <int CTRL>
+__device__ __forceinline__ void ef_argmin_step(double &best, int &code)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(best);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)u, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(u >> 32), (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
+    const double d = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    const int c = __builtin_amdgcn_update_dpp(code, code, CTRL, 0xf, 0xf, false);
+    if (d < best || (d == best && c < code)) {
+        best = d;
+        code = c;
+    }
+}
+
 // Matrix operands of a (head, subspace): slices of 16 slots; lane (col, g) of an operand holds slots 8g .. 8g+7 of its
 // row (centroid) or column (key).
-//   DP >= 16: slice s carries coordinates 16s .. 16s+15; one operand of hi terms and one of lo terms;
-//   DP == 8:  one operand, hi terms in slots 0..7, lo terms in 8..15; the key's terms stand twice;
-//   DP == 4:  one operand, slots hi(4) lo(4) hi(4) lo(4); the key's hi terms in slots 0..7, its lo terms (fp32 keys;
-//             zero for fp16 keys) in 8..15.
-template <typename KT, int DP>
+//   DP >= 16: slice s carries coordinates 16s .. 16s+15, one fp16 term each; FINE: two terms each, in two operands;
+//   DP == 8:  hi terms of the centroids in slots 0..7, lo terms in 8..15; the key's single term stands twice; FINE: its
+//             second term in an operand of its own;
+//   DP == 4:  slots hi(4) lo(4) hi(4) norm(3); the key's hi terms in slots 0..7, its lo terms (fp32 keys;
+//             zero for fp16 keys) in 8..11, 2^x against the norm's three terms.
+// FINE leaves no term out, as DP == 4: for launches of few pairs, where the undecided keys' extra round trip to memory is what
+// counts and not the matrix instructions.
+template <typename KT, int DP, bool FINE>
 struct EfShape {
     static constexpr bool K32 = std::is_same<KT, float>::value;
     static constexpr int NS = DP >= 16 ? DP / 16 : 1;              // slices
-    static constexpr int NA = DP >= 16 ? 2 * NS : 1;               // centroid operands per row tile
-    static constexpr int NB = DP == 4 ? 1 : (K32 ? 2 * NS : NS);   // key operands
-    static constexpr int NI = DP == 4 ? 1 : (DP == 8 ? NB : (K32 ? 3 : 2) * NS);   // instructions per row tile
     static constexpr int NL = DP == 4 ? 1 : 2 * NS;                // 4-coordinate pieces a lane loads of a key
-    static constexpr bool ALDS = DP >= 16;                         // centroid operands in LDS, not in registers
-    static constexpr bool NORM_SLOTS = DP == 4;                    // the norm sits in spare slots, else it starts the accumulator
-    static constexpr int WAVES = DP <= 16 ? (K32 && DP == 8 ? 3 : 4) : (DP <= 32 ? 3 : 2); // wavefronts per SIMD the registers (and LDS) allow
-    // which operands instruction k of a row tile takes: hi.hi and lo.hi of every slice, then hi.lo
-    static __device__ __forceinline__ constexpr int a_of(int k) { return DP >= 16 ? (k < NA ? k : 2 * (k - NA)) : 0; }
-    static __device__ __forceinline__ constexpr int b_of(int k) { return DP >= 16 ? (k < NA ? k / 2 : NS + (k - NA)) : k; }
+    static constexpr bool SLOTS = DP == 4;                         // the norm sits in spare slots, else it starts the accumulator
+    static constexpr bool KLO = K32 && DP >= 8 && !FINE;           // the keys' lo terms are left out and bounded
+    static constexpr bool CLO = DP >= 16 && !FINE;                 // the centroids' lo terms are left out and bounded
+    static constexpr int NA = DP >= 16 && FINE ? 2 : 1;            // operands per slice: centroids
+    static constexpr int NB = K32 && DP >= 8 && FINE ? 2 : 1;      //                     keys
+    static constexpr bool AHEAD = !(K32 && DP == 64) && !FINE;     // a tile pair's operands are read from LDS before they are due
+    static constexpr int NREG = (DP == 8 || DP == 16) && !FINE ? (K32 && DP == 16 ? 5 : 6) : 0;   // tiles whose norms stay in registers (16 each)
+    static constexpr bool AREG = DP <= 8 || (DP == 16 && !K32 && !FINE);   // centroid operands in 32 registers, else read from LDS
 };
 
 // grid: one workgroup per (unit of a head's keys, subspace); all subspaces of a unit follow each other on one die,
 // whose L2 then serves a key row's cache lines to all of them.
-template <typename KT, int DP, bool FULL>
-__global__ __launch_bounds__(kEfThreads, (EfShape<KT, DP>::WAVES)) void encode_filter_kernel(const KT *__restrict__ keys,
+template <typename KT, int DP, bool FULL, int THREADS, bool FINE>
+__global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) void encode_filter_kernel(const KT *__restrict__ keys,
                                                                       const float *__restrict__ codebooks,
                                                                       uint8_t *__restrict__ codes,
                                                                       int64_t code_stride_bh, int B, int H, int64_t N,
                                                                       int d_k, int m, int d_sub_arg, int blocks_per_bh,
-                                                                      int splits)
+                                                                      int splits, int pairs_per_wg)
 {
-    typedef EfShape<KT, DP> Sh;
+    typedef EfShape<KT, DP, FINE> Sh;
     constexpr bool K32 = Sh::K32;
-    constexpr int NS = Sh::NS, NA = Sh::NA, NB = Sh::NB, NI = Sh::NI, NL = Sh::NL;
+    constexpr int NS = Sh::NS, NL = Sh::NL, NA = Sh::NA, NB = Sh::NB;
+    constexpr int kEfWaves = THREADS / kWave;
+    static_assert(THREADS >= kCentroids, "thread c looks after centroid c while the codebook is set up");
     __shared__ __align__(16) float cn_s[kCentroids];
-    __shared__ float red_s[3][kEfWaves];
-    __shared__ uint64_t todo_s[kEfWaves][kEfRounds];   // per pair of blocks: the keys that take the exact rule
-    __shared__ __align__(16) ef_v8h a_s[Sh::ALDS ? kEfTiles * NA * kWave : 1];
+    __shared__ float red_s[4][kCentroids / kWave];
+    __shared__ int next_s, count_s[kEfWaves];
+    __shared__ uint2 list_s[kEfWaves][kEfList];        // undecided keys: (local pair, lane), candidate digits
+    __shared__ __align__(16) ef_v8h a_s[kEfTiles * NS * NA * kWave];
 
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int unit = (slot / m) * 8 + xcd;
@@ -223,11 +293,13 @@ __global__ __launch_bounds__(kEfThreads, (EfShape<KT, DP>::WAVES)) void encode_f
     const int g = lane >> 5;
     const float *cb = codebooks + ((int64_t)h * m + i) * kCentroids * d_sub;
 
-    // ---- the wavefront's key blocks: pairs 2p, 2p + 1 of the head's 32-key blocks, p = first, first + step, ... ----
+    // ---- the workgroup's key blocks: pairs 2p, 2p + 1 of the head's 32-key blocks, p = first .. first + mine - 1 ----
     const int total_blocks = B * blocks_per_bh;
     const int pairs = (total_blocks + 1) / 2;
-    const int step = splits * kEfWaves;
-    const int first = part * kEfWaves + wave;
+    const int first = part * pairs_per_wg;
+    const int mine = pairs - first < pairs_per_wg ? pairs - first : pairs_per_wg;
+    if (mine <= 0)
+        return;
     KT raw[2][NL][4];
     // Where a pair's two blocks start: (b,h) slab, key, and how many of its 32 keys exist.  All of it is uniform over the
     // wavefront (scalar registers); a lane adds its column.
@@ -253,40 +325,44 @@ __global__ __launch_bounds__(kEfThreads, (EfShape<KT, DP>::WAVES)) void encode_f
         return w;
     };
     Where here[2] = {}, ahead[2] = {};
-    if (first < pairs) {
-        ahead[0] = fetch_keys(2 * first, raw[0]);
-        ahead[1] = fetch_keys(2 * first + 1, raw[1]);
+    int p = wave, pn = wave + kEfWaves;     // this wavefront's pair, and the next one
+    if (p < mine) {
+        ahead[0] = fetch_keys(2 * (first + p), raw[0]);
+        ahead[1] = fetch_keys(2 * (first + p) + 1, raw[1]);
     }
+    if (tid == 0)
+        next_s = 2 * kEfWaves;
 
-    // ---- norms and scales: thread c reads centroid c ----
-    float cn = 0.f, cm = 0.f;
+    // ---- scale, operands, norms: thread c < 256 looks after centroid c ----
+    const bool owner = tid < kCentroids;
+    float v[DP];
+    float cm = 0.f;
     bool bad = false;
+    if (owner) {
 #pragma unroll
-    for (int j0 = 0; j0 < DP; j0 += 4) {
-        float v[4];
-        ef_load4<FULL, float>(cb + tid * d_sub, j0, d_sub, v);
+        for (int j0 = 0; j0 < DP; j0 += 4) {
+            float v4[4];
+            ef_load4<FULL, float>(cb + tid * d_sub, j0, d_sub, v4);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            cn = cn + v[e] * v[e];
-            cm = fmaxf(cm, fabsf(v[e]));
-            bad |= !(fabsf(v[e]) < INFINITY);
+            for (int e = 0; e < 4; ++e) {
+                v[j0 + e] = v4[e];
+                cm = fmaxf(cm, fabsf(v4[e]));
+                bad |= !(fabsf(v4[e]) < INFINITY);
+            }
+        }
+        const uint64_t any_bad = __ballot(bad);
+        cm = wave_max(cm);
+        if (lane == 0) {
+            red_s[0][wave] = cm;
+            red_s[1][wave] = any_bad ? 1.f : 0.f;
         }
     }
-    const uint64_t any_bad = __ballot(bad);
-    cm = wave_max(cm);
-    const float cw = wave_max(cn);
-    if (lane == 0) {
-        red_s[0][wave] = cm;
-        red_s[1][wave] = cw;
-        red_s[2][wave] = any_bad ? 1.f : 0.f;
-    }
     __syncthreads();
-    float cmax = red_s[0][0], cnmax = red_s[1][0], nbad = red_s[2][0];
+    float cmax = red_s[0][0], nbad = red_s[1][0];
 #pragma unroll
-    for (int w = 1; w < kEfWaves; ++w) {
+    for (int w = 1; w < kCentroids / kWave; ++w) {
         cmax = fmaxf(cmax, red_s[0][w]);
-        cnmax = fmaxf(cnmax, red_s[1][w]);
-        nbad += red_s[2][w];
+        nbad += red_s[1][w];
     }
     int se = 13 - ((int)((__float_as_uint(cmax) >> 23) & 0xffu) - 127);   // 13 - floor(log2(cmax)) for normal numbers
     if (cmax == 0.f)
@@ -297,312 +373,480 @@ __global__ __launch_bounds__(kEfThreads, (EfShape<KT, DP>::WAVES)) void encode_f
     }
     const int ske = K32 ? se - 6 : 0;
     const float sc = __uint_as_float((uint32_t)(se + 127) << 23), sk = __uint_as_float((uint32_t)(ske + 127) << 23);
-    const float cns = (sc * cn) * sk;
-    cn_s[tid] = cns;
+    if (owner) {
+        const float unscale = __uint_as_float((uint32_t)(ske - se - 2 + 127) << 23);   // |2 s_c C|^2 -> s_c s_k |C|^2
+        ef_v8h row[DP == 4 ? 1 : DP / 8], low[DP == 4 ? 1 : DP / 8];
+        double n2 = 0.0;
+        float rest = 0.f;
+#pragma unroll
+        for (int j = 0; j < DP; ++j) {
+            const float w = -2.f * sc * v[j];                   // exact (powers of two) unless it overflows
+            const _Float16 wh = (_Float16)w;
+            const float r = w - (float)wh;                      // exact
+            if constexpr (Sh::CLO) {
+                row[j / 8][j % 8] = wh;
+                rest = __builtin_fmaf(r, r, rest);
+                n2 += (double)(float)wh * (double)(float)wh;
+            } else {
+                n2 += (double)w * (double)w;
+                if constexpr (DP >= 8) {
+                    row[j / 8][j % 8] = wh;
+                    low[j / 8][j % 8] = (_Float16)r;
+                } else {
+                    row[0][j] = wh;
+                    row[0][4 + j] = (_Float16)r;
+                }
+            }
+        }
+        const float cns = (float)n2 * unscale;
+        cn_s[tid] = cns;
+        ef_v8h *at = a_s + tid / 32 * NS * NA * kWave + col;    // (row `col` of tile tid / 32)
+        if constexpr (DP >= 16) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                at[s * NA * kWave] = row[2 * s];
+                at[s * NA * kWave + 32] = row[2 * s + 1];
+                if constexpr (NA == 2) {
+                    at[(2 * s + 1) * kWave] = low[2 * s];
+                    at[(2 * s + 1) * kWave + 32] = low[2 * s + 1];
+                }
+            }
+        } else {
+            at[0] = row[0];
+            if constexpr (DP == 8)
+                at[32] = low[0];
+        }
+        const float cw = wave_max(cns), rw = wave_max(rest * unscale);
+        if (lane == 0) {
+            red_s[2][wave] = cw;
+            red_s[3][wave] = rw;
+        }
+    }
+    __syncthreads();
+    float cnmax = red_s[2][0], restmax = red_s[3][0];
+#pragma unroll
+    for (int w = 1; w < kCentroids / kWave; ++w) {
+        cnmax = fmaxf(cnmax, red_s[2][w]);
+        restmax = fmaxf(restmax, red_s[3][w]);
+    }
     // Norms as matrix operands: norm = (nh + nm + nl) 2^x, three fp16 terms against 2^x.  x puts the largest near 2^14; where
     // 2^x would leave fp16's normal range and the terms could not hold the norm, the filter decides nothing.
-    float xs = 1.f, xinv = 1.f;
-    if constexpr (Sh::NORM_SLOTS) {
-        const float top = (sc * cnmax) * sk;
-        int x = (int)((__float_as_uint(top) >> 23) & 0xffu) - 127 - 14;
-        if (top == 0.f)
+    float xs = 1.f;
+    if constexpr (Sh::SLOTS) {
+        int x = (int)((__float_as_uint(cnmax) >> 23) & 0xffu) - 127 - 14;
+        if (cnmax == 0.f)
             x = 0;
         if (x < -28 || x > 15)
             nbad = 1.f;
         x = x < -14 ? -14 : (x > 15 ? 15 : x);
         xs = __uint_as_float((uint32_t)(x + 127) << 23);
-        xinv = __uint_as_float((uint32_t)(127 - x) << 23);
-    }
-    // threshold: tau = t_k |s_k k|^2 + t_c
-    const float bound_factor = (float)(K32 ? 4 * DP + 16 : 2 * DP + 4) * 0x1.2p-22f;   // 2.25 (..) 2^-23
-    const float t_k = bound_factor * __uint_as_float((uint32_t)(se - ske + 127) << 23);
-    const float t_c = nbad != 0.f ? INFINITY : bound_factor * 2.f * ((sc * cnmax) * sk) + 1e-30f;
-
-    // ---- centroid operands ----
-    ef_v8h a_r[Sh::ALDS ? 1 : kEfTiles][NA];
-    auto split8 = [&](int row, int j0, ef_v8h &hi, ef_v8h &lo) {
+        if (owner) {
+            ef_v8h hi = {};                                  // slots 8..11 (fp16 keys: nothing there), 12..14
+            if constexpr (K32) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            float v[4];
-            ef_load4<FULL, float>(cb + row * d_sub, j0 + 4 * p, d_sub, v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float w = -2.f * sc * v[e];                   // exact (powers of two) unless it overflows
-                const _Float16 wh = (_Float16)w;
-                hi[4 * p + e] = wh;
-                lo[4 * p + e] = (_Float16)(w - (float)wh);          // exact difference, then one rounding
+                for (int e = 0; e < 4; ++e)
+                    hi[e] = (_Float16)(-2.f * sc * v[e]);
             }
+            const float w = cn_s[tid] * __uint_as_float((uint32_t)(127 - x) << 23);
+            const _Float16 nh = (_Float16)w;
+            const float w1 = w - (float)nh;
+            const _Float16 nm = (_Float16)w1;
+            hi[4] = nh;
+            hi[5] = nm;
+            hi[6] = (_Float16)(w1 - (float)nm);
+            a_s[tid / 32 * kWave + 32 + col] = hi;
         }
-    };
-    if constexpr (Sh::ALDS) {
-#pragma unroll 1
-        for (int t = 2 * wave; t < 2 * wave + 2; ++t)
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                ef_v8h hi, lo;
-                split8(32 * t + col, 16 * s + 8 * g, hi, lo);
-                a_s[(t * NA + 2 * s) * kWave + lane] = hi;
-                a_s[(t * NA + 2 * s + 1) * kWave + lane] = lo;
-            }
-    } else {
-#pragma unroll
-        for (int t = 0; t < kEfTiles; ++t) {
-            ef_v8h hi, lo;
-            if constexpr (DP == 4) {
-                float v[4];
-                ef_load4<FULL, float>(cb + (32 * t + col) * d_sub, 0, d_sub, v);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float w = -2.f * sc * v[e];
-                    const _Float16 wh = (_Float16)w;
-                    a_r[t][0][e] = wh;
-                    a_r[t][0][4 + e] = (_Float16)(w - (float)wh);
-                }
-            } else if constexpr (DP == 8) {
-                split8(32 * t + col, 0, hi, lo);
-                a_r[t][0] = g ? lo : hi;
-            } else {
-                split8(32 * t + col, 8 * g, hi, lo);
-                a_r[t][0] = hi;
-                a_r[t][1] = lo;
-            }
-        }
+        __syncthreads();
     }
-    __syncthreads();   // norms (and operands) are in LDS
-    const ef_v4f *cn4 = reinterpret_cast<const ef_v4f *>(cn_s) + g;
     const _Float16 one = (_Float16)xs;
-    if constexpr (Sh::NORM_SLOTS) {
-#pragma unroll
-        for (int t = 0; t < kEfTiles; ++t)
-            if (g) {                                  // slots 12..14 (fp16 keys: and nothing in 8..11)
-                const float w = cn_s[32 * t + col] * xinv;
-                const _Float16 nh = (_Float16)w;
-                const float w1 = w - (float)nh;
-                const _Float16 nm = (_Float16)w1;
-                if constexpr (!K32)
-                    a_r[t][0] = ef_v8h{};
-                a_r[t][0][4] = nh;
-                a_r[t][0][5] = nm;
-                a_r[t][0][6] = (_Float16)(w1 - (float)nm);
-                a_r[t][0][7] = (_Float16)0.f;
-            }
-    }
+    float minus_one = -1.f;
+    asm("" : "+s"(minus_one));   // (kept from the compiler: a mixed-precision multiply-add instead of two instructions)
+    // limit: tau = (t_k kn + t_c) + 4 delta (d + delta), kn = |s_k k|^2 (see the header)
+    const float ratio = __uint_as_float((uint32_t)(se - ske + 127) << 23);             // s_c / s_k
+    constexpr int kTerms = DP == 4 || FINE ? (K32 ? 4 * DP + 16 : 2 * DP + 4) : (DP == 8 ? 2 * DP + 4 : DP + 4);
+    constexpr float kBound = (float)kTerms * 0x1.2p-22f;                               // 2.25 (..) 2^-23
+    const float t_k = kBound * ratio;
+    const float t_c = nbad != 0.f ? INFINITY : kBound * 2.f * cnmax + 1e-30f;
+    const float delta_c = Sh::CLO ? 1.002f * __builtin_amdgcn_sqrtf(restmax) : 0.f;
+    const float delta_ratio = 1.002f * 1.002f * ratio;
 
-    for (int p = first, round = 0; p < pairs; p += step, ++round) {
-        float kpart[2];             // this lane's share of |s_k k|^2 for its column of the two blocks
-        float dq[2][4], de[2][4], dt[2][kEfTiles];   // minima over the candidates that share a digit
-        // ---- operand B: this lane's part of its keys ----
-        ef_v8h kf[2][NB];
+    for (;;) {   // until no pair is left; the list of undecided keys is worked off whenever it is nearly full
+        // ---- centroid operands and norms ----
+        ef_v8h a_r[Sh::AREG ? kEfTiles : 1];
+        ef_v16f n_r[Sh::NREG ? Sh::NREG : 1];
+        const ef_v4f *cn4 = reinterpret_cast<const ef_v4f *>(cn_s) + g;
+        auto norms = [&](int t, ef_v16f &n) {   // rows 8q + 4g + (0..3) of the tile
 #pragma unroll
-        for (int blk = 0; blk < 2; ++blk) {
-            float ks = 0.f;
-            if constexpr (!K32) {
-                _Float16 x[NL * 4];
-                __builtin_memcpy(x, raw[blk], sizeof(x));
+            for (int q = 0; q < 4; ++q) {
+                const ef_v4f c4 = cn4[8 * t + 2 * q];
 #pragma unroll
-                for (int l = 0; l < NL * 2; ++l) {
-                    const ef_v2h v = {x[2 * l], x[2 * l + 1]};
-                    ks = __builtin_amdgcn_fdot2(v, v, ks, false);
-                }
-                if constexpr (DP == 4) {
+                for (int e = 0; e < 4; ++e)
+                    n[4 * q + e] = c4[e];
+            }
+        };
+        if constexpr (Sh::AREG) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        kf[blk][0][e] = g ? (e < 4 ? (_Float16)0.f : (e < 7 ? one : (_Float16)0.f)) : x[e % 4];
-                } else {
+            for (int t = 0; t < kEfTiles; ++t)
+                a_r[t] = a_s[t * kWave + lane];
+        }
 #pragma unroll
-                    for (int s = 0; s < NS; ++s)
+        for (int t = 0; t < Sh::NREG; ++t)
+            norms(t, n_r[t]);
+        auto start = [&](int t, ef_v16f &n) {
+            if (t < Sh::NREG)
+                n = n_r[t < Sh::NREG ? t : 0];
+            else
+                norms(t, n);
+        };
+
+        int noted = 0;
+        while (p < mine) {
+            asm volatile("" ::: "memory");   // (operands and norms that are read from LDS are not kept in registers across pairs)
+            float kpart[2], klow[2];    // this lane's share of |s_k k|^2, and of what the fp16 terms leave out, for its columns
+            float dq[2][4], de[2][4], dt[2][kEfTiles];   // minima over the candidates that share a digit
+            // ---- operand B: this lane's part of its keys ----
+            ef_v8h kf[2][NS][NB];
+#pragma unroll
+            for (int blk = 0; blk < 2; ++blk) {
+                float ks = Sh::SLOTS ? 0.f : (float)DP * 0x1p-28f, kl = 0.f;   // (room for flushed fp16 subnormals)
+                if constexpr (!K32) {
+                    _Float16 x[NL * 4];
+                    __builtin_memcpy(x, raw[blk], sizeof(x));
+#pragma unroll
+                    for (int l = 0; l < NL * 2; ++l) {
+                        const ef_v2h w = {x[2 * l], x[2 * l + 1]};
+                        ks = __builtin_amdgcn_fdot2(w, w, ks, false);
+                    }
+                    if constexpr (DP == 4) {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
-                            kf[blk][s][e] = x[8 * s + e];
-                }
-            } else {
-                _Float16 xh[NL * 4], xl[NL * 4];
+                            kf[blk][0][0][e] = g ? (e < 4 ? (_Float16)0.f : (e < 7 ? one : (_Float16)0.f)) : x[e % 4];
+                    } else {
 #pragma unroll
-                for (int l = 0; l < NL * 2; ++l) {
-                    const float u0 = sk * raw[blk][l / 2][2 * (l % 2)], u1 = sk * raw[blk][l / 2][2 * (l % 2) + 1];
-                    ks = __builtin_fmaf(u0, u0, ks);
-                    ks = __builtin_fmaf(u1, u1, ks);
-                    const ef_v2fp hh = __builtin_amdgcn_cvt_pkrtz(u0, u1);
-                    const ef_v2fp ll = __builtin_amdgcn_cvt_pkrtz(u0 - (float)hh[0], u1 - (float)hh[1]);
-                    __builtin_memcpy(xh + 2 * l, &hh, 4);
-                    __builtin_memcpy(xl + 2 * l, &ll, 4);
-                }
-                if constexpr (DP == 4) {
+                        for (int s = 0; s < NS; ++s)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                kf[blk][s][0][e] = x[8 * s + e];
+                    }
+                } else if constexpr (DP == 4) {
+                    _Float16 xh[4], xl[4];
+#pragma unroll
+                    for (int l = 0; l < 2; ++l) {
+                        const float u0 = sk * raw[blk][0][2 * l], u1 = sk * raw[blk][0][2 * l + 1];
+                        ks = __builtin_fmaf(u0, u0, ks);
+                        ks = __builtin_fmaf(u1, u1, ks);
+                        const ef_v2fp hh = __builtin_amdgcn_cvt_pkrtz(u0, u1);
+                        const ef_v2fp ll = __builtin_amdgcn_cvt_pkrtz(u0 - (float)hh[0], u1 - (float)hh[1]);
+                        __builtin_memcpy(xh + 2 * l, &hh, 4);
+                        __builtin_memcpy(xl + 2 * l, &ll, 4);
+                    }
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        kf[blk][0][e] = g ? (e < 4 ? xl[e % 4] : (e < 7 ? one : (_Float16)0.f)) : xh[e % 4];
+                        kf[blk][0][0][e] = g ? (e < 4 ? xl[e % 4] : (e < 7 ? one : (_Float16)0.f)) : xh[e % 4];
                 } else {
 #pragma unroll
-                    for (int s = 0; s < NS; ++s)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            kf[blk][s][e] = xh[8 * s + e];
-                            kf[blk][NS + s][e] = xl[8 * s + e];
+                    for (int l = 0; l < NL * 2; ++l) {
+                        float u0 = sk * raw[blk][l / 2][2 * (l % 2)], u1 = sk * raw[blk][l / 2][2 * (l % 2) + 1];
+                        asm("" : "+v"(u0), "+v"(u1));   // (else the product is formed twice, once to round it)
+                        const ef_v2h hh = {(_Float16)u0, (_Float16)u1};
+                        if constexpr (FINE) {
+                            ks = __builtin_fmaf(u0, u0, ks);
+                            ks = __builtin_fmaf(u1, u1, ks);
+                        } else {
+                            ks = __builtin_amdgcn_fdot2(hh, hh, ks, false);
                         }
+                        const float r0 = __builtin_fmaf((float)hh[0], minus_one, u0), r1 = __builtin_fmaf((float)hh[1], minus_one, u1);   // exact
+                        kf[blk][l / 4][0][2 * (l % 4)] = hh[0];
+                        kf[blk][l / 4][0][2 * (l % 4) + 1] = hh[1];
+                        if constexpr (FINE) {
+                            kf[blk][l / 4][NB - 1][2 * (l % 4)] = (_Float16)r0;
+                            kf[blk][l / 4][NB - 1][2 * (l % 4) + 1] = (_Float16)r1;
+                        } else {
+                            kl = __builtin_fmaf(r0, r0, kl);
+                            kl = __builtin_fmaf(r1, r1, kl);
+                        }
+                    }
                 }
+                kpart[blk] = ks;
+                klow[blk] = kl;
             }
-            kpart[blk] = ks;
-        }
-        here[0] = ahead[0];
-        here[1] = ahead[1];
-        if (p + step < pairs) {   // the next pair's keys arrive while this one is scored
-            ahead[0] = fetch_keys(2 * (p + step), raw[0]);
-            ahead[1] = fetch_keys(2 * (p + step) + 1, raw[1]);
-        }
+            here[0] = ahead[0];
+            here[1] = ahead[1];
+            int taken = 0;
+            if (lane == 0)
+                taken = atomicAdd(&next_s, 1);
+            if (pn < mine) {   // the next pair's keys arrive while this one is scored
+                ahead[0] = fetch_keys(2 * (first + pn), raw[0]);
+                ahead[1] = fetch_keys(2 * (first + pn) + 1, raw[1]);
+            }
 
-        float gm[16];               // minima over the row tiles, by accumulator register (4 q + e)
-        auto start_tile = [&](int blk, int t, ef_v16f &acc) {
-            if constexpr (Sh::NORM_SLOTS) {
-                acc = ef_v16f{};
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {   // rows 8q + 4g + (0..3) of the tile start at their norms
-                    const ef_v4f c4 = cn4[8 * t + 2 * q];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        acc[4 * q + e] = c4[e];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NI; ++k) {
-                ef_v8h av;
-                if constexpr (Sh::ALDS)
-                    av = a_s[(t * NA + Sh::a_of(k)) * kWave + lane];
-                else
-                    av = a_r[t][Sh::a_of(k)];
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, kf[blk][Sh::b_of(k)], acc, 0, 0, 0);
-            }
-        };
-        auto tile_min = [](const ef_v16f &x) {
-            const float a = ef_min3(x[0], x[1], x[2]), b = ef_min3(x[3], x[4], x[5]), c = ef_min3(x[6], x[7], x[8]);
-            const float d = ef_min3(x[9], x[10], x[11]), e = ef_min3(x[12], x[13], x[14]);
-            return ef_min(ef_min3(a, b, c), ef_min3(d, e, x[15]));
-        };
-        // Row tiles two at a time, first of block 0, then of block 1.  The scheduling barriers keep the accumulators of one
-        // step alive at a time: the other wavefronts of the SIMD fill the wait for the matrix instructions (holding the
-        // next two tiles in flight as well measured the same at half the wavefronts, and the compiler's own order
-        // up to three times the time).
-#pragma unroll
-        for (int u = 0; u < kEfTiles; ++u) {
-            const int blk = u / (kEfTiles / 2), t = 2 * (u % (kEfTiles / 2));
-            ef_v16f x0, x1;
-            start_tile(blk, t, x0);
-            start_tile(blk, t + 1, x1);
-            __builtin_amdgcn_sched_barrier(0);
-            dt[blk][t] = tile_min(x0);
-            dt[blk][t + 1] = tile_min(x1);
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                gm[r] = (t == 0) ? ef_min(x0[r], x1[r]) : ef_min3(gm[r], x0[r], x1[r]);
-            if (t + 2 == kEfTiles) {
+            auto tile_min = [](const ef_v16f &x) {
+                const float a = ef_min3(x[0], x[1], x[2]), b = ef_min3(x[3], x[4], x[5]), c = ef_min3(x[6], x[7], x[8]);
+                const float d = ef_min3(x[9], x[10], x[11]), e = ef_min3(x[12], x[13], x[14]);
+                return ef_min(ef_min3(a, b, c), ef_min3(d, e, x[15]));
+            };
+            auto digits = [](const float (&gm)[16], float (&q4)[4], float (&e4)[4]) {
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    dq[blk][x] = ef_min(ef_min3(gm[4 * x], gm[4 * x + 1], gm[4 * x + 2]), gm[4 * x + 3]);
-                    de[blk][x] = ef_min(ef_min3(gm[x], gm[4 + x], gm[8 + x]), gm[12 + x]);
+                    q4[x] = ef_min(ef_min3(gm[4 * x], gm[4 * x + 1], gm[4 * x + 2]), gm[4 * x + 3]);
+                    e4[x] = ef_min(ef_min3(gm[x], gm[4 + x], gm[8 + x]), gm[12 + x]);
                 }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // ---- lane l now finishes key l % 32 of block l / 32: the two lane halves hold disjoint centroids ----
-        auto halves = [](float x0, float x1, float &a, float &b) {   // (block 0, block 1) -> own block's halves 0 and 1
-            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
-            a = __uint_as_float(r[0]);
-            b = __uint_as_float(r[1]);
-        };
-        float best = 0.f, second = INFINITY;
-        auto scan = [&](auto &d0, auto &d1, int n) {      // digit of the smallest group minimum; best, second updated
-            int digit = 0;
-            float s = INFINITY, bst = 0.f;
+            };
+            // Row tiles two at a time.  The scheduling barriers keep the accumulators of one step alive at a time.
+            if constexpr (Sh::AREG) {   // first all tiles of block 0, then of block 1
+                float gm[16];               // minima over the row tiles, by accumulator register (4 q + e)
 #pragma unroll
-            for (int x = 0; x < n; ++x) {
+                for (int u = 0; u < kEfTiles; ++u) {
+                    const int blk = u / (kEfTiles / 2), t = 2 * (u % (kEfTiles / 2));
+                    ef_v16f x0 = {}, x1 = {};
+                    if constexpr (!Sh::SLOTS) {
+                        start(t, x0);
+                        start(t + 1, x1);
+                    }
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        x0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_r[t], kf[blk][0][b], x0, 0, 0, 0);
+                        x1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_r[t + 1], kf[blk][0][b], x1, 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    dt[blk][t] = tile_min(x0);
+                    dt[blk][t + 1] = tile_min(x1);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        gm[r] = (t == 0) ? ef_min(x0[r], x1[r]) : ef_min3(gm[r], x0[r], x1[r]);
+                    if (t + 2 == kEfTiles)
+                        digits(gm, dq[blk], de[blk]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {                    // both blocks share what is read of a tile
+                float gm[2][16];
+                ef_v8h a0[NS * NA], a1[NS * NA];
+                auto operands = [&](int t) {
+#pragma unroll
+                    for (int s = 0; s < NS * NA; ++s) {
+                        a0[s] = a_s[(t * NS * NA + s) * kWave + lane];
+                        a1[s] = a_s[((t + 1) * NS * NA + s) * kWave + lane];
+                    }
+                };
+                if constexpr (Sh::AHEAD)
+                    operands(0);
+#pragma unroll
+                for (int t = 0; t < kEfTiles; t += 2) {
+                    ef_v16f n0, n1;
+                    start(t, n0);
+                    start(t + 1, n1);
+                    if constexpr (!Sh::AHEAD)
+                        operands(t);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int blk = 0; blk < 2; ++blk) {
+                        ef_v16f x0 = n0, x1 = n1;
+#pragma unroll
+                        for (int s = 0; s < NS; ++s)
+#pragma unroll
+                            for (int k = 0; k < NA + NB - 1; ++k) {   // hi.hi, lo.hi, hi.lo
+                                const int a = NA * s + (k < NA ? k : 0), b = k < NA ? 0 : 1;
+                                x0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0[a], kf[blk][s][b < NB ? b : 0], x0, 0, 0, 0);
+                                x1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[a], kf[blk][s][b < NB ? b : 0], x1, 0, 0, 0);
+                            }
+                        if (Sh::AHEAD && blk == 1 && t + 2 < kEfTiles)
+                            operands(t + 2);      // (arrive behind this block's minima)
+                        __builtin_amdgcn_sched_barrier(0);
+                        dt[blk][t] = tile_min(x0);
+                        dt[blk][t + 1] = tile_min(x1);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            gm[blk][r] = (t == 0) ? ef_min(x0[r], x1[r]) : ef_min3(gm[blk][r], x0[r], x1[r]);
+                        if (t + 2 == kEfTiles)
+                            digits(gm[blk], dq[blk], de[blk]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            // ---- lane l now finishes key l % 32 of block l / 32: the two lane halves hold disjoint centroids ----
+            auto halves = [](float x0, float x1, float &a, float &b) {   // (block 0, block 1) -> own block's halves 0 and 1
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+                a = __uint_as_float(r[0]);
+                b = __uint_as_float(r[1]);
+            };
+            float mx[8], me[4], mt[kEfTiles];        // group minima by 2 q + h, e and t
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                halves(dq[0][x], dq[1][x], mx[2 * x], mx[2 * x + 1]);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
                 float a, b;
-                halves(d0[x], d1[x], a, b);
-                const float v = ef_min(a, b);
-                if (x == 0) {
-                    bst = v;
-                } else {
-                    digit = (v < bst) ? x : digit;
-                    s = __builtin_amdgcn_fmed3f(bst, v, s);    // bst <= s: the middle one
-                    bst = ef_min(bst, v);
-                }
+                halves(de[0][x], de[1][x], a, b);
+                me[x] = ef_min(a, b);
             }
-            best = bst;                                        // (every digit's smallest minimum is the smallest score)
-            second = fminf(second, s);
-            return digit;
-        };
-        const int iq = scan(dq[0], dq[1], 4);
-        const int ie = scan(de[0], de[1], 4);
-        const int it = scan(dt[0], dt[1], kEfTiles);
-        float half0, half1;
-        halves(ef_min(ef_min3(dq[0][0], dq[0][1], dq[0][2]), dq[0][3]), ef_min(ef_min3(dq[1][0], dq[1][1], dq[1][2]), dq[1][3]),
-               half0, half1);
-        second = fminf(second, fmaxf(half0, half1));
-        int code = 32 * it + 8 * iq + 4 * (half1 < half0 ? 1 : 0) + ie;
-        float ka, kb2;
-        halves(kpart[0], kpart[1], ka, kb2);
-        const float kn = (DP >= 16) ? ka + kb2 : ka;           // up to 8 coordinates every lane holds the whole key
-        // beyond 2^31 a scaled fp32 key may not fit fp16 (2^15.5 squared); NaN and infinities fail the comparison
-        const float tau = (kn < (K32 ? 0x1p31f : INFINITY)) ? t_k * kn + t_c : INFINITY;
-        const bool unique = (second - best) > tau;             // false for NaN / inf on either side
+#pragma unroll
+            for (int x = 0; x < kEfTiles; ++x) {
+                float a, b;
+                halves(dt[0][x], dt[1][x], a, b);
+                mt[x] = ef_min(a, b);
+            }
+            float ka, kb2;
+            halves(kpart[0], kpart[1], ka, kb2);
+            const float kn = (DP >= 16) ? ka + kb2 : ka;           // up to 8 coordinates every lane holds the whole key
+            const float best = ef_min(ef_min3(ef_min3(mx[0], mx[1], mx[2]), mx[3], mx[4]), ef_min3(mx[5], mx[6], mx[7]));
+            float tau = __builtin_fmaf(t_k, kn, t_c);
+            if constexpr (Sh::KLO || Sh::CLO) {
+                float delta = delta_c;
+                if constexpr (Sh::KLO) {
+                    halves(klow[0], klow[1], ka, kb2);
+                    delta += __builtin_amdgcn_sqrtf(delta_ratio * ((DP >= 16) ? ka + kb2 : ka));
+                }
+                // (the rounding of best and kn cannot make the square smaller than it is: tau is twice their bound)
+                const float d = __builtin_amdgcn_sqrtf(fmaxf(__builtin_fmaf(ratio, kn, best) + tau, 0.f));
+                tau = __builtin_fmaf(4.01f * delta, d + delta, tau);
+            }
+            const float limit = best + tau;
+            // One bit per digit value, set where no candidate with that digit is within the limit.
+            uint32_t out = 0;
+            auto push = [&](float m) { out = __builtin_amdgcn_alignbit(out, __float_as_uint(limit - m), 31); };
+#pragma unroll
+            for (int x = kEfTiles - 1; x >= 0; --x)
+                push(mt[x]);
+#pragma unroll
+            for (int x = 3; x >= 0; --x)
+                push(me[x]);
+#pragma unroll
+            for (int x = 7; x >= 0; --x)
+                push(mx[x]);
+            // NaN or infinite on either side (fp32 keys whose lo terms count: beyond 2^31 the scaled key may not fit
+            // fp16, 2^15.5 squared): everything is a candidate
+            const bool sound = limit < INFINITY && limit > -INFINITY && (!(K32 && (DP == 4 || FINE)) || kn < 0x1p31f);
+            const uint32_t among = sound ? out ^ kEfAll : kEfAll;
+            const bool unique = __builtin_popcount(among) == 3;
+            const int code = 32 * __builtin_ctz(among >> 12) + 4 * __builtin_ctz(among) + __builtin_ctz(among >> 8);
 
-        const bool valid = col < (g ? here[1].live : here[0].live);
-        const int64_t at0 = here[0].bh * code_stride_bh + here[0].n0 * m, at1 = here[1].bh * code_stride_bh + here[1].n0 * m;
-        // keys the filter could not decide: noted, and left for the end
-        const uint64_t todo = __ballot(valid && !unique);
-        if (lane == 0)
-            todo_s[wave][round] = todo;
-        if (valid && unique)
-            codes[(g ? at1 : at0) + col * m + i] = (uint8_t)code;
-    }
-    // ---- the exact rule for the noted keys, shared out to the workgroup's wavefronts ----
-    __syncthreads();
-    int turn = 0;
-    for (int w = 0; w < kEfWaves; ++w) {
-        const int first_w = part * kEfWaves + w;
-        const int rounds = first_w < pairs ? (pairs - first_w + step - 1) / step : 0;
-        for (int r0 = 0; r0 < rounds; r0 += kWave) {
-            const uint64_t mine = r0 + lane < rounds ? todo_s[w][r0 + lane] : 0ull;
-            uint64_t some = __ballot(mine != 0);
-            while (some) {
-                const int r = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(some));
-                some &= some - 1;
-                uint64_t todo = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), r) << 32) |
-                                (uint32_t)__builtin_amdgcn_readlane((int)mine, r);
-                while (todo) {
-                    const int l = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(todo));
-                    todo &= todo - 1;
-                    if ((turn++ & (kEfWaves - 1)) != wave)
-                        continue;
-                    const Where w2 = locate(2 * (first_w + (r0 + r) * step) + (l >> 5));
-                    const int64_t n = w2.n0 + (l & 31);
-                    const int exact = ef_exact_code<KT>(keys + (w2.bh * N + n) * d_k + (int64_t)i * d_sub, cb, d_sub, lane);
-                    if (lane == 0)
-                        codes[w2.bh * code_stride_bh + n * m + i] = (uint8_t)exact;
-                }
+            const bool valid = col < (g ? here[1].live : here[0].live);
+            const int64_t at0 = here[0].bh * code_stride_bh + here[0].n0 * m, at1 = here[1].bh * code_stride_bh + here[1].n0 * m;
+            if (valid && unique)
+                codes[(g ? at1 : at0) + col * m + i] = (uint8_t)code;
+            const int done = p;
+            p = pn;
+            pn = __builtin_amdgcn_readfirstlane(taken);
+            // keys the filter could not decide are noted with their candidates, and left for later
+            const uint64_t todo = __ballot(valid && !unique);
+            if (todo) {
+                if (valid && !unique)
+                    list_s[wave][noted + (int)__popcll(todo & ((1ull << lane) - 1ull))] = make_uint2((uint32_t)done << 6 | lane, among);
+                noted += (int)__popcll(todo);
+                if (noted > kEfList - kWave)
+                    break;
             }
+        }
+        if (lane == 0)
+            count_s[wave] = noted | (p < mine ? kEfMore : 0);
+        __syncthreads();
+        // ---- the exact rule for the noted keys: eight lanes share a key's candidates ----
+        int until[kEfWaves];      // entries of the lists up to and with the w-th
+        int more = 0;
+#pragma unroll
+        for (int w = 0; w < kEfWaves; ++w) {
+            more |= count_s[w] & kEfMore;
+            until[w] = (w ? until[w - 1] : 0) + (count_s[w] & (kEfMore - 1));
+        }
+        const int count = until[kEfWaves - 1];
+        for (int b0 = wave * 8; b0 < count; b0 += kEfWaves * 8) {
+            const bool exists = b0 + lane / 8 < count;
+            const int at = exists ? b0 + lane / 8 : count - 1;
+            int list = 0, start = 0;
+#pragma unroll
+            for (int w = 0; w < kEfWaves - 1; ++w)
+                if (at >= until[w]) {
+                    list = w + 1;
+                    start = until[w];
+                }
+            const uint2 entry = list_s[list][at - start];
+            const int l = (int)(entry.x & 63u);
+            const Where where = locate(2 * (first + (int)(entry.x >> 6)) + (l >> 5));
+            const int64_t n = where.n0 + (l & 31);
+            const KT *key_sub = keys + (where.bh * N + n) * d_k + (int64_t)i * d_sub;
+            uint8_t *dst = codes + where.bh * code_stride_bh + n * m + i;
+            const uint32_t mx = entry.y & 255u, me = entry.y >> 8 & 15u, mt = entry.y >> 12;
+            const int nx = __builtin_popcount(mx), ne = __builtin_popcount(me), nt = __builtin_popcount(mt);
+            const int all = nx * ne * nt;
+            auto evaluate = [&](int c) { return argmin_value(ef_exact_distance<KT, DP, FULL>(key_sub, cb + c * d_sub, d_sub), c); };
+            // the lowest or the highest value of each digit, by the lane's bits: all combinations where there are no others
+            int code = 32 * (lane & 4 ? 31 - __builtin_clz(mt) : __builtin_ctz(mt)) +
+                       4 * (lane & 1 ? 31 - __builtin_clz(mx) : __builtin_ctz(mx)) +
+                       (lane & 2 ? 31 - __builtin_clz(me) : __builtin_ctz(me));
+            double best = evaluate(code);
+            const int upto = all <= kEfShared && (nx > 2 || ne > 2 || nt > 2) ? all : 0;
+            for (int k = lane % 8; __ballot(k < upto); k += 8)
+                if (k < upto) {   // the k-th combination (quotients below 256: floor is exact)
+                    const int r1 = (int)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)nx));
+                    const int r2 = (int)(((float)r1 + 0.5f) * __builtin_amdgcn_rcpf((float)ne));
+                    const int c = 32 * ef_nth_bit(mt, r2) + 4 * ef_nth_bit(mx, k - r1 * nx) + ef_nth_bit(me, r1 - r2 * ne);
+                    const double d = evaluate(c);
+                    if (d < best || (d == best && c < code)) {
+                        best = d;
+                        code = c;
+                    }
+                }
+            ef_argmin_step<0xB1>(best, code);     // lane ^ 1, lane ^ 2, the other quad of each eight
+            ef_argmin_step<0x4E>(best, code);
+            ef_argmin_step<0x141>(best, code);
+            const bool writes = lane % 8 == 0 && exists;
+            if (writes && all <= kEfShared)
+                *dst = (uint8_t)code;
+            // many candidates: the wavefront takes such a key together, all centroids
+            uint64_t whole = __ballot(writes && all > kEfShared);
+            while (whole) {
+                const int turn = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(whole));
+                whole &= whole - 1;
+                const uint64_t src = (uint64_t)(uintptr_t)key_sub;
+                const KT *one = reinterpret_cast<const KT *>((uintptr_t)(
+                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(src >> 32), turn) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)src, turn)));
+                const float *rows = cb;
+                if constexpr (DP > 16)
+                    asm volatile("" : "+s"(rows));   // (rows kept in registers from one key to the next would spill)
+                const int exact = ef_exact_code<KT>(one, rows, d_sub, lane);
+                if (lane == turn)
+                    *dst = (uint8_t)exact;
+            }
+        }
+        if (!more)
+            break;
+        __syncthreads();     // (the lists are read)
+        if (p < mine) {      // (the keys of the pair at hand were on their way when the list filled up)
+            ahead[0] = fetch_keys(2 * (first + p), raw[0]);
+            ahead[1] = fetch_keys(2 * (first + p) + 1, raw[1]);
         }
     }
 }
 
-// Workgroups per (head, subspace).  A wavefront pays for the codebook (norms, scale, operands: about as much as kSetup
-// pairs of key blocks) before its first key; `resident` workgroups run at once.  The count
-// with the least (rounds of workgroups) x (set-up + pairs per wavefront) is taken.
-static int64_t ef_splits(int64_t units, int64_t pairs, int64_t resident)
+// Workgroups per (head, subspace) and threads per workgroup.  A compute unit holds one workgroup of 512 threads or two of 256
+// (three with up to four coordinates, which keep no norms in registers).  Two wavefronts saturate a SIMD, so a launch takes
+// about as long as the compute unit with the most pairs of key blocks needs for them, and kSetup more for every workgroup it
+// runs in turn (scale, operands, norms); one wavefront alone on a SIMD needs half as long again for a pair.  The choice with
+// the least is taken; where it comes out the same, the smaller workgroup for a few pairs and else the larger, whose
+// wavefronts share out the pairs as they go.
+struct EfGrid {
+    int64_t splits;
+    int threads;
+    bool fine;       // a pair or two per wavefront
+};
+static EfGrid ef_grid(int64_t units, int64_t pairs, bool small_rows)
 {
-    constexpr int64_t kSetup = 4;
-    // (a wavefront has room to note the undecided keys of kEfRounds pairs)
-    int64_t best = (pairs + kEfWaves * kEfRounds - 1) / (kEfWaves * kEfRounds);
+    constexpr int64_t kSetup = 96;     // in 1/32 of a pair's time on a saturated SIMD
+    EfGrid best = {1, 256, false};
     int64_t best_cost = INT64_MAX;
-    for (int64_t s = best; s <= 1024; ++s) {
-        const int64_t per_wave = (pairs + s * kEfWaves - 1) / (s * kEfWaves);
-        const int64_t rounds = (units * s + resident - 1) / resident;
-        const int64_t cost = rounds * (kSetup + per_wave);
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = s;
+    for (int threads = 256; threads <= (small_rows ? 256 : 512); threads *= 2) {
+        const int64_t per_simd = threads / 256, waves = threads / kWave, resident = (small_rows ? 3 : 2) / per_simd;
+        for (int64_t s = 1; s <= 1024; ++s) {
+            const int64_t per_wave = (pairs + s * waves - 1) / (s * waves);
+            const int64_t wgs = (units * s + 255) / 256;         // on the fullest compute unit
+            const int64_t cost = (wgs + resident - 1) / resident * kSetup + (wgs * per_simd == 1 ? 48 : small_rows && wgs == 2 ? 68 : 32 * wgs * per_simd) * per_wave;
+            if (cost < best_cost || (cost == best_cost && threads == 512 && per_wave >= 4)) {
+                best_cost = cost;
+                best = EfGrid{s, threads, threads == 256 && per_wave <= 2};
+            }
+            if (per_wave == 1)
+                break;
         }
-        if (per_wave == 1)
-            break;
     }
     return best;
 }
@@ -619,35 +863,42 @@ static bool launch_encode_filter_t(const lookat_shape *s, int64_t N, const void 
     // the exact scan of them all is faster (320 (b,h) x 2787 fp16 keys, 32 subspaces: 1.46 ms; with the filter 13.0 ms).
     if (d_sub < 2 || d_sub > 64 || total_blocks > 0x3fffffff)
         return false;
-    const int64_t resident = 256 * (d_sub <= 4    ? EfShape<KT, 4>::WAVES
-                                    : d_sub <= 8  ? EfShape<KT, 8>::WAVES
-                                    : d_sub <= 16 ? EfShape<KT, 16>::WAVES
-                                    : d_sub <= 32 ? EfShape<KT, 32>::WAVES
-                                                  : EfShape<KT, 64>::WAVES);
-    const int64_t splits = ef_splits((int64_t)s->H * s->m, (total_blocks + 1) / 2, resident);
+    const int64_t pairs = (total_blocks + 1) / 2;
+    const EfGrid chosen = ef_grid((int64_t)s->H * s->m, pairs, d_sub <= 4);
+    const int64_t splits = chosen.splits;
     const int64_t wgs = ((int64_t)s->H * splits + 7) / 8 * 8 * s->m;
     if (wgs > 0xffffff)   // (a grid of 2^32 threads)
         return false;
-    const dim3 grid((unsigned)wgs), block(kEfThreads);
+    const dim3 grid((unsigned)wgs), block((unsigned)chosen.threads);
     const KT *k = static_cast<const KT *>(keys);
-#define LOOKAT_EF_LAUNCH(D, FULL)                                                                                         \
-    hipLaunchKernelGGL((encode_filter_kernel<KT, D, FULL>), grid, block, 0, st, k, codebooks, codes, code_stride_bh,      \
-                       s->B, s->H, N, s->d_k, s->m, d_sub, (int)blocks_per_bh, (int)splits)
+#define LOOKAT_EF_LAUNCH(D, FULL, THREADS, FINE)                                                                          \
+    hipLaunchKernelGGL((encode_filter_kernel<KT, D, FULL, THREADS, FINE>), grid, block, 0, st, k, codebooks, codes,       \
+                       code_stride_bh, s->B, s->H, N, s->d_k, s->m, d_sub, (int)blocks_per_bh, (int)splits,               \
+                       (int)((pairs + splits - 1) / splits))
+#define LOOKAT_EF_FORM(D, FULL)                                                                                           \
+    do {                                                                                                                  \
+        constexpr int kLarge = D > 4 ? 512 : 256;                                                                         \
+        constexpr bool kFine = D > 8 || (D == 8 && sizeof(KT) == 4);                                                      \
+        if (chosen.threads == 512)                                                                                        \
+            LOOKAT_EF_LAUNCH(D, FULL, kLarge, false);                                                                     \
+        else if (chosen.fine)                                                                                             \
+            LOOKAT_EF_LAUNCH(D, FULL, 256, kFine);                                                                        \
+        else                                                                                                              \
+            LOOKAT_EF_LAUNCH(D, FULL, 256, false);                                                                        \
+        return true;                                                                                                      \
+    } while (0)
 #define LOOKAT_EF_CASE(D)                                                                                                 \
-    if (d_sub == D) {                                                                                                     \
-        LOOKAT_EF_LAUNCH(D, true);                                                                                        \
-        return true;                                                                                                      \
-    }                                                                                                                     \
-    if (d_sub < D) {                                                                                                      \
-        LOOKAT_EF_LAUNCH(D, false);                                                                                       \
-        return true;                                                                                                      \
-    }
+    if (d_sub == D)                                                                                                       \
+        LOOKAT_EF_FORM(D, true);                                                                                          \
+    if (d_sub < D)                                                                                                        \
+        LOOKAT_EF_FORM(D, false);
     LOOKAT_EF_CASE(4)
     LOOKAT_EF_CASE(8)
     LOOKAT_EF_CASE(16)
     LOOKAT_EF_CASE(32)
     LOOKAT_EF_CASE(64)
 #undef LOOKAT_EF_CASE
+#undef LOOKAT_EF_FORM
 #undef LOOKAT_EF_LAUNCH
     return false;
 }

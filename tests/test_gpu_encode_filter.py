@@ -1,0 +1,55 @@
+"""Cache fills large enough for every form of the ranking encoder (two sizes of workgroup, one or two fp16 terms per value, notes of
+undecided keys that fill up and are worked off in between) against the exact scan of all centroids, code for code."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+H = 2
+
+
+@pytest.fixture(scope="module")
+def lk():
+    import paper_2601_10155_amd as pkg
+    pkg.load_library()
+    return pkg
+
+
+def _inputs(kind, d_sub, M, B, N, dtype):
+    g = torch.Generator(device="cuda").manual_seed(d_sub + N)
+    cb = torch.randn((H, M, 256, d_sub), generator=g, device="cuda")
+    keys = torch.randn((B, H, N, M, d_sub), generator=g, device="cuda")
+    if kind == "near ties":         # every other key between two centroids, 0 to 1e-3 of their distance off the middle
+        i = torch.randint(0, 256, (2, B, H, N, M, 1), generator=g, device="cuda")
+        rows = [cb.view(1, H, 1, M, 256, d_sub).expand(B, H, 1, M, 256, d_sub).permute(0, 1, 3, 2, 4, 5).reshape(B, H, M, 256, d_sub)
+                .gather(3, j.permute(0, 1, 3, 2, 4).expand(B, H, M, N, d_sub)).permute(0, 1, 3, 2, 4) for j in i]
+        off = torch.tensor([0.0, 1e-8, 1e-6, 1e-4, 1e-3], device="cuda")[torch.randint(0, 5, (B, H, N, 1, 1), generator=g, device="cuda")]
+        keys[:, :, 1::2] = (rows[0] * (0.5 + off) + rows[1] * (0.5 - off))[:, :, 1::2]
+    elif kind == "pairs of centroids":   # every key has two equally near ones: the lower index, and none is ever decided
+        cb[:, :, 1::2] = cb[:, :, 0::2]
+    elif kind == "filler":          # no scale serves this codebook: every centroid is a candidate for every key
+        cb[:, :, 200:] = 1e30
+    elif kind == "magnitudes":      # norms over six orders of magnitude
+        cb *= torch.tensor([1.0, 1e-3, 1e-6], device="cuda")[torch.randint(0, 3, (H, M, 256, 1), generator=g, device="cuda")]
+        keys *= torch.tensor([1.0, 1e-3], device="cuda")[torch.randint(0, 2, (B, H, N, 1, 1), generator=g, device="cuda")]
+    elif kind == "far keys":
+        keys *= 300.0
+    elif kind == "subnormal keys":  # fp16 keys below 2^-14
+        cb *= 1e-5
+        keys *= 1e-5
+    return keys.view(B, H, N, M * d_sub).to(getattr(torch, dtype)), cb.contiguous()
+
+
+# sub-vectors that fill an operand and sub-vectors that are padded; 90001 keys: 256 threads, 3 x 66671 and more: 512
+@pytest.mark.parametrize("d_sub", [3, 4, 7, 8, 12, 16, 24, 32, 48, 64])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+@pytest.mark.parametrize("kind,B,N", [("near ties", 1, 90001), ("near ties", 3, 66671), ("pairs of centroids", 1, 300001),
+                                      ("filler", 1, 300001), ("magnitudes", 1, 200001), ("far keys", 1, 90001),
+                                      ("subnormal keys", 1, 200001)])
+def test_large_fills_match_the_exact_scan(lk, monkeypatch, kind, B, N, d_sub, dtype):
+    m = 8 if d_sub % 2 else 2       # (head sizes are multiples of 8)
+    keys, cb = _inputs(kind, d_sub, m, B, N * 2 // m, dtype)
+    got = lk.lookat_encode_keys(keys, cb).clone()
+    monkeypatch.setenv("LOOKAT_ENCODE_EXACT", "1")
+    ref = lk.lookat_encode_keys(keys, cb)
+    assert torch.equal(got, ref), f"{int((got != ref).sum())} of {ref.numel()} codes differ"
