@@ -13,6 +13,18 @@ __device__ __forceinline__ float to_f32<float>(float v) { return v; }
 template <>
 __device__ __forceinline__ float to_f32<__half>(__half v) { return __half2float(v); }
 
+// (b, t) of a head's query in flattened order (B*T < 2^31).  A decode step has one query per sequence: no division on the way to
+// its address.
+__device__ __forceinline__ void split_query(int64_t qi, int T, int64_t &b, int64_t &t)
+{
+    b = qi;
+    t = 0;
+    if (T != 1) {
+        b = (uint32_t)qi / (uint32_t)T;
+        t = qi - b * T;
+    }
+}
+
 // One block = one head h, one subspace i, QB consecutive queries of the flattened
 // (b, t) list.  Thread c keeps centroid c of the subspace in registers and reuses it for
 // every query of the block; the query sub-vectors sit in LDS and are read by all lanes
@@ -36,7 +48,8 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(const QT *__rest
         const int64_t qi = q0 + e / DSUB;
         float v = 0.f;
         if (qi < nq) {
-            const int64_t b = qi / T, t = qi % T;
+            int64_t b, t;
+            split_query(qi, T, b, t);
             v = to_f32<QT>(q[((b * H + h) * T + t) * d_k + (int64_t)i * DSUB + e % DSUB]);
         }
         q_s[e] = v;
@@ -57,33 +70,78 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(const QT *__rest
 #pragma unroll
         for (int j = 0; j < DSUB; ++j)
             acc = fmaf(q_s[k * DSUB + j], row[j], acc);
-        const int64_t b = qi / T, t = qi % T;
+        int64_t b, t;
+        split_query(qi, T, b, t);
         lut[((((b * H + h) * T + t) * m) + i) * kCentroids + c] = acc;
     }
 }
 
-// Any d_sub: centroid row streamed from memory per query.
-template <typename QT>
+// Any d_sub: the same, the centroid's row taken JB coordinates at a time (8 for the shortest rows, else 32; longer rows come from cache
+// again for every query).  Latency is what counts in a decode step (one query per sequence): the row is requested at once, in 16-byte
+// pieces where it has them, beside the queries.  us per call, element by element as they were needed / now: 32 x 12 (b,h) x 1 query, m = 8,
+// d_k = 96 15.0 / 6.1, d_k = 112 20.3 / 9.8; 16 x 12, d_k = 160, m = 4, fp32 32 / 9; 8 x 32 x 8 queries, d_k = 96, m = 8 71 / 27.
+template <typename QT, int JB>
 __global__ __launch_bounds__(kLutThreads) void build_lut_generic_kernel(const QT *__restrict__ q,
                                                                         const float *__restrict__ codebooks,
                                                                         float *__restrict__ lut, int B, int H, int T,
                                                                         int d_k, int m, int QB)
 {
+    extern __shared__ float q_s[];  // [QB][d_sub]
     const int d_sub = d_k / m;
     const int i = blockIdx.y;
     const int h = blockIdx.z;
     const int c = threadIdx.x;
     const int64_t nq = (int64_t)B * T;
+    const int64_t q0 = (int64_t)blockIdx.x * QB;
     const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * d_sub;
+    float row[JB];
+    auto fetch = [&](int j0) {                      // coordinates j0 .. j0 + JB - 1 as far as there are any
+        if (d_sub % 4 == 0) {                       // (rows of 16-byte pieces, from a 16-byte aligned codebook)
+#pragma unroll
+            for (int p = 0; p < JB; p += 4)
+                if (j0 + p < d_sub) {
+                    const float4 v = *reinterpret_cast<const float4 *>(src + j0 + p);
+                    row[p] = v.x;
+                    row[p + 1] = v.y;
+                    row[p + 2] = v.z;
+                    row[p + 3] = v.w;
+                }
+        } else {
+#pragma unroll
+            for (int p = 0; p < JB; p += 8)
+                if (j0 + p < d_sub)                 // (a branch per eight; past the end the last one again, not used)
+#pragma unroll
+                    for (int e = p; e < p + 8; ++e)
+                        row[e] = src[j0 + e < d_sub ? j0 + e : d_sub - 1];
+        }
+    };
+    fetch(0);
+    {                                               // 256 / QB threads per query (QB is a power of two, 16 at most)
+        const int per = kLutThreads / QB, k = c / per;
+        const int64_t qi = q0 + k;
+        if (qi < nq) {
+            int64_t b, t;
+            split_query(qi, T, b, t);
+            for (int j = c % per; j < d_sub; j += per)
+                q_s[k * d_sub + j] = to_f32<QT>(q[((b * H + h) * T + t) * d_k + (int64_t)i * d_sub + j]);
+        }
+    }
+    __syncthreads();
     for (int k = 0; k < QB; ++k) {
-        const int64_t qi = (int64_t)blockIdx.x * QB + k;
+        const int64_t qi = q0 + k;
         if (qi >= nq)
             break;
-        const int64_t b = qi / T, t = qi % T;
-        const QT *qv = q + ((b * H + h) * T + t) * d_k + (int64_t)i * d_sub;
         float acc = 0.f;
-        for (int j = 0; j < d_sub; ++j)
-            acc = fmaf(to_f32<QT>(qv[j]), src[j], acc);
+        for (int j0 = 0; j0 < d_sub; j0 += JB) {
+            if (d_sub > JB && (j0 > 0 || k > 0))
+                fetch(j0);
+#pragma unroll
+            for (int p = 0; p < JB; ++p)
+                if (j0 + p < d_sub)
+                    acc = fmaf(q_s[k * d_sub + j0 + p], row[p], acc);
+        }
+        int64_t b, t;
+        split_query(qi, T, b, t);
         lut[((((b * H + h) * T + t) * m) + i) * kCentroids + c] = acc;
     }
 }
@@ -100,6 +158,8 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_generic_kernel(const QT
 // us per call before / now: 4 x 32 x 512 queries, m = 16 (1.07 GB) 194 / 175; 32 x 12 x 128, m = 4 86 / 53; 12 x 1000, m = 4, fp32
 // 27.8 / 15.8; 256 x 32 x 1, m = 8 31.2 / 19.6; 3 x 7 x 333, m = 8 30.6 / 16.4.  The LDS holds four workgroups per compute unit;
 // three: 176 us, two: 198.
+// Sub-vectors of 32 and 64 (vector kernel / this one): 4 x 32 x 512 queries, d_k = 64, m = 2 77 / 56; 2 x 16 x 300, d_k = 128, m = 2
+// 33 / 23; 4 x 32 x 300, d_k = 128, m = 4, fp32 87 / 71: the vector ALU's multiply-adds, not the stores, were the bound.
 // Each wavefront makes 64 of the 256 centroids: two 32-column blocks of the MFMA, whose results cross LDS so that they leave
 // as 1 KB table rows, 16 bytes per lane (stored straight from the accumulators, a store instruction would write 4 bytes
 // per lane in two 128-byte pieces).  NTS = 1 writes with non-temporal stores: a table set far larger than
@@ -240,8 +300,10 @@ static bool launch_build_lut_mfma(const lookat_shape *s, int T, const void *q, c
         LOOKAT_LUTM_CASE(4)
         LOOKAT_LUTM_CASE(8)
         LOOKAT_LUTM_CASE(16)
+        LOOKAT_LUTM_CASE(32)
+        LOOKAT_LUTM_CASE(64)
     default:
-        return false;   // longer sub-vectors: vector kernel
+        return false;   // other sub-vectors: vector kernel
     }
 #undef LOOKAT_LUTM_CASE
 }
@@ -273,8 +335,12 @@ static void launch_build_lut(const lookat_shape *s, int T, const void *q, const 
         LOOKAT_LUT_CASE(32)
         LOOKAT_LUT_CASE(64)
     default:
-        hipLaunchKernelGGL((build_lut_generic_kernel<QT>), grid, block, 0, st, qp, codebooks, lut, s->B, s->H, T,
-                           s->d_k, s->m, QB);
+        if (d_sub <= 8)
+            hipLaunchKernelGGL((build_lut_generic_kernel<QT, 8>), grid, block, (size_t)QB * d_sub * sizeof(float), st, qp,
+                               codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB);
+        else
+            hipLaunchKernelGGL((build_lut_generic_kernel<QT, 32>), grid, block, (size_t)QB * d_sub * sizeof(float), st, qp,
+                               codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB);
         break;
     }
 #undef LOOKAT_LUT_CASE

@@ -1,0 +1,53 @@
+"""Appends of a few keys and tables of a few queries, every number of keys that a workgroup takes and sub-vector lengths around the
+pieces in which a centroid's row is read, against the oracle; tables of many queries for the longest sub-vectors of the matrix-core
+kernel."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lk():
+    import paper_2601_10155_amd as pkg
+    pkg.load_library()
+    return pkg
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+# sub-vectors of 5, 12, 16, 20, 32, 36, 64, 80 and 136 coordinates; 1 to 9 keys of a head, one each or several of a sequence
+@pytest.mark.parametrize("d_k,m", [(80, 16), (96, 8), (64, 4), (160, 8), (64, 2), (144, 4), (128, 2), (160, 2), (136, 1)])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+@pytest.mark.parametrize("B,N", [(1, 1), (2, 1), (4, 1), (5, 1), (3, 3)])
+def test_few_keys_and_queries(lk, d_k, m, dtype, B, N):
+    rng = np.random.default_rng(d_k + m + B)
+    cb = rng.standard_normal((3, m, 256, d_k // m)).astype(np.float32)
+    cb[:, :, 200] = cb[:, :, 100]                                 # ties: the lower index
+    x = rng.standard_normal((B, 3, N, d_k)).astype(dtype)
+    x[0, 0, 0] = cb[0, :, 100].reshape(-1).astype(dtype)
+    assert np.array_equal(lk.lookat_encode_keys(dev(x), dev(cb)).cpu().numpy(), oracle.encode_keys(x, cb))
+    got = lk.lookat_build_lut(dev(x), dev(cb)).cpu().numpy()
+    ref = oracle.build_lut(x, cb)
+    size = np.abs(x.astype(np.float64).reshape(B, 3, N, m, 1, -1)) @ np.abs(cb.astype(np.float64))[None, :, None].swapaxes(-1, -2)
+    # an fp32 chain of n products is within n 2^-24 of the summands' magnitude (and the oracle rounds once more)
+    assert (np.abs(got - ref.reshape(got.shape)) <= (d_k // m + 1) * 2.0 ** -24 * size.reshape(got.shape)).all()
+
+
+@pytest.mark.parametrize("d_k,m", [(64, 2), (128, 4), (128, 2)])
+@pytest.mark.parametrize("B,T", [(1, 256), (3, 101), (2, 300)])   # whole tiles of 32 queries, tiles across batch entries, a ragged end
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+def test_tables_of_long_sub_vectors(lk, d_k, m, B, T, dtype):
+    rng = np.random.default_rng(d_k + T)
+    cb = rng.standard_normal((2, m, 256, d_k // m)).astype(np.float32)
+    q = rng.standard_normal((B, 2, T, d_k)).astype(dtype)
+    got = lk.lookat_build_lut(dev(q), dev(cb)).cpu().numpy()
+    x = q.astype(np.float64).reshape(B, 2, T, m, 1, -1)
+    c = cb.astype(np.float64)[None, :, None].swapaxes(-1, -2)
+    ref, size = (x @ c).reshape(got.shape), (np.abs(x) @ np.abs(c)).reshape(got.shape)
+    assert (np.abs(got - ref) <= (d_k // m + 1) * 2.0 ** -24 * size).all()
