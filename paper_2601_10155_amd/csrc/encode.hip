@@ -83,23 +83,39 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const KT *__restric
 // ---- few keys per head (decode-time append) -------------------------------------------
 // With a handful of keys per head the thread-per-key kernel above leaves the chip empty and
 // each thread walks all 256 centroids serially.  Here the centroids are spread over the
-// threads instead: one block = one (head, subspace) and up to kEncFewKeys keys; thread c
-// holds centroid c in registers as fp64, evaluates its distance to every key of the block
+// threads instead: one block = one (head, subspace) and KEYS keys (1, 2, 4 or 8, the smallest that takes a head's keys in
+// one block); thread c holds centroid c in registers, evaluates its distance to every key of the block
 // (same arithmetic, same order) and the block takes the argmin over (distance, index).
+// What bounds it: latency -- the codebook's and the keys' way from memory, then KEYS serial chains of fp64 operations and as many
+// reductions over the wavefront.  So the centroid's row is requested in 16-byte pieces, sixteen coordinates at once, beside the keys (element
+// by element, four in flight, the row of a 12-coordinate sub-vector took three round trips), and no key is evaluated that is not there.
+// us per call before / now: 4 x 16 (b,h), d_k = 96, m = 8 4.9 / 3.5; 2 x 8, d_k = 128, m = 2, fp32 12.5 / 5.4; 1 x 8, d_k = 160, m = 16 4.7 / 3.7.
 constexpr int kEncFewKeys = 8;
 
-// Per key the minimum over the wavefront's 64 centroids (cross-lane moves on the vector ALU, the eight chains
+// Flat (b, n) of a head's keys.  (A decode step appends one key per sequence: no 64-bit division on the way to its address.)
+__device__ __forceinline__ void split_row(int64_t r, int64_t N, int64_t &b, int64_t &n)
+{
+    b = r;
+    n = 0;
+    if (N != 1) {
+        b = r / N;
+        n = r % N;
+    }
+}
+
+// Per key the minimum over the wavefront's 64 centroids (cross-lane moves on the vector ALU, the keys' chains
 // interleaved), the lowest lane that holds it (the serial scan's choice among exact ties), and the same over the
 // block's wavefronts.
-__device__ __forceinline__ void encode_few_finish(const double (&dv)[kEncFewKeys], double (&dm)[kEncFewKeys],
-                                                  double (&red_d)[kEncFewKeys][kCentroids / kWave],
-                                                  int (&red_c)[kEncFewKeys][kCentroids / kWave], uint8_t *codes,
+template <int KEYS>
+__device__ __forceinline__ void encode_few_finish(const double (&dv)[KEYS], double (&dm)[KEYS],
+                                                  double (&red_d)[KEYS][kCentroids / kWave],
+                                                  int (&red_c)[KEYS][kCentroids / kWave], uint8_t *codes,
                                                   int64_t code_stride_bh, int B, int H, int64_t N, int m, int i, int h,
                                                   int64_t r0, int lane, int wave)
 {
-    dmin_wave<kEncFewKeys>(dm);
+    dmin_wave<KEYS>(dm);
 #pragma unroll
-    for (int k = 0; k < kEncFewKeys; ++k) {
+    for (int k = 0; k < KEYS; ++k) {
         const uint64_t holders = __ballot(dv[k] == dm[k]);
         if (lane == 0) {
             red_d[k][wave] = dm[k];
@@ -107,7 +123,7 @@ __device__ __forceinline__ void encode_few_finish(const double (&dv)[kEncFewKeys
         }
     }
     __syncthreads();
-    if (threadIdx.x < kEncFewKeys) {
+    if (threadIdx.x < KEYS) {
         const int k = threadIdx.x;
         const int64_t r = r0 + k;
         if (r < (int64_t)B * N) {
@@ -122,34 +138,36 @@ __device__ __forceinline__ void encode_few_finish(const double (&dv)[kEncFewKeys
                 bd = better ? d : bd;
                 best = better ? cw : best;
             }
-            const int64_t b = r / N, n = r % N;
+            int64_t b, n;
+            split_row(r, N, b, n);
             codes[(b * H + h) * code_stride_bh + n * m + i] = (uint8_t)best;
         }
     }
 }
 
-template <typename KT, int DSUB>
+template <typename KT, int DSUB, int KEYS>
 __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__restrict__ keys,
                                                                 const float *__restrict__ codebooks,
                                                                 uint8_t *__restrict__ codes, int64_t code_stride_bh,
                                                                 int B, int H, int64_t N, int d_k, int m)
 {
-    __shared__ double x_s[kEncFewKeys][DSUB];
-    __shared__ double red_d[kEncFewKeys][kCentroids / kWave];
-    __shared__ int red_c[kEncFewKeys][kCentroids / kWave];
+    __shared__ double x_s[KEYS][DSUB];
+    __shared__ double red_d[KEYS][kCentroids / kWave];
+    __shared__ int red_c[KEYS][kCentroids / kWave];
 
     const int i = blockIdx.y;
     const int h = blockIdx.z;
     const int c = threadIdx.x;
     const int lane = c & (kWave - 1), wave = c / kWave;
-    const int64_t r0 = (int64_t)blockIdx.x * kEncFewKeys;   // first flat (b, n) of the block
+    const int64_t r0 = (int64_t)blockIdx.x * KEYS;   // first flat (b, n) of the block
     const int64_t rows = (int64_t)B * N;
 
-    for (int e = threadIdx.x; e < kEncFewKeys * DSUB; e += kCentroids) {
+    for (int e = threadIdx.x; e < KEYS * DSUB; e += kCentroids) {
         const int64_t r = r0 + e / DSUB;
         double v = 0.0;
         if (r < rows) {
-            const int64_t b = r / N, n = r % N;
+            int64_t b, n;
+            split_row(r, N, b, n);
             v = widen<KT>(keys[((b * H + h) * N + n) * d_k + (int64_t)i * DSUB + e % DSUB]);
         }
         x_s[e / DSUB][e % DSUB] = v;
@@ -164,9 +182,9 @@ __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__rest
     __syncthreads();
 
     // Distances of centroid c to the block's keys.
-    double dv[kEncFewKeys], dm[kEncFewKeys];
+    double dv[KEYS], dm[KEYS];
 #pragma unroll
-    for (int k = 0; k < kEncFewKeys; ++k) {
+    for (int k = 0; k < KEYS; ++k) {
         double acc = 0.0;
 #pragma unroll
         for (int j = 0; j < DSUB; ++j) {
@@ -177,20 +195,21 @@ __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__rest
         dv[k] = argmin_value(acc, c);
         dm[k] = dv[k];
     }
-    encode_few_finish(dv, dm, red_d, red_c, codes, code_stride_bh, B, H, N, m, i, h, r0, lane, wave);
+    encode_few_finish<KEYS>(dv, dm, red_d, red_c, codes, code_stride_bh, B, H, N, m, i, h, r0, lane, wave);
 }
 
-// Any sub-vector length: the same with the centroid's coordinates read as they are needed (each serves the block's
-// eight keys) instead of kept in registers.  The keys' sub-vectors sit in dynamic LDS.
-template <typename KT>
+// Any sub-vector length: the same, the centroid's coordinates taken sixteen at a time, the next sixteen requested before the
+// last are used.  The keys' sub-vectors sit in dynamic LDS.
+template <typename KT, int KEYS>
 __global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__restrict__ keys,
                                                                     const float *__restrict__ codebooks,
                                                                     uint8_t *__restrict__ codes, int64_t code_stride_bh,
                                                                     int B, int H, int64_t N, int d_k, int m)
 {
-    extern __shared__ __align__(16) double xs[];   // [d_sub][kEncFewKeys]
-    __shared__ double red_d[kEncFewKeys][kCentroids / kWave];
-    __shared__ int red_c[kEncFewKeys][kCentroids / kWave];
+    constexpr int JB = 16;
+    extern __shared__ __align__(16) double xs[];   // [d_sub][KEYS]
+    __shared__ double red_d[KEYS][kCentroids / kWave];
+    __shared__ int red_c[KEYS][kCentroids / kWave];
     const int d_sub = d_k / m;
     const int i = blockIdx.y;
     const int h = blockIdx.z;
@@ -198,41 +217,76 @@ __global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__
     const int lane = c & (kWave - 1), wave = c / kWave;
     const int64_t rows = (int64_t)B * N;
     const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * d_sub;
-    for (int64_t r0 = (int64_t)blockIdx.x * kEncFewKeys; r0 < rows; r0 += (int64_t)gridDim.x * kEncFewKeys) {
-        for (int e = c; e < kEncFewKeys * d_sub; e += kCentroids) {
-            const int k = e / d_sub, j = e % d_sub;
-            const int64_t r = r0 + k;
-            double v = 0.0;
-            if (r < rows) {
-                const int64_t b = r / N, n = r % N;
-                v = widen<KT>(keys[((b * H + h) * N + n) * d_k + (int64_t)i * d_sub + j]);
+    const bool pieces = d_sub % 4 == 0;             // a row is 16-byte pieces (from a 16-byte aligned codebook)
+    auto fetch = [&](int j0, float (&y)[JB]) {      // coordinates j0 .. j0 + 15 as far as there are any
+#pragma unroll
+        for (int q = 0; q < JB; q += 4)
+            if (j0 + q < d_sub) {
+                const float4 v = *reinterpret_cast<const float4 *>(src + j0 + q);
+                y[q] = v.x;
+                y[q + 1] = v.y;
+                y[q + 2] = v.z;
+                y[q + 3] = v.w;
             }
-            xs[j * kEncFewKeys + k] = v;
+    };
+    for (int64_t r0 = (int64_t)blockIdx.x * KEYS; r0 < rows; r0 += (int64_t)gridDim.x * KEYS) {
+        float y[JB], ahead[JB];
+        if (pieces)
+            fetch(0, y);
+        {                                           // 256 / KEYS threads per key
+            constexpr int kPer = kCentroids / KEYS;
+            const int k = c / kPer;
+            const int64_t r = r0 + k;
+            int64_t b = 0, n = 0;
+            if (r < rows)
+                split_row(r, N, b, n);
+            for (int j = c % kPer; j < d_sub; j += kPer)
+                xs[j * KEYS + k] = r < rows ? widen<KT>(keys[((b * H + h) * N + n) * d_k + (int64_t)i * d_sub + j]) : 0.0;
         }
         __syncthreads();
-        double dv[kEncFewKeys], dm[kEncFewKeys];
+        double dv[KEYS], dm[KEYS];
 #pragma unroll
-        for (int k = 0; k < kEncFewKeys; ++k)
+        for (int k = 0; k < KEYS; ++k)
             dv[k] = 0.0;
-#pragma unroll 4
-        for (int j = 0; j < d_sub; ++j) {
-            const double y = (double)src[j];
+        auto add = [&](int j, double yd) {
 #pragma unroll
-            for (int k = 0; k < kEncFewKeys; ++k) {
-                double diff = xs[j * kEncFewKeys + k] - y;
+            for (int k = 0; k < KEYS; ++k) {
+                double diff = xs[j * KEYS + k] - yd;
                 double sq = diff * diff;
                 dv[k] = dv[k] + sq;
             }
+        };
+        if (pieces) {
+            for (int j0 = 0; j0 < d_sub; j0 += JB) {
+                if (j0 + JB < d_sub)
+                    fetch(j0 + JB, ahead);
+#pragma unroll
+                for (int q = 0; q < JB; q += 4)
+                    if (j0 + q < d_sub) {
+#pragma unroll
+                        for (int e = q; e < q + 4; ++e)
+                            add(j0 + e, (double)y[e]);
+                    }
+#pragma unroll
+                for (int q = 0; q < JB; ++q)
+                    y[q] = ahead[q];
+            }
+        } else {                                    // (5, 7, 10, 14 ..: 16 single elements ahead measured 5 to 15% slower)
+#pragma unroll 4
+            for (int j = 0; j < d_sub; ++j)
+                add(j, (double)src[j]);
         }
 #pragma unroll
-        for (int k = 0; k < kEncFewKeys; ++k) {
+        for (int k = 0; k < KEYS; ++k) {
             dv[k] = argmin_value(dv[k], c);
             dm[k] = dv[k];
         }
-        encode_few_finish(dv, dm, red_d, red_c, codes, code_stride_bh, B, H, N, m, i, h, r0, lane, wave);
+        encode_few_finish<KEYS>(dv, dm, red_d, red_c, codes, code_stride_bh, B, H, N, m, i, h, r0, lane, wave);
         __syncthreads();   // the next keys overwrite the staged ones
     }
 }
+
+static int few_keys(int64_t rows) { return rows <= 1 ? 1 : (rows <= 2 ? 2 : (rows <= 4 ? 4 : kEncFewKeys)); }
 
 // (also the exact scan of sub-vector lengths without an encode_kernel instance, however many keys)
 template <typename KT>
@@ -240,10 +294,22 @@ static void launch_encode_few_any(const lookat_shape *s, int64_t N, const void *
                                   uint8_t *codes, int64_t code_stride_bh, hipStream_t st)
 {
     const int64_t rows = (int64_t)s->B * N;
-    const int64_t blocks = (rows + kEncFewKeys - 1) / kEncFewKeys;
+    const int keys_wg = few_keys(rows);
+    const int64_t blocks = (rows + keys_wg - 1) / keys_wg;
     const dim3 grid((unsigned)(blocks < 65536 ? blocks : 65536), (unsigned)s->m, (unsigned)s->H);
-    hipLaunchKernelGGL((encode_few_any_kernel<KT>), grid, dim3(kCentroids), (size_t)kEncFewKeys * (s->d_k / s->m) * sizeof(double),
-                       st, static_cast<const KT *>(keys), codebooks, codes, code_stride_bh, s->B, s->H, N, s->d_k, s->m);
+#define LOOKAT_ENCA_LAUNCH(KEYS)                                                                                          \
+    hipLaunchKernelGGL((encode_few_any_kernel<KT, KEYS>), grid, dim3(kCentroids),                                         \
+                       (size_t)KEYS * (s->d_k / s->m) * sizeof(double), st, static_cast<const KT *>(keys), codebooks,     \
+                       codes, code_stride_bh, s->B, s->H, N, s->d_k, s->m)
+    if (keys_wg == 1)
+        LOOKAT_ENCA_LAUNCH(1);
+    else if (keys_wg == 2)
+        LOOKAT_ENCA_LAUNCH(2);
+    else if (keys_wg == 4)
+        LOOKAT_ENCA_LAUNCH(4);
+    else
+        LOOKAT_ENCA_LAUNCH(8);
+#undef LOOKAT_ENCA_LAUNCH
 }
 
 template <typename KT>
@@ -252,13 +318,23 @@ static bool launch_encode_few(const lookat_shape *s, int64_t N, const void *keys
 {
     const int d_sub = s->d_k / s->m;
     const int64_t rows = (int64_t)s->B * N;
-    dim3 grid((unsigned)((rows + kEncFewKeys - 1) / kEncFewKeys), (unsigned)s->m, (unsigned)s->H);
+    const int keys_wg = few_keys(rows);
+    dim3 grid((unsigned)((rows + keys_wg - 1) / keys_wg), (unsigned)s->m, (unsigned)s->H);
     dim3 block(kCentroids);
     const KT *k = static_cast<const KT *>(keys);
+#define LOOKAT_ENCF_LAUNCH(D, KEYS)                                                                             \
+    hipLaunchKernelGGL((encode_few_kernel<KT, D, KEYS>), grid, block, 0, st, k, codebooks, codes,               \
+                       code_stride_bh, s->B, s->H, N, s->d_k, s->m)
 #define LOOKAT_ENCF_CASE(D)                                                                                     \
     case D:                                                                                                     \
-        hipLaunchKernelGGL((encode_few_kernel<KT, D>), grid, block, 0, st, k, codebooks, codes, code_stride_bh, \
-                           s->B, s->H, N, s->d_k, s->m);                                                        \
+        if (keys_wg == 1)                                                                                       \
+            LOOKAT_ENCF_LAUNCH(D, 1);                                                                           \
+        else if (keys_wg == 2)                                                                                  \
+            LOOKAT_ENCF_LAUNCH(D, 2);                                                                           \
+        else if (keys_wg == 4)                                                                                  \
+            LOOKAT_ENCF_LAUNCH(D, 4);                                                                           \
+        else                                                                                                    \
+            LOOKAT_ENCF_LAUNCH(D, 8);                                                                           \
         return true;
     switch (d_sub) {
         LOOKAT_ENCF_CASE(1)
@@ -272,6 +348,7 @@ static bool launch_encode_few(const lookat_shape *s, int64_t N, const void *keys
         return true;
     }
 #undef LOOKAT_ENCF_CASE
+#undef LOOKAT_ENCF_LAUNCH
 }
 
 template <typename KT>
