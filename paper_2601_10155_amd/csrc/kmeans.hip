@@ -11,9 +11,9 @@ namespace lookat {
 // kKmChunk at a time; for a chunk the workgroup turns the assignment column into per-centroid member lists in LDS
 // and thread (centroid, piece) adds the members of its centroid to sums it keeps in registers.  The lists hold
 // the members in ascending key order, so every sum is taken in the order a scan of all keys would take.
-// List building is a stable counting sort by code.  Each of the sixteen wavefronts owns a contiguous
+// List building is a stable counting sort by code.  Each of the sixteen (eight) wavefronts owns a contiguous
 // share of the chunk and keeps its codes in registers: it histograms them (LDS atomics; counts do not depend on
-// order), 256 threads turn the sixteen histograms into every (wavefront, code) pair's first slot, and
+// order), 256 threads turn these histograms into every (wavefront, code) pair's first slot, and
 // each wavefront then walks its share 64 keys at a time in ascending order: the lanes that hold
 // equal codes find each other with eight ballots (one per code bit), a lane's slot is the pair's
 // running offset plus the number of equal-code lanes below it, and the lowest of them advances
@@ -27,22 +27,22 @@ namespace lookat {
 // and eight in flight; 86 us with the subspaces of a head on one die and chunks of 4096 keys (2048: 93, 8192: 93, 16384: 103;
 // 12 or 16 pieces in flight: no change; the lists alone: 29).
 //   LDS: first[257] | run[16][256] | list [kKmChunk] uint16
-//   grid = (8 heads x m x groups of a sub-vector's pieces, ceil(H / 8)), 1024 threads; consecutive workgroups go to the
+//   grid = (8 heads x m x groups of a sub-vector's pieces, ceil(H / 8)), 512 or 1024 threads; consecutive workgroups go to the
 //   eight dies in turn
-constexpr int kKmThreads = 1024;
-constexpr int kKmWaves = kKmThreads / kWave;
+constexpr int kKmPieces = 4;                         // 1024 threads, one (centroid, piece) each
 constexpr int kKmChunk = 4096;
-constexpr int kKmRounds = kKmChunk / kKmThreads;     // 64-key rounds of a wavefront in a full chunk
-constexpr int kKmPieces = kKmThreads / kCentroids;   // one (centroid, piece) per thread
 constexpr int kKmBatch = 8;
 
-template <int V>
-__global__ __launch_bounds__(kKmThreads) void kmeans_update_kernel(const float *__restrict__ calib,
+template <int V, int THREADS>
+__global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__restrict__ calib,
                                                                    const uint8_t *__restrict__ assign,
                                                                    const float *__restrict__ cb_in,
                                                                    float *__restrict__ cb_out, int64_t Nc, int d_k,
                                                                    int H, int m, int groups, int pieces_per_wg)
 {
+    constexpr int kKmThreads = THREADS;
+    constexpr int kKmWaves = kKmThreads / kWave;
+    constexpr int kKmRounds = kKmChunk / kKmThreads;     // 64-key rounds of a wavefront in a full chunk
     __shared__ uint32_t first_s[kCentroids + 1];
     __shared__ uint32_t run_s[kKmWaves][kCentroids];
     __shared__ uint16_t list_s[kKmChunk];
@@ -210,11 +210,23 @@ extern "C" int lookat_kmeans_step(const lookat_shape *shape, int64_t Nc, const f
     const int groups = (pieces + per - 1) / per;      // workgroups per (head, subspace)
     const dim3 grid((unsigned)(8 * shape->m * groups), (unsigned)(((int64_t)shape->H + 7) / 8));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (V == 4)
-        hipLaunchKernelGGL(kmeans_update_kernel<4>, grid, dim3(kKmThreads), 0, st, calib, assign, codebooks_in, codebooks_out,
-                           Nc, shape->d_k, shape->H, shape->m, groups, per);
+    // With one or two pieces per workgroup half of 1024 threads or more would only build lists.  Where there are more workgroups than
+    // compute units, two of 512 on one list and add at different times (us per step, 1024 / 512 threads: 40 heads x 2000 keys, d_k = 128,
+    // m = 16 67 / 60; 32 x 8000, d_k = 64, m = 16 127 / 113; 25 x 700 23.8 / 20.0), and up to 1024 keys there is little to list (12 x 600,
+    // d_k = 64, m = 8 15.0 / 14.3); else the lists are made faster by all (4 x 24000, d_k = 64, m = 2 90.0 / 91.2; with four pieces, whose
+    // lists two workgroups would build twice, 32 x 16384, d_k = 128, m = 8 175 / 203).
+    const bool half = per <= 2 && ((int64_t)shape->m * shape->H * groups > 256 || Nc <= 1024);
+#define LOOKAT_KM_LAUNCH(V, THREADS)                                                                                      \
+    hipLaunchKernelGGL((kmeans_update_kernel<V, THREADS>), grid, dim3(THREADS), 0, st, calib, assign, codebooks_in,       \
+                       codebooks_out, Nc, shape->d_k, shape->H, shape->m, groups, per)
+    if (V == 4 && half)
+        LOOKAT_KM_LAUNCH(4, 512);
+    else if (V == 4)
+        LOOKAT_KM_LAUNCH(4, 1024);
+    else if (half)
+        LOOKAT_KM_LAUNCH(1, 512);
     else
-        hipLaunchKernelGGL(kmeans_update_kernel<1>, grid, dim3(kKmThreads), 0, st, calib, assign, codebooks_in, codebooks_out,
-                           Nc, shape->d_k, shape->H, shape->m, groups, per);
+        LOOKAT_KM_LAUNCH(1, 1024);
+#undef LOOKAT_KM_LAUNCH
     return check_launch("lookat_kmeans_step (update kernel)");
 }

@@ -51,3 +51,14 @@ def test_tables_of_long_sub_vectors(lk, d_k, m, B, T, dtype):
     c = cb.astype(np.float64)[None, :, None].swapaxes(-1, -2)
     ref, size = (x @ c).reshape(got.shape), (np.abs(x) @ np.abs(c)).reshape(got.shape)
     assert (np.abs(got - ref) <= (d_k // m + 1) * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("H,d_k,m,Nc", [(33, 64, 16, 4099), (35, 64, 8, 1030), (3, 64, 16, 1024), (3, 64, 16, 1025), (129, 24, 8, 70)])
+def test_learning_with_the_smaller_workgroup(lk, H, d_k, m, Nc):
+    """One or two pieces of four coordinates (or single ones) per workgroup, with more workgroups than compute units or few keys."""
+    rng = np.random.default_rng(H + Nc)
+    cb = rng.standard_normal((H, m, 256, d_k // m)).astype(np.float32)
+    calib = rng.standard_normal((H, Nc, d_k)).astype(np.float32)
+    ref, _ = oracle.kmeans_step(calib, cb)
+    got, _ = lk.lookat_kmeans_step(dev(calib), dev(cb))
+    assert np.array_equal(got.cpu().numpy(), ref)
