@@ -1,0 +1,49 @@
+"""What keys that the ranking encoder cannot decide cost: differences and ratios of launch times, far from the limits on both sides."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lk():
+    import paper_2601_10155_amd as pkg
+    pkg.load_library()
+    return pkg
+
+
+def best_us(*calls, repeats=12, rounds=10):
+    """Smallest time of each call, back to back, the calls in turn."""
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    best = [float("inf")] * len(calls)
+    for r in range(rounds + 1):                     # (the first round warms up)
+        for n, call in enumerate(calls):
+            e[0].record()
+            for _ in range(repeats):
+                call()
+            e[1].record()
+            torch.cuda.synchronize()
+            if r:
+                best[n] = min(best[n], e[0].elapsed_time(e[1]) * 1e3 / repeats)
+    return best
+
+
+@pytest.mark.parametrize("d_sub", [40, 56])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+def test_undecided_keys_of_padded_sub_vectors(lk, d_sub, dtype):
+    """A workgroup whose keys all have two equally near centroids, worked off in eight rounds: 14 to 17 us where a round requests all
+    pieces of its sub-vectors at once, 27 to 30 where each piece was waited for before the next."""
+    H, m, N = 4, 4, 1000
+    g = torch.Generator(device="cuda").manual_seed(d_sub)
+    cb = torch.randn((H, m, 256, d_sub), generator=g, device="cuda").half().float()
+    cb[:, :, 1] = cb[:, :, 0]
+    pick = torch.randint(2, 256, (H, N, m), generator=g, device="cuda")
+    plain = cb[torch.arange(H, device="cuda")[:, None, None], torch.arange(m, device="cuda"), pick].reshape(1, H, N, m * d_sub)
+    plain = plain.to(getattr(torch, dtype)).contiguous()
+    tied = plain.clone()
+    tied[0, 0, :250, :d_sub] = cb[0, 0, 0].to(tied.dtype)
+    codes = torch.empty((1, H, N, m), dtype=torch.uint8, device="cuda")
+    a, b = best_us(lambda: lk.lookat_encode_keys(plain, cb, codes_out=codes), lambda: lk.lookat_encode_keys(tied, cb, codes_out=codes))
+    print(f"d_sub {d_sub} {dtype}: {a:.2f} us decided, {b:.2f} us with 250 undecided keys")
+    assert not codes[0, 0, :250, 0].any()
+    assert b - a < 22, (a, b)
