@@ -282,6 +282,7 @@ struct EfShape {
     static constexpr int NB = K32 && DP >= 8 && FINE ? 2 : 1;      //                     keys
     static constexpr bool AHEAD = !(K32 && DP == 64) && !FINE;     // a tile pair's operands are read from LDS before they are due
     static constexpr int NREG = (DP == 8 || DP == 16) && !FINE ? (K32 && DP == 16 ? 5 : 6) : 0;   // tiles whose norms stay in registers (16 each)
+    static constexpr bool NTWICE = K32 && DP == 64 && !FINE;       // norms are read for each block: registers that hold them for both spill others
     static constexpr bool AREG = DP <= 8 || (DP == 16 && !K32 && !FINE);   // centroid operands in 32 registers, else read from LDS
 };
 
@@ -660,13 +661,19 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
 #pragma unroll
                 for (int t = 0; t < kEfTiles; t += 2) {
                     ef_v16f n0, n1;
-                    start(t, n0);
-                    start(t + 1, n1);
+                    if constexpr (!Sh::NTWICE) {
+                        start(t, n0);
+                        start(t + 1, n1);
+                    }
                     if constexpr (!Sh::AHEAD)
                         operands(t);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int blk = 0; blk < 2; ++blk) {
+                        if constexpr (Sh::NTWICE) {
+                            start(t, n0);
+                            start(t + 1, n1);
+                        }
                         ef_v16f x0 = n0, x1 = n1;
 #pragma unroll
                         for (int s = 0; s < NS; ++s)
