@@ -88,30 +88,55 @@ __device__ __forceinline__ float ef_to_f32<__half>(__half v) { return __half2flo
 __device__ __forceinline__ float ef_min(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 __device__ __forceinline__ float ef_min3(float a, float b, float c) { return ef_min(ef_min(a, b), c); }
 
-// Coordinates j0 .. j0+3 of a sub-vector of d_sub coordinates, zero past its end.  FULL: all four exist and the start
+// Coordinates j0 .. j0+3 of a sub-vector whose length d_sub is a multiple of four, zero past its end.  FULL: all four exist and the start
 // is a multiple of four elements from a 16-byte aligned row.
 template <bool FULL, typename T>
 __device__ __forceinline__ void ef_load4(const T *sub, int j0, int d_sub, T (&out)[4])
 {
     typedef unsigned int chunk_t __attribute__((ext_vector_type(sizeof(T))));   // 4 elements: 8 or 16 bytes
-    if (FULL || d_sub % 4 == 0) {
-        chunk_t v = {};
-        if (FULL || j0 < d_sub)
-            v = *reinterpret_cast<const chunk_t *>(sub + j0);
-        __builtin_memcpy(out, &v, sizeof(v));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            out[e] = (j0 + e < d_sub) ? sub[j0 + e] : T(0.f);
-    }
+    chunk_t v = {};
+    if (FULL || j0 < d_sub)
+        v = *reinterpret_cast<const chunk_t *>(sub + j0);
+    __builtin_memcpy(out, &v, sizeof(v));
 }
 
-// Coordinates j0 .. j0+N-1 of two sub-vectors of d_sub coordinates, all requested at once: past the end the last ones again, which the
-// callers leave out.  (With a branch around every piece that may not be there the compiler waits for each before the next.  us per call,
-// so / now: 32 heads x 8000 keys, 2 subspaces of 40, fp16 48.4 / 38.4, fp32 66.6 / 54.2; 8 x 16 x 2048, 4 of 48, fp32 116 / 95; 8 of 12
-// 71 / 63; eight rounds of the exact rule over 40 coordinates 27 / 14.)
+// The same for the other lengths and two-byte elements, in two steps, so that nothing is done with a request before it is due (elements
+// that are requested one by one are packed in pairs as they arrive, and the pair loop waited for the next pair's keys; us per call, so / now:
+// 8 x 16 x 2048 keys, 8 subspaces of 10 78.5 / 57.2, of 14 83.1 / 56.2, of 6 61.7 / 44.0; 32 x 16 x 2116, 32 of 3 705 / 601): the last
+// four coordinates of the sub-vector where j0 .. j0+3 reach past its end (of two or three: the first two, then the last one), ..
+template <typename T>
+__device__ __forceinline__ void ef_load_tail(const T *sub, int j0, int d_sub, T (&out)[4])
+{
+    static_assert(sizeof(T) == 2, "two-byte elements");
+    struct __attribute__((packed, aligned(2))) two_t { uint32_t v; };
+    struct __attribute__((packed, aligned(2))) four_t { uint64_t v; };
+    uint64_t v;
+    if (d_sub < 4)
+        v = (uint64_t)reinterpret_cast<const two_t *>(sub)->v | (uint64_t)*reinterpret_cast<const uint16_t *>(sub + d_sub - 1) << 32;
+    else
+        v = reinterpret_cast<const four_t *>(sub + (j0 < d_sub - 4 ? j0 : d_sub - 4))->v;
+    __builtin_memcpy(out, &v, sizeof(v));
+}
+// .. shifted to where they belong.
+template <typename T>
+__device__ __forceinline__ void ef_align_tail(T (&x)[4], int j0, int d_sub)
+{
+    uint64_t v;
+    __builtin_memcpy(&v, x, sizeof(v));
+    const int past = j0 + 4 - d_sub;
+    if (d_sub < 4)
+        v = j0 ? 0 : (d_sub == 3 ? v : v & 0xffffffffu);
+    else
+        v = past >= 4 ? 0 : v >> (past > 0 ? 16 * past : 0);
+    __builtin_memcpy(x, &v, sizeof(v));
+}
+
+// Coordinates j0 .. j0+N-1 of a sub-vector of d_sub coordinates, and of M rows of the codebook beside it, all requested at once: past the
+// end the last ones again, which the callers leave out.  (With a branch around every piece that may not be there the compiler waits for
+// each before the next.  us per call, so / now: 32 heads x 8000 keys, 2 subspaces of 40, fp16 48.4 / 38.4, fp32 66.6 / 54.2; 8 x 16 x 2048,
+// 4 of 48, fp32 116 / 95; 8 of 12 71 / 63; eight rounds of the exact rule over 40 coordinates 27 / 14.)
 template <int N, int M, typename T>
-__device__ __forceinline__ void ef_load_clamped(const T *x_sub, const float *(&rows)[M], int j0, int d_sub, T (&x)[N], float (&y)[M][N])
+__device__ __forceinline__ void ef_load_clamped(const T *x_sub, const float *const (&rows)[M], int j0, int d_sub, T (&x)[N], float (&y)[M][N])
 {
     if (d_sub % 4 == 0) {
         typedef unsigned int chunk_t __attribute__((ext_vector_type(sizeof(T))));   // 4 elements: 8 or 16 bytes
@@ -136,6 +161,21 @@ __device__ __forceinline__ void ef_load_clamped(const T *x_sub, const float *(&r
             for (int u = 0; u < M; ++u)
                 y[u][e] = rows[u][at];
         }
+    }
+}
+template <int N>
+__device__ __forceinline__ void ef_load_clamped(const float *row, int j0, int d_sub, float (&y)[N])
+{
+    if (d_sub % 4 == 0) {
+        ef_v4f yv[N / 4];
+#pragma unroll
+        for (int q = 0; q < N / 4; ++q)
+            yv[q] = *reinterpret_cast<const ef_v4f *>(row + (j0 + 4 * q < d_sub ? j0 + 4 * q : d_sub - 4));
+        __builtin_memcpy(y, yv, sizeof(y));
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+            y[e] = row[j0 + e < d_sub ? j0 + e : d_sub - 1];
     }
 }
 
@@ -270,7 +310,7 @@ __device__ __forceinline__ void ef_argmin_step(double &best, int &code)
 //             zero for fp16 keys) in 8..11, 2^x against the norm's three terms.
 // FINE leaves no term out, as DP == 4: for launches of few pairs, where the undecided keys' extra round trip to memory is what
 // counts and not the matrix instructions.
-template <typename KT, int DP, bool FINE>
+template <typename KT, int DP, bool FULL, bool FINE>
 struct EfShape {
     static constexpr bool K32 = std::is_same<KT, float>::value;
     static constexpr int NS = DP >= 16 ? DP / 16 : 1;              // slices
@@ -282,7 +322,7 @@ struct EfShape {
     static constexpr int NB = K32 && DP >= 8 && FINE ? 2 : 1;      //                     keys
     static constexpr bool AHEAD = !(K32 && DP == 64) && !FINE;     // a tile pair's operands are read from LDS before they are due
     static constexpr int NREG = (DP == 8 || DP == 16) && !FINE ? (K32 && DP == 16 ? 5 : 6) : 0;   // tiles whose norms stay in registers (16 each)
-    static constexpr bool NTWICE = K32 && DP == 64 && !FINE;       // norms are read for each block: registers that hold them for both spill others
+    static constexpr bool NTWICE = DP == 64 && (K32 || !FULL) && !FINE;   // norms are read for each block: registers that hold them for both spill others
     static constexpr bool AREG = DP <= 8 || (DP == 16 && !K32 && !FINE);   // centroid operands in 32 registers, else read from LDS
 };
 
@@ -296,7 +336,7 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                                                                       int d_k, int m, int d_sub_arg, int blocks_per_bh,
                                                                       int splits, int pairs_per_wg)
 {
-    typedef EfShape<KT, DP, FINE> Sh;
+    typedef EfShape<KT, DP, FULL, FINE> Sh;
     constexpr bool K32 = Sh::K32;
     constexpr int NS = Sh::NS, NL = Sh::NL, NA = Sh::NA, NB = Sh::NB;
     constexpr int kEfWaves = THREADS / kWave;
@@ -341,15 +381,29 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
         const int64_t left = N - n0;
         return Where{(int64_t)b * H + h, n0, kb < total_blocks ? (left < 32 ? (int)left : 32) : 0};
     };
+    const bool whole = FULL || d_sub % 4 == 0;    // pieces of four coordinates: all of one or nothing
+    auto piece = [&](int l) { return DP >= 16 ? 16 * (l / 2) + 8 * g + 4 * (l % 2) : 4 * l; };   // its first coordinate
     auto fetch_keys = [&](int kb, KT(&dst)[NL][4]) -> Where {
         const Where w = locate(kb);
         // (columns without a key read the block's last key; a block that does not exist reads a key of the first slab)
         const KT *block = w.live ? keys + (w.bh * N + w.n0) * d_k + (int64_t)i * d_sub : keys + (int64_t)h * N * d_k + (int64_t)i * d_sub;
         const int c = col < w.live ? col : (w.live ? w.live - 1 : 0);
         const KT *sub = block + (uint32_t)(c * d_k);
+        if (FULL || whole) {
 #pragma unroll
-        for (int l = 0; l < NL; ++l)
-            ef_load4<FULL, KT>(sub, DP >= 16 ? 16 * (l / 2) + 8 * g + 4 * (l % 2) : 4 * l, d_sub, dst[l]);
+            for (int l = 0; l < NL; ++l)
+                ef_load4<FULL, KT>(sub, piece(l), d_sub, dst[l]);
+        } else if constexpr (K32) {
+#pragma unroll
+            for (int l = 0; l < NL; ++l)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    dst[l][e] = piece(l) + e < d_sub ? sub[piece(l) + e] : 0.f;
+        } else {
+#pragma unroll
+            for (int l = 0; l < NL; ++l)
+                ef_load_tail(sub, piece(l), d_sub, dst[l]);
+        }
         return w;
     };
     Where here[2] = {}, ahead[2] = {};
@@ -367,16 +421,26 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
     float cm = 0.f;
     bool bad = false;
     if (owner) {
+        const float *row = cb + tid * d_sub;
+        if constexpr (FULL) {
 #pragma unroll
-        for (int j0 = 0; j0 < DP; j0 += 4) {
-            float v4[4];
-            ef_load4<FULL, float>(cb + tid * d_sub, j0, d_sub, v4);
+            for (int j0 = 0; j0 < DP; j0 += 4) {
+                float v4[4];
+                ef_load4<true, float>(row, j0, d_sub, v4);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[j0 + e] = v4[e];
-                cm = fmaxf(cm, fabsf(v4[e]));
-                bad |= !(fabsf(v4[e]) < INFINITY);
+                for (int e = 0; e < 4; ++e)
+                    v[j0 + e] = v4[e];
             }
+        } else {
+            ef_load_clamped(row, 0, d_sub, v);
+#pragma unroll
+            for (int j = 0; j < DP; ++j)
+                v[j] = j < d_sub ? v[j] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < DP; ++j) {
+            cm = fmaxf(cm, fabsf(v[j]));
+            bad |= !(fabsf(v[j]) < INFINITY);
         }
         const uint64_t any_bad = __ballot(bad);
         cm = wave_max(cm);
@@ -539,6 +603,11 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                 float ks = Sh::SLOTS ? 0.f : (float)DP * 0x1p-28f, kl = 0.f;   // (room for flushed fp16 subnormals)
                 if constexpr (!K32) {
                     _Float16 x[NL * 4];
+                    if (!whole) {
+#pragma unroll
+                        for (int l = 0; l < NL; ++l)
+                            ef_align_tail(raw[blk][l], piece(l), d_sub);
+                    }
                     __builtin_memcpy(x, raw[blk], sizeof(x));
 #pragma unroll
                     for (int l = 0; l < NL * 2; ++l) {

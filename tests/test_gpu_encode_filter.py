@@ -40,6 +40,22 @@ def _inputs(kind, d_sub, M, B, N, dtype):
     return keys.view(B, H, N, M * d_sub).to(getattr(torch, dtype)), cb.contiguous()
 
 
+# every length up to 64 that a head size can have; few pairs per wavefront (two terms of everything) and many, a ragged last block
+@pytest.mark.parametrize("d_sub", [d for d in range(2, 65) if d % 4 == 0 or d % 2 == 0 or d <= 31])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+@pytest.mark.parametrize("N", [797, 30001])
+def test_every_length_matches_the_exact_scan(lk, monkeypatch, N, d_sub, dtype):
+    m = 8 if d_sub % 2 else (4 if d_sub % 4 else 2)
+    keys, cb = _inputs("near ties", d_sub, m, 1, N, dtype)
+    keys[0, 0, 5, 0] = float("nan")
+    keys[0, 1, 6, d_sub - 1] = float("inf")
+    keys[0, 0, N - 1, m * d_sub - 1] = -float("inf")                # the last element of a slab
+    got = lk.lookat_encode_keys(keys, cb).clone()
+    monkeypatch.setenv("LOOKAT_ENCODE_EXACT", "1")
+    ref = lk.lookat_encode_keys(keys, cb)
+    assert torch.equal(got, ref), f"{int((got != ref).sum())} of {ref.numel()} codes differ"
+
+
 # sub-vectors that fill an operand and sub-vectors that are padded; 90001 keys: 256 threads, 3 x 66671 and more: 512
 @pytest.mark.parametrize("d_sub", [3, 4, 7, 8, 12, 16, 24, 32, 48, 64])
 @pytest.mark.parametrize("dtype", ["float16", "float32"])
