@@ -61,6 +61,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "encode_grid.h"
 
 #pragma clang fp contract(off)
 
@@ -921,39 +922,6 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
     }
 }
 
-// Workgroups per (head, subspace) and threads per workgroup.  A compute unit holds one workgroup of 512 threads or two of 256
-// (three with up to four coordinates, which keep no norms in registers).  Two wavefronts saturate a SIMD, so a launch takes
-// about as long as the compute unit with the most pairs of key blocks needs for them, and kSetup more for every workgroup it
-// runs in turn (scale, operands, norms); one wavefront alone on a SIMD needs half as long again for a pair.  The choice with
-// the least is taken; where it comes out the same, the smaller workgroup for a few pairs and else the larger, whose
-// wavefronts share out the pairs as they go.
-struct EfGrid {
-    int64_t splits;
-    int threads;
-    bool fine;       // a pair or two per wavefront
-};
-static EfGrid ef_grid(int64_t units, int64_t pairs, bool small_rows)
-{
-    constexpr int64_t kSetup = 96;     // in 1/32 of a pair's time on a saturated SIMD
-    EfGrid best = {1, 256, false};
-    int64_t best_cost = INT64_MAX;
-    for (int threads = 256; threads <= (small_rows ? 256 : 512); threads *= 2) {
-        const int64_t per_simd = threads / 256, waves = threads / kWave, resident = (small_rows ? 3 : 2) / per_simd;
-        for (int64_t s = 1; s <= 1024; ++s) {
-            const int64_t per_wave = (pairs + s * waves - 1) / (s * waves);
-            const int64_t wgs = (units * s + 255) / 256;         // on the fullest compute unit
-            const int64_t cost = (wgs + resident - 1) / resident * kSetup + (wgs * per_simd == 1 ? 48 : small_rows && wgs == 2 ? 68 : 32 * wgs * per_simd) * per_wave;
-            if (cost < best_cost || (cost == best_cost && threads == 512 && per_wave >= 4)) {
-                best_cost = cost;
-                best = EfGrid{s, threads, threads == 256 && per_wave <= 2};
-            }
-            if (per_wave == 1)
-                break;
-        }
-    }
-    return best;
-}
-
 // Launches the filter encoder if the shape has an instance; returns false otherwise.
 template <typename KT>
 static bool launch_encode_filter_t(const lookat_shape *s, int64_t N, const void *keys, const float *codebooks,
@@ -967,7 +935,7 @@ static bool launch_encode_filter_t(const lookat_shape *s, int64_t N, const void 
     if (d_sub < 2 || d_sub > 64 || total_blocks > 0x3fffffff)
         return false;
     const int64_t pairs = (total_blocks + 1) / 2;
-    const EfGrid chosen = ef_grid((int64_t)s->H * s->m, pairs, d_sub <= 4);
+    const EfGrid chosen = ef_grid((int64_t)s->H * s->m, pairs, ef_operand(d_sub), sizeof(KT) == 4);
     const int64_t splits = chosen.splits;
     const int64_t wgs = ((int64_t)s->H * splits + 7) / 8 * 8 * s->m;
     if (wgs > 0xffffff)   // (a grid of 2^32 threads)
@@ -980,8 +948,8 @@ static bool launch_encode_filter_t(const lookat_shape *s, int64_t N, const void 
                        (int)((pairs + splits - 1) / splits))
 #define LOOKAT_EF_FORM(D, FULL)                                                                                           \
     do {                                                                                                                  \
-        constexpr int kLarge = D > 4 ? 512 : 256;                                                                         \
-        constexpr bool kFine = D > 8 || (D == 8 && sizeof(KT) == 4);                                                      \
+        constexpr int kLarge = ef_has_large(D) ? 512 : 256;                                                               \
+        constexpr bool kFine = ef_has_fine(D, sizeof(KT) == 4);                                                           \
         if (chosen.threads == 512)                                                                                        \
             LOOKAT_EF_LAUNCH(D, FULL, kLarge, false);                                                                     \
         else if (chosen.fine)                                                                                             \

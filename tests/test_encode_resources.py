@@ -60,3 +60,81 @@ def kernels(tmp_path_factory):
 def test_no_instance_spills(kernels):
     """A spilled register's reload in the pair loop waits for the key requests ahead of it."""
     assert not {form: k for form, k in kernels.items() if k["scratch"] or k["spilled"]}
+
+
+SHIM = r"""
+#include "encode_grid.h"
+using namespace lookat;
+extern "C" void choose(long units, long pairs, int dp, int key32, int *out)
+{
+    const EfGrid g = ef_grid(units, pairs, dp, key32);
+    out[0] = g.splits, out[1] = g.threads, out[2] = g.fine;
+}
+extern "C" long cost(long units, long pairs, int dp, int key32, int threads, int fine, long s)
+{
+    const long waves = threads / 64;
+    return EfForm(dp, key32, threads, fine).cost((units * s + 255) / 256, (pairs + s * waves - 1) / (s * waves));
+}
+extern "C" long least(long units, long pairs, int dp, int key32)      // over every split count up to one pair per wavefront
+{
+    long best = 1L << 62;
+    for (int f = ef_has_large(dp) ? 0 : 1; f < (ef_has_fine(dp, key32) ? 3 : 2); ++f)
+        for (long s = 1; s <= 1024; ++s) {
+            const int threads = f ? 256 : 512;
+            const long c = cost(units, pairs, dp, key32, threads, f == 2, s);
+            best = c < best ? c : best;
+            if (s * (threads / 64) >= pairs)
+                break;
+        }
+    return best;
+}
+extern "C" int resident(int dp, int threads, int fine) { return ef_resident(dp, threads, fine); }
+"""
+
+
+@pytest.fixture(scope="module")
+def grid(tmp_path_factory):
+    import ctypes
+    folder = tmp_path_factory.mktemp("grid")
+    (folder / "shim.cpp").write_text(SHIM)
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2601_10155_amd", "csrc")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover", "-shared", "-fPIC", "-I", csrc,
+                    str(folder / "shim.cpp"), "-o", str(folder / "shim.so")], check=True)
+    lib = ctypes.CDLL(str(folder / "shim.so"))
+    for name in ("cost", "least"):
+        getattr(lib, name).restype = ctypes.c_long
+    long, integer = ctypes.c_long, ctypes.c_int
+    lib.choose.argtypes = [long, long, integer, integer, ctypes.POINTER(integer)]
+    lib.cost.argtypes = [long, long, integer, integer, integer, integer, long]
+    lib.least.argtypes = [long, long, integer, integer]
+
+    def choose(units, pairs, dp, key32):
+        out = (ctypes.c_int * 3)()
+        lib.choose(units, pairs, dp, key32, out)
+        return tuple(out)
+    lib.chosen = choose
+    return lib
+
+
+def test_the_choice_knows_how_many_workgroups_a_compute_unit_holds(kernels, grid):
+    """512 registers per SIMD lane, handed out in eights, and 160 KB of LDS."""
+    for (dtype, dp, full, threads, fine), k in kernels.items():
+        on_a_simd = 512 // (-(-k["registers"] // 8) * 8)
+        fits = min(on_a_simd // (threads // 256), 160 * 1024 // k["lds"])
+        assert fits == grid.resident(dp, threads, fine), (dtype, dp, full, threads, fine, k)
+
+
+def test_the_choice_is_the_cheapest_split(grid):
+    """The few split counts that are looked at against all of them; a launch in two terms does not queue behind itself."""
+    worst = 1.0
+    for dp in (4, 8, 16, 32, 64):
+        for key32 in (0, 1):
+            for units in (1, 2, 7, 16, 24, 48, 64, 96, 129, 200, 256, 257, 320, 512, 1000, 1542, 2560, 40000, 2097120):
+                for pairs in (1, 2, 5, 13, 32, 63, 100, 128, 511, 2000, 16384, (1 << 29) - 1):
+                    splits, threads, fine = grid.chosen(units, pairs, dp, key32)
+                    assert 1 <= splits <= 1024 and threads in (256, 512) and (threads == 256 or not fine)
+                    got = grid.cost(units, pairs, dp, key32, threads, fine, splits)
+                    worst = max(worst, got / grid.least(units, pairs, dp, key32))
+                    if fine and dp == 64 and units <= 256:
+                        assert units * splits <= 256, (key32, units, pairs, splits)
+    assert worst <= 1.04
