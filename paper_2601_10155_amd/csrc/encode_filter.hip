@@ -41,7 +41,9 @@
 // for both.  A digit value whose group minimum exceeds the limit holds no candidate; the remaining values of 2q + h, e and t, as bits of
 // a word, give every combination that can be one.  One bit per digit: the key is decided, and the bits are its code.  A NaN anywhere
 // makes the minima NaN (v_minimum3 propagates it).  Two blocks of 32 keys are finished together, one per lane half.
-// An undecided key is noted with its word in LDS; when the pairs are through, eight lanes share a noted key's combinations.
+// An undecided key is noted with its word in LDS; when the pairs are through, eight lanes share a noted key's combinations.  A key that
+// fills a large part of the notes is decided once: with half of the keys zero and a centroid near zero that has a rival (2 codebooks in a
+// hundred), 32 x 12 x 1024 fp32 keys, 4 of 16, took 102 us where every copy was worked off, 51 now, and 42 without such keys.
 //
 // What bounds it: vector issue and power.  A pair of blocks costs 410 to 480 vector instructions, 256 of them the minima; matrix
 // instructions of one wavefront hide behind another's minima, but the chip lowers its clock for them (a loop like this one with
@@ -74,7 +76,7 @@ typedef _Float16 ef_v2h __attribute__((ext_vector_type(2)));
 typedef __fp16 ef_v2fp __attribute__((ext_vector_type(2)));
 
 constexpr int kEfTiles = kCentroids / 32;
-constexpr int kEfList = 512;           // undecided keys a wavefront can note before they are worked off
+constexpr int kEfList = 832;           // undecided keys a wavefront can note before they are worked off (up to 16 coordinates: LDS below 64 KB, one base register)
 constexpr int kEfShared = 48;           // candidates that eight lanes share; for a key with more the whole wavefront takes all centroids
 constexpr int kEfMore = 1 << 16;       // flag beside the number of noted keys: the wavefront has pairs left
 constexpr uint32_t kEfAll = 0xfffffu;  // every value of every digit: 2q + h in bits 0..7, e in 8..11, t in 12..19
@@ -136,20 +138,21 @@ __device__ __forceinline__ void ef_align_tail(T (&x)[4], int j0, int d_sub)
 // end the last ones again, which the callers leave out.  (With a branch around every piece that may not be there the compiler waits for
 // each before the next.  us per call, so / now: 32 heads x 8000 keys, 2 subspaces of 40, fp16 48.4 / 38.4, fp32 66.6 / 54.2; 8 x 16 x 2048,
 // 4 of 48, fp32 116 / 95; 8 of 12 71 / 63; eight rounds of the exact rule over 40 coordinates 27 / 14.)
-template <int N, int M, typename T>
-__device__ __forceinline__ void ef_load_clamped(const T *x_sub, const float *const (&rows)[M], int j0, int d_sub, T (&x)[N], float (&y)[M][N])
+template <int N, int M, typename T, typename R>
+__device__ __forceinline__ void ef_load_clamped(const T *x_sub, const R *const (&rows)[M], int j0, int d_sub, T (&x)[N], R (&y)[M][N])
 {
     if (d_sub % 4 == 0) {
         typedef unsigned int chunk_t __attribute__((ext_vector_type(sizeof(T))));   // 4 elements: 8 or 16 bytes
+        typedef unsigned int row_t __attribute__((ext_vector_type(sizeof(R))));
         chunk_t xv[N / 4];
-        ef_v4f yv[M][N / 4];
+        row_t yv[M][N / 4];
 #pragma unroll
         for (int q = 0; q < N / 4; ++q) {
             const int at = j0 + 4 * q < d_sub ? j0 + 4 * q : d_sub - 4;
             xv[q] = *reinterpret_cast<const chunk_t *>(x_sub + at);
 #pragma unroll
             for (int u = 0; u < M; ++u)
-                yv[u][q] = *reinterpret_cast<const ef_v4f *>(rows[u] + at);
+                yv[u][q] = *reinterpret_cast<const row_t *>(rows[u] + at);
         }
         __builtin_memcpy(x, xv, sizeof(x));
         __builtin_memcpy(y, yv, sizeof(y));
@@ -272,6 +275,42 @@ __device__ __forceinline__ double ef_exact_distance(const KT *key_sub, const flo
     return acc;
 }
 
+// Whether key sub-vectors x[u] hold the bits of `one`.
+template <int DP, bool FULL, int M, typename KT>
+__device__ __forceinline__ void ef_same_key(const KT *one, const KT *const (&x)[M], int d_sub, bool (&same)[M])
+{
+    constexpr int JB = DP < 16 ? DP : 16;
+    typedef unsigned int word_t __attribute__((ext_vector_type(JB * sizeof(KT) / 4)));
+    uint32_t differ[M] = {};
+#pragma unroll 1
+    for (int j0 = 0; j0 < d_sub; j0 += JB) {
+        KT a[JB], b[M][JB];
+        if constexpr (FULL) {
+#pragma unroll
+            for (int q = 0; q < JB; q += 4) {
+                ef_load4<true, KT>(one, j0 + q, d_sub, reinterpret_cast<KT(&)[4]>(a[q]));
+#pragma unroll
+                for (int u = 0; u < M; ++u)
+                    ef_load4<true, KT>(x[u], j0 + q, d_sub, reinterpret_cast<KT(&)[4]>(b[u][q]));
+            }
+        } else {
+            ef_load_clamped(one, x, j0, d_sub, a, b);
+        }
+        word_t wa, wb;
+        __builtin_memcpy(&wa, a, sizeof(a));
+#pragma unroll
+        for (int u = 0; u < M; ++u) {
+            __builtin_memcpy(&wb, b[u], sizeof(a));
+#pragma unroll
+            for (int k = 0; k < (int)(JB * sizeof(KT) / 4); ++k)
+                differ[u] |= wa[k] ^ wb[k];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < M; ++u)
+        same[u] = differ[u] == 0;
+}
+
 // Index of the n-th set bit (n from 0, below the number of set bits) of an eight-bit word.
 __device__ __forceinline__ int ef_nth_bit(uint32_t bits, int n)
 {
@@ -322,7 +361,7 @@ struct EfShape {
     static constexpr int NA = DP >= 16 && FINE ? 2 : 1;            // operands per slice: centroids
     static constexpr int NB = K32 && DP >= 8 && FINE ? 2 : 1;      //                     keys
     static constexpr bool AHEAD = !(K32 && DP == 64) && !FINE;     // a tile pair's operands are read from LDS before they are due
-    static constexpr int NREG = (DP == 8 || DP == 16) && !FINE ? (K32 && DP == 16 ? 5 : 6) : 0;   // tiles whose norms stay in registers (16 each)
+    static constexpr int NREG = (DP == 8 || DP == 16) && !FINE ? (K32 && DP == 16 ? (FULL ? 5 : 4) : 6) : 0;   // tiles whose norms stay in registers (16 each)
     static constexpr bool NTWICE = DP == 64 && (K32 || !FULL) && !FINE;   // norms are read for each block: registers that hold them for both spill others
     static constexpr bool AREG = DP <= 8 || (DP == 16 && !K32 && !FINE);   // centroid operands in 32 registers, else read from LDS
 };
@@ -344,7 +383,7 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
     static_assert(THREADS >= kCentroids, "thread c looks after centroid c while the codebook is set up");
     __shared__ __align__(16) float cn_s[kCentroids];
     __shared__ float red_s[4][kCentroids / kWave];
-    __shared__ int next_s, count_s[kEfWaves];
+    __shared__ int next_s, repeated_s, count_s[kEfWaves];
     __shared__ uint2 list_s[kEfWaves][kEfList];        // undecided keys: (local pair, lane), candidate digits
     __shared__ __align__(16) ef_v8h a_s[kEfTiles * NS * NA * kWave];
 
@@ -846,16 +885,16 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
         __syncthreads();
         // ---- the exact rule for the noted keys: eight lanes share a key's candidates ----
         int until[kEfWaves];      // entries of the lists up to and with the w-th
-        int more = 0;
+        int more = 0, count;
+        auto lengths = [&] {
 #pragma unroll
-        for (int w = 0; w < kEfWaves; ++w) {
-            more |= count_s[w] & kEfMore;
-            until[w] = (w ? until[w - 1] : 0) + (count_s[w] & (kEfMore - 1));
-        }
-        const int count = until[kEfWaves - 1];
-        for (int b0 = wave * 8; b0 < count; b0 += kEfWaves * 8) {
-            const bool exists = b0 + lane / 8 < count;
-            const int at = exists ? b0 + lane / 8 : count - 1;
+            for (int w = 0; w < kEfWaves; ++w) {
+                more |= count_s[w] & kEfMore;
+                until[w] = (w ? until[w - 1] : 0) + (count_s[w] & (kEfMore - 1));
+            }
+            count = until[kEfWaves - 1];
+        };
+        auto noted_at = [&](int at) {      // the at-th entry of all lists
             int list = 0, start = 0;
 #pragma unroll
             for (int w = 0; w < kEfWaves - 1; ++w)
@@ -863,12 +902,87 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                     list = w + 1;
                     start = until[w];
                 }
-            const uint2 entry = list_s[list][at - start];
-            const int l = (int)(entry.x & 63u);
-            const Where where = locate(2 * (first + (int)(entry.x >> 6)) + (l >> 5));
-            const int64_t n = where.n0 + (l & 31);
-            const KT *key_sub = keys + (where.bh * N + n) * d_k + (int64_t)i * d_sub;
-            uint8_t *dst = codes + where.bh * code_stride_bh + n * m + i;
+            return list_s[list][at - start];
+        };
+        auto place = [&](const uint2 &entry, int64_t &n) {
+            const Where where = locate(2 * (first + (int)(entry.x >> 6)) + (int)((entry.x & 63u) >> 5));
+            n = where.n0 + (int)(entry.x & 31u);
+            return where.bh;
+        };
+        auto key_of = [&](const uint2 &entry) {
+            int64_t n;
+            const int64_t bh = place(entry, n);
+            return keys + (bh * N + n) * d_k + (int64_t)i * d_sub;
+        };
+        lengths();
+        // A long list may hold one key many times over (zeros that fill up a batch of prompts, say, where a centroid near them has a rival).
+        // If one of four entries is met 16 times or more among 64 that are spread over the lists, that key is decided once, and every
+        // entry that holds its bits takes its code and leaves the lists; then the next such key.  (One wavefront looks, so that all do the
+        // same.  Up to eight rounds of the exact rule are not worth the look.)
+        for (int passes = 0; count > kEfWaves * 64 && passes < 8; ++passes) {
+            if (wave == 0) {
+                auto spread = [&](int k) { return (int)((uint32_t)k * (uint32_t)count / 64u); };
+                const KT *own = key_of(noted_at(spread(lane)));
+                int most = 15, which = -1;
+#pragma unroll 1
+                for (int k = 13; k < kWave && most < 32; k += 16) {
+                    const KT *few[1] = {key_of(noted_at(spread(k)))};
+                    bool same[1];
+                    ef_same_key<DP, FULL>(own, few, d_sub, same);
+                    const int equal = (int)__popcll(__ballot(same[0]));
+                    which = equal > most ? spread(k) : which;
+                    most = equal > most ? equal : most;
+                }
+                if (which >= 0)
+                    which = which << 8 | ef_exact_code<KT>(key_of(noted_at(which)), cb, d_sub, lane);
+                if (lane == 0)
+                    repeated_s = which;
+            }
+            __syncthreads();
+            const int found = repeated_s;      // (entry, code)
+            if (found < 0)
+                break;
+            const KT *one = key_of(noted_at(found >> 8));
+            __syncthreads();                   // (the lists are read)
+            int kept = 0;
+            noted = count_s[wave] & (kEfMore - 1);
+            for (int k0 = 0; k0 < noted; k0 += 2 * kWave) {
+                uint2 e[2];
+                const KT *x[2];
+                bool same[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int k = k0 + u * kWave + lane;
+                    e[u] = list_s[wave][k < noted ? k : noted - 1];
+                    x[u] = key_of(e[u]);
+                }
+                ef_same_key<DP, FULL>(one, x, d_sub, same);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const bool there = k0 + u * kWave + lane < noted;
+                    if (there && same[u]) {
+                        int64_t n;
+                        const int64_t bh = place(e[u], n);
+                        codes[bh * code_stride_bh + n * m + i] = (uint8_t)found;
+                    }
+                    const uint64_t others = __ballot(there && !same[u]);
+                    if (there && !same[u])
+                        list_s[wave][kept + (int)__popcll(others & ((1ull << lane) - 1ull))] = e[u];
+                    kept += (int)__popcll(others);
+                }
+            }
+            if (lane == 0)
+                count_s[wave] = kept;
+            __syncthreads();
+            lengths();
+        }
+        for (int b0 = wave * 8; b0 < count; b0 += kEfWaves * 8) {
+            const bool exists = b0 + lane / 8 < count;
+            const uint2 entry = noted_at(exists ? b0 + lane / 8 : count - 1);
+            int64_t n;
+            const int64_t bh = place(entry, n);
+            const KT *key_sub = keys + (bh * N + n) * d_k + (int64_t)i * d_sub;
+            uint8_t *dst = codes + bh * code_stride_bh + n * m + i;
             const uint32_t mx = entry.y & 255u, me = entry.y >> 8 & 15u, mt = entry.y >> 12;
             const int nx = __builtin_popcount(mx), ne = __builtin_popcount(me), nt = __builtin_popcount(mt);
             const int all = nx * ne * nt;

@@ -27,6 +27,14 @@ def _inputs(kind, d_sub, M, B, N, dtype):
         keys[:, :, 1::2] = (rows[0] * (0.5 + off) + rows[1] * (0.5 - off))[:, :, 1::2]
     elif kind == "pairs of centroids":   # every key has two equally near ones: the lower index, and none is ever decided
         cb[:, :, 1::2] = cb[:, :, 0::2]
+    elif kind == "repeated keys":   # the same with few values: zeros, -0.0 once, two others, NaN, and one key in eight of its own
+        cb[:, :, 1::2] = cb[:, :, 0::2]
+        few = torch.stack([torch.zeros_like(keys[:, :, 0]), keys[:1, :, 0].expand_as(keys[:, :, 0]), keys[:1, :, 1].expand_as(keys[:, :, 0]),
+                           torch.full_like(keys[:, :, 0], float("nan"))])
+        which = torch.tensor([0, 0, 0, 1, 1, 2, 3], device="cuda")
+        for j in range(7):
+            keys[:, :, j::8] = few[which[j]][:, :, None]
+        keys[:, :, 8:9] = -0.0
     elif kind == "filler":          # no scale serves this codebook: every centroid is a candidate for every key
         cb[:, :, 200:] = 1e30
     elif kind == "magnitudes":      # norms over six orders of magnitude
@@ -60,6 +68,7 @@ def test_every_length_matches_the_exact_scan(lk, monkeypatch, N, d_sub, dtype):
 @pytest.mark.parametrize("d_sub", [3, 4, 7, 8, 12, 16, 24, 32, 48, 64])
 @pytest.mark.parametrize("dtype", ["float16", "float32"])
 @pytest.mark.parametrize("kind,B,N", [("near ties", 1, 90001), ("near ties", 3, 66671), ("pairs of centroids", 1, 300001),
+                                      ("repeated keys", 1, 300001), ("repeated keys", 3, 20011),
                                       ("filler", 1, 300001), ("magnitudes", 1, 200001), ("far keys", 1, 90001),
                                       ("subnormal keys", 1, 200001)])
 def test_large_fills_match_the_exact_scan(lk, monkeypatch, kind, B, N, d_sub, dtype):

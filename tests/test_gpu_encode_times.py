@@ -31,7 +31,7 @@ def best_us(*calls, repeats=12, rounds=10):
 @pytest.mark.parametrize("d_sub", [40, 56])
 @pytest.mark.parametrize("dtype", ["float16", "float32"])
 def test_undecided_keys_of_padded_sub_vectors(lk, d_sub, dtype):
-    """A workgroup whose keys all have two equally near centroids, worked off in eight rounds: 14 to 17 us where a round requests all
+    """A workgroup whose keys all have two equally near centroids, worked off in eight rounds: 14 to 19 us where a round requests all
     pieces of its sub-vectors at once, 27 to 30 where each piece was waited for before the next."""
     H, m, N = 4, 4, 1000
     g = torch.Generator(device="cuda").manual_seed(d_sub)
@@ -41,12 +41,12 @@ def test_undecided_keys_of_padded_sub_vectors(lk, d_sub, dtype):
     plain = cb[torch.arange(H, device="cuda")[:, None, None], torch.arange(m, device="cuda"), pick].reshape(1, H, N, m * d_sub)
     plain = plain.to(getattr(torch, dtype)).contiguous()
     tied = plain.clone()
-    tied[0, 0, :250, :d_sub] = cb[0, 0, 0].to(tied.dtype)
+    tied[0, 0, :250, :d_sub] = (cb[0, 0, 0] + 0.05 * torch.randn((250, d_sub), generator=g, device="cuda")).to(tied.dtype)
     codes = torch.empty((1, H, N, m), dtype=torch.uint8, device="cuda")
     a, b = best_us(lambda: lk.lookat_encode_keys(plain, cb, codes_out=codes), lambda: lk.lookat_encode_keys(tied, cb, codes_out=codes))
     print(f"d_sub {d_sub} {dtype}: {a:.2f} us decided, {b:.2f} us with 250 undecided keys")
     assert not codes[0, 0, :250, 0].any()
-    assert b - a < 22, (a, b)
+    assert b - a < 23.5, (a, b)
 
 
 @pytest.mark.parametrize("d_sub", [10, 14])
@@ -64,3 +64,25 @@ def test_odd_sub_vectors_against_the_next_full_one(lk, d_sub):
     a, b = best_us(*calls)
     print(f"d_sub 16: {a:.2f} us, {d_sub}: {b:.2f} us")
     assert b < 1.55 * a, (a, b)
+
+
+@pytest.mark.parametrize("d_sub", [16, 32])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+@pytest.mark.parametrize("value", [0.0, 0.25])
+def test_a_repeated_key_that_is_never_decided(lk, d_sub, dtype, value):
+    """Half of the keys hold one value, which is equally near to two centroids everywhere: decided once per workgroup, not once per key (1.2
+    to 1.5 times a fill whose keys are all decided; 2.5 to 3 where every one is worked off)."""
+    B, H, m, N = 8, 12, 4, 2048
+    g = torch.Generator(device="cuda").manual_seed(d_sub)
+    cb = 3.0 * torch.randn((H, m, 256, d_sub), generator=g, device="cuda").half().float()
+    cb[:, :, 1] = cb[:, :, 0] = value
+    pick = torch.randint(2, 256, (B, H, N, m), generator=g, device="cuda")
+    plain = cb[torch.arange(H, device="cuda")[:, None, None], torch.arange(m, device="cuda"), pick].reshape(B, H, N, m * d_sub)
+    plain = plain.to(getattr(torch, dtype)).contiguous()
+    same = plain.clone()
+    same[:, :, N // 2:] = value
+    codes = torch.empty((B, H, N, m), dtype=torch.uint8, device="cuda")
+    a, b = best_us(lambda: lk.lookat_encode_keys(plain, cb, codes_out=codes), lambda: lk.lookat_encode_keys(same, cb, codes_out=codes))
+    print(f"d_sub {d_sub} {dtype} {value}: {a:.2f} us decided, {b:.2f} us with one key repeated")
+    assert not codes[:, :, N // 2:].any() and torch.equal(codes[:, :, :N // 2].long(), pick[:, :, :N // 2])
+    assert b < 2 * a, (a, b)
