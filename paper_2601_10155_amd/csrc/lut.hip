@@ -368,9 +368,13 @@ extern "C" int lookat_build_lut(const lookat_shape *shape, int32_t T, const void
     hipStream_t st = static_cast<hipStream_t>(stream);
     // From 256 queries per head on, the build is a dense [B*T x d_sub].[d_sub x 256] contraction
     // per (head, subspace) and runs on the matrix cores; below that the 32-row MFMA tiles would be
-    // mostly padding and the vector kernel is used.
+    // mostly padding and the vector kernel is used.  With 32 and 64 coordinates a tile is a chain of 16 or 32 matrix instructions, and
+    // up to three tables per compute unit the vector kernel ends sooner (us, vector / matrix; m = 1 or 2, d_sub 64: 256 tables 4.0 / 7.6, fp32
+    // queries 8.1; 512 5.8 / 7.7; 768 7.9 / 7.7, 8.1; 900 9.5 / 7.7, 8.2; d_sub 32: 256 3.4 / 4.7, 5.2; 768 4.9 / 4.8, 5.3; 900 5.7 / 4.8, 5.3).
+    // Both kernels add the products in the same order: the tables have the same bits.
+    const int64_t queries = (int64_t)shape->B * T;
     bool done = false;
-    if ((int64_t)shape->B * T >= 256)
+    if (queries >= 256 && (shape->d_k / shape->m < 32 || queries * shape->H * shape->m > 768))
         done = (q_dtype == LOOKAT_F16) ? launch_build_lut_mfma<__half>(shape, T, q, codebooks, lut, st)
                                        : launch_build_lut_mfma<float>(shape, T, q, codebooks, lut, st);
     if (!done) {

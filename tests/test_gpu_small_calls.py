@@ -53,6 +53,36 @@ def test_tables_of_long_sub_vectors(lk, d_k, m, B, T, dtype):
     assert (np.abs(got - ref) <= (d_k // m + 1) * 2.0 ** -24 * size).all()
 
 
+def test_few_tables_of_long_sub_vectors_stay_on_the_vector_kernel(lk):
+    """One head, one subspace of 64: 256 queries take as long as 255 (4 us; 8 on the matrix cores)."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    cb = torch.randn((1, 1, 256, 64), generator=g, device="cuda")
+    q = torch.randn((1, 1, 256, 64), generator=g, device="cuda").half()
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    best = {}
+    for _ in range(12):
+        for T in (255, 256):
+            x, out = q[:, :, :T].contiguous(), torch.empty((1, 1, T, 1, 256), device="cuda")
+            e[0].record()
+            for _ in range(50):
+                lk.lookat_build_lut(x, cb, lut_out=out)
+            e[1].record()
+            torch.cuda.synchronize()
+            best[T] = min(best.get(T, 1e9), e[0].elapsed_time(e[1]))
+    assert best[256] < 1.45 * best[255], best
+
+
+# around 768 tables, from which the matrix cores take over; at 300 queries either side
+@pytest.mark.parametrize("H,T,d_k,m", [(1, 256, 64, 1), (3, 256, 64, 1), (1, 769, 64, 1), (1, 383, 64, 2), (1, 385, 64, 2), (3, 300, 128, 2), (4, 300, 128, 4)])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+def test_tables_have_the_bits_of_smaller_calls(lk, H, T, d_k, m, dtype):
+    g = torch.Generator(device="cuda").manual_seed(T + d_k)
+    cb = torch.randn((H, m, 256, d_k // m), generator=g, device="cuda")
+    q = torch.randn((1, H, T, d_k), generator=g, device="cuda").to(getattr(torch, dtype))
+    pieces = [lk.lookat_build_lut(q[:, :, t:t + 200].contiguous(), cb) for t in range(0, T, 200)]
+    assert torch.equal(lk.lookat_build_lut(q, cb), torch.cat(pieces, 2))
+
+
 @pytest.mark.parametrize("H,d_k,m,Nc", [(33, 64, 16, 4099), (35, 64, 8, 1030), (3, 64, 16, 1024), (3, 64, 16, 1025), (129, 24, 8, 70)])
 def test_learning_with_the_smaller_workgroup(lk, H, d_k, m, Nc):
     """One or two pieces of four coordinates (or single ones) per workgroup, with more workgroups than compute units or few keys."""
