@@ -92,14 +92,18 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const KT *__restric
 // us per call before / now: 4 x 16 (b,h), d_k = 96, m = 8 4.9 / 3.5; 2 x 8, d_k = 128, m = 2, fp32 12.5 / 5.4; 1 x 8, d_k = 160, m = 16 4.7 / 3.7.
 constexpr int kEncFewKeys = 8;
 
-// Flat (b, n) of a head's keys.  (A decode step appends one key per sequence: no 64-bit division on the way to its address.)
+// Flat (b, n) of a head's keys.  (A decode step appends one key per sequence: no division on the way to its address; else a 32-bit
+// one where that does.)
 __device__ __forceinline__ void split_row(int64_t r, int64_t N, int64_t &b, int64_t &n)
 {
     b = r;
     n = 0;
-    if (N != 1) {
+    if (N > 0xffffffffLL || r > 0xffffffffLL) {
         b = r / N;
         n = r % N;
+    } else if (N != 1) {
+        b = (uint32_t)r / (uint32_t)N;
+        n = r - b * N;
     }
 }
 
@@ -162,6 +166,14 @@ __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__rest
     const int64_t r0 = (int64_t)blockIdx.x * KEYS;   // first flat (b, n) of the block
     const int64_t rows = (int64_t)B * N;
 
+    // (the row is requested ahead of the keys: their addresses take a division, and staging them waits for them)
+    float row[DSUB];
+    {
+        const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * DSUB;
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j)
+            row[j] = src[j];
+    }
     for (int e = threadIdx.x; e < KEYS * DSUB; e += kCentroids) {
         const int64_t r = r0 + e / DSUB;
         double v = 0.0;
