@@ -185,12 +185,9 @@ __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__rest
         x_s[e / DSUB][e % DSUB] = v;
     }
     double y[DSUB];
-    {
-        const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * DSUB;
 #pragma unroll
-        for (int j = 0; j < DSUB; ++j)
-            y[j] = (double)src[j];
-    }
+    for (int j = 0; j < DSUB; ++j)
+        y[j] = (double)row[j];
     __syncthreads();
 
     // Distances of centroid c to the block's keys.
