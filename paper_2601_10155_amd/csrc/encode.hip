@@ -207,15 +207,18 @@ __global__ __launch_bounds__(kCentroids) void encode_few_kernel(const KT *__rest
     encode_few_finish<KEYS>(dv, dm, red_d, red_c, codes, code_stride_bh, B, H, N, m, i, h, r0, lane, wave);
 }
 
-// Any sub-vector length: the same, the centroid's coordinates taken sixteen at a time, the next sixteen requested before the
-// last are used.  The keys' sub-vectors sit in dynamic LDS.
-template <typename KT, int KEYS>
-__global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__restrict__ keys,
+// Any sub-vector length: the same.  A row of 16-byte pieces (from a 16-byte aligned codebook) is taken JB coordinates at a time, the next
+// ones requested before the last are used; JB = 0: its elements are read as they are needed (5, 7, 10, 14 ..: 16 single elements
+// ahead measured 5 to 15% slower).  The keys' sub-vectors sit in dynamic LDS.  With many workgroups registers count (one kernel for all took
+// 100): 40 heads x 34 keys, 16 subspaces of 5, 15.1 / 13.2 us, 8 of 12 11.7 / 11.1; rows of 128 want sixteen ahead (16 heads x 2000 keys,
+// 2 of 128, eight ahead / sixteen 248 / 237).
+template <typename KT, int KEYS, int JB>
+__global__ __launch_bounds__(kCentroids, (KEYS == 8 && JB == 0 ? 8 : 4)) void encode_few_any_kernel(const KT *__restrict__ keys,
                                                                     const float *__restrict__ codebooks,
                                                                     uint8_t *__restrict__ codes, int64_t code_stride_bh,
                                                                     int B, int H, int64_t N, int d_k, int m)
 {
-    constexpr int JB = 16;
+    constexpr bool PIECES = JB > 0;
     extern __shared__ __align__(16) double xs[];   // [d_sub][KEYS]
     __shared__ double red_d[KEYS][kCentroids / kWave];
     __shared__ int red_c[KEYS][kCentroids / kWave];
@@ -226,8 +229,7 @@ __global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__
     const int lane = c & (kWave - 1), wave = c / kWave;
     const int64_t rows = (int64_t)B * N;
     const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * d_sub;
-    const bool pieces = d_sub % 4 == 0;             // a row is 16-byte pieces (from a 16-byte aligned codebook)
-    auto fetch = [&](int j0, float (&y)[JB]) {      // coordinates j0 .. j0 + 15 as far as there are any
+    auto fetch = [&](int j0, float (&y)[PIECES ? JB : 1]) {      // coordinates j0 .. j0 + JB - 1 as far as there are any
 #pragma unroll
         for (int q = 0; q < JB; q += 4)
             if (j0 + q < d_sub) {
@@ -239,8 +241,8 @@ __global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__
             }
     };
     for (int64_t r0 = (int64_t)blockIdx.x * KEYS; r0 < rows; r0 += (int64_t)gridDim.x * KEYS) {
-        float y[JB], ahead[JB];
-        if (pieces)
+        [[maybe_unused]] float y[PIECES ? JB : 1], ahead[PIECES ? JB : 1];
+        if constexpr (PIECES)
             fetch(0, y);
         {                                           // 256 / KEYS threads per key
             constexpr int kPer = kCentroids / KEYS;
@@ -265,7 +267,7 @@ __global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__
                 dv[k] = dv[k] + sq;
             }
         };
-        if (pieces) {
+        if constexpr (PIECES) {
             for (int j0 = 0; j0 < d_sub; j0 += JB) {
                 if (j0 + JB < d_sub)
                     fetch(j0 + JB, ahead);
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(kCentroids) void encode_few_any_kernel(const KT *__
                 for (int q = 0; q < JB; ++q)
                     y[q] = ahead[q];
             }
-        } else {                                    // (5, 7, 10, 14 ..: 16 single elements ahead measured 5 to 15% slower)
+        } else {
 #pragma unroll 4
             for (int j = 0; j < d_sub; ++j)
                 add(j, (double)src[j]);
@@ -306,10 +308,19 @@ static void launch_encode_few_any(const lookat_shape *s, int64_t N, const void *
     const int keys_wg = few_keys(rows);
     const int64_t blocks = (rows + keys_wg - 1) / keys_wg;
     const dim3 grid((unsigned)(blocks < 65536 ? blocks : 65536), (unsigned)s->m, (unsigned)s->H);
+    const int d_sub = s->d_k / s->m;
+#define LOOKAT_ENCA_FORM(KEYS, JB)                                                                                        \
+    hipLaunchKernelGGL((encode_few_any_kernel<KT, KEYS, JB>), grid, dim3(kCentroids), (size_t)KEYS * d_sub * sizeof(double), \
+                       st, static_cast<const KT *>(keys), codebooks, codes, code_stride_bh, s->B, s->H, N, s->d_k, s->m)
 #define LOOKAT_ENCA_LAUNCH(KEYS)                                                                                          \
-    hipLaunchKernelGGL((encode_few_any_kernel<KT, KEYS>), grid, dim3(kCentroids),                                         \
-                       (size_t)KEYS * (s->d_k / s->m) * sizeof(double), st, static_cast<const KT *>(keys), codebooks,     \
-                       codes, code_stride_bh, s->B, s->H, N, s->d_k, s->m)
+    do {                                                                                                                  \
+        if (d_sub % 4)                                                                                                    \
+            LOOKAT_ENCA_FORM(KEYS, 0);                                                                                    \
+        else if (d_sub <= 24)                                                                                             \
+            LOOKAT_ENCA_FORM(KEYS, (KEYS == 8 ? 8 : 16));                                                                 \
+        else                                                                                                              \
+            LOOKAT_ENCA_FORM(KEYS, 16);                                                                                   \
+    } while (0)
     if (keys_wg == 1)
         LOOKAT_ENCA_LAUNCH(1);
     else if (keys_wg == 2)
@@ -318,6 +329,7 @@ static void launch_encode_few_any(const lookat_shape *s, int64_t N, const void *
         LOOKAT_ENCA_LAUNCH(4);
     else
         LOOKAT_ENCA_LAUNCH(8);
+#undef LOOKAT_ENCA_FORM
 #undef LOOKAT_ENCA_LAUNCH
 }
 

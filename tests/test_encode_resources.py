@@ -25,36 +25,48 @@ def code_objects(path):
                 yield data[found.start() + offset:found.start() + offset + size]
 
 
-def encoder_kernels(path, tmp_path):
-    """(type, DP, FULL, THREADS, FINE) -> registers, LDS bytes and scratch bytes of every encode_filter_kernel instance."""
+def notes(path, kernel, tmp_path):
+    """The template arguments of every instance of a kernel -> its registers, LDS bytes and scratch bytes."""
     out = {}
     for n, blob in enumerate(code_objects(path)):
-        if b"encode_filter_kernel" not in blob:
+        if kernel.encode() not in blob:
             continue
         file = tmp_path / f"{n}.co"
         file.write_bytes(blob)
         text = subprocess.run([READELF, "--notes", str(file)], check=True, stdout=subprocess.PIPE, text=True).stdout
         for part in text.split(".agpr_count:")[1:]:
-            name = re.search(r"\.name:\s+(\S*encode_filter_kernel\S*)", part)
+            name = re.search(rf"\.name:\s+\S*\d{kernel}I(f|6__half)(\S*?)EEv", part)
             if not name:
                 continue
-            form = re.search(r"kernelI(f|6__half)Li(\d+)ELb(\d)ELi(\d+)ELb(\d)E", name.group(1)).groups()
+            form = tuple(int(v) if kind == "i" else v == "1" for kind, v in re.findall(r"L([ib])(\d+)E", name.group(2) + "E"))
             value = lambda key: int(re.search(rf"\.{key}:\s+(\d+)", part).group(1))
-            out[("float32" if form[0] == "f" else "float16", int(form[1]), form[2] == "1", int(form[3]), form[4] == "1")] = {
+            out[("float32" if name.group(1) == "f" else "float16", *form)] = {
                 "registers": value("vgpr_count"), "lds": value("group_segment_fixed_size"), "scratch": value("private_segment_fixed_size"),
                 "spilled": value("vgpr_spill_count")}
     return out
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
+def lib_path():
     if not os.path.exists(READELF):
         pytest.skip("llvm-readelf not found")
     import paper_2601_10155_amd as pkg
     pkg.load_library()
-    found = encoder_kernels(pkg.lib_path(), tmp_path_factory.mktemp("co"))
+    return pkg.lib_path()
+
+
+@pytest.fixture(scope="module")
+def kernels(lib_path, tmp_path_factory):
+    """(type, DP, FULL, THREADS, FINE) -> ..."""
+    found = notes(lib_path, "encode_filter_kernel", tmp_path_factory.mktemp("co"))
     assert len(found) > 40
     return found
+
+
+def test_appends_of_odd_sub_vectors_fill_a_compute_unit(lib_path, tmp_path):
+    """Eight wavefronts per SIMD take at most 64 registers each."""
+    found = {form: k for form, k in notes(lib_path, "encode_few_any_kernel", tmp_path).items() if form[1:] == (8, 0)}
+    assert len(found) == 2 and all(k["registers"] <= 64 and not k["spilled"] for k in found.values()), found
 
 
 def test_no_instance_spills(kernels):

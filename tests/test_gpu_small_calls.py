@@ -24,7 +24,7 @@ def dev(a):
 # sub-vectors of 5, 12, 16, 20, 32, 36, 64, 80 and 136 coordinates; 1 to 9 keys of a head, one each or several of a sequence
 @pytest.mark.parametrize("d_k,m", [(80, 16), (96, 8), (64, 4), (160, 8), (64, 2), (144, 4), (128, 2), (160, 2), (136, 1)])
 @pytest.mark.parametrize("dtype", ["float16", "float32"])
-@pytest.mark.parametrize("B,N", [(1, 1), (2, 1), (4, 1), (5, 1), (3, 3)])
+@pytest.mark.parametrize("B,N", [(1, 1), (2, 1), (4, 1), (5, 1), (3, 3), (9, 4)])
 def test_few_keys_and_queries(lk, d_k, m, dtype, B, N):
     rng = np.random.default_rng(d_k + m + B)
     cb = rng.standard_normal((3, m, 256, d_k // m)).astype(np.float32)
