@@ -26,7 +26,7 @@ namespace lookat {
 // four single floats in flight and every thread taking d_sub chains in turn; 113 us with 1024 threads, 16-byte pieces
 // and eight in flight; 86 us with the subspaces of a head on one die and chunks of 4096 keys (2048: 93, 8192: 93, 16384: 103;
 // 12 or 16 pieces in flight: no change; the lists alone: 29).
-//   LDS: first[257] | run[16][256] | list [kKmChunk] uint16
+//   LDS: first[257] | run[16][256] (512 threads: [8][256]) | list [kKmChunk] uint16
 //   grid = (8 heads x m x groups of a sub-vector's pieces, ceil(H / 8)), 512 or 1024 threads; consecutive workgroups go to the
 //   eight dies in turn
 constexpr int kKmPieces = 4;                         // 1024 threads, one (centroid, piece) each

@@ -1,5 +1,5 @@
-"""Cache fills large enough for every form of the ranking encoder (two sizes of workgroup, one or two fp16 terms per value, notes of
-undecided keys that fill up and are worked off in between) against the exact scan of all centroids, code for code."""
+"""Cache fills for every form of the ranking encoder (two sizes of workgroup, one or two fp16 terms per value, notes of undecided keys that
+fill up and are worked off in between) against the exact scan of all centroids, code for code."""
 import pytest
 import torch
 
@@ -15,7 +15,7 @@ def lk():
     return pkg
 
 
-def _inputs(kind, d_sub, M, B, N, dtype):
+def _inputs(kind, d_sub, M, B, N, dtype, H=H):
     g = torch.Generator(device="cuda").manual_seed(d_sub + N)
     cb = torch.randn((H, M, 256, d_sub), generator=g, device="cuda")
     keys = torch.randn((B, H, N, M, d_sub), generator=g, device="cuda")
@@ -64,7 +64,8 @@ def test_every_length_matches_the_exact_scan(lk, monkeypatch, N, d_sub, dtype):
     assert torch.equal(got, ref), f"{int((got != ref).sum())} of {ref.numel()} codes differ"
 
 
-# sub-vectors that fill an operand and sub-vectors that are padded; 90001 keys: 256 threads, 3 x 66671 and more: 512
+# sub-vectors that fill an operand and sub-vectors that are padded: 512 threads, 256 with up to four coordinates (3 x 20011 keys of 12 to 32: 256
+# in two terms).  Ten pairs of key blocks per wavefront: 640 notes where none is decided.
 @pytest.mark.parametrize("d_sub", [3, 4, 7, 8, 12, 16, 24, 32, 48, 64])
 @pytest.mark.parametrize("dtype", ["float16", "float32"])
 @pytest.mark.parametrize("kind,B,N", [("near ties", 1, 90001), ("near ties", 3, 66671), ("pairs of centroids", 1, 300001),
@@ -78,3 +79,26 @@ def test_large_fills_match_the_exact_scan(lk, monkeypatch, kind, B, N, d_sub, dt
     monkeypatch.setenv("LOOKAT_ENCODE_EXACT", "1")
     ref = lk.lookat_encode_keys(keys, cb)
     assert torch.equal(got, ref), f"{int((got != ref).sum())} of {ref.numel()} codes differ"
+
+
+def _compare(lk, monkeypatch, keys, cb):
+    got = lk.lookat_encode_keys(keys, cb).clone()
+    monkeypatch.setenv("LOOKAT_ENCODE_EXACT", "1")
+    ref = lk.lookat_encode_keys(keys, cb)
+    assert torch.equal(got, ref), f"{int((got != ref).sum())} of {ref.numel()} codes differ"
+
+
+# 17 to 33 pairs per wavefront where none, or few different keys, are decided: more than the 832 notes hold
+@pytest.mark.parametrize("d_sub,m,heads,N", [(3, 8, 2, 200003), (4, 16, 2, 200003), (16, 16, 32, 4155), (32, 8, 64, 5180), (64, 4, 128, 5690)])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+@pytest.mark.parametrize("kind", ["pairs of centroids", "repeated keys"])
+def test_notes_of_small_workgroups_fill_up(lk, monkeypatch, kind, d_sub, m, heads, N, dtype):
+    _compare(lk, monkeypatch, *_inputs(kind, d_sub, m, 1, N, dtype, heads))
+
+
+# 5 to 8 coordinates: 256 threads, one term; fp32 keys also in two terms (129 (head, subspace) pairs, 17 pairs of key blocks)
+@pytest.mark.parametrize("d_sub,m,heads,N", [(7, 8, 48, 1500), (8, 8, 40, 700), (8, 1, 129, 1080), (6, 4, 33, 1080)])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+@pytest.mark.parametrize("kind", ["near ties", "repeated keys"])
+def test_forms_of_short_sub_vectors(lk, monkeypatch, kind, d_sub, m, heads, N, dtype):
+    _compare(lk, monkeypatch, *_inputs(kind, d_sub, m, 1, N, dtype, heads))

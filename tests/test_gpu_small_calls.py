@@ -83,9 +83,11 @@ def test_tables_have_the_bits_of_smaller_calls(lk, H, T, d_k, m, dtype):
     assert torch.equal(lk.lookat_build_lut(q, cb), torch.cat(pieces, 2))
 
 
-@pytest.mark.parametrize("H,d_k,m,Nc", [(33, 64, 16, 4099), (35, 64, 8, 1030), (3, 64, 16, 1024), (3, 64, 16, 1025), (129, 24, 8, 70)])
+@pytest.mark.parametrize("H,d_k,m,Nc", [(33, 64, 16, 4099), (35, 64, 8, 1030), (3, 64, 16, 1024), (3, 64, 16, 1025), (129, 24, 8, 70),
+                                         (129, 16, 8, 4099), (3, 24, 8, 1000)])
 def test_learning_with_the_smaller_workgroup(lk, H, d_k, m, Nc):
-    """One or two pieces of four coordinates (or single ones) per workgroup, with more workgroups than compute units or few keys."""
+    """One or two pieces of four coordinates (single ones in the last two) per workgroup, with more workgroups than compute units or few
+    keys; (129, 24, 8, 70) has three pieces per workgroup, and 1024 threads."""
     rng = np.random.default_rng(H + Nc)
     cb = rng.standard_normal((H, m, 256, d_k // m)).astype(np.float32)
     calib = rng.standard_normal((H, Nc, d_k)).astype(np.float32)
