@@ -1049,7 +1049,7 @@ static bool launch_encode_filter_t(const lookat_shape *s, int64_t N, const void 
     if (d_sub < 2 || d_sub > 64 || total_blocks > 0x3fffffff)
         return false;
     const int64_t pairs = (total_blocks + 1) / 2;
-    const EfGrid chosen = ef_grid((int64_t)s->H * s->m, pairs, ef_operand(d_sub), sizeof(KT) == 4);
+    const EfGrid chosen = ef_grid(s->H, s->m, pairs, ef_operand(d_sub), sizeof(KT) == 4);
     const int64_t splits = chosen.splits;
     const int64_t wgs = ((int64_t)s->H * splits + 7) / 8 * 8 * s->m;
     if (wgs > 0xffffff)   // (a grid of 2^32 threads)

@@ -77,23 +77,23 @@ def test_no_instance_spills(kernels):
 SHIM = r"""
 #include "encode_grid.h"
 using namespace lookat;
-extern "C" void choose(long units, long pairs, int dp, int key32, int *out)
+extern "C" void choose(int heads, int m, long pairs, int dp, int key32, int *out)
 {
-    const EfGrid g = ef_grid(units, pairs, dp, key32);
+    const EfGrid g = ef_grid(heads, m, pairs, dp, key32);
     out[0] = g.splits, out[1] = g.threads, out[2] = g.fine;
 }
-extern "C" long cost(long units, long pairs, int dp, int key32, int threads, int fine, long s)
+extern "C" long cost(int heads, int m, long pairs, int dp, int key32, int threads, int fine, long s)
 {
-    const long waves = threads / 64;
-    return EfForm(dp, key32, threads, fine).cost((units * s + 255) / 256, (pairs + s * waves - 1) / (s * waves));
+    const long on_a_cu = ((heads * s + 7) / 8 * m + 31) / 32;      // the grid deals heads x splits to eight dies of 32 compute units
+    return EfForm(dp, key32, threads, fine).cost(on_a_cu, ((pairs + s - 1) / s + 3) / 4);
 }
-extern "C" long least(long units, long pairs, int dp, int key32)      // over every split count up to one pair per wavefront
+extern "C" long least(int heads, int m, long pairs, int dp, int key32)      // over every split count up to one pair per wavefront
 {
     long best = 1L << 62;
     for (int f = ef_has_large(dp) ? 0 : 1; f < (ef_has_fine(dp, key32) ? 3 : 2); ++f)
         for (long s = 1; s <= 1024; ++s) {
             const int threads = f ? 256 : 512;
-            const long c = cost(units, pairs, dp, key32, threads, f == 2, s);
+            const long c = cost(heads, m, pairs, dp, key32, threads, f == 2, s);
             best = c < best ? c : best;
             if (s * (threads / 64) >= pairs)
                 break;
@@ -116,13 +116,13 @@ def grid(tmp_path_factory):
     for name in ("cost", "least"):
         getattr(lib, name).restype = ctypes.c_long
     long, integer = ctypes.c_long, ctypes.c_int
-    lib.choose.argtypes = [long, long, integer, integer, ctypes.POINTER(integer)]
-    lib.cost.argtypes = [long, long, integer, integer, integer, integer, long]
-    lib.least.argtypes = [long, long, integer, integer]
+    lib.choose.argtypes = [integer, integer, long, integer, integer, ctypes.POINTER(integer)]
+    lib.cost.argtypes = [integer, integer, long, integer, integer, integer, integer, long]
+    lib.least.argtypes = [integer, integer, long, integer, integer]
 
-    def choose(units, pairs, dp, key32):
+    def choose(heads, m, pairs, dp, key32):
         out = (ctypes.c_int * 3)()
-        lib.choose(units, pairs, dp, key32, out)
+        lib.choose(heads, m, pairs, dp, key32, out)
         return tuple(out)
     lib.chosen = choose
     return lib
@@ -141,12 +141,13 @@ def test_the_choice_is_the_cheapest_split(grid):
     worst = 1.0
     for dp in (4, 8, 16, 32, 64):
         for key32 in (0, 1):
-            for units in (1, 2, 7, 16, 24, 48, 64, 96, 129, 200, 256, 257, 320, 512, 1000, 1542, 2560, 40000, 2097120):
+            for heads, m in ((1, 1), (2, 1), (1, 7), (2, 5), (2, 8), (12, 2), (25, 1), (12, 4), (25, 5), (32, 2), (40, 4), (12, 16), (25, 16),
+                             (32, 8), (40, 10), (32, 16), (40, 32), (129, 1), (1000, 3), (65535, 32)):
                 for pairs in (1, 2, 5, 13, 32, 63, 100, 128, 511, 2000, 16384, (1 << 29) - 1):
-                    splits, threads, fine = grid.chosen(units, pairs, dp, key32)
+                    splits, threads, fine = grid.chosen(heads, m, pairs, dp, key32)
                     assert 1 <= splits <= 1024 and threads in (256, 512) and (threads == 256 or not fine)
-                    got = grid.cost(units, pairs, dp, key32, threads, fine, splits)
-                    worst = max(worst, got / grid.least(units, pairs, dp, key32))
-                    if fine and dp == 64 and units <= 256:
-                        assert units * splits <= 256, (key32, units, pairs, splits)
+                    got = grid.cost(heads, m, pairs, dp, key32, threads, fine, splits)
+                    worst = max(worst, got / grid.least(heads, m, pairs, dp, key32))
+                    if fine and dp == 64 and -(-heads // 8) * m <= 32:
+                        assert -(-heads * splits // 8) * m <= 32, (key32, heads, m, pairs, splits)
     assert worst <= 1.04
