@@ -157,32 +157,23 @@ __device__ __forceinline__ void ef_load_clamped(const T *x_sub, const R *const (
         __builtin_memcpy(x, xv, sizeof(x));
         __builtin_memcpy(y, yv, sizeof(y));
     } else {
+        constexpr int kUsed = N == 4 ? 3 : N;      // (lengths of up to four that are not four)
 #pragma unroll
-        for (int e = 0; e < N; ++e) {
+        for (int e = 0; e < kUsed; ++e) {
             const int at = j0 + e < d_sub ? j0 + e : d_sub - 1;
             x[e] = x_sub[at];
 #pragma unroll
             for (int u = 0; u < M; ++u)
                 y[u][e] = rows[u][at];
         }
+        if constexpr (kUsed < N) {
+            x[kUsed] = x[0];
+#pragma unroll
+            for (int u = 0; u < M; ++u)
+                y[u][kUsed] = y[u][0];
+        }
     }
 }
-template <int N>
-__device__ __forceinline__ void ef_load_clamped(const float *row, int j0, int d_sub, float (&y)[N])
-{
-    if (d_sub % 4 == 0) {
-        ef_v4f yv[N / 4];
-#pragma unroll
-        for (int q = 0; q < N / 4; ++q)
-            yv[q] = *reinterpret_cast<const ef_v4f *>(row + (j0 + 4 * q < d_sub ? j0 + 4 * q : d_sub - 4));
-        __builtin_memcpy(y, yv, sizeof(y));
-    } else {
-#pragma unroll
-        for (int e = 0; e < N; ++e)
-            y[e] = row[j0 + e < d_sub ? j0 + e : d_sub - 1];
-    }
-}
-
 // The exact rule for one key sub-vector (uniform over the wavefront): lane l takes the centroids l, l + 64,
 // l + 128, l + 192, one chain per centroid, coordinates ascending; then the smallest distance with the lowest index
 // over the wavefront.  Operands are re-read from memory (the matrix fragments are scaled and split).
@@ -471,11 +462,18 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                 for (int e = 0; e < 4; ++e)
                     v[j0 + e] = v4[e];
             }
-        } else {
-            ef_load_clamped(row, 0, d_sub, v);
+        } else if (whole) {
+            ef_v4f piece4[DP / 4];
+#pragma unroll
+            for (int q = 0; q < DP / 4; ++q)
+                piece4[q] = *reinterpret_cast<const ef_v4f *>(row + (4 * q < d_sub ? 4 * q : d_sub - 4));
 #pragma unroll
             for (int j = 0; j < DP; ++j)
-                v[j] = j < d_sub ? v[j] : 0.f;
+                v[j] = j < d_sub ? piece4[j / 4][j % 4] : 0.f;
+        } else {
+#pragma unroll
+            for (int j = 0; j < DP; ++j)
+                v[j] = j < d_sub ? row[j] : 0.f;
         }
 #pragma unroll
         for (int j = 0; j < DP; ++j) {
@@ -922,19 +920,20 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
         for (int passes = 0; count > kEfWaves * 64 && passes < 8; ++passes) {
             if (wave == 0) {
                 auto spread = [&](int k) { return (int)((uint32_t)k * (uint32_t)count / 64u); };
-                const KT *own = key_of(noted_at(spread(lane)));
+                const uint2 own = noted_at(spread(lane));
                 int most = 15, which = -1;
 #pragma unroll 1
-                for (int k = 13; k < kWave && most < 32; k += 16) {
-                    const KT *few[1] = {key_of(noted_at(spread(k)))};
-                    bool same[1];
-                    ef_same_key<DP, FULL>(own, few, d_sub, same);
-                    const int equal = (int)__popcll(__ballot(same[0]));
+                for (int k = 13; k < kWave; k += 16) {      // (equal keys have equal candidates)
+                    const int equal = (int)__popcll(__ballot(own.y == noted_at(spread(k)).y));
                     which = equal > most ? spread(k) : which;
                     most = equal > most ? equal : most;
                 }
-                if (which >= 0)
-                    which = which << 8 | ef_exact_code<KT>(key_of(noted_at(which)), cb, d_sub, lane);
+                if (which >= 0) {
+                    const KT *one = key_of(noted_at(which)), *some[1] = {key_of(own)};
+                    bool same[1];
+                    ef_same_key<DP, FULL>(one, some, d_sub, same);
+                    which = __popcll(__ballot(same[0])) >= 16 ? which << 8 | ef_exact_code<KT>(one, cb, d_sub, lane) : -1;
+                }
                 if (lane == 0)
                     repeated_s = which;
             }
