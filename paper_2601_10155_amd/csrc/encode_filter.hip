@@ -20,7 +20,7 @@
 //   * sub-vectors of up to 8 have room for two terms of a centroid, -2 s_c C = hi + lo, |error| <= 2^-22 |2 s_c C|, beside
 //     one term of the key;
 //   * sub-vectors of up to 4 have room for both terms of both, and for the norm;
-//   * launches of a pair of key blocks or two per wavefront (FINE) take both terms of everything, in more instructions: there
+//   * launches of few pairs of key blocks per wavefront (FINE) take both terms of everything, in more instructions: there
 //     the undecided keys' round trip to memory would be a fifth of the launch.
 //
 // Error bound.  Let delta be a bound on |k - k'| + max_c |C[c] - C'[c]| (exact differences, squared and summed in fp32, with
@@ -45,18 +45,19 @@
 // fills a large part of the notes is decided once: with half of the keys zero and a centroid near zero that has a rival (2 codebooks in a
 // hundred), 32 x 12 x 1024 fp32 keys, 4 of 16, took 102 us where every copy was worked off, 51 now, and 42 without such keys.
 //
-// What bounds it: vector issue and power.  A pair of blocks costs 410 to 480 vector instructions, 256 of them the minima; matrix
-// instructions of one wavefront hide behind another's minima, but the chip lowers its clock for them (a loop like this one with
-// the three instructions per tile that two terms of both need runs at 1.5 GHz, with one at 1.85 GHz, and takes 823 and 514 ns per block and
-// SIMD), and reads of operands and norms from LDS count as well (66 ns of 514 for the norms).  Hence one term, norms (and operands, where they
-// fit) in registers, two wavefronts per SIMD, both blocks sharing what is still read; a spilled register in the loop costs far
-// more than it saves, since its reload waits for the key requests ahead of it.  Wavefronts take their pairs from a shared counter: the
-// SIMD favours its oldest wavefront, and with fixed shares the last one ran alone for a third of the time.
+// What bounds it: vector issue and power.  A pair of blocks costs 410 to 480 vector instructions, 256 of them a candidate's minima and 48
+// those that form the digits; matrix instructions of one wavefront hide behind another's minima, but the chip lowers its clock for them (a
+// loop like this one with four wavefronts per SIMD and operands and norms from LDS or registers as they fit takes 823 ns per block and
+// SIMD at 1.48 GHz with the three instructions per tile that two terms of both need, 514 at 1.80 with one), and reads of norms from LDS
+// count as well (with two wavefronts 478 ns, 421 from registers).  Hence one term, norms (and operands, where they fit) in registers, two
+// wavefronts per SIMD, both blocks sharing what is still read; a spilled register in the loop costs far more than it saves, since its reload
+// waits for the key requests ahead of it (no instance spills).  Wavefronts take their pairs from a shared counter: the SIMD favours its oldest
+// wavefront, and with fixed shares the last one ran alone for a third of the time.
 //   Measured (us per call, this kernel / the one with two terms of everything, norms and operands from LDS, 256 centroids exactly for
-// every undecided key): 4 x 32 heads x 2048 fp16 keys, 16 subspaces of 8: 80 / 85; 32 x 12 heads x 1024 fp32 keys, 4 of 16: 44 / 62;
-// 32 heads x 16384 fp32 keys, 8 of 16: 95 / 135; 8 x 16 x 2048, d_k = 128: fp16 8 of 16 45 / 59, 4 of 32 35 / 54, 2 of 64 33 / 55;
-// fp32 16 of 8 81 / 110, 4 of 32 41 / 72, 2 of 64 43 / 80; fp16, d_k = 64, 16 of 4 74 / 78.  Small ones: 24 (b,h) x 100 keys, fp16
-// 8 of 16: 6.9 / 7.2 (with one term 8.5).
+// every undecided key): 4 x 32 heads x 2048 fp16 keys, 16 subspaces of 8: 75 / 85; 32 x 12 heads x 1024 fp32 keys, 4 of 16: 42 / 62;
+// 32 heads x 16384 fp32 keys, 8 of 16: 95 / 135; 8 x 16 x 2048, d_k = 128: fp16 8 of 16 45 / 59, 4 of 32 35 / 54, 2 of 64 33 / 57;
+// fp32 4 of 32 41 / 72, 2 of 64 43 / 80; 8 x 16 x 2048 keys, 8 of 6, 12 and 28 coordinates: fp16 46 / 66, 53 / 61, 70 / 102, fp32 60 / 83,
+// 57 / 77, 81 / 141.  Small ones: 24 (b,h) x 100 keys, fp16 8 of 16: 6.9 / 7.2 (with one term 8.5).
 //
 // This translation unit must be compiled with -ffp-contract=off (the exact rule).
 #include <cstdlib>
