@@ -77,7 +77,9 @@ typedef _Float16 ef_v2h __attribute__((ext_vector_type(2)));
 typedef __fp16 ef_v2fp __attribute__((ext_vector_type(2)));
 
 constexpr int kEfTiles = kCentroids / 32;
-constexpr int kEfList = 832;           // undecided keys a wavefront can note before they are worked off (up to 16 coordinates: LDS below 64 KB, one base register)
+// Undecided keys a wavefront can note before they are worked off.  (832: up to 16 coordinates the LDS stays below 64 KB and one base
+// register reaches all of it; with 1024 the fp32 form of 16 spilled.)
+constexpr int kEfList = 832;
 constexpr int kEfShared = 48;           // candidates that eight lanes share; for a key with more the whole wavefront takes all centroids
 constexpr int kEfMore = 1 << 16;       // flag beside the number of noted keys: the wavefront has pairs left
 constexpr uint32_t kEfAll = 0xfffffu;  // every value of every digit: 2q + h in bits 0..7, e in 8..11, t in 12..19

@@ -19,11 +19,11 @@ constexpr int ef_resident(int dp, int threads, bool fine)
 
 // What a launch takes on the fullest compute unit, in 1/32 of the time of a pair of key blocks on a SIMD that two wavefronts share (about 1.05
 // us with 8 coordinates, 1.85 with 64 fp16 ones): with n workgroups at once start[n] (scale, operands, norms, the round of undecided keys) and
-// pair[n] for a pair on each SIMD.  A workgroup of 512 threads sets up once for two wavefronts per SIMD; two of 256 measured 5 to 15% slower at
-// the same work, but their later rounds start while others still run, where 512 threads wait for their slowest.  One wavefront alone on a SIMD needs half as long again for a pair.  Two
-// terms of everything save the undecided keys' round and cost more matrix instructions.
-// Fitted to 780 fills of 1 to 3000 pairs per (head, subspace), every form and up to 20 split counts timed: the choice is 0.9% from the best on
-// average (4% with a choice that knew neither the dies nor that one workgroup of the fine form fills a compute unit).
+// pair[n] for a pair on each SIMD.  A workgroup of 512 threads sets up once for two wavefronts per SIMD; two of 256 measured 5 to 15% slower
+// at the same work, but their later rounds start while others still run, where 512 threads wait for their slowest.  One wavefront alone on a
+// SIMD needs half as long again for a pair.  Two terms of everything save the undecided keys' round and cost more matrix instructions.
+// Fitted to 780 fills of 1 to 3000 pairs per (head, subspace), every form and up to 20 split counts timed: the choice is 0.9% from the best
+// on average (4% with a choice that knew neither the dies nor that one workgroup of the fine form fills a compute unit).
 struct EfForm {
     int threads;
     bool fine;
