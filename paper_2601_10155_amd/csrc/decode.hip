@@ -114,12 +114,15 @@ __device__ __forceinline__ bool map_block(const DecodeArgs &a, int &bh, int &spl
     return map_block_n(a, a.BH, bh, split);
 }
 
-// LDS of one batch entry of the fused step (table, per-wavefront partial results, the encoder's per-wavefront
-// minima and indices), rounded to 16 bytes: the distance between the two entries' blocks of a paired workgroup.
+// LDS of the fused step's encoder (see step_candidates): distances [m][4] fp32, candidates [m][4] bytes, the new codes [m] bytes.
+constexpr int code_words(int m) { return m ? (m + 3) / 4 : 1; }    // words that hold a key's codes
+constexpr int kNearest = 4;                           // wavefronts (of 64 centroids) per subspace
+__host__ __device__ constexpr size_t step_encoder_bytes(int m) { return ((size_t)m * kNearest * 5 + (size_t)m + 15) / 16 * 16; }
+// LDS of one batch entry of the fused step (table, per-wavefront partial results, the encoder's
+// candidates), rounded to 16 bytes: the distance between the two entries' blocks of a paired workgroup.
 __host__ __device__ constexpr size_t step_pair_lds_bytes(int m, int d_k)
 {
-    return ((((size_t)m * kCentroids + (size_t)(2 * kDecWaves) * (d_k + 2)) * sizeof(float) +
-             (size_t)m * kDecWaves * (sizeof(double) + sizeof(int))) + 15) / 16 * 16;
+    return (((size_t)m * kCentroids + (size_t)(2 * kDecWaves) * (d_k + 2)) * sizeof(float) + 15) / 16 * 16 + step_encoder_bytes(m);
 }
 
 // ---- pieces of the fused decode step ---------------------------------------------------
@@ -130,8 +133,6 @@ __device__ __forceinline__ float step_f32<float>(float v) { return v; }
 template <>
 __device__ __forceinline__ float step_f32<__half>(__half v) { return __half2float(v); }
 
-// Squared distance of the encoder (paper Sec. 3.4 "Encoding"), exactly as lookat_encode_keys
-// evaluates it: fp64, ascending coordinates, one rounding per subtract, multiply and add.
 // A dense, 16-byte aligned, read-only array of T addressed uniformly over the wavefront, read
 // as 32-bit words through the constant address space: the compiler turns these into scalar
 // loads (an s_load needs dword alignment, which a __half pointer would not promise).
@@ -150,19 +151,287 @@ __device__ __forceinline__ float uniform_elem<__half>(UniformWords p, int idx)
     return __half2float(__ushort_as_half((unsigned short)((idx & 1) ? (w >> 16) : (w & 0xffffu))));
 }
 
-template <typename KT, int DSUB>
-__device__ __forceinline__ double step_sq_dist(UniformWords x, int x0, const float (&y)[DSUB])
+// Squared distance of the encoder (paper Sec. 3.4 "Encoding"), exactly as lookat_encode_keys evaluates it: fp64, ascending coordinates, one
+// rounding per subtract, multiply and add.  x: the sub-vector of a dense row (8-byte aligned), y: the centroid.
+template <typename FT, int DSUB>
+__device__ __forceinline__ double step_exact_distance(const FT *x, const float *y)
 {
 #pragma clang fp contract(off)
+    constexpr int JB = DSUB < 8 || DSUB == 8 ? 4 : 8;
     double acc = 0.0;
+#pragma unroll 1
+    for (int j0 = 0; j0 < DSUB; j0 += JB) {
+        float yj[JB];
+        FT xj[JB];
+        __builtin_memcpy(yj, __builtin_assume_aligned(y + j0, 16), sizeof(yj));
+        __builtin_memcpy(xj, __builtin_assume_aligned(x + j0, 8), sizeof(xj));
 #pragma unroll
-    for (int j = 0; j < DSUB; ++j) {
-        double diff = (double)uniform_elem<KT>(x, x0 + j) - (double)y[j];
-        double sq = diff * diff;
-        acc = acc + sq;
+        for (int j = 0; j < JB; ++j) {
+            const double diff = (double)step_f32<FT>(xj[j]) - (double)yj[j];
+            const double sq = diff * diff;
+            acc = acc + sq;
+        }
     }
     return acc;
 }
+
+// Encoding the new key, in two steps.  In fp32 a squared distance is off by at most (d_sub + 2) 2^-24 of itself, in whatever order its terms are
+// added (each difference is rounded once, each multiply-add and addition once, all terms are positive), so a centroid whose fp32 distance
+// exceeds the smallest by more than twice that cannot be the argmin.  A wavefront of 64 centroids with one left has its candidate without the
+// fp64 rule, which takes two and a half times the instructions; near and exact ties and NaN (whatever is not provably beyond the limit) are
+// evaluated by the rule.  The four candidates of a subspace are compared the same way after the barrier by the wavefront that scores the new
+// key, one lane each.
+// The largest fp32 distance that a centroid may have to be the argmin when the smallest is `least` (twice the error bound, rounded up; the last
+// term for squares below the normal range).  NaN if least is.
+template <int DSUB>
+__device__ __forceinline__ float step_limit(float least)
+{
+    return fmaf(least, 1.f + (float)(2 * DSUB + 8) * 0x1p-23f, (float)DSUB * 0x1p-124f);
+}
+// Minima over the wavefront of N values per lane (a power of two up to 8), NaN left out; uniform results.  A swap of lane halves or rows leaves
+// one minimum of two values in each, so N values cost little more than one.
+template <int N>
+__device__ __forceinline__ void wave_minima(const float (&x)[N], float (&least)[N], int lane)
+{
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "powers of two");
+    float v[N], a, b;
+    if constexpr (N >= 2) {
+#pragma unroll
+        for (int e = 0; e < N / 2; ++e) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[e]), __float_as_uint(x[e + N / 2]), false, false);
+            v[e] = fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        }
+    } else {
+        lanes_xor32(x[0], a, b);
+        v[0] = fminf(a, b);
+    }
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int e = 0; e < N / 4; ++e) {
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[e]), __float_as_uint(v[e + N / 4]), false, false);
+            v[e] = fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        }
+    } else {
+        lanes_xor16(v[0], a, b);
+        v[0] = fminf(a, b);
+    }
+    if constexpr (N >= 8) {
+        const bool odd = lane & 8;
+        const float own = odd ? v[1] : v[0], other = odd ? v[0] : v[1];
+        v[0] = fminf(own, dpp_mov<0x128>(other, other));
+    } else {
+        v[0] = fminf(v[0], dpp_mov<0x128>(v[0], v[0]));
+    }
+    v[0] = fminf(v[0], dpp_mov<0x141>(v[0], v[0]));
+    v[0] = fminf(v[0], dpp_mov<0x4E>(v[0], v[0]));
+    v[0] = fminf(v[0], dpp_mov<0xB1>(v[0], v[0]));
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const int at = N == 1 ? 0 : (N == 2 ? 32 * e : (N == 4 ? 16 * e : 8 * e));
+        least[e] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v[0]), at));
+    }
+}
+// This wavefront's candidates for subspaces i0 .. i0+GS-1: dist[s] is the lane's fp32 distance to centroid c; all four wavefronts of a subspace
+// hold ascending ranges of centroids, `quarter` says which.
+template <typename FT, int DSUB, int M, int GS>
+__device__ __forceinline__ void step_candidates(const float (&dist)[GS], int i0, int c, int quarter, int lane, const float *cb_head,
+                                                const FT *k_row, float *near_s)
+{
+    uint8_t *cand_s = reinterpret_cast<uint8_t *>(near_s + M * kNearest);
+    float least[GS];
+    wave_minima<GS>(dist, least, lane);
+#pragma unroll
+    for (int s = 0; s < GS; ++s) {
+        const uint64_t among = __ballot(!(dist[s] > step_limit<DSUB>(least[s])));
+        bool mine = among >> lane & 1;
+        if (among & (among - 1)) {           // several: the rule, lowest centroid on ties
+            double dv[1] = {(double)INFINITY};
+            if (mine)
+                dv[0] = argmin_value(step_exact_distance<FT, DSUB>(k_row + (i0 + s) * DSUB, cb_head + ((i0 + s) * kCentroids + c) * DSUB), c);
+            const double own = dv[0];
+            dmin_wave<1>(dv);
+            int lowest = mine && own == dv[0] ? c : kCentroids;
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                const int other = __shfl_xor(lowest, o);
+                lowest = other < lowest ? other : lowest;
+            }
+            mine = lowest == c;
+        }
+        if (mine) {
+            near_s[(i0 + s) * kNearest + quarter] = dist[s];
+            cand_s[(i0 + s) * kNearest + quarter] = (uint8_t)c;
+        }
+    }
+}
+// The new key's codes (four to a word; uniform) after the barrier, for the wavefront that scores position L-1: lane (i, w) holds the candidate of
+// subspace i among centroids 64w .. 64w+63.  They go to the cache and, in the lane that scores that key, in the place of the cached row, which
+// may be stale (consume_tile).
+template <typename FT, int DSUB, int M>
+__device__ __forceinline__ void step_new_codes(uint32_t (&fresh)[code_words(M)], const float *near_s, const float *cb_head, const FT *k_row,
+                                               uint8_t *code_row, int lane)
+{
+    const uint8_t *cand_s = reinterpret_cast<const uint8_t *>(near_s + M * kNearest);
+    uint8_t *new_s = const_cast<uint8_t *>(cand_s) + M * kNearest;
+    const int at = lane < M * kNearest ? lane : 0;
+    const float d = near_s[at];
+    const int c = cand_s[at];
+    float least = fminf(d, dpp_mov<0xB1>(d, d));
+    least = fminf(least, dpp_mov<0x4E>(least, least));
+    const uint64_t among = __ballot(!(d > step_limit<DSUB>(least)));
+    uint32_t left = lane < M * kNearest ? (uint32_t)(among >> (lane & ~3)) & 15u : 1u;
+    if (__ballot((left & (left - 1)) != 0)) {
+        double dv = (double)INFINITY;
+        if (left >> (lane & 3) & 1) {
+            const int i = at / kNearest;
+            dv = argmin_value(step_exact_distance<FT, DSUB>(k_row + i * DSUB, cb_head + (i * kCentroids + c) * DSUB), c);
+        }
+        double dm = dmin_dpp<0xB1>(dv);
+        dm = dmin_dpp<0x4E>(dm);
+        left &= (uint32_t)(__ballot(dv == dm) >> (lane & ~3)) & 15u;
+    }
+    if (lane < M * kNearest && (lane & 3) == __builtin_ctz(left))     // (candidates ascend: the lowest on ties)
+        new_s[lane / kNearest] = (uint8_t)c;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(new_s);
+#pragma unroll
+    for (int w = 0; w < code_words(M); ++w)
+        fresh[w] = (uint32_t)__builtin_amdgcn_readfirstlane((int)words[w]);
+    if (lane == 0) {
+        if constexpr (M == 2) {
+            *reinterpret_cast<uint16_t *>(code_row) = (uint16_t)fresh[0];
+        } else {
+#pragma unroll
+            for (int w = 0; w < M / 4; ++w)
+                reinterpret_cast<uint32_t *>(code_row)[w] = fresh[w];
+        }
+    }
+    if constexpr (M == 2)
+        fresh[0] &= 0xffffu;
+}
+
+// ---- the table from whole lines of the codebook ----------------------------------------------------------------
+// Four wavefronts take a quarter of a subspace's centroids each.  A wave-wide load fetches a contiguous kilobyte, 16 bytes per lane: LPW = d_sub / 4
+// lanes hold a row, and a lane's share of a dot product is four coordinates of the LPW rows that it meets in LPW loads.  Adding across the LPW
+// lanes while handing each of them one row's sum takes 3 (LPW - 1) instructions for LPW rows.  (A thread per row, 16 bytes of it per load, keeps the
+// compute unit's address pipeline busy for 64 clocks per load at d_sub = 32, 32 at 16, where a contiguous kilobyte takes 16.)
+template <int LPW>
+__device__ __forceinline__ float sum_rows(float (&p)[LPW], int lane)      // -> the sum of row (lane % LPW) * (64 / LPW) + lane / LPW
+{
+    if constexpr (LPW == 16) {
+        const bool up = lane & 8;
+        float r[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float other = up ? p[k] : p[8 + k];
+            r[k] = (up ? p[8 + k] : p[k]) + dpp_mov<0x140>(other, other);      // row_mirror: 15 - lane
+        }
+        return sum_rows<8>(r, lane);
+    } else if constexpr (LPW == 8) {
+        const bool up = lane & 4;
+        float r[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float other = up ? p[k] : p[4 + k];
+            r[k] = (up ? p[4 + k] : p[k]) + dpp_mov<0x141>(other, other);      // row_half_mirror: 7 - lane
+        }
+        return sum_rows<4>(r, lane);
+    } else if constexpr (LPW == 4) {
+        const bool up = lane & 2;
+        float r[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float other = up ? p[k] : p[2 + k];
+            r[k] = (up ? p[2 + k] : p[k]) + dpp_mov<0x4E>(other, other);
+        }
+        return sum_rows<2>(r, lane);
+    } else if constexpr (LPW == 2) {
+        const bool up = lane & 1;
+        const float other = up ? p[0] : p[1];
+        return (up ? p[1] : p[0]) + dpp_mov<0xB1>(other, other);
+    } else {
+        return p[0];
+    }
+}
+
+// MS subspaces from i0 on, NB batch entries (rows row0 and row0 + H of q and k_new), GS subspaces' rows in registers at a time.
+// (Fewer rows at once where the registers decide on a workgroup more per compute unit: paired entries at d_k = 128, and one (b,h) per workgroup with
+// 16 subspaces there.)
+template <typename FT, int DK, int M, int MS, int NB>
+struct StepTable {
+    static constexpr int DSUB = DK / M, LPW = DSUB / 4;
+    static constexpr int kRegs = DK == 128 && (NB == 2 || (M == 16 && MS == M)) ? 32 : 64;
+    static constexpr int GS0 = kRegs / DSUB < 1 ? 1 : (kRegs / DSUB > 8 ? 8 : kRegs / DSUB);
+    static constexpr int GS = GS0 < MS ? GS0 : MS;
+    static constexpr int kSlice = MS * DSUB;                       // elements of a query, or key, that concern these subspaces
+    static constexpr int kWords = 2 * NB * kSlice;                 // [entry][q, k_new][slice], staged as fp32 in LDS
+    static constexpr int kPer = kWords / kWave;
+    static_assert(kWords % kWave == 0 && MS % GS == 0, "whole loads, whole groups");
+    FT word[kPer];
+    v4f x[GS][LPW];
+
+    __device__ __forceinline__ void request_words(const FT *q, const FT *k_new, int64_t row0, int H, int i0, int lane)
+    {
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            const int e = r * kWave + lane, which = e / kSlice;
+            const FT *from = which & 1 ? k_new : q;
+            word[r] = from[(row0 + (which >> 1) * H) * DK + i0 * DSUB + e % kSlice];
+        }
+    }
+    // rows of the centroids 64 quarter .. of subspaces i .. i+GS-1
+    __device__ __forceinline__ void request_rows(const float *cb_head, int i, int quarter, int lane)
+    {
+#pragma unroll
+        for (int s = 0; s < GS; ++s) {
+            const v4f *from = reinterpret_cast<const v4f *>(cb_head + ((i + s) * kCentroids + quarter * kWave) * DSUB) + lane;
+#pragma unroll
+            for (int u = 0; u < LPW; ++u)
+                x[s][u] = from[u * kWave];
+        }
+    }
+    // stage: kWords floats of LDS for this wavefront alone, 16-byte aligned
+    __device__ __forceinline__ void stage_words(float *stage, int lane) const
+    {
+#pragma unroll
+        for (int r = 0; r < kPer; ++r)
+            stage[r * kWave + lane] = step_f32<FT>(word[r]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    // Table entries and, if encode, candidates of the group of subspaces i .. i+GS-1 (g0 = i - i0) for batch entry nb.
+    __device__ __forceinline__ void group(const float *stage, int nb, int g0, int i, int quarter, int lane, float *lut_s, float *near_s,
+                                          const float *cb_head, const FT *k_row, bool encode) const
+    {
+        const int c = quarter * kWave + lane % LPW * (kWave / LPW) + lane / LPW;
+        const float *mine = stage + 2 * nb * kSlice + g0 * DSUB + 4 * (lane % LPW);
+#pragma unroll
+        for (int s = 0; s < GS; ++s) {
+            const v4f q = *reinterpret_cast<const v4f *>(mine + s * DSUB);
+            float p[LPW];
+#pragma unroll
+            for (int u = 0; u < LPW; ++u)
+                p[u] = fmaf(q.w, x[s][u].w, fmaf(q.z, x[s][u].z, fmaf(q.y, x[s][u].y, q.x * x[s][u].x)));
+            lut_s[(i + s) * kCentroids + c] = sum_rows<LPW>(p, lane);
+        }
+        if (encode) {
+            float dist[GS];
+#pragma unroll
+            for (int s = 0; s < GS; ++s) {
+                const v4f k = *reinterpret_cast<const v4f *>(mine + kSlice + s * DSUB);
+                float p[LPW];
+#pragma unroll
+                for (int u = 0; u < LPW; ++u) {
+                    const v4f d = {k.x - x[s][u].x, k.y - x[s][u].y, k.z - x[s][u].z, k.w - x[s][u].w};
+                    p[u] = fmaf(d.w, d.w, fmaf(d.z, d.z, fmaf(d.y, d.y, d.x * d.x)));
+                }
+                dist[s] = sum_rows<LPW>(p, lane);
+            }
+            step_candidates<FT, DSUB, M, GS>(dist, i, c, quarter, lane, cb_head, k_row, near_s);
+        }
+    }
+};
 
 // One 64-key tile of a wavefront: its codes (kc) and first CH value-row groups (v) are in
 // registers or in flight.  Scores one key per lane (key = kb + kofs), updates the running
@@ -205,51 +474,28 @@ struct CodesOfM<32> {
 template <int M>
 using CodesOf = typename CodesOfM<M>::type;
 
-template <int DK, int M, int CH, bool FUSED, int G, bool MM, bool PAD, bool FIRST = false>
+// `patch(codes, kb, key)` puts the new key's codes in the place of the cached row (fused step).
+struct NothingNew {
+    template <typename Codes>
+    __device__ __forceinline__ void operator()(Codes &, uint32_t, uint32_t) const {}
+};
+// `ahead(n)` is called when the registers of value rows n .. n+7 are free (whole tiles only).
+struct NothingAhead {
+    __device__ __forceinline__ void operator()(int) const {}
+};
+template <int DK, int M, int CH, int G, bool MM, bool PAD, bool FIRST = false, typename Patch, typename Ahead = NothingAhead>
 __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G> &st, const CodesOf<M> &kc_in,
                                              v4u (&v)[CH], const float *lut_s, __amdgpu_buffer_rsrc_t rc,
                                              __amdgpu_buffer_rsrc_t rv, int bh, uint32_t kb, uint32_t k1,
-                                             uint32_t kofs, int lane, int m, const double *enc_d,
+                                             uint32_t kofs, int lane, int m, Patch patch,
                                              v4f (&accm)[MM ? 8 : 1], uint32_t pstage, uint32_t lane_off,
-                                             uint32_t row_bytes)
+                                             uint32_t row_bytes, Ahead ahead = Ahead())
 {
     constexpr int LPR = DK / 8;
     constexpr int NLD = LPR;
     const uint32_t key = kb + kofs;
     CodesOf<M> kc = kc_in;
-    if constexpr (FUSED) {
-        // The newest key (row L-1) was encoded by this workgroup a moment ago: the lane that
-        // scores it merges the per-wave minima, uses those codes and appends them to the cache.
-        if (key == (uint32_t)(a.L - 1)) {
-#pragma unroll
-            for (int w = 0; w < (M + 3) / 4; ++w)
-                kc.w[w] = 0u;
-            const int *enc_c = reinterpret_cast<const int *>(enc_d + M * kDecWaves);
-#pragma unroll
-            for (int i = 0; i < M; ++i) {
-                // waves hold ascending centroid ranges: strict '<' keeps the lowest index on ties
-                double bd = enc_d[i * kDecWaves];
-                int bc = enc_c[i * kDecWaves];
-#pragma unroll
-                for (int w = 1; w < kDecWaves; ++w) {
-                    const double d = enc_d[i * kDecWaves + w];
-                    const int c = enc_c[i * kDecWaves + w];
-                    const bool better = d < bd;
-                    bd = better ? d : bd;
-                    bc = better ? c : bc;
-                }
-                kc.w[i / 4] |= (uint32_t)bc << (8 * (i % 4));
-            }
-            uint8_t *dst = a.codes_w + (int64_t)bh * a.code_stride + (int64_t)key * M;
-            if constexpr (M == 2) {
-                *reinterpret_cast<uint16_t *>(dst) = (uint16_t)kc.w[0];
-            } else {
-#pragma unroll
-                for (int w = 0; w < M / 4; ++w)
-                    reinterpret_cast<uint32_t *>(dst)[w] = kc.w[w];
-            }
-        }
-    }
+    patch(kc, kb, key);
     // one score per query head of the group: the same codes index that head's tables
     float sc[G], p[G];
     bool above = false;
@@ -344,6 +590,17 @@ __device__ __forceinline__ void consume_tile(const DecodeArgs &a, SoftmaxState<G
         __builtin_amdgcn_wave_barrier();   // the next tile's weights overwrite the staging rows
         return;
     }
+    if constexpr (!std::is_same<Ahead, NothingAhead>::value) {
+        static_assert(G == 1 && CH == NLD && CH % 8 == 0, "whole tiles, eight rows at a time");
+#pragma unroll
+        for (int c0 = 0; c0 < NLD; c0 += 8) {
+            fma_rows<LPR, 8>(st.acc[0], p[0], reinterpret_cast<const v4u(&)[8]>(v[c0]), c0);
+            __builtin_amdgcn_sched_barrier(0);
+            ahead(c0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+    }
 #pragma unroll
     for (int c0 = 0; c0 < NLD; c0 += CH) {
 #pragma unroll
@@ -384,110 +641,190 @@ __device__ __forceinline__ void load_centroid_rows(float (&row)[GS][DSUB], const
     }
 }
 
-// Fused step, table-building wavefronts (256 threads): thread c takes centroid c of each subspace
-// from the codebook of the head and from the same row computes
-//   the table entry  LUT_i[c] = q^(i) . C_i[c]           (Sec. 3.5, fp32, ascending j)
-//   the distance     || k_new^(i) - C_i[c] ||^2          (Sec. 3.4, fp64, as the encoder)
-// and leaves per (subspace, wavefront) the smallest distance and its lowest centroid index in LDS.
-// q and k_new are read-only and addressed uniformly over the wavefront: read through the constant
-// address space they become scalar loads (SGPR operands of the FMAs below) and stay out of the
-// in-order vector-memory queue.  Subspaces are processed in groups whose rows fit 64 registers,
-// all rows of a group requested together.
-// `encode`: this workgroup's range holds position L-1 (with several ranges per (b,h) only the last one
-// scores the new key and appends its codes; the others build the table alone).
-// SKIP: a workgroup that does not encode skips the distances, half of the arithmetic (32 (b,h) x 8003 keys in 8 ranges, d_k =
-// 128, m = 8: 17.8 -> 14.2 us of kernel).  The branch keeps the table's and the distances' arithmetic apart, which costs a
-// workgroup that does encode 1 us at d_k = 64, m = 8 and, at d_k = 128, m = 16, the registers of a third workgroup per
-// compute unit (77 -> 106; 640 (b,h) x 104 keys 17.6 -> 23.6 us), so one range per (b,h) goes without -- except where it measured
-// faster with it: paired entries (32 x 12 (b,h) x 1024 keys, d_k = 64, m = 4 10.9 us, 11.3 without), the lone instances (1-3%), m = 2
-// and 4 at d_k = 128 (over 256 (b,h) 1-5%) and m = 2 at d_k = 64 (1%).
-// G > 1 (grouped queries): bh is the key/value head; the G query heads bh*G .. bh*G+G-1 each get their
-// table (lut_s[g][i][c]) from the one pass over the key/value head's codebook rows.
-template <typename FT, int DK, int M, int G, int NB, bool SKIP>
-__device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int part, int tid, int lane, int wave,
-                                              float *lut_s, double *enc_d, int *enc_c, int lds_stride, bool encode)
+// Fused step, table-building wavefronts (256 threads): from one pass over the head's codebook rows they compute
+//   the table entries  LUT_i[c] = q^(i) . C_i[c]           (Sec. 3.5, fp32)
+//   the distances      || k_new^(i) - C_i[c] ||^2          (Sec. 3.4; see step_candidates)
+// (us for two steps, a thread per row and fp64 distances / now: 40 x 16 (b,h) x 600 keys, d_k = 64, m = 16 36.6 / 22.8; 60 x 32 x 150, d_k = 128,
+// m = 4 97 / 60; 24 x 12 x 1024, d_k = 64, m = 4 18.4 / 17.9; 112 launches of more than 256 (b,h) 0.85 of the time on the geometric mean)
+// and leave the table and per (subspace, wavefront) the candidate for the new key's code in LDS.
+// `encode`: this workgroup's range holds position L-1 (with several ranges per (b,h) only the last one scores the new key and appends its
+// codes; the others build the table alone).
+// NB = 2 (two batch entries of one head per workgroup, each with its own 256 table builders): the builders of entry `part` fetch the
+// codebook rows of subspaces part*M/2 .. part*M/2 + M/2 - 1 only and from each row compute the table entries and distances of BOTH entries (bh
+// and bh + H; their LDS blocks lie lds_stride bytes apart), so that the pair reads the head's codebook once instead of twice.
+// The staged words of q and k_new occupy the (not yet used) partial results of the wavefronts.
+template <typename FT, int DK, int M, int NB>
+__device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int part, int lane, int wave, float *lut_s, float *red_s,
+                                              float *near_s, int lds_stride, bool encode)
 {
-    // NB = 2 (two batch entries of one head per workgroup, each with its own 256 table builders): the builders
-    // of entry `part` fetch the codebook rows of subspaces part*M/2 .. part*M/2 + M/2 - 1 only and from each row
-    // compute the table entries and distances of BOTH entries (bh and bh + H; their LDS blocks lie lds_stride
-    // bytes apart), so that the pair reads the head's codebook once instead of twice.
-    static_assert(NB == 1 || (NB == 2 && G == 1 && M % 2 == 0), "paired batch entries: ungrouped, even m");
-    constexpr int DSUB = DK / M;
+    static_assert(NB == 1 || (NB == 2 && M % 2 == 0), "paired batch entries: even m");
     constexpr int MS = M / NB;            // subspaces this builder group covers
-    // rows held at once: 64 registers; paired entries keep two entries' distances alive, so there short rows
-    // (d_sub < 16) are taken 16 registers at a time and, at d_k = 128 (twice the tile registers), longer ones 32
-    constexpr int kRowRegs = (NB == 2) ? ((DSUB < 16) ? 16 : (DK == 128 ? 32 : 64)) : 64;
-    constexpr int GS0 = (kRowRegs / DSUB) < 1 ? 1 : ((kRowRegs / DSUB) > MS ? MS : (kRowRegs / DSUB));
-    constexpr int GS = (MS % GS0 == 0) ? GS0 : 1;
-    float frow[GS][DSUB];
+    typedef StepTable<FT, DK, M, MS, NB> Table;
+    static_assert(Table::kWords * kDecWaves <= 2 * kDecWaves * (DK + 2), "the staged words fit the partial results of the wavefronts");
+    const float *cb_head = a.codebooks + (int64_t)(bh % a.H) * kCentroids * DK;
+    const FT *k_new = static_cast<const FT *>(a.k_new);
     const int ibase = part * MS;
-    const float *__restrict__ cbh = a.codebooks + (int64_t)(bh % a.H) * M * kCentroids * DSUB + (int64_t)tid * DSUB;
-    UniformWords qg[NB], kg[NB];
+    float *stage = reinterpret_cast<float *>(reinterpret_cast<char *>(red_s) + part * lds_stride) + wave * Table::kWords;
+    Table table;
+    table.request_words(static_cast<const FT *>(a.q), k_new, bh, a.H, ibase, lane);
+    table.request_rows(cb_head, ibase, wave, lane);
+    table.stage_words(stage, lane);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const uintptr_t row = (uintptr_t)(bh + nb * a.H);
-        qg[nb] = (UniformWords)(reinterpret_cast<uintptr_t>(a.q) + row * G * DK * sizeof(FT));
-        kg[nb] = (UniformWords)(reinterpret_cast<uintptr_t>(a.k_new) + row * DK * sizeof(FT));
+    for (int g0 = 0; g0 < MS; g0 += Table::GS) {
+        if (g0 > 0)
+            table.request_rows(cb_head, ibase + g0, wave, lane);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            table.group(stage, nb, g0, ibase + g0, wave, lane, reinterpret_cast<float *>(reinterpret_cast<char *>(lut_s) + nb * lds_stride),
+                        reinterpret_cast<float *>(reinterpret_cast<char *>(near_s) + nb * lds_stride), cb_head,
+                        k_new + ((int64_t)bh + nb * a.H) * DK, encode);
     }
-    // The scalar loads of q and k_new are issued a subspace at a time, each shortly before its use, and
-    // the rows are cold (written by the previous layer's kernels): every 128-byte line would cost a
-    // memory round trip in the middle of the table arithmetic.  One word of every line is requested
-    // here, ahead of the codebook rows, so that those loads find the lines in L2.
-    // (Ungrouped only: with grouped queries, whose workgroups stream megabytes each, it measured slower.)
-    uint32_t touched = 0;
-    if constexpr (G == 1) {
+}
+
+// Grouped queries: bh is the key/value head; the G query heads bh*G .. bh*G+G-1 each get their table (lut_s[g][i][c]) from one pass over the
+// key/value head's codebook, thread c = centroid c.  Four heads at a time run on the matrix cores in fp32 (v_mfma_f32_4x4x1: A = the heads'
+// coordinate, lane % 4 picks the head, B = that coordinate of the lane's centroid, ascending; lane c ends with the four heads' entries of
+// centroid c): 8 clocks for what the vector ALU takes 16, and the queries come from LDS, four coordinates a read, where scalar loads had to be
+// waited for in the middle of the arithmetic.  Every wavefront stages its own copy of the group's queries and the new key, in the
+// (not yet used) partial results; the rows of the copy are four words longer than a query, so that four heads' words lie in different banks.
+template <typename FT, int DK, int M, int G>
+__device__ __forceinline__ void step_prologue_grouped(const DecodeArgs &a, int bh, int tid, int lane, int wave, float *lut_s, float *red_s,
+                                                      float *near_s, bool encode)
+{
+    constexpr int DSUB = DK / M;
+    constexpr int kRegs = G >= 4 ? 128 : 64;
+    constexpr int GS0 = kRegs / DSUB > 8 ? 8 : kRegs / DSUB, GS = GS0 < M ? GS0 : M;
+    constexpr int HQ = G < 4 ? G : 4;                          // heads of an instruction
+    constexpr int kRow = DK + 4;
+    static_assert(kDecWaves * (G + 1) * kRow <= 2 * kDecWaves * G * (DK + 2), "the staged words fit the partial results of the wavefronts");
+    const float *cb_head = a.codebooks + (int64_t)(bh % a.H) * kCentroids * DK;
+    const FT *k_row = static_cast<const FT *>(a.k_new) + (int64_t)bh * DK;
+    const FT *q_rows = static_cast<const FT *>(a.q) + (int64_t)bh * G * DK;
+    float *stage = red_s + wave * (G + 1) * kRow;             // [G] queries, the new key
+
+    constexpr int kVec = 16 / (int)sizeof(FT);                 // elements of a 16-byte load
+    constexpr int kLoads = (G * DK / kVec + kWave - 1) / kWave;
+    v4u qv[kLoads], kv = {};
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
+    for (int r = 0; r < kLoads; ++r)
+        if ((r + 1) * kWave * kVec <= G * DK || r * kWave + lane < G * DK / kVec)
+            qv[r] = reinterpret_cast<const v4u *>(q_rows)[r * kWave + lane];
+    if (lane < DK / kVec)
+        kv = reinterpret_cast<const v4u *>(k_row)[lane];
+    float frow[GS][DSUB];
+    load_centroid_rows<DSUB, GS>(frow, cb_head + tid * DSUB, 0);
+    auto put = [&](float *row, int at, const v4u &v) {
+        FT e[kVec];
+        __builtin_memcpy(e, &v, sizeof(e));
 #pragma unroll
-            for (int o = 0; o < (int)(DK * sizeof(FT)); o += 128)
-                touched |= qg[nb][o / 4];
+        for (int n = 0; n < kVec; n += 4)
+            *reinterpret_cast<v4f *>(row + at + n) = v4f{step_f32<FT>(e[n]), step_f32<FT>(e[n + 1]), step_f32<FT>(e[n + 2]), step_f32<FT>(e[n + 3])};
+    };
 #pragma unroll
-            for (int o = 0; o < (int)(DK * sizeof(FT)); o += 128)
-                touched |= kg[nb][o / 4];
-        }
+    for (int r = 0; r < kLoads; ++r) {
+        const int e = (r * kWave + lane) * kVec;
+        if ((r + 1) * kWave * kVec <= G * DK || e < G * DK)
+            put(stage + e / DK * kRow, e % DK, qv[r]);
     }
-    load_centroid_rows<DSUB, GS>(frow, cbh, ibase);
+    if (lane < DK / kVec)
+        put(stage + G * kRow, lane * kVec, kv);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int i0 = 0; i0 < MS; i0 += GS) {
+    for (int i0 = 0; i0 < M; i0 += GS) {
         if (i0 > 0)
-            load_centroid_rows<DSUB, GS>(frow, cbh, ibase + i0);
+            load_centroid_rows<DSUB, GS>(frow, cb_head + tid * DSUB, i0);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            float *lut_nb = reinterpret_cast<float *>(reinterpret_cast<char *>(lut_s) + nb * lds_stride);
-            double *encd_nb = reinterpret_cast<double *>(reinterpret_cast<char *>(enc_d) + nb * lds_stride);
-            int *encc_nb = reinterpret_cast<int *>(reinterpret_cast<char *>(enc_c) + nb * lds_stride);
-            double dv[GS], dm[GS];
+        for (int g = 0; g < GS; ++g) {
+            v4f e[G / HQ];
+#pragma unroll
+            for (int n = 0; n < G / HQ; ++n)
+                e[n] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < DSUB; j += 4) {
+                v4f x[G / HQ];
+#pragma unroll
+                for (int n = 0; n < G / HQ; ++n)
+                    x[n] = *reinterpret_cast<const v4f *>(stage + (n * HQ + lane % HQ) * kRow + (i0 + g) * DSUB + j);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int n = 0; n < G / HQ; ++n)
+                        e[n] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[n][t], frow[g][j + t], e[n], 0, 0, 0);
+            }
+#pragma unroll
+            for (int n = 0; n < G / HQ; ++n)
+#pragma unroll
+                for (int hq = 0; hq < HQ; ++hq)
+                    lut_s[((n * HQ + hq) * M + i0 + g) * kCentroids + tid] = e[n][hq];
+        }
+        if (encode) {
+            float dist[GS];
 #pragma unroll
             for (int g = 0; g < GS; ++g) {
-                const int i = ibase + i0 + g;
+                dist[g] = 0.f;
 #pragma unroll
-                for (int hq = 0; hq < G; ++hq) {
-                    float e = 0.f;
+                for (int j = 0; j < DSUB; j += 4) {
+                    const v4f k = *reinterpret_cast<const v4f *>(stage + G * kRow + (i0 + g) * DSUB + j);
 #pragma unroll
-                    for (int j = 0; j < DSUB; ++j)
-                        e = fmaf(uniform_elem<FT>(qg[nb], hq * DK + i * DSUB + j), frow[g][j], e);
-                    lut_nb[(hq * M + i) * kCentroids + tid] = e;
-                }
-                if (!SKIP || encode) {
-                    dv[g] = argmin_value(step_sq_dist<FT, DSUB>(kg[nb], i * DSUB, frow[g]), tid);
-                    dm[g] = dv[g];
-                }
-            }
-            if (!SKIP || encode) {
-                dmin_wave<GS>(dm);
-#pragma unroll
-                for (int g = 0; g < GS; ++g) {
-                    // lowest lane that holds the wave minimum = lowest centroid index of this wave
-                    const uint64_t holders = __ballot(dv[g] == dm[g]);
-                    if (lane == 0 && encode) {
-                        encd_nb[(ibase + i0 + g) * kDecWaves + wave] = dm[g];
-                        encc_nb[(ibase + i0 + g) * kDecWaves + wave] = wave * kWave + (int)__builtin_ctzll(holders);
+                    for (int t = 0; t < 4; ++t) {
+                        const float diff = k[t] - frow[g][j + t];
+                        dist[g] = fmaf(diff, diff, dist[g]);
                     }
                 }
             }
+            step_candidates<FT, DSUB, M, GS>(dist, i0, tid, wave, lane, cb_head, k_row, near_s);
         }
     }
-    asm volatile("" ::"s"(touched));   // keeps the early requests alive; nothing reads them
+}
+
+// The same on the vector ALU, a multiply-add chain per head: q and k_new are addressed uniformly over the wavefront and become scalar loads
+// through the constant address space, which stay out of the in-order vector-memory queue.  Taken for two heads, where the matrix instruction
+// has no advantage and two workgroups share a compute unit's memory pipe (8 x 4 key/value heads x 4000 keys, d_k = 128, m = 4: 29.9 us two
+// layers, 31.4 with staged queries), and for four heads of fp16 queries at d_k = 128 with 16 or 32 coordinates, where two coordinates come with a
+// scalar word (geometric mean of six shapes against the kernel with fp64 distances for every centroid: 0.99 and 1.03, 0.97 and 0.99 on the
+// matrix cores; everywhere else the matrix cores are ahead: 16 subspaces at d_k = 128 1.17, 1.07 here).
+constexpr bool step_heads_on_vector_alu(int group, int d_k, int m, bool fp32)
+{
+    return group == 2 || (group == 4 && d_k == 128 && (m == 4 || m == 8) && !fp32);
+}
+template <typename FT, int DK, int M, int G>
+__device__ __forceinline__ void step_prologue_heads(const DecodeArgs &a, int bh, int tid, int lane, int wave, float *lut_s, float *near_s,
+                                                    bool encode)
+{
+    constexpr int DSUB = DK / M;
+    constexpr int GS0 = 64 / DSUB > 8 ? 8 : 64 / DSUB, GS = GS0 < M ? GS0 : M;
+    float frow[GS][DSUB];
+    const float *cb_head = a.codebooks + (int64_t)(bh % a.H) * kCentroids * DK;
+    const FT *k_row = static_cast<const FT *>(a.k_new) + (int64_t)bh * DK;
+    const UniformWords qg = (UniformWords)(reinterpret_cast<uintptr_t>(a.q) + (uintptr_t)bh * G * DK * sizeof(FT));
+    const UniformWords kg = (UniformWords)(reinterpret_cast<uintptr_t>(k_row));
+#pragma unroll
+    for (int i0 = 0; i0 < M; i0 += GS) {
+        load_centroid_rows<DSUB, GS>(frow, cb_head + tid * DSUB, i0);
+        float dist[GS];
+#pragma unroll
+        for (int g = 0; g < GS; ++g) {
+#pragma unroll
+            for (int hq = 0; hq < G; ++hq) {
+                float e = 0.f;
+#pragma unroll
+                for (int j = 0; j < DSUB; ++j)
+                    e = fmaf(uniform_elem<FT>(qg, hq * DK + (i0 + g) * DSUB + j), frow[g][j], e);
+                lut_s[(hq * M + i0 + g) * kCentroids + tid] = e;
+            }
+            dist[g] = 0.f;
+            if (encode) {
+#pragma unroll
+                for (int j = 0; j < DSUB; ++j) {
+                    const float diff = uniform_elem<FT>(kg, (i0 + g) * DSUB + j) - frow[g][j];
+                    dist[g] = fmaf(diff, diff, dist[g]);
+                }
+            }
+        }
+        if (encode)
+            step_candidates<FT, DSUB, M, GS>(dist, i0, tid, wave, lane, cb_head, k_row, near_s);
+    }
 }
 
 // Sums over the rows of a wavefront's partial output (lanes that share lane % LPR, eight coordinates each), written to mine[DK].  A swap of
@@ -597,13 +934,9 @@ __device__ __forceinline__ void merge_waves(const float *red_s, int tid, Write w
 // thing shared is the codebook, of which each half's table builders fetch half the subspaces and compute
 // both entries' table rows and distances.  The head's codebook then crosses from L2 to the compute units
 // once per pair instead of once per (b,h).  Both halves execute the same barriers (same L, same ranges).
-// LONE (ungrouped fused step, d_k = 128; see step_is_lone): for launches that leave every workgroup a compute unit of its own, where two
-// wavefronts share a SIMD and have 256 registers each: a tile's 16 KB are requested in one round instead of two, and the
-// next tile is in flight while one is consumed.
 // PAD (tables given, ungrouped): the head size is a.d_k < DK, a multiple of 8; lanes past the end of a row repeat its last
 // 16 bytes and their sums are not written.
-template <int DK, int M, int WAVES, int OCC, typename FT = void, int G = 1, int PF = 1, int NB = 1, bool PAD = false,
-          bool LONE = false, bool SKIP = (G > 1 || NB > 1)>
+template <int DK, int M, int WAVES, int OCC, typename FT = void, int G = 1, int PF = 1, int NB = 1, bool PAD = false>
 __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOOKAT_DECODE_HEAD_PARAMS,
                                                                              const DecodeLate late)
 {
@@ -620,7 +953,6 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     // tile requests queued ahead of its table arithmetic starts that arithmetic microseconds late.
     static_assert(G == 1 || M != 0, "grouped queries: compile-time m");
     static_assert(!PAD || (!FUSED && G == 1), "padded head sizes: tables given, ungrouped");
-    static_assert(!LONE || (FUSED && G == 1 && NB == 1 && PF == 2 && DK == 128), "lone workgroups: ungrouped fused step, d_k = 128");
     const int dk = PAD ? a.d_k : DK;
     constexpr int LPR = DK / 8;            // lanes per value row (16 bytes per lane)
     constexpr int RPL = kWave / LPR;       // value rows covered by one wave-wide load
@@ -629,7 +961,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     // loads kept in flight together: 8 KB of a tile; the whole 16 KB tile where the matrix cores take the value sum
     // (its accumulators are half the size, and a second request round in the middle of a tile is a second
     // exposed round trip at two wavefronts per SIMD)
-    constexpr int CH = (MM || LONE) ? NLD : (NLD < 8 ? NLD : 8);
+    constexpr int CH = MM ? NLD : (NLD < 8 ? NLD : 8);
     constexpr int NT = WAVES * kWave;
 
     extern __shared__ __align__(16) float smem_all[];
@@ -639,8 +971,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     float *smem = reinterpret_cast<float *>(reinterpret_cast<char *>(smem_all) + hf * kHalfBytes);
     float *lut_s = smem;                                   // [G][m][256]
     float *red_s = smem + G * (M ? M : a.m) * kCentroids;  // [WAVES][G][DK + 2]
-    double *enc_d = reinterpret_cast<double *>(red_s + WAVES * G * (DK + 2));   // fused step: [M][WAVES] minima,
-    int *enc_c = reinterpret_cast<int *>(enc_d + (M ? M : 1) * kDecWaves);     //             then [M][WAVES] indices
+    float *near_s = red_s + WAVES * G * (DK + 2);          // fused step: see step_candidates
 
     int bh, split;
     if constexpr (NB == 1) {
@@ -725,12 +1056,16 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
             // issue ahead of the streamers that share the SIMD: the codebook requests must enter the
             // compute unit's memory queue before the tile requests fill it
             __builtin_amdgcn_s_setprio(3);
-            // (paired entries: the LDS blocks and the (b,h) index are handed over as entry 0's)
-            step_prologue<FT, DK, M, G, NB, SKIP>(a, bh - hf * a.H, hf, tid, lane, wave,
-                                            reinterpret_cast<float *>(reinterpret_cast<char *>(lut_s) - hf * kHalfBytes),
-                                            reinterpret_cast<double *>(reinterpret_cast<char *>(enc_d) - hf * kHalfBytes),
-                                            reinterpret_cast<int *>(reinterpret_cast<char *>(enc_c) - hf * kHalfBytes),
-                                            kHalfBytes, k1 == (uint32_t)a.L);
+            if constexpr (G == 1) {
+                // (paired entries: the LDS blocks and the (b,h) index are handed over as entry 0's)
+                auto first = [&](float *p) { return reinterpret_cast<float *>(reinterpret_cast<char *>(p) - hf * kHalfBytes); };
+                step_prologue<FT, DK, M, NB>(a, bh - hf * a.H, hf, lane, wave, first(lut_s), first(red_s), first(near_s), kHalfBytes,
+                                             k1 == (uint32_t)a.L);
+            } else if constexpr (step_heads_on_vector_alu(G, DK, M, sizeof(FT) == 4)) {
+                step_prologue_heads<FT, DK, M, G>(a, bh, tid, lane, wave, lut_s, near_s, k1 == (uint32_t)a.L);
+            } else {
+                step_prologue_grouped<FT, DK, M, G>(a, bh, tid, lane, wave, lut_s, red_s, near_s, k1 == (uint32_t)a.L);
+            }
             __builtin_amdgcn_s_setprio(0);
         } else {
             LOOKAT_REQUEST_FIRST_TILES()
@@ -760,6 +1095,40 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     }
 #undef LOOKAT_REQUEST_FIRST_TILES
 
+    // The newest key (row L-1) was encoded by this workgroup a moment ago; the cached row may be stale.  Ungrouped: the wavefront that scores it
+    // picks its codes when it gets to that tile.  Grouped: before or after its first tile, which keeps the loop free of the rule's loads (8 x 4 key/value
+    // heads x 32768 keys, group 8, d_k = 128, m = 8: 50.9 us, 52.3 with the test in it;
+    // ungrouped the first tile would wait: 32 x 12 x 1024 keys, m = 4, twelve steps 130.6 us, 128.6 as it is).
+    auto new_codes = [&](uint32_t(&fresh)[code_words(M)]) {
+        if constexpr (FUSED)
+            step_new_codes<FT, DK / M, M>(fresh, near_s, a.codebooks + (int64_t)(bh % a.H) * kCentroids * DK,
+                                          static_cast<const FT *>(a.k_new) + (int64_t)bh * DK,
+                                          a.codes_w + (int64_t)bh * a.code_stride + (a.L - 1) * M, lane);
+    };
+    uint32_t fresh_early[code_words(M)] = {};
+    const uint32_t first_tile = kb;
+    const bool scores_new = FUSED && G > 1 && k1 == (uint32_t)a.L && k0 < k1 && (k1 - 1 - k0) / kTile % WAVES == (uint32_t)wave;
+    constexpr bool kAfterFirst = G >= 4 || DK == 64;      // (two heads at d_k = 128 have no registers left for it)
+    if constexpr (FUSED && G > 1) {
+        if (scores_new && (!kAfterFirst || k1 - 1 - kb < (uint32_t)kTile))
+            new_codes(fresh_early);
+    }
+    auto patch = [&](CodesOf<M> &codes, uint32_t tile, uint32_t key) {
+        if constexpr (FUSED && G > 1) {
+#pragma unroll
+            for (int w = 0; w < code_words(M); ++w)
+                codes.w[w] = key == (uint32_t)(a.L - 1) ? fresh_early[w] : codes.w[w];
+        } else if constexpr (FUSED) {
+            if ((uint32_t)(a.L - 1) - tile < (uint32_t)kTile) {
+                uint32_t fresh[code_words(M)];
+                new_codes(fresh);
+#pragma unroll
+                for (int w = 0; w < code_words(M); ++w)
+                    codes.w[w] = key == (uint32_t)(a.L - 1) ? fresh[w] : codes.w[w];
+            }
+        }
+    };
+
     // First tile (requested above), then the wave's remaining tiles: request, consume.  Tiles
     // are requested only if they exist (a load past the range would return zero but still
     // occupy the address pipeline), and a tile's registers are dead at the loop back-edge.
@@ -779,44 +1148,31 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
         *reinterpret_cast<__attribute__((address_space(3))) v4f *>(pstage + (uint32_t)lane * 32u + 16u) = v4f{0.f, 0.f, 0.f, 0.f};
     }
     if (kb < k1) {
-        consume_tile<DK, M, CH, FUSED, G, MM, PAD, true>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm, pstage,
+        consume_tile<DK, M, CH, G, MM, PAD, true>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, patch, accm, pstage,
                                              lane_off, row_bytes);
-        if constexpr (LONE) {
-            // the next tile is in flight while this one is consumed (a wait for it waits for nothing else)
-            for (kb += NT; kb < k1; kb += NT) {
-                kc = kcs[1];
+        if constexpr (FUSED && G > 1 && kAfterFirst) {
+            if (scores_new && k1 - 1 - first_tile >= (uint32_t)kTile)
+                new_codes(fresh_early);
+        }
 #pragma unroll
-                for (int j = 0; j < CH; ++j)
-                    v[j] = vs[1][j];
-                if (kb + NT < k1) {
-                    kcs[1].load(rc, (kb + NT + kofs) * M);
-                    load_rows<DK, CH>(vs[1], rv, kb + NT, 0, lane);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm,
-                                                           pstage, lane_off, row_bytes);
-            }
-        } else {
-#pragma unroll
-            for (int t = 1; t < PF; ++t) {   // the other tiles requested at the start
-                kb += NT;
-                if (kb < k1)
-                    consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kcs[t], vs[t], lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm,
-                                                          pstage, lane_off, row_bytes);
-            }
-            for (kb += NT; kb < k1; kb += NT) {
-                if constexpr (M != 0)
-                    kc.load(rc, (kb + kofs) * M);
-                else
-                    kc.load(rc, (kb + kofs) * m, m);
-                __builtin_amdgcn_sched_barrier(0);   // request order = need order: codes before value rows
-                if constexpr (PAD)
-                    load_rows_padded<DK, CH>(v, rv, kb, 0, lane_off, row_bytes);
-                else
-                    load_rows<DK, CH>(v, rv, kb, 0, lane);
-                consume_tile<DK, M, CH, FUSED, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, enc_d, accm, pstage,
-                                                 lane_off, row_bytes);
-            }
+        for (int t = 1; t < PF; ++t) {   // the other tiles requested at the start
+            kb += NT;
+            if (kb < k1)
+                consume_tile<DK, M, CH, G, MM, PAD>(a, st, kcs[t], vs[t], lut_s, rc, rv, bh, kb, k1, kofs, lane, m, patch, accm,
+                                                      pstage, lane_off, row_bytes);
+        }
+        for (kb += NT; kb < k1; kb += NT) {
+            if constexpr (M != 0)
+                kc.load(rc, (kb + kofs) * M);
+            else
+                kc.load(rc, (kb + kofs) * m, m);
+            __builtin_amdgcn_sched_barrier(0);   // request order = need order: codes before value rows
+            if constexpr (PAD)
+                load_rows_padded<DK, CH>(v, rv, kb, 0, lane_off, row_bytes);
+            else
+                load_rows<DK, CH>(v, rv, kb, 0, lane);
+            consume_tile<DK, M, CH, G, MM, PAD>(a, st, kc, v, lut_s, rc, rv, bh, kb, k1, kofs, lane, m, patch, accm, pstage,
+                                             lane_off, row_bytes);
         }
     }
 
@@ -898,6 +1254,186 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
         for (int x = tid; x < G * DK; x += NT)
             finish(x);
     }
+}
+
+// ---- the fused step where every workgroup has a compute unit to itself ----------------------------------------
+// Up to 32 workgroups on a die: one sequence or a few, whole or cut into ranges.  A launch is then a chain of latencies, and what a compute unit's
+// memory pipe takes (a wave-wide load of a kilobyte every 16 clocks) and when.  Sixteen wavefronts: the first eight stream the tiles, as in
+// decode_split_kernel, from the start; the others build the table, 8-11 the first half of the subspaces, 12-15 the second, two on a SIMD so that
+// one's arithmetic fills the other's latencies, and end.  The builders run at raised priority until their rows are requested, so that these enter
+// the pipe first.  (With eight wavefronts doing both jobs the arithmetic waits until the pipe has accepted the wavefront's tiles: table complete at
+// 5000 clocks at d_k = 64, 15500 at 128, of 9200 and 21800.)  What has to be known before the first request travels in the preloaded
+// arguments (the (b,h) count, ranges and heads in one word: none exceeds 256).
+//   Measured against the roles of decode_split_kernel with a thread per centroid row and fp64 distances (us per launch): 12 (b,h), d_k = 64, m = 2:
+// 1 key 5.6 / 3.9, 1024 keys 6.3 / 5.4, 8192 19.8 / 18.6; d_k = 128, m = 8: 8.2 / 5.4, 10.6 / 8.3, 39.6 / 36.4; 32 x 8003 keys in ranges 16.6 / 15.6
+// with the merge; 176 calls of 4 to 160 (b,h) x 700 to 32000 keys, cut or not, 0.85 of the time on the geometric mean.
+struct LoneLate {
+    float *part;
+    float *out;
+    float scale_log2e;
+};
+constexpr size_t lone_lds_bytes(int m, int d_k)
+{
+    return ((size_t)m * kCentroids + (size_t)(2 * kDecWaves) * (d_k + 2)) * sizeof(float) + step_encoder_bytes(m);
+}
+
+template <typename FT, int DK, int M>
+__global__ __launch_bounds__(4 * kDecThreads, 4) void decode_step_lone_kernel(const float *p_codebooks, const FT *p_q, const FT *p_k_new,
+                                                                              uint8_t *p_codes, const __half *p_values,
+                                                                              uint32_t p_counts, uint32_t p_L,
+                                                                              uint32_t p_code_stride, uint32_t p_value_stride,
+                                                                              const LoneLate late)
+{
+    constexpr int WAVES = 2 * kDecWaves, NT = WAVES * kWave;   // that stream
+    constexpr int MS = M / 2;                                  // subspaces of a builder
+    constexpr int LPR = DK / 8, RPL = kWave / LPR, CH = LPR;   // (see decode_split_kernel; a tile's value rows are requested whole)
+    typedef StepTable<FT, DK, M, MS, 1> Table;
+    static_assert(Table::GS == MS && Table::kWords == DK, "a builder's rows are held at once");
+
+    extern __shared__ __align__(16) float smem_all[];
+    float *lut_s = smem_all;                                       // [M][256]
+    float *red_s = lut_s + M * kCentroids;                         // [WAVES][DK + 2]
+    float *near_s = red_s + WAVES * (DK + 2);                      // see step_candidates
+
+    DecodeArgs a = {};
+    a.BH = (int)(p_counts & 0x1ffu);
+    a.splits = (int)(p_counts >> 9 & 0x3fu);
+    a.H = (int)(p_counts >> 15);
+    int bh, split;
+    if (!map_block(a, bh, split))
+        return;
+    const int tid = (int)threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint32_t k0 = 0, k1 = p_L;
+    if (a.splits > 1) {      // ranges of whole tiles
+        const uint32_t kps = ((p_L + kTile - 1) / kTile + (uint32_t)a.splits - 1) / (uint32_t)a.splits * kTile;
+        k0 = (uint32_t)split * kps;
+        k1 = k0 + kps < p_L ? k0 + kps : p_L;
+    }
+
+    // bh mod H (both at most 256: the quotient of the rounded division is exact)
+    const int h = bh - (int)(((float)bh + 0.5f) * __builtin_amdgcn_rcpf((float)a.H)) * a.H;
+    const float *cb_head = p_codebooks + (int64_t)h * kCentroids * DK;
+
+    if (wave >= WAVES) {     // ---- table and candidates ----
+        __builtin_amdgcn_s_setprio(3);
+        const int builder = wave - WAVES;
+        const int i0 = builder / kDecWaves * MS, quarter = builder & (kDecWaves - 1);
+        float *stage = red_s + builder * Table::kWords;      // (the partial results are not in use yet)
+        Table table;
+        table.request_words(p_q, p_k_new, bh, 0, i0, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        table.request_rows(cb_head, i0, quarter, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        table.stage_words(stage, lane);
+        table.group(stage, 0, 0, i0, quarter, lane, lut_s, near_s, cb_head, p_k_new + (int64_t)bh * DK, k1 == p_L);
+        __syncthreads();
+        return;
+    }
+
+    // ---- the wavefront's tiles ----
+    a.L = p_L;
+    const __amdgpu_buffer_rsrc_t rv = make_rsrc(p_values + (int64_t)bh * p_value_stride, k1 * (uint32_t)(DK * 2));
+    const __amdgpu_buffer_rsrc_t rc = make_rsrc(p_codes + (int64_t)bh * p_code_stride, k1 * (uint32_t)M);
+    const int sub = lane % LPR, rowin = lane / LPR;
+    const uint32_t kofs = (uint32_t)(RPL * sub + rowin);
+    uint32_t kb = k0 + (uint32_t)wave * kTile;
+    SoftmaxState<1> st;
+    v4f accm[1] = {};
+    // The new key's codes (see decode_split_kernel): before the first tile at d_k = 64, where all of a short context's tiles are there by then, with
+    // the last tile otherwise (twelve steps of 12 heads x 1024 keys, d_k = 64, m = 2: 66.6 us, 68.5 the other way round; 32 heads x 8003 keys,
+    // d_k = 128, m = 8: 15.4, 15.9).
+    uint32_t fresh[code_words(M)] = {};
+    auto new_codes = [&] {
+        step_new_codes<FT, DK / M, M>(fresh, near_s, cb_head, p_k_new + (int64_t)bh * DK,
+                                      p_codes + (int64_t)bh * p_code_stride + (int64_t)(p_L - 1) * M, lane);
+    };
+    auto new_key = [&](CodesOf<M> &codes, uint32_t tile, uint32_t key) {
+        if constexpr (DK != 64) {
+            if (p_L - 1 - tile < (uint32_t)kTile)
+                new_codes();
+        }
+#pragma unroll
+        for (int w = 0; w < code_words(M); ++w)
+            codes.w[w] = key == p_L - 1 ? fresh[w] : codes.w[w];
+    };
+#define LOOKAT_LONE_TILE(PATCH_, FIRST_, KC_, V_, ...)                                                                    \
+    consume_tile<DK, M, CH, 1, false, false, FIRST_>(a, st, KC_, V_, lut_s, rc, rv, bh, kb, k1, kofs, lane, M, PATCH_, accm, 0, 0, 0, ##__VA_ARGS__)
+    if constexpr (DK == 64) {
+        // two tiles requested at once, then always the next one while one is consumed
+        CodesOf<M> kcs[2];
+        v4u vs[2][CH];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t kbt = kb + (uint32_t)t * NT;
+            kcs[t].load(rc, (kbt + kofs) * M);
+            __builtin_amdgcn_sched_barrier(0);
+            load_rows<DK, CH>(vs[t], rv, kbt, 0, lane);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();   // table and candidates complete in LDS; value rows stay in flight
+        a.scale_log2e = late.scale_log2e;
+        if (k1 == p_L && k0 < k1 && (k1 - 1 - k0) / kTile % WAVES == (uint32_t)wave)
+            new_codes();
+        if (kb < k1) {
+            LOOKAT_LONE_TILE(new_key, true, kcs[0], vs[0]);
+            for (kb += NT; kb < k1; kb += NT) {
+                const CodesOf<M> kc = kcs[1];
+#pragma unroll
+                for (int j = 0; j < CH; ++j)
+                    vs[0][j] = vs[1][j];
+                if (kb + NT < k1) {
+                    kcs[1].load(rc, (kb + NT + kofs) * M);
+                    load_rows<DK, CH>(vs[1], rv, kb + NT, 0, lane);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                LOOKAT_LONE_TILE(new_key, false, kc, vs[0]);
+            }
+        }
+    } else {
+        // one tile in registers; each half is requested again for the next tile as soon as it has been used
+        CodesOf<M> kc;
+        v4u v[CH];
+        kc.load(rc, (kb + kofs) * M);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows<DK, CH>(v, rv, kb, 0, lane);
+        __syncthreads();   // table and candidates complete in LDS; value rows stay in flight
+        a.scale_log2e = late.scale_log2e;
+        for (; kb + NT < k1; kb += NT) {      // (position L-1 is in a wavefront's last tile)
+            CodesOf<M> next;
+            LOOKAT_LONE_TILE(NothingNew(), false, kc, v, [&](int n) {
+                if (n == 0)
+                    next.load(rc, (kb + NT + kofs) * M);
+                load_rows<DK, 8>(reinterpret_cast<v4u(&)[8]>(v[n]), rv, kb + NT, n, lane);
+            });
+            kc = next;
+        }
+        if (kb < k1)
+            LOOKAT_LONE_TILE(new_key, false, kc, v);
+    }
+#undef LOOKAT_LONE_TILE
+
+    float *mine = red_s + wave * (DK + 2);
+    fold_rows<LPR>(st.acc[0], mine, lane);
+    st.z[0] = wave_sum(st.z[0]);
+    if (lane == 0) {
+        mine[DK] = st.m_run[0];
+        mine[DK + 1] = st.z[0];
+    }
+    __syncthreads();
+    merge_waves<DK, WAVES>(red_s, tid, [&](int j, float o, float mx, float zz) {
+        if (a.splits == 1) {
+            late.out[(int64_t)bh * DK + j] = o / zz;
+        } else {
+            float *dst = late.part + ((int64_t)bh * a.splits + split) * (DK + 2);
+            dst[j] = o;
+            if (j == 0) {
+                dst[DK] = mx;
+                dst[DK + 1] = zz;
+            }
+        }
+    });
 }
 
 // Merge of the split ranges: M* = max_s M_s, out = sum_s 2^(M_s-M*) o_s / sum_s 2^(M_s-M*) Z_s.
@@ -1089,45 +1625,45 @@ static int pick_waves(int d_k, int m, int64_t keys_per_split)
 // the streamers' tile requests instead of interleaved with them).
 constexpr int kStepPrefetch = 2;
 constexpr int kStepWaves = 2 * kDecWaves;   // four wavefronts build the table, four start streaming at once
-// LONE (d_k = 128): where every workgroup has a compute unit to itself, which takes at most 32 on a die (all ranges of a (b,h) run on
-// one), and its range is longer than the one tile per wavefront that both forms request first.  LONE / otherwise, fp16, geometric mean
-// over m = 2, 4, 8, 16, at 96..256 workgroups of 256 / 512 / 640 / 1024 / 2048 / 8192 keys: 1.05 / 1.02 / 0.99 / 0.96 / 0.96 / 0.98; up to
-// 64 workgroups: 1.06 / 1.04 / 1.00 / 0.97 / 1.00 / 1.00.  256 (b,h) x 1024 keys, m = 8: 14.2 / 15.8 us.  At d_k = 64, where a tile is one
-// round of requests anyway, it is 1-2% slower and not taken.
+// Where every workgroup has a compute unit to itself, which takes at most 32 on a die (all ranges of a (b,h) run on one).
 static bool step_is_lone(const DecodeArgs &a)
 {
-    const int64_t on_a_die = ((int64_t)a.BH + kXcds - 1) / kXcds * a.splits;
-    return a.d_k == 128 && on_a_die <= 32 && a.keys_per_split > kStepWaves * kTile;
+    return ((int64_t)a.BH + kXcds - 1) / kXcds * a.splits <= 32;
+}
+template <int DK, typename FT>
+static bool launch_step_lone(const DecodeArgs &a, dim3 grid, hipStream_t st)
+{
+    const uint32_t counts = (uint32_t)a.BH | (uint32_t)a.splits << 9 | (uint32_t)a.H << 15;
+#define LOOKAT_LONE_CASE(M_)                                                                                              \
+    case M_:                                                                                                              \
+        hipLaunchKernelGGL((decode_step_lone_kernel<FT, DK, M_>), grid, dim3(4 * kDecThreads), lone_lds_bytes(M_, DK), st,  \
+                           a.codebooks, static_cast<const FT *>(a.q), static_cast<const FT *>(a.k_new), a.codes_w, a.values, \
+                           counts, (uint32_t)a.L, (uint32_t)a.code_stride, (uint32_t)a.value_stride,                      \
+                           LoneLate{a.part, a.out, a.scale_log2e});                                                       \
+        return true;
+    switch (a.m) {
+        LOOKAT_LONE_CASE(2)
+        LOOKAT_LONE_CASE(4)
+        LOOKAT_LONE_CASE(8)
+        LOOKAT_LONE_CASE(16)
+    default:
+        return false;
+    }
+#undef LOOKAT_LONE_CASE
 }
 template <int DK, typename FT>
 static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
 {
     dim3 block(kStepWaves * kWave);
-    const size_t lds = ((size_t)a.m * kCentroids + (size_t)kStepWaves * (DK + 2)) * sizeof(float) +
-                       (size_t)a.m * kDecWaves * (sizeof(double) + sizeof(int));
-    const bool lone = step_is_lone(a);
-    const bool cut = a.splits > 1;
-#define LOOKAT_STEP_LAUNCH(M_, OCC_, PF_, LONE_, SKIP_)                                                                   \
-    hipLaunchKernelGGL((decode_split_kernel<DK, M_, kStepWaves, OCC_, FT, 1, PF_, 1, false, LONE_, SKIP_>), grid, block,  \
-                       lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true), late_of(a))
-    // One range skips nothing, but the branch also separates the two jobs: with few subspaces, and in the lone instances, that is
-    // faster (see SKIP); with 16 subspaces of 4 it costs registers that the 128 do not hold.
+    const size_t lds = ((size_t)a.m * kCentroids + (size_t)kStepWaves * (DK + 2)) * sizeof(float) + step_encoder_bytes(a.m);
+    if (step_is_lone(a))
+        return launch_step_lone<DK, FT>(a, grid, st);
+    // (16 subspaces: registers for a third workgroup on a compute unit; 640 (b,h) x 600 keys, d_k = 128, two steps 41.3 us, 49 with two.)
 #define LOOKAT_STEP_CASE(M_)                                                                                              \
-    case M_: {                                                                                                            \
-        constexpr bool kAlways = M_ <= (DK == 128 ? 4 : 2), kNever = DK == 64 && M_ == 16;                                 \
-        constexpr int kAhead = M_ == 16 ? 1 : kStepPrefetch;                                                              \
-        if constexpr (DK == 128) {                                                                                        \
-            if (lone) {                                                                                                   \
-                LOOKAT_STEP_LAUNCH(M_, 2, 2, true, true);                                                                 \
-                return true;                                                                                              \
-            }                                                                                                             \
-        }                                                                                                                 \
-        if (cut || kAlways)                                                                                               \
-            LOOKAT_STEP_LAUNCH(M_, 4, kAhead, false, !kNever);                                                            \
-        else                                                                                                              \
-            LOOKAT_STEP_LAUNCH(M_, 4, kAhead, false, kAlways);                                                            \
-        return true;                                                                                                      \
-    }
+    case M_:                                                                                                              \
+        hipLaunchKernelGGL((decode_split_kernel<DK, M_, kStepWaves, M_ == 16 ? 6 : 4, FT, 1, M_ == 16 ? 1 : kStepPrefetch>), grid, block,  \
+                           lds, st, LOOKAT_DECODE_HEAD_ARGS(a, true), late_of(a));                                        \
+        return true;
     switch (a.m) {
         LOOKAT_STEP_CASE(2)
         LOOKAT_STEP_CASE(4)
@@ -1137,7 +1673,6 @@ static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
         return false;
     }
 #undef LOOKAT_STEP_CASE
-#undef LOOKAT_STEP_LAUNCH
 }
 
 // Two batch entries of one head per workgroup (1024 threads): see decode_split_kernel, NB = 2.
@@ -1262,7 +1797,7 @@ static int launch_gqa(const DecodeArgs &a, dim3 grid, hipStream_t st)
 // compute unit at group 2, one from group 4 on (as the unfused grouped kernel).
 static size_t step_gqa_lds_bytes(int group, int m, int d_k)
 {
-    return gqa_lds_bytes(group, m, d_k, kStepWaves) + (size_t)m * kDecWaves * (sizeof(double) + sizeof(int));
+    return gqa_lds_bytes(group, m, d_k, kStepWaves) + step_encoder_bytes(m);
 }
 template <int DK, typename FT, int G>
 static int launch_step_gqa(const DecodeArgs &a, dim3 grid, hipStream_t st)
