@@ -25,15 +25,19 @@ namespace lookat {
 // the same time, so that its L2 serves the other half.  32 heads x 16384 keys x 128 coordinates, m = 8: 305 us with 256 threads,
 // four single floats in flight and every thread taking d_sub chains in turn; 113 us with 1024 threads, 16-byte pieces
 // and eight in flight; 86 us with the subspaces of a head on one die and chunks of 4096 keys (2048: 93, 8192: 93, 16384: 103;
-// 12 or 16 pieces in flight: no change; the lists alone: 29).
-//   LDS: first[257] | run[16][256] (512 threads: [8][256]) | list [kKmChunk] uint16
+// 12 or 16 pieces in flight: no change; the lists alone: 29); 80 us with the next chunk's lists built while members are on their way (AHEAD: for
+// sets of more than one chunk; whole steps, without / with: 32 x 16384, d_k = 128, m = 8 184.6 / 178.5 us, 4 x 24000, d_k = 64, m = 4 85 / 70;
+// for one chunk there is nothing to overlap, and the second buffer costs a workgroup per compute unit: 40 x 512, d_k = 64, m = 16 19.4 / 22.6).
+// Left at 32 x 16384: 341 MB fetched where 268 are needed, the address pipeline busy 61% of the time.  Centroids dealt to the wavefronts by
+// size, so that none waits for the largest lists: 84 us; the codes requested a chunk ahead: 84.
+//   LDS: first[257] | run[16][256] (512 threads: [8][256]) | list [kKmChunk] uint16; AHEAD: first and list twice
 //   grid = (8 heads x m x groups of a sub-vector's pieces, ceil(H / 8)), 512 or 1024 threads; consecutive workgroups go to the
 //   eight dies in turn
 constexpr int kKmPieces = 4;                         // 1024 threads, one (centroid, piece) each
 constexpr int kKmChunk = 4096;
 constexpr int kKmBatch = 8;
 
-template <int V, int THREADS>
+template <int V, int THREADS, bool AHEAD>
 __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__restrict__ calib,
                                                                    const uint8_t *__restrict__ assign,
                                                                    const float *__restrict__ cb_in,
@@ -43,9 +47,10 @@ __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__r
     constexpr int kKmThreads = THREADS;
     constexpr int kKmWaves = kKmThreads / kWave;
     constexpr int kKmRounds = kKmChunk / kKmThreads;     // 64-key rounds of a wavefront in a full chunk
-    __shared__ uint32_t first_s[kCentroids + 1];
+    typedef float vec_t __attribute__((ext_vector_type(V)));
+    __shared__ uint32_t first_s[AHEAD ? 2 : 1][kCentroids + 1];
     __shared__ uint32_t run_s[kKmWaves][kCentroids];
-    __shared__ uint16_t list_s[kKmChunk];
+    __shared__ uint16_t list_s[AHEAD ? 2 : 1][kKmChunk];
     __shared__ uint32_t wave_tot[kCentroids / kWave];
 
     const int d_sub = d_k / m;
@@ -71,8 +76,38 @@ __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__r
         sum[e] = 0.0;
     int64_t members = 0;
 
-    for (int64_t n0 = 0; n0 < Nc; n0 += kKmChunk) {
-        const int len = (Nc - n0 < kKmChunk) ? (int)(Nc - n0) : kKmChunk;
+    // The members at hand, [at, end) of the lists of one chunk, kKmBatch of them requested.
+    uint32_t at = 0, end = 0;
+    const uint16_t *list = list_s[0];
+    const float *rows = x;
+    vec_t v[kKmBatch];
+    auto fetch = [&] {
+#pragma unroll
+        for (int k = 0; k < kKmBatch; ++k)   // past the end: the last member again, not added
+            v[k] = *reinterpret_cast<const vec_t *>(rows + (int64_t)list[at + k < end ? at + k : end - 1] * d_k);
+    };
+    auto take = [&] {
+#pragma unroll
+        for (int k = 0; k < kKmBatch; ++k)
+            if (at + k < end) {
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    sum[e] += (double)v[k][e];
+            }
+        at += kKmBatch;
+    };
+    auto request = [&] {
+        if (at < end)
+            fetch();
+    };
+    auto add = [&] {
+        if (at < end)
+            take();
+    };
+
+    // AHEAD: chunk n0's lists are built while the members of the chunk before it are fetched, each step of the sort starts with a batch requested.
+    for (int64_t n0 = 0, buf = 0;; n0 += kKmChunk, buf ^= AHEAD ? 1 : 0) {
+        const int len = n0 >= Nc ? 0 : (Nc - n0 < kKmChunk ? (int)(Nc - n0) : kKmChunk);
         // this wavefront's share of the chunk: [q0, q1), a multiple of 64 long except at the end
         const int rounds = (len + kKmThreads - 1) / kKmThreads;
         const int q0 = wave * rounds * kWave < len ? wave * rounds * kWave : len;
@@ -83,6 +118,11 @@ __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__r
             const int n = q0 + r * kWave + lane;
             code[r] = (r < rounds && n < q1) ? as[(n0 + n) * m] : 0u;
         }
+        if constexpr (AHEAD) {
+            request();
+            if (len == 0)
+                break;
+        }
         for (int e = tid; e < kKmWaves * kCentroids; e += kKmThreads)
             run_s[e / kCentroids][e % kCentroids] = 0u;
         __syncthreads();
@@ -91,6 +131,10 @@ __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__r
         for (int r = 0; r < kKmRounds; ++r)
             if (r < rounds && q0 + r * kWave + lane < q1)
                 atomicAdd(&run_w[code[r]], 1u);
+        if constexpr (AHEAD) {
+            add();
+            request();
+        }
         __syncthreads();
 
         // thread t < 256: members of centroid t per wavefront -> first slot of (wavefront, t); exclusive prefix sum over t
@@ -114,9 +158,9 @@ __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__r
             uint32_t pos = incl - cnt;
             for (int w = 0; w < wave; ++w)
                 pos += wave_tot[w];
-            first_s[tid] = pos;
+            first_s[buf][tid] = pos;
             if (tid == kCentroids - 1)
-                first_s[kCentroids] = pos + cnt;
+                first_s[buf][kCentroids] = pos + cnt;
 #pragma unroll
             for (int w = 0; w < kKmWaves; ++w) {
                 const uint32_t mine = run_s[w][tid];
@@ -126,6 +170,10 @@ __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__r
         }
         __syncthreads();
 
+        if constexpr (AHEAD) {
+            add();
+            request();
+        }
 #pragma unroll
         for (int r = 0; r < kKmRounds; ++r) {
             if (r < rounds) {   // wave-uniform
@@ -138,39 +186,46 @@ __global__ __launch_bounds__(THREADS) void kmeans_update_kernel(const float *__r
                     peers &= ((code[r] >> bit) & 1u) ? set : ~set;
                 }
                 const uint32_t below = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
-                const uint32_t slot = run_w[code[r]];
+                const uint32_t to = run_w[code[r]];
                 if (valid)
-                    list_s[slot + below] = (uint16_t)n;
+                    list_s[buf][to + below] = (uint16_t)n;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();   // every lane has read the offset before it moves
                 if (valid && below == 0)
-                    run_w[code[r]] = slot + (uint32_t)__popcll(peers);
+                    run_w[code[r]] = to + (uint32_t)__popcll(peers);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             }
         }
-        __syncthreads();
-
-        if (sums) {
-            typedef float vec_t __attribute__((ext_vector_type(V)));
-            const uint32_t f = first_s[c], l = first_s[c + 1];
-            const float *xc = x + n0 * d_k;
-            members += l - f;
-            for (uint32_t u = f; u < l; u += kKmBatch) {
-                vec_t v[kKmBatch];
-#pragma unroll
-                for (int k = 0; k < kKmBatch; ++k)   // past the end: the last member again, not added
-                    v[k] = *reinterpret_cast<const vec_t *>(xc + (int64_t)list_s[u + k < l ? u + k : l - 1] * d_k);
-#pragma unroll
-                for (int k = 0; k < kKmBatch; ++k)
-                    if (u + k < l) {
-#pragma unroll
-                        for (int e = 0; e < V; ++e)
-                            sum[e] += (double)v[k][e];
-                    }
+        if constexpr (AHEAD) {
+            while (at < end) {
+                add();
+                request();
             }
         }
-        __syncthreads();   // the lists are rebuilt by the next chunk
+        __syncthreads();   // the chunk's lists are there, those of the chunk before it are read
+        if (sums) {
+            at = first_s[buf][c];
+            end = first_s[buf][c + 1];
+            members += end - at;
+            list = list_s[buf];
+            rows = x + n0 * d_k;
+        }
+        if constexpr (!AHEAD) {
+            while (at < end) {
+                fetch();
+                take();
+            }
+            if (n0 + kKmChunk >= Nc)
+                break;
+            __syncthreads();
+        }
+    }
+    if constexpr (AHEAD) {
+        while (at < end) {
+            add();
+            request();
+        }
     }
     if (sums) {
 #pragma unroll
@@ -216,9 +271,16 @@ extern "C" int lookat_kmeans_step(const lookat_shape *shape, int64_t Nc, const f
     // d_k = 64, m = 8 15.0 / 14.3); else the lists are made faster by all (4 x 24000, d_k = 64, m = 2 90.0 / 91.2; with four pieces, whose
     // lists two workgroups would build twice, 32 x 16384, d_k = 128, m = 8 175 / 203).
     const bool half = per <= 2 && ((int64_t)shape->m * shape->H * groups > 256 || Nc <= 1024);
-#define LOOKAT_KM_LAUNCH(V, THREADS)                                                                                      \
-    hipLaunchKernelGGL((kmeans_update_kernel<V, THREADS>), grid, dim3(THREADS), 0, st, calib, assign, codebooks_in,       \
+#define LOOKAT_KM_LAUNCH_AHEAD(V, THREADS, AHEAD)                                                                         \
+    hipLaunchKernelGGL((kmeans_update_kernel<V, THREADS, AHEAD>), grid, dim3(THREADS), 0, st, calib, assign, codebooks_in, \
                        codebooks_out, Nc, shape->d_k, shape->H, shape->m, groups, per)
+#define LOOKAT_KM_LAUNCH(V, THREADS)                                                                                      \
+    do {                                                                                                                  \
+        if (Nc > kKmChunk)                                                                                                \
+            LOOKAT_KM_LAUNCH_AHEAD(V, THREADS, true);                                                                     \
+        else                                                                                                              \
+            LOOKAT_KM_LAUNCH_AHEAD(V, THREADS, false);                                                                    \
+    } while (0)
     if (V == 4 && half)
         LOOKAT_KM_LAUNCH(4, 512);
     else if (V == 4)
@@ -228,5 +290,6 @@ extern "C" int lookat_kmeans_step(const lookat_shape *shape, int64_t Nc, const f
     else
         LOOKAT_KM_LAUNCH(1, 1024);
 #undef LOOKAT_KM_LAUNCH
+#undef LOOKAT_KM_LAUNCH_AHEAD
     return check_launch("lookat_kmeans_step (update kernel)");
 }
