@@ -25,7 +25,9 @@
 // stored as NaN, and 32 keys of which one meets such a NaN (or an infinite query) are scored again from the fp32 codebook in
 // plain fp32, on the fp32 matrix instruction, which takes operands and results in the same lanes.
 // What bounds it: LDS.  Per 64 keys 4 d_k / 16 reads of 1 KB at random 16-byte addresses (about 12 clocks each), then the set-up
-// of a workgroup (d_k KB of fp32 codebook through one compute unit, about 3 us).  Figures: see short_block.
+// of a workgroup (d_k KB of fp32 codebook through one compute unit, about 3 us).  The codebook is requested 50 instructions after the start, from
+// preloaded arguments (470, two 64-bit divisions and four round trips to the argument block before: 4 x 32 heads x 8 queries x 4096 keys, d_k = 128,
+// m = 16 13.5 / 12.9 us, 1 x 8 x 2 x 600 7.6 / 6.7).  Figures: see short_block.
 #include <type_traits>
 
 #include "common.h"
@@ -42,20 +44,31 @@ constexpr int kPsThreads = 1024;
 constexpr int kPsWaves = kPsThreads / kWave;
 constexpr float kPsLoScale = 2048.f;
 
-struct PrefillShortArgs {
+// What is needed before the codebook and the first codes can be requested comes first, as scalars (14 dwords are delivered in registers at
+// wave launch; everything else is a round trip to memory away), and the shares are counted on the host.
+#define LOOKAT_PS_PARAMS                                                                                                  \
+    const float *__restrict__ p_codebooks /* [H, m, 256, d_sub] */,                                                       \
+        const uint8_t *__restrict__ p_codes /* (bh, l, i) at bh*code_stride + l*m + i */, int64_t p_code_stride, int64_t p_L, \
+        int p_H, uint32_t p_per_head /* workgroups */, uint32_t p_shares /* per (head, query tile) */,                    \
+        uint32_t p_blocks /* of a wavefront */, uint32_t p_rest /* the first so many have one more */,                    \
+        uint32_t p_blocks_per_bh /* 32-key blocks */, const PrefillShortLate late
+struct PrefillShortLate {
     const void *q;            // [BH, T, d_k] fp16 or fp32
-    const float *codebooks;   // [H, m, 256, d_sub]
-    const uint8_t *codes;     // (bh, l, i) at bh*code_stride + l*m + i
     float *scores;            // [BH, T, L]
+    int T;
+    int vec4;                 // L % 4 == 0 and scores 16-byte aligned
+};
+struct PrefillShortArgs {
+    const void *q;
+    const float *codebooks;
+    const uint8_t *codes;
+    float *scores;
     int64_t code_stride;
     int64_t L;
     int T;
     int H;
-    int tiles;                // query tiles of 16 NG
-    int shares;               // workgroups per (head, query tile)
-    int blocks_per_bh;        // 32-key blocks
-    int blocks;               // of a head: B times as many
-    int vec4;                 // L % 4 == 0 and scores 16-byte aligned
+    int vec4;
+    uint32_t per_head, shares, blocks, rest, blocks_per_bh;
 };
 
 // A power of two that brings magnitudes of this (biased) exponent near 2^13, and its inverse.
@@ -119,7 +132,7 @@ __device__ __forceinline__ ps_v4f ps_plain(const float *cb_h, const uint8_t *cp,
 }
 
 template <typename QT, int DK, int M, int NG>
-__global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(const PrefillShortArgs a)
+__global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(LOOKAT_PS_PARAMS)
 {
     constexpr bool Q32 = std::is_same<QT, float>::value;
     constexpr int DSUB = DK / M;
@@ -131,24 +144,39 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
     __shared__ uint32_t range_s[kPsWaves];
 
     // all workgroups of a head on one die, whose L2 then holds its codebook, codes and queries
-    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    const int per_head = a.tiles * a.shares;
-    const int h = (slot / per_head) * 8 + xcd;
-    if (h >= a.H)
+    const uint32_t xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int h = (int)(slot / p_per_head * 8 + xcd);
+    if (h >= p_H)
         return;
-    const int tile = (slot % per_head) / a.shares, share = slot % a.shares;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    // the codebook (into LDS below) is what the workgroup waits for: requested before anything else is worked out
+    constexpr int NV = DK * kCentroids / 4 / kPsThreads;
+    const ps_v4f *cb = reinterpret_cast<const ps_v4f *>(p_codebooks + (int64_t)h * M * kCentroids * DSUB);
+    ps_v4f cv[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+        cv[k] = cb[tid + k * kPsThreads];
+    __builtin_amdgcn_sched_barrier(0);
+    PrefillShortArgs a;
+    a.q = late.q;
+    a.codebooks = p_codebooks;
+    a.codes = p_codes;
+    a.scores = late.scores;
+    a.code_stride = p_code_stride;
+    a.L = p_L;
+    a.T = late.T;
+    a.H = p_H;
+    a.vec4 = late.vec4;
+    const uint32_t within = slot % p_per_head, share = within % p_shares;
+    const int tile = (int)(within / p_shares);
     const int n = lane & 15, kg = lane >> 4;
-    const int64_t off = a.L - a.T;
-    const int t0 = tile * 16 * NG;
-    const int64_t seen = (t0 + 16 * NG < a.T ? t0 + 16 * NG : a.T) + off;    // keys from here on: -inf for every query of the tile
 
     // ---- this wavefront's blocks, and the codes of the next one (key n of each half, in every lane group) ----
-    const int64_t parts = (int64_t)a.shares * kPsWaves, part = (int64_t)share * kPsWaves + wave;
-    const int blk0 = (int)(part * a.blocks / parts), blk1 = (int)((part + 1) * a.blocks / parts);
-    int b = blk0 / a.blocks_per_bh, lb = blk0 - b * a.blocks_per_bh;       // the block's batch entry and number within it
+    const uint32_t part = share * kPsWaves + (uint32_t)wave;
+    const int blk0 = (int)(part * p_blocks + (part < p_rest ? part : p_rest)), blk1 = blk0 + (int)(p_blocks + (part < p_rest ? 1u : 0u));
+    int b = (int)((uint32_t)blk0 / p_blocks_per_bh), lb = blk0 - b * (int)p_blocks_per_bh;       // the block's batch entry and number within it
     constexpr int kCodeWords = (M + 3) / 4;
     uint32_t ahead[2][kCodeWords];
     auto load_codes = [&](int b_, int lb_) {
@@ -178,12 +206,6 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
         load_codes(b, lb);
 
     // ---- codebook: registers -> largest magnitude -> LDS, scaled and split ----
-    constexpr int NV = DK * kCentroids / 4 / kPsThreads;
-    const ps_v4f *cb = reinterpret_cast<const ps_v4f *>(a.codebooks + (int64_t)h * M * kCentroids * DSUB);
-    ps_v4f cv[NV];
-#pragma unroll
-    for (int k = 0; k < NV; ++k)
-        cv[k] = cb[tid + k * kPsThreads];
     // largest magnitude, and twice the bits of the smallest that is not zero (less one: zero wraps to the top)
     float top = 0.f;
     uint32_t low = ~0u;
@@ -261,6 +283,9 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
     }
     __syncthreads();
 
+    const int64_t off = a.L - a.T;
+    const int t0 = tile * 16 * NG;
+    const int64_t seen = (t0 + 16 * NG < a.T ? t0 + 16 * NG : a.T) + off;    // keys from here on: -inf for every query of the tile
     ps_v8h qh[NG][KS], ql[Q32 ? NG : 1][Q32 ? KS : 1];     // the batch entry's queries: operand B
     float qinv[NG];
     float *row[NG];                                          // this lane's query of every group (past the end: a repeat, not stored)
@@ -315,7 +340,7 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
 #pragma unroll
             for (int w = 0; w < kCodeWords; ++w)
                 now[half][w] = ahead[half][w];
-        if (++lb == a.blocks_per_bh) {
+        if (++lb == (int)p_blocks_per_bh) {
             lb = 0;
             ++b;
         }
@@ -430,7 +455,7 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(cons
 }
 
 template <typename QT, int DK, int M, int NG>
-static int launch_prefill_short_case(const PrefillShortArgs &a, hipStream_t st)
+static int launch_prefill_short_case(const PrefillShortArgs &a, int64_t wgs, hipStream_t st)
 {
     const size_t lds = (size_t)DK * kCentroids * 4;
     auto kern = score_prefill_short_kernel<QT, DK, M, NG>;
@@ -440,8 +465,8 @@ static int launch_prefill_short_case(const PrefillShortArgs &a, hipStream_t st)
         if (e != hipSuccess)
             return fail(LOOKAT_ERR_HIP, "lookat_score_prefill: cannot reserve %zu bytes of LDS: %s", lds, hipGetErrorString(e));
     }
-    const int64_t wgs = (int64_t)((a.H + 7) / 8 * 8) * a.tiles * a.shares;
-    hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(kPsThreads), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(kPsThreads), lds, st, a.codebooks, a.codes, a.code_stride, a.L, a.H, a.per_head, a.shares,
+                       a.blocks, a.rest, a.blocks_per_bh, PrefillShortLate{a.q, a.scores, a.T, a.vec4});
     return check_launch("lookat_score_prefill");
 }
 
@@ -543,23 +568,25 @@ bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q
     a.L = L;
     a.T = T;
     a.H = s->H;
-    a.tiles = o.tiles;
-    a.shares = (int)o.shares;
+    a.shares = (uint32_t)o.shares;
+    a.per_head = (uint32_t)(o.tiles * o.shares);
     a.vec4 = (L % 4 == 0) && aligned16(scores);
-    a.blocks_per_bh = (int)o.blocks_per_bh;
-    a.blocks = (int)(s->B * o.blocks_per_bh);
+    a.blocks_per_bh = (uint32_t)o.blocks_per_bh;
+    const int64_t wavefronts = o.shares * kPsWaves;
+    a.blocks = (uint32_t)(s->B * o.blocks_per_bh / wavefronts);
+    a.rest = (uint32_t)(s->B * o.blocks_per_bh % wavefronts);
 #define LOOKAT_PS_CASE(DK_, M_)                                                                              \
     if (s->d_k == DK_ && s->m == M_) {                                                                       \
         if constexpr (DK_ == 128) {                                                                          \
             if (q_fp32) {                                                                                    \
-                *rc = launch_prefill_short_case<float, DK_, M_, 1>(a, st);                                   \
+                *rc = launch_prefill_short_case<float, DK_, M_, 1>(a, o.wgs, st);                                   \
                 return true;                                                                                 \
             }                                                                                                \
         }                                                                                                    \
         if (ng == 1)                                                                                         \
-            *rc = launch_prefill_short_case<__half, DK_, M_, 1>(a, st);                                      \
+            *rc = launch_prefill_short_case<__half, DK_, M_, 1>(a, o.wgs, st);                                      \
         else                                                                                                 \
-            *rc = launch_prefill_short_case<__half, DK_, M_, 2>(a, st);                                      \
+            *rc = launch_prefill_short_case<__half, DK_, M_, 2>(a, o.wgs, st);                                      \
         return true;                                                                                         \
     }
     LOOKAT_PS_CASE(64, 2)
