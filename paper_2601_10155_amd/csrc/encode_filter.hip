@@ -367,7 +367,8 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                                                                       const float *__restrict__ codebooks,
                                                                       uint8_t *__restrict__ codes,
                                                                       int64_t code_stride_bh, int B, int H, int64_t N,
-                                                                      int d_k, int m, int d_sub_arg, int blocks_per_bh,
+                                                                      int d_k, int m, int d_sub_arg, uint32_t blocks_per_bh,
+                                                                      uint32_t per_block /* floor((2^32 - 1) / blocks_per_bh) */,
                                                                       int splits, int pairs_per_wg)
 {
     typedef EfShape<KT, DP, FULL, FINE> Sh;
@@ -396,33 +397,50 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
     const float *cb = codebooks + ((int64_t)h * m + i) * kCentroids * d_sub;
 
     // ---- the workgroup's key blocks: pairs 2p, 2p + 1 of the head's 32-key blocks, p = first .. first + mine - 1 ----
-    const int total_blocks = B * blocks_per_bh;
-    const int pairs = (total_blocks + 1) / 2;
+    const uint32_t total_blocks = (uint32_t)B * blocks_per_bh;
+    const int pairs = (int)(total_blocks + 1) / 2;
     const int first = part * pairs_per_wg;
     const int mine = pairs - first < pairs_per_wg ? pairs - first : pairs_per_wg;
     if (mine <= 0)
         return;
     KT raw[2][NL][4];
-    // Where a pair's two blocks start: (b,h) slab, key, and how many of its 32 keys exist.  All of it is uniform over the
-    // wavefront (scalar registers); a lane adds its column.
+    // Where a block lies: batch entry, number within it, and how many of its 32 keys exist.  A pair's are uniform over the wavefront (scalar
+    // registers; a lane adds its column), and all that is worked out for each pair is one product for the quotient, corrected once (below
+    // 2^30 the estimate is at most one short), and two for either address: what the scalar unit does the wavefront waits for (a generic
+    // division per block and two full 64-bit address sums, 215 scalar instructions a pair; now 154: 32 x 12 x 1024 fp32 keys, 4 of 16, 42.8 / 41.8
+    // us, 4 x 32 x 2048 fp16, 16 of 8 77.5 / 76.6, 32 x 16384 fp32, 8 of 16 105 / 101).
     struct Where {
-        int64_t bh, n0;
+        uint32_t b, lb;
         int live;
     };
-    auto locate = [&](int kb) {
-        const int b = kb / blocks_per_bh;
-        const int64_t n0 = (int64_t)(kb - b * blocks_per_bh) * 32;
-        const int64_t left = N - n0;
-        return Where{(int64_t)b * H + h, n0, kb < total_blocks ? (left < 32 ? (int)left : 32) : 0};
+    const int tail = (int)(N - (int64_t)(blocks_per_bh - 1) * 32);       // keys of a batch entry's last block
+    auto live_of = [&](uint32_t lb) { return lb == blocks_per_bh - 1 ? tail : 32; };
+    auto locate = [&](uint32_t kb) {
+        uint32_t b = __umulhi(kb, per_block), lb = kb - b * blocks_per_bh;
+        if (lb >= blocks_per_bh) {
+            ++b;
+            lb -= blocks_per_bh;
+        }
+        return Where{b, lb, live_of(lb)};
     };
+    auto after = [&](const Where &w, uint32_t kb) {      // the block behind w, number kb; one that does not exist has no keys and lies where w does
+        if (kb >= total_blocks)
+            return Where{w.b, w.lb, 0};
+        const bool over = w.lb + 1 == blocks_per_bh;
+        const uint32_t lb = over ? 0 : w.lb + 1;
+        return Where{w.b + (over ? 1u : 0u), lb, live_of(lb)};
+    };
+    const KT *keys_h = keys + (int64_t)h * N * d_k + (int64_t)i * d_sub;
+    uint8_t *codes_h = codes + h * code_stride_bh + i;
+    const uint64_t keys_b = (uint64_t)H * (uint64_t)N * (uint32_t)d_k, codes_b = (uint64_t)H * (uint64_t)code_stride_bh;
+    auto keys_at = [&](const Where &w) { return keys_h + (w.b * keys_b + (uint64_t)w.lb * (32u * (uint32_t)d_k)); };
+    auto codes_at = [&](const Where &w) { return codes_h + (w.b * codes_b + (uint64_t)w.lb * (32u * (uint32_t)m)); };
     const bool whole = FULL || d_sub % 4 == 0;    // pieces of four coordinates: all of one or nothing
     auto piece = [&](int l) { return DP >= 16 ? 16 * (l / 2) + 8 * g + 4 * (l % 2) : 4 * l; };   // its first coordinate
-    auto fetch_keys = [&](int kb, KT(&dst)[NL][4]) -> Where {
-        const Where w = locate(kb);
-        // (columns without a key read the block's last key; a block that does not exist reads a key of the first slab)
-        const KT *block = w.live ? keys + (w.bh * N + w.n0) * d_k + (int64_t)i * d_sub : keys + (int64_t)h * N * d_k + (int64_t)i * d_sub;
+    auto fetch_keys = [&](const Where &w, KT(&dst)[NL][4]) {
+        // (columns without a key read the block's last key)
         const int c = col < w.live ? col : (w.live ? w.live - 1 : 0);
-        const KT *sub = block + (uint32_t)(c * d_k);
+        const KT *sub = keys_at(w) + (uint32_t)(c * d_k);
         if (FULL || whole) {
 #pragma unroll
             for (int l = 0; l < NL; ++l)
@@ -438,14 +456,18 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
             for (int l = 0; l < NL; ++l)
                 ef_load_tail(sub, piece(l), d_sub, dst[l]);
         }
-        return w;
     };
     Where here[2] = {}, ahead[2] = {};
+    auto fetch_pair = [&](int pair) {
+        const uint32_t kb = 2u * (uint32_t)(first + pair);
+        ahead[0] = locate(kb);
+        ahead[1] = after(ahead[0], kb + 1);
+        fetch_keys(ahead[0], raw[0]);
+        fetch_keys(ahead[1], raw[1]);
+    };
     int p = wave, pn = wave + kEfWaves;     // this wavefront's pair, and the next one
-    if (p < mine) {
-        ahead[0] = fetch_keys(2 * (first + p), raw[0]);
-        ahead[1] = fetch_keys(2 * (first + p) + 1, raw[1]);
-    }
+    if (p < mine)
+        fetch_pair(p);
     if (tid == 0)
         next_s = 2 * kEfWaves;
 
@@ -713,10 +735,8 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
             int taken = 0;
             if (lane == 0)
                 taken = atomicAdd(&next_s, 1);
-            if (pn < mine) {   // the next pair's keys arrive while this one is scored
-                ahead[0] = fetch_keys(2 * (first + pn), raw[0]);
-                ahead[1] = fetch_keys(2 * (first + pn) + 1, raw[1]);
-            }
+            if (pn < mine)     // the next pair's keys arrive while this one is scored
+                fetch_pair(pn);
 
             auto tile_min = [](const ef_v16f &x) {
                 const float a = ef_min3(x[0], x[1], x[2]), b = ef_min3(x[3], x[4], x[5]), c = ef_min3(x[6], x[7], x[8]);
@@ -865,9 +885,9 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
             const int code = 32 * __builtin_ctz(among >> 12) + 4 * __builtin_ctz(among) + __builtin_ctz(among >> 8);
 
             const bool valid = col < (g ? here[1].live : here[0].live);
-            const int64_t at0 = here[0].bh * code_stride_bh + here[0].n0 * m, at1 = here[1].bh * code_stride_bh + here[1].n0 * m;
+            uint8_t *const at0 = codes_at(here[0]), *const at1 = codes_at(here[1]);
             if (valid && unique)
-                codes[(g ? at1 : at0) + col * m + i] = (uint8_t)code;
+                (g ? at1 : at0)[(uint32_t)(col * m)] = (uint8_t)code;
             const int done = p;
             p = pn;
             pn = __builtin_amdgcn_readfirstlane(taken);
@@ -905,16 +925,9 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                 }
             return list_s[list][at - start];
         };
-        auto place = [&](const uint2 &entry, int64_t &n) {
-            const Where where = locate(2 * (first + (int)(entry.x >> 6)) + (int)((entry.x & 63u) >> 5));
-            n = where.n0 + (int)(entry.x & 31u);
-            return where.bh;
-        };
-        auto key_of = [&](const uint2 &entry) {
-            int64_t n;
-            const int64_t bh = place(entry, n);
-            return keys + (bh * N + n) * d_k + (int64_t)i * d_sub;
-        };
+        auto place = [&](const uint2 &entry) { return locate(2u * ((uint32_t)first + (entry.x >> 6)) + ((entry.x & 63u) >> 5)); };
+        auto key_of = [&](const uint2 &entry) { return keys_at(place(entry)) + (entry.x & 31u) * (uint32_t)d_k; };
+        auto code_of = [&](const uint2 &entry) { return codes_at(place(entry)) + (entry.x & 31u) * (uint32_t)m; };
         lengths();
         // A long list may hold one key many times over (zeros that fill up a batch of prompts, say, where a centroid near them has a rival).
         // If one of four entries is met 16 times or more among 64 that are spread over the lists, that key is decided once, and every
@@ -962,11 +975,8 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const bool there = k0 + u * kWave + lane < noted;
-                    if (there && same[u]) {
-                        int64_t n;
-                        const int64_t bh = place(e[u], n);
-                        codes[bh * code_stride_bh + n * m + i] = (uint8_t)found;
-                    }
+                    if (there && same[u])
+                        *code_of(e[u]) = (uint8_t)found;
                     const uint64_t others = __ballot(there && !same[u]);
                     if (there && !same[u])
                         list_s[wave][kept + (int)__popcll(others & ((1ull << lane) - 1ull))] = e[u];
@@ -981,10 +991,8 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
         for (int b0 = wave * 8; b0 < count; b0 += kEfWaves * 8) {
             const bool exists = b0 + lane / 8 < count;
             const uint2 entry = noted_at(exists ? b0 + lane / 8 : count - 1);
-            int64_t n;
-            const int64_t bh = place(entry, n);
-            const KT *key_sub = keys + (bh * N + n) * d_k + (int64_t)i * d_sub;
-            uint8_t *dst = codes + bh * code_stride_bh + n * m + i;
+            const KT *key_sub = key_of(entry);
+            uint8_t *dst = code_of(entry);
             const uint32_t mx = entry.y & 255u, me = entry.y >> 8 & 15u, mt = entry.y >> 12;
             const int nx = __builtin_popcount(mx), ne = __builtin_popcount(me), nt = __builtin_popcount(mt);
             const int all = nx * ne * nt;
@@ -1031,10 +1039,8 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
         if (!more)
             break;
         __syncthreads();     // (the lists are read)
-        if (p < mine) {      // (the keys of the pair at hand were on their way when the list filled up)
-            ahead[0] = fetch_keys(2 * (first + p), raw[0]);
-            ahead[1] = fetch_keys(2 * (first + p) + 1, raw[1]);
-        }
+        if (p < mine)        // (the keys of the pair at hand were on their way when the list filled up)
+            fetch_pair(p);
     }
 }
 
@@ -1060,7 +1066,8 @@ static bool launch_encode_filter_t(const lookat_shape *s, int64_t N, const void 
     const KT *k = static_cast<const KT *>(keys);
 #define LOOKAT_EF_LAUNCH(D, FULL, THREADS, FINE)                                                                          \
     hipLaunchKernelGGL((encode_filter_kernel<KT, D, FULL, THREADS, FINE>), grid, block, 0, st, k, codebooks, codes,       \
-                       code_stride_bh, s->B, s->H, N, s->d_k, s->m, d_sub, (int)blocks_per_bh, (int)splits,               \
+                       code_stride_bh, s->B, s->H, N, s->d_k, s->m, d_sub, (uint32_t)blocks_per_bh,                           \
+                       (uint32_t)(0xffffffffu / (uint32_t)blocks_per_bh), (int)splits,                                    \
                        (int)((pairs + splits - 1) / splits))
 #define LOOKAT_EF_FORM(D, FULL)                                                                                           \
     do {                                                                                                                  \
