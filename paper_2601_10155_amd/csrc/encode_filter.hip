@@ -466,8 +466,6 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
         fetch_keys(ahead[1], raw[1]);
     };
     int p = wave, pn = wave + kEfWaves;     // this wavefront's pair, and the next one
-    if (p < mine)
-        fetch_pair(p);
     if (tid == 0)
         next_s = 2 * kEfWaves;
 
@@ -500,6 +498,12 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
             for (int j = 0; j < DP; ++j)
                 v[j] = j < d_sub ? row[j] : 0.f;
         }
+    }
+    // (the first pair's keys behind the rows, which everything waits for and L2 holds; without a branch, so that the rows can be waited for alone)
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_pair(p < mine ? p : mine - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (owner) {
 #pragma unroll
         for (int j = 0; j < DP; ++j) {
             cm = fmaxf(cm, fabsf(v[j]));
