@@ -231,11 +231,13 @@ __device__ __forceinline__ int ef_exact_code(const KT *key_sub, const float *cb,
     return c;
 }
 
-// Squared distance by the exact rule: fp64, one rounding per subtract, multiply and add, coordinates ascending.
+// Squared distance by the exact rule: fp64, one rounding per subtract, multiply and add, coordinates ascending.  (32 of them requested at once: with
+// 16, fills of 32 and 64 coordinates took 1 to 10% longer, with 64 registers spill.  Four lanes to a key with two candidates each instead of
+// eight: 5 to 20% slower from 16 coordinates on, the chain of additions counts and not the round trip.)
 template <typename KT, int DP, bool FULL>
 __device__ __forceinline__ double ef_exact_distance(const KT *key_sub, const float *row, int d_sub)
 {
-    constexpr int JB = DP < 16 ? DP : 16;
+    constexpr int JB = DP < 32 ? DP : 32;
     double acc = 0.0;
     const float *rows[1] = {row};
 #pragma unroll 1
