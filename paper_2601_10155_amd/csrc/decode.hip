@@ -114,10 +114,10 @@ __device__ __forceinline__ bool map_block(const DecodeArgs &a, int &bh, int &spl
     return map_block_n(a, a.BH, bh, split);
 }
 
-// LDS of the fused step's encoder (see step_candidates): distances [m][4] fp32, candidates [m][4] bytes, the new codes [m] bytes.
+// LDS of the fused step's encoder (see step_candidates): (distance, candidate) [m][4], the new codes [m] bytes.
 constexpr int code_words(int m) { return m ? (m + 3) / 4 : 1; }    // words that hold a key's codes
 constexpr int kNearest = 4;                           // wavefronts (of 64 centroids) per subspace
-__host__ __device__ constexpr size_t step_encoder_bytes(int m) { return ((size_t)m * kNearest * 5 + (size_t)m + 15) / 16 * 16; }
+__host__ __device__ constexpr size_t step_encoder_bytes(int m) { return ((size_t)m * kNearest * 8 + (size_t)m + 15) / 16 * 16; }
 // LDS of one batch entry of the fused step (table, per-wavefront partial results, the encoder's
 // candidates), rounded to 16 bytes: the distance between the two entries' blocks of a paired workgroup.
 __host__ __device__ constexpr size_t step_pair_lds_bytes(int m, int d_k)
@@ -235,69 +235,84 @@ __device__ __forceinline__ void wave_minima(const float (&x)[N], float (&least)[
 // hold ascending ranges of centroids, `quarter` says which.
 template <typename FT, int DSUB, int M, int GS>
 __device__ __forceinline__ void step_candidates(const float (&dist)[GS], int i0, int c, int quarter, int lane, const float *cb_head,
-                                                const FT *k_row, float *near_s)
+                                                const FT *k_row, uint2 *near_s)
 {
-    uint8_t *cand_s = reinterpret_cast<uint8_t *>(near_s + M * kNearest);
     float least[GS];
     wave_minima<GS>(dist, least, lane);
+    uint64_t among[GS], several = 0;
 #pragma unroll
     for (int s = 0; s < GS; ++s) {
-        const uint64_t among = __ballot(!(dist[s] > step_limit<DSUB>(least[s])));
-        bool mine = among >> lane & 1;
-        if (among & (among - 1)) {           // several: the rule, lowest centroid on ties
-            double dv[1] = {(double)INFINITY};
-            if (mine)
-                dv[0] = argmin_value(step_exact_distance<FT, DSUB>(k_row + (i0 + s) * DSUB, cb_head + ((i0 + s) * kCentroids + c) * DSUB), c);
-            const double own = dv[0];
-            dmin_wave<1>(dv);
-            int lowest = mine && own == dv[0] ? c : kCentroids;
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                const int other = __shfl_xor(lowest, o);
-                lowest = other < lowest ? other : lowest;
-            }
-            mine = lowest == c;
-        }
-        if (mine) {
-            near_s[(i0 + s) * kNearest + quarter] = dist[s];
-            cand_s[(i0 + s) * kNearest + quarter] = (uint8_t)c;
-        }
+        among[s] = __ballot(!(dist[s] > step_limit<DSUB>(least[s])));
+        several |= among[s] & (among[s] - 1);
     }
+    if (several) {                           // the rule, lowest centroid on ties
+#pragma unroll
+        for (int s = 0; s < GS; ++s)
+            if (among[s] & (among[s] - 1)) {
+                const bool mine = among[s] >> lane & 1;
+                double dv[1] = {(double)INFINITY};
+                if (mine)
+                    dv[0] = argmin_value(step_exact_distance<FT, DSUB>(k_row + (i0 + s) * DSUB, cb_head + ((i0 + s) * kCentroids + c) * DSUB), c);
+                const double own = dv[0];
+                dmin_wave<1>(dv);
+                int lowest = mine && own == dv[0] ? c : kCentroids;
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) {
+                    const int other = __shfl_xor(lowest, o);
+                    lowest = other < lowest ? other : lowest;
+                }
+                among[s] = __ballot(lowest == c);
+            }
+    }
+#pragma unroll
+    for (int s = 0; s < GS; ++s)
+        if (among[s] >> lane & 1)
+            near_s[(i0 + s) * kNearest + quarter] = make_uint2(__float_as_uint(dist[s]), (uint32_t)c);
 }
 // The new key's codes (four to a word; uniform) after the barrier, for the wavefront that scores position L-1: lane (i, w) holds the candidate of
 // subspace i among centroids 64w .. 64w+63.  They go to the cache and, in the lane that scores that key, in the place of the cached row, which
 // may be stale (consume_tile).
 template <typename FT, int DSUB, int M>
-__device__ __forceinline__ void step_new_codes(uint32_t (&fresh)[code_words(M)], const float *near_s, const float *cb_head, const FT *k_row,
+__device__ __forceinline__ void step_new_codes(uint32_t (&fresh)[code_words(M)], uint2 *near_s, const float *cb_head, const FT *k_row,
                                                uint8_t *code_row, int lane)
 {
-    const uint8_t *cand_s = reinterpret_cast<const uint8_t *>(near_s + M * kNearest);
-    uint8_t *new_s = const_cast<uint8_t *>(cand_s) + M * kNearest;
     const int at = lane < M * kNearest ? lane : 0;
-    const float d = near_s[at];
-    const int c = cand_s[at];
+    const uint2 mine = near_s[at];
+    const float d = __uint_as_float(mine.x);
+    const int c = (int)mine.y;
     float least = fminf(d, dpp_mov<0xB1>(d, d));
     least = fminf(least, dpp_mov<0x4E>(least, least));
-    const uint64_t among = __ballot(!(d > step_limit<DSUB>(least)));
-    uint32_t left = lane < M * kNearest ? (uint32_t)(among >> (lane & ~3)) & 15u : 1u;
-    if (__ballot((left & (left - 1)) != 0)) {
+    uint64_t left = __ballot(!(d > step_limit<DSUB>(least)));      // the candidates that may be the argmin, four bits a subspace
+    constexpr uint64_t kLowest = M == 16 ? 0x1111111111111111ull : (1ull << (M * kNearest % 64)) / 15u;       // bit 0 of every subspace
+    constexpr uint64_t kLanes = kLowest * 15u;
+    left &= kLanes;
+    // (one each: then no subspace has fewer, and all have M together)
+    if (__popcll(left) != M) {
         double dv = (double)INFINITY;
-        if (left >> (lane & 3) & 1) {
+        if (left >> lane & 1) {
             const int i = at / kNearest;
             dv = argmin_value(step_exact_distance<FT, DSUB>(k_row + i * DSUB, cb_head + (i * kCentroids + c) * DSUB), c);
         }
         double dm = dmin_dpp<0xB1>(dv);
         dm = dmin_dpp<0x4E>(dm);
-        left &= (uint32_t)(__ballot(dv == dm) >> (lane & ~3)) & 15u;
+        left &= __ballot(dv == dm);
     }
-    if (lane < M * kNearest && (lane & 3) == __builtin_ctz(left))     // (candidates ascend: the lowest on ties)
-        new_s[lane / kNearest] = (uint8_t)c;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const uint32_t *words = reinterpret_cast<const uint32_t *>(new_s);
+    if constexpr (M <= 4) {
+        fresh[0] = 0;
 #pragma unroll
-    for (int w = 0; w < code_words(M); ++w)
-        fresh[w] = (uint32_t)__builtin_amdgcn_readfirstlane((int)words[w]);
+        for (int i = 0; i < M; ++i)            // (candidates ascend: the lowest on ties)
+            fresh[0] |= (uint32_t)__builtin_amdgcn_readlane(c, kNearest * i + __builtin_ctz((uint32_t)(left >> (kNearest * i)) & 15u)) << (8 * i);
+    } else {
+        uint8_t *new_s = reinterpret_cast<uint8_t *>(near_s + M * kNearest);
+        if (lane < M * kNearest && (lane & 3) == __builtin_ctz((uint32_t)(left >> (lane & ~3)) & 15u))
+            new_s[lane / kNearest] = (uint8_t)c;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t *words = reinterpret_cast<const uint32_t *>(new_s);
+#pragma unroll
+        for (int w = 0; w < code_words(M); ++w)
+            fresh[w] = (uint32_t)__builtin_amdgcn_readfirstlane((int)words[w]);
+    }
     if (lane == 0) {
         if constexpr (M == 2) {
             *reinterpret_cast<uint16_t *>(code_row) = (uint16_t)fresh[0];
@@ -307,8 +322,6 @@ __device__ __forceinline__ void step_new_codes(uint32_t (&fresh)[code_words(M)],
                 reinterpret_cast<uint32_t *>(code_row)[w] = fresh[w];
         }
     }
-    if constexpr (M == 2)
-        fresh[0] &= 0xffffu;
 }
 
 // ---- the table from whole lines of the codebook ----------------------------------------------------------------
@@ -401,7 +414,7 @@ struct StepTable {
         __builtin_amdgcn_wave_barrier();
     }
     // Table entries and, if encode, candidates of the group of subspaces i .. i+GS-1 (g0 = i - i0) for batch entry nb.
-    __device__ __forceinline__ void group(const float *stage, int nb, int g0, int i, int quarter, int lane, float *lut_s, float *near_s,
+    __device__ __forceinline__ void group(const float *stage, int nb, int g0, int i, int quarter, int lane, float *lut_s, uint2 *near_s,
                                           const float *cb_head, const FT *k_row, bool encode) const
     {
         const int c = quarter * kWave + lane % LPW * (kWave / LPW) + lane / LPW;
@@ -655,7 +668,7 @@ __device__ __forceinline__ void load_centroid_rows(float (&row)[GS][DSUB], const
 // The staged words of q and k_new occupy the (not yet used) partial results of the wavefronts.
 template <typename FT, int DK, int M, int NB>
 __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int part, int lane, int wave, float *lut_s, float *red_s,
-                                              float *near_s, int lds_stride, bool encode)
+                                              uint2 *near_s, int lds_stride, bool encode)
 {
     static_assert(NB == 1 || (NB == 2 && M % 2 == 0), "paired batch entries: even m");
     constexpr int MS = M / NB;            // subspaces this builder group covers
@@ -676,7 +689,7 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
             table.group(stage, nb, g0, ibase + g0, wave, lane, reinterpret_cast<float *>(reinterpret_cast<char *>(lut_s) + nb * lds_stride),
-                        reinterpret_cast<float *>(reinterpret_cast<char *>(near_s) + nb * lds_stride), cb_head,
+                        reinterpret_cast<uint2 *>(reinterpret_cast<char *>(near_s) + nb * lds_stride), cb_head,
                         k_new + ((int64_t)bh + nb * a.H) * DK, encode);
     }
 }
@@ -689,7 +702,7 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
 // (not yet used) partial results; the rows of the copy are four words longer than a query, so that four heads' words lie in different banks.
 template <typename FT, int DK, int M, int G>
 __device__ __forceinline__ void step_prologue_grouped(const DecodeArgs &a, int bh, int tid, int lane, int wave, float *lut_s, float *red_s,
-                                                      float *near_s, bool encode)
+                                                      uint2 *near_s, bool encode)
 {
     constexpr int DSUB = DK / M;
     constexpr int kRegs = G >= 4 ? 128 : 64;
@@ -789,7 +802,7 @@ constexpr bool step_heads_on_vector_alu(int group, int d_k, int m, bool fp32)
     return group == 2 || (group == 4 && d_k == 128 && (m == 4 || m == 8) && !fp32);
 }
 template <typename FT, int DK, int M, int G>
-__device__ __forceinline__ void step_prologue_heads(const DecodeArgs &a, int bh, int tid, int lane, int wave, float *lut_s, float *near_s,
+__device__ __forceinline__ void step_prologue_heads(const DecodeArgs &a, int bh, int tid, int lane, int wave, float *lut_s, uint2 *near_s,
                                                     bool encode)
 {
     constexpr int DSUB = DK / M;
@@ -971,7 +984,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     float *smem = reinterpret_cast<float *>(reinterpret_cast<char *>(smem_all) + hf * kHalfBytes);
     float *lut_s = smem;                                   // [G][m][256]
     float *red_s = smem + G * (M ? M : a.m) * kCentroids;  // [WAVES][G][DK + 2]
-    float *near_s = red_s + WAVES * G * (DK + 2);          // fused step: see step_candidates
+    uint2 *near_s = reinterpret_cast<uint2 *>(red_s + WAVES * G * (DK + 2));   // fused step: see step_candidates
 
     int bh, split;
     if constexpr (NB == 1) {
@@ -1058,7 +1071,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
             __builtin_amdgcn_s_setprio(3);
             if constexpr (G == 1) {
                 // (paired entries: the LDS blocks and the (b,h) index are handed over as entry 0's)
-                auto first = [&](float *p) { return reinterpret_cast<float *>(reinterpret_cast<char *>(p) - hf * kHalfBytes); };
+                auto first = [&](auto *p) { return reinterpret_cast<decltype(p)>(reinterpret_cast<char *>(p) - hf * kHalfBytes); };
                 step_prologue<FT, DK, M, NB>(a, bh - hf * a.H, hf, lane, wave, first(lut_s), first(red_s), first(near_s), kHalfBytes,
                                              k1 == (uint32_t)a.L);
             } else if constexpr (step_heads_on_vector_alu(G, DK, M, sizeof(FT) == 4)) {
@@ -1258,15 +1271,16 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
 
 // ---- the fused step where every workgroup has a compute unit to itself ----------------------------------------
 // Up to 32 workgroups on a die: one sequence or a few, whole or cut into ranges.  A launch is then a chain of latencies, and what a compute unit's
-// memory pipe takes (a wave-wide load of a kilobyte every 16 clocks) and when.  Sixteen wavefronts: the first eight stream the tiles, as in
-// decode_split_kernel, from the start; the others build the table, 8-11 the first half of the subspaces, 12-15 the second, two on a SIMD so that
-// one's arithmetic fills the other's latencies, and end.  The builders run at raised priority until their rows are requested, so that these enter
-// the pipe first.  (With eight wavefronts doing both jobs the arithmetic waits until the pipe has accepted the wavefront's tiles: table complete at
+// memory pipe takes (a wave-wide load of a kilobyte every 16 clocks) and when.  Sixteen wavefronts: the first eight build the table, 0-3 the first
+// half of the subspaces, 4-7 the second, two on a SIMD so that one's arithmetic fills the other's latencies, and end; the others stream the tiles,
+// as in decode_split_kernel, from the start.  The builders are the first wavefronts of the workgroup, which start first, and run at raised
+// priority until their rows are requested, so that these enter the pipe first.  (With eight wavefronts doing both jobs the arithmetic waits until the pipe has accepted the wavefront's tiles: table complete at
 // 5000 clocks at d_k = 64, 15500 at 128, of 9200 and 21800.)  What has to be known before the first request travels in the preloaded
 // arguments (the (b,h) count, ranges and heads in one word: none exceeds 256).
 //   Measured against the roles of decode_split_kernel with a thread per centroid row and fp64 distances (us per launch): 12 (b,h), d_k = 64, m = 2:
-// 1 key 5.6 / 3.9, 1024 keys 6.3 / 5.4, 8192 19.8 / 18.6; d_k = 128, m = 8: 8.2 / 5.4, 10.6 / 8.3, 39.6 / 36.4; 32 x 8003 keys in ranges 16.6 / 15.6
-// with the merge; 176 calls of 4 to 160 (b,h) x 700 to 32000 keys, cut or not, 0.85 of the time on the geometric mean.
+// 1 key 5.6 / 4.0, 1024 keys 6.3 / 5.2, 8192 19.8 / 18.3; d_k = 128, m = 8: 8.2 / 5.0, 10.6 / 7.8, 39.6 / 36.2; 32 x 8003 keys in ranges 16.6 / 15.6
+// with the merge; 176 calls of 4 to 160 (b,h) x 700 to 32000 keys, cut or not, 0.85 of the time on the geometric mean.  (The builders as the last
+// wavefronts, and a candidate's distance and number in two places: up to 11% longer, 1024 keys 5.4 and 8.3.)
 struct LoneLate {
     float *part;
     float *out;
@@ -1293,7 +1307,7 @@ __global__ __launch_bounds__(4 * kDecThreads, 4) void decode_step_lone_kernel(co
     extern __shared__ __align__(16) float smem_all[];
     float *lut_s = smem_all;                                       // [M][256]
     float *red_s = lut_s + M * kCentroids;                         // [WAVES][DK + 2]
-    float *near_s = red_s + WAVES * (DK + 2);                      // see step_candidates
+    uint2 *near_s = reinterpret_cast<uint2 *>(red_s + WAVES * (DK + 2));       // see step_candidates
 
     DecodeArgs a = {};
     a.BH = (int)(p_counts & 0x1ffu);
@@ -1302,9 +1316,8 @@ __global__ __launch_bounds__(4 * kDecThreads, 4) void decode_step_lone_kernel(co
     int bh, split;
     if (!map_block(a, bh, split))
         return;
-    const int tid = (int)threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = (int)threadIdx.x & (kWave - 1);
+    const int any_wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     uint32_t k0 = 0, k1 = p_L;
     if (a.splits > 1) {      // ranges of whole tiles
         const uint32_t kps = ((p_L + kTile - 1) / kTile + (uint32_t)a.splits - 1) / (uint32_t)a.splits * kTile;
@@ -1316,9 +1329,9 @@ __global__ __launch_bounds__(4 * kDecThreads, 4) void decode_step_lone_kernel(co
     const int h = bh - (int)(((float)bh + 0.5f) * __builtin_amdgcn_rcpf((float)a.H)) * a.H;
     const float *cb_head = p_codebooks + (int64_t)h * kCentroids * DK;
 
-    if (wave >= WAVES) {     // ---- table and candidates ----
+    if (any_wave < WAVES) {  // ---- table and candidates ----
         __builtin_amdgcn_s_setprio(3);
-        const int builder = wave - WAVES;
+        const int builder = any_wave;
         const int i0 = builder / kDecWaves * MS, quarter = builder & (kDecWaves - 1);
         float *stage = red_s + builder * Table::kWords;      // (the partial results are not in use yet)
         Table table;
@@ -1333,6 +1346,7 @@ __global__ __launch_bounds__(4 * kDecThreads, 4) void decode_step_lone_kernel(co
     }
 
     // ---- the wavefront's tiles ----
+    const int wave = any_wave - WAVES, tid = (int)threadIdx.x - NT;
     a.L = p_L;
     const __amdgpu_buffer_rsrc_t rv = make_rsrc(p_values + (int64_t)bh * p_value_stride, k1 * (uint32_t)(DK * 2));
     const __amdgpu_buffer_rsrc_t rc = make_rsrc(p_codes + (int64_t)bh * p_code_stride, k1 * (uint32_t)M);
