@@ -83,13 +83,13 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const KT *__restric
 // ---- few keys per head (decode-time append) -------------------------------------------
 // With a handful of keys per head the thread-per-key kernel above leaves the chip empty and
 // each thread walks all 256 centroids serially.  Here the centroids are spread over the
-// threads instead: one block = one (head, subspace) and KEYS keys (1, 2, 4 or 8, the smallest that takes a head's keys in
-// one block); thread c holds centroid c in registers, evaluates its distance to every key of the block
+// threads instead: one block = one (head, subspace) and KEYS keys (1, 2, 4 or 8: see few_keys);
+// thread c holds centroid c in registers, evaluates its distance to every key of the block
 // (same arithmetic, same order) and the block takes the argmin over (distance, index).
 // What bounds it: latency -- the codebook's and the keys' way from memory, then KEYS serial chains of fp64 operations and as many
 // reductions over the wavefront.  So the centroid's row is requested in 16-byte pieces, sixteen coordinates at once, beside the keys (element
 // by element, four in flight, the row of a 12-coordinate sub-vector took three round trips), and no key is evaluated that is not there.
-// us per call before / now: 4 x 16 (b,h), d_k = 96, m = 8 4.9 / 3.5; 2 x 8, d_k = 128, m = 2, fp32 12.5 / 5.4; 1 x 8, d_k = 160, m = 16 4.7 / 3.7.
+// us per call before / now: 4 x 16 (b,h), d_k = 96, m = 8 4.9 / 3.0; 2 x 8, d_k = 128, m = 2, fp32 12.5 / 5.4; 1 x 8, d_k = 160, m = 16 4.7 / 3.7.
 constexpr int kEncFewKeys = 8;
 
 // Flat (b, n) of a head's keys.  (A decode step appends one key per sequence: no division on the way to its address; else a 32-bit
@@ -297,7 +297,20 @@ __global__ __launch_bounds__(kCentroids, (KEYS == 8 && JB == 0 ? 8 : 4)) void en
     }
 }
 
-static int few_keys(int64_t rows) { return rows <= 1 ? 1 : (rows <= 2 ? 2 : (rows <= 4 ? 4 : kEncFewKeys)); }
+// Keys of a workgroup: as few as leave two workgroups on a compute unit, one where rows are longer than 16 coordinates.  Up to there all run at
+// once, and a workgroup's time is its chain, which the further keys make longer: their fp64 distances and minima take the vector ALU in turn.
+// With more workgroups the rows' fetch counts, which the keys share.  us per call, 1 / 2 / 4 / 8 keys, subspaces x heads x keys a head: 8
+// coordinates, 48 x 12 2.4 / 2.7 / 2.9 / 3.6, 256 x 8 4.5 / 3.2 / 3.2 / 3.8; 12, 128 x 4 3.0 / 3.0 / 3.6, 128 x 8 4.3 / 3.4 / 3.5 / 4.7; 16, 256 x 2
+// 2.8 / 2.8, 256 x 4 4.7 / 3.3 / 3.3, 128 x 16 5.0 / 5.5 / 4.1 / 4.5; 20, 16 x 16 3.0 / 3.2 / 3.9 / 5.3, 128 x 4 4.4 / 3.3 / 4.1; 32, 16 x 16
+// 3.2 / 3.5 / 4.5 / 6.5, 16 x 24 4.0 / 3.6 / 4.6 / 6.6, 128 x 8 8.0 / 6.2 / 4.8 / 6.7, 256 x 60 54 / 31 / 23 / 22.
+static int few_keys(const lookat_shape *s, int64_t rows)
+{
+    const int64_t most = s->d_k / s->m <= 16 ? 512 : 256;
+    int keys = 1;
+    while (keys < kEncFewKeys && keys < rows && (rows + keys - 1) / keys * s->m * s->H > most)
+        keys *= 2;
+    return keys;
+}
 
 // (also the exact scan of sub-vector lengths without an encode_kernel instance, however many keys)
 template <typename KT>
@@ -305,7 +318,7 @@ static void launch_encode_few_any(const lookat_shape *s, int64_t N, const void *
                                   uint8_t *codes, int64_t code_stride_bh, hipStream_t st)
 {
     const int64_t rows = (int64_t)s->B * N;
-    const int keys_wg = few_keys(rows);
+    const int keys_wg = few_keys(s, rows);
     const int64_t blocks = (rows + keys_wg - 1) / keys_wg;
     const dim3 grid((unsigned)(blocks < 65536 ? blocks : 65536), (unsigned)s->m, (unsigned)s->H);
     const int d_sub = s->d_k / s->m;
@@ -339,7 +352,7 @@ static bool launch_encode_few(const lookat_shape *s, int64_t N, const void *keys
 {
     const int d_sub = s->d_k / s->m;
     const int64_t rows = (int64_t)s->B * N;
-    const int keys_wg = few_keys(rows);
+    const int keys_wg = few_keys(s, rows);
     dim3 grid((unsigned)((rows + keys_wg - 1) / keys_wg), (unsigned)s->m, (unsigned)s->H);
     dim3 block(kCentroids);
     const KT *k = static_cast<const KT *>(keys);
