@@ -29,21 +29,29 @@ __device__ __forceinline__ void split_query(int64_t qi, int T, int64_t &b, int64
 // (b, t) list.  Thread c keeps centroid c of the subspace in registers and reuses it for
 // every query of the block; the query sub-vectors sit in LDS and are read by all lanes
 // at the same address (broadcast).  Each query's 256 table entries are written as one
-// contiguous 1 KB row.
-//   grid = (ceil(B*T / QB), m, H)
+// contiguous 1 KB row.  Rows of 32 and 64 coordinates are requested first, as staging the queries waits for them (4 tables of 32 coordinates
+// 2.8 / 2.7 us, 1024 of 64 10.6 / 9.1); shorter ones behind the queries (first: 30720 tables of 8 coordinates 10.8 / 13.8 us).
+//   grid = (ceil(B*T / QB), m, H), or (m, H, ceil(B*T / QB)): see lut_rows_together
 template <typename QT, int DSUB>
 __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(const QT *__restrict__ q,
                                                                 const float *__restrict__ codebooks,
                                                                 float *__restrict__ lut, int B, int H, int T, int d_k,
-                                                                int m, int QB)
+                                                                int m, int QB, bool rows_together)
 {
     extern __shared__ float q_s[];  // [QB][DSUB]
-    const int i = blockIdx.y;
-    const int h = blockIdx.z;
+    const RowBlock block = row_block(rows_together);
+    const int i = block.i, h = block.h;
     const int c = threadIdx.x;
     const int64_t nq = (int64_t)B * T;
-    const int64_t q0 = (int64_t)blockIdx.x * QB;
+    const int64_t q0 = (int64_t)block.part * QB;
 
+    float row[DSUB];
+    if constexpr (DSUB >= 32) {
+        const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * DSUB;
+#pragma unroll
+        for (int j = 0; j < DSUB; ++j)
+            row[j] = src[j];
+    }
     for (int e = threadIdx.x; e < QB * DSUB; e += kLutThreads) {
         const int64_t qi = q0 + e / DSUB;
         float v = 0.f;
@@ -54,12 +62,12 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(const QT *__rest
         }
         q_s[e] = v;
     }
-
-    float row[DSUB];
-    const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * DSUB;
+    if constexpr (DSUB < 32) {
+        const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * DSUB;
 #pragma unroll
-    for (int j = 0; j < DSUB; ++j)
-        row[j] = src[j];
+        for (int j = 0; j < DSUB; ++j)
+            row[j] = src[j];
+    }
     __syncthreads();
 
     for (int k = 0; k < QB; ++k) {
@@ -84,15 +92,15 @@ template <typename QT, int JB>
 __global__ __launch_bounds__(kLutThreads) void build_lut_generic_kernel(const QT *__restrict__ q,
                                                                         const float *__restrict__ codebooks,
                                                                         float *__restrict__ lut, int B, int H, int T,
-                                                                        int d_k, int m, int QB)
+                                                                        int d_k, int m, int QB, bool rows_together)
 {
     extern __shared__ float q_s[];  // [QB][d_sub]
     const int d_sub = d_k / m;
-    const int i = blockIdx.y;
-    const int h = blockIdx.z;
+    const RowBlock block = row_block(rows_together);
+    const int i = block.i, h = block.h;
     const int c = threadIdx.x;
     const int64_t nq = (int64_t)B * T;
-    const int64_t q0 = (int64_t)blockIdx.x * QB;
+    const int64_t q0 = (int64_t)block.part * QB;
     const float *src = codebooks + (((int64_t)h * m + i) * kCentroids + c) * d_sub;
     float row[JB];
     auto fetch = [&](int j0) {                      // coordinates j0 .. j0 + JB - 1 as far as there are any
@@ -308,6 +316,17 @@ static bool launch_build_lut_mfma(const lookat_shape *s, int T, const void *q, c
 #undef LOOKAT_LUTM_CASE
 }
 
+// Which workgroups follow each other: the queries of one subspace, which go to the eight dies in turn so that every die fetches the subspace's rows
+// (d_sub KB), or the subspaces of the same queries: with m*H a multiple of eight a subspace's rows are then fetched by one die and found there by
+// the next queries.  Else, with rows so short that the tables (a KB a query) are what counts, the first order is up to 4% faster.  us per call, first /
+// second: 256 (head, subspace) x 4 queries, d_sub 4 2.5 / 2.5, 8 2.8 / 2.5, 12 4.9 / 3.9, 16 4.7 / 3.0, 20 6.1 / 4.2, 32 7.6 / 5.7; x 32, 4 4.7 / 4.6,
+// 8 5.5 / 4.8, 16 7.2 / 5.9, 32 10.7 / 10.0; x 240, 8 18.3 / 17.2, 16 22.8 / 22.3, 32 39.6 / 38.5; 64 x 128, 40 52.5 / 35.8; 100 x 32, 8 3.3 / 3.4,
+// 16 5.1 / 4.2.  (The grid's last dimension ends at 65535.)
+static bool lut_rows_together(const lookat_shape *s, int64_t blocks)
+{
+    return blocks <= 65535 && (s->m * s->H % 8 == 0 || s->d_k / s->m >= 12);
+}
+
 template <typename QT>
 static void launch_build_lut(const lookat_shape *s, int T, const void *q, const float *codebooks, float *lut,
                              hipStream_t st)
@@ -318,13 +337,15 @@ static void launch_build_lut(const lookat_shape *s, int T, const void *q, const 
     int QB = 1;
     while (QB < 16 && (nq / (QB * 2)) * s->m * s->H >= 1024)
         QB *= 2;
-    dim3 grid((unsigned)((nq + QB - 1) / QB), (unsigned)s->m, (unsigned)s->H);
+    const int64_t blocks = (nq + QB - 1) / QB;
+    const bool together = lut_rows_together(s, blocks);
+    const dim3 grid = row_grid(s, blocks, together);
     dim3 block(kLutThreads);
     const QT *qp = static_cast<const QT *>(q);
 #define LOOKAT_LUT_CASE(D)                                                                                         \
     case D:                                                                                                        \
         hipLaunchKernelGGL((build_lut_kernel<QT, D>), grid, block, (size_t)QB * D * sizeof(float), st, qp,         \
-                           codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB);                                       \
+                           codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB, together);                             \
         break;
     switch (d_sub) {
         LOOKAT_LUT_CASE(1)
@@ -337,10 +358,10 @@ static void launch_build_lut(const lookat_shape *s, int T, const void *q, const 
     default:
         if (d_sub <= 8)
             hipLaunchKernelGGL((build_lut_generic_kernel<QT, 8>), grid, block, (size_t)QB * d_sub * sizeof(float), st, qp,
-                               codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB);
+                               codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB, together);
         else
             hipLaunchKernelGGL((build_lut_generic_kernel<QT, 32>), grid, block, (size_t)QB * d_sub * sizeof(float), st, qp,
-                               codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB);
+                               codebooks, lut, s->B, s->H, T, s->d_k, s->m, QB, together);
         break;
     }
 #undef LOOKAT_LUT_CASE
