@@ -1274,9 +1274,9 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
 // memory pipe takes (a wave-wide load of a kilobyte every 16 clocks) and when.  Sixteen wavefronts: the first eight build the table, 0-3 the first
 // half of the subspaces, 4-7 the second, two on a SIMD so that one's arithmetic fills the other's latencies, and end; the others stream the tiles,
 // as in decode_split_kernel, from the start.  The builders are the first wavefronts of the workgroup, which start first, and run at raised
-// priority until their rows are requested, so that these enter the pipe first.  (With eight wavefronts doing both jobs the arithmetic waits until the pipe has accepted the wavefront's tiles: table complete at
-// 5000 clocks at d_k = 64, 15500 at 128, of 9200 and 21800.)  What has to be known before the first request travels in the preloaded
-// arguments (the (b,h) count, ranges and heads in one word: none exceeds 256).
+// priority until their rows are requested, so that these enter the pipe first.  (With eight wavefronts doing both jobs the arithmetic waits
+// until the pipe has accepted the wavefront's tiles: table complete at 5000 clocks at d_k = 64, 15500 at 128, of 9200 and 21800.)  What has to
+// be known before the first request travels in the preloaded arguments (the (b,h) count, ranges and heads in one word: none exceeds 256).
 //   Measured against the roles of decode_split_kernel with a thread per centroid row and fp64 distances (us per launch): 12 (b,h), d_k = 64, m = 2:
 // 1 key 5.6 / 4.0, 1024 keys 6.3 / 5.2, 8192 19.8 / 18.3; d_k = 128, m = 8: 8.2 / 5.0, 10.6 / 7.8, 39.6 / 36.2; 32 x 8003 keys in ranges 16.6 / 15.6
 // with the merge; 176 calls of 4 to 160 (b,h) x 700 to 32000 keys, cut or not, 0.85 of the time on the geometric mean.  (The builders as the last

@@ -54,7 +54,7 @@
 // waits for the key requests ahead of it (no instance spills).  Wavefronts take their pairs from a shared counter: the SIMD favours its oldest
 // wavefront, and with fixed shares the last one ran alone for a third of the time.
 //   Measured (us per call, this kernel / the one with two terms of everything, norms and operands from LDS, 256 centroids exactly for
-// every undecided key): 4 x 32 heads x 2048 fp16 keys, 16 subspaces of 8: 75 / 85; 32 x 12 heads x 1024 fp32 keys, 4 of 16: 42 / 62;
+// every undecided key): 4 x 32 heads x 2048 fp16 keys, 16 subspaces of 8: 74 / 85; 32 x 12 heads x 1024 fp32 keys, 4 of 16: 42 / 62;
 // 32 heads x 16384 fp32 keys, 8 of 16: 95 / 135; 8 x 16 x 2048, d_k = 128: fp16 8 of 16 45 / 59, 4 of 32 35 / 54, 2 of 64 33 / 57;
 // fp32 4 of 32 41 / 72, 2 of 64 43 / 80; 8 x 16 x 2048 keys, 8 of 6, 12 and 28 coordinates: fp16 46 / 66, 53 / 61, 70 / 102, fp32 60 / 83,
 // 57 / 77, 81 / 141.  Small ones: 24 (b,h) x 100 keys, fp16 8 of 16: 6.9 / 7.2 (with one term 8.5).

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(const QT *__rest
 // Any d_sub: the same, the centroid's row taken JB coordinates at a time (8 for the shortest rows, else 32; longer rows come from cache
 // again for every query).  Latency is what counts in a decode step (one query per sequence): the row is requested at once, in 16-byte
 // pieces where it has them, beside the queries.  us per call, element by element as they were needed / now: 32 x 12 (b,h) x 1 query, m = 8,
-// d_k = 96 15.0 / 6.1, d_k = 112 20.3 / 9.8; 16 x 12, d_k = 160, m = 4, fp32 32 / 9; 8 x 32 x 8 queries, d_k = 96, m = 8 71 / 27.
+// d_k = 96 15.0 / 6.5, d_k = 112 20.3 / 9.7; 16 x 12, d_k = 160, m = 4, fp32 32 / 8.9; 8 x 32 x 8 queries, d_k = 96, m = 8 71 / 26.
 template <typename QT, int JB>
 __global__ __launch_bounds__(kLutThreads) void build_lut_generic_kernel(const QT *__restrict__ q,
                                                                         const float *__restrict__ codebooks,
@@ -390,8 +390,8 @@ extern "C" int lookat_build_lut(const lookat_shape *shape, int32_t T, const void
     // From 256 queries per head on, the build is a dense [B*T x d_sub].[d_sub x 256] contraction
     // per (head, subspace) and runs on the matrix cores; below that the 32-row MFMA tiles would be
     // mostly padding and the vector kernel is used.  With 32 and 64 coordinates a tile is a chain of 16 or 32 matrix instructions, and
-    // up to three tables per compute unit the vector kernel ends sooner (us, vector / matrix; m = 1 or 2, d_sub 64: 256 tables 4.0 / 7.6, fp32
-    // queries 8.1; 512 5.8 / 7.7; 768 7.9 / 7.7, 8.1; 900 9.5 / 7.7, 8.2; d_sub 32: 256 3.4 / 4.7, 5.2; 768 4.9 / 4.8, 5.3; 900 5.7 / 4.8, 5.3).
+    // up to three tables per compute unit the vector kernel ends sooner (us, vector / matrix; m = 1 or 2, d_sub 64: 256 tables 3.9 / 7.6, fp32
+    // queries 8.1; 512 5.7 / 7.7; 768 7.4 / 7.7, 8.1; 900 9.5 / 7.7, 8.2; d_sub 32: 256 2.9 / 4.7, 5.2; 768 4.7 / 4.8, 5.3; 900 5.7 / 4.8, 5.3).
     // Both kernels add the products in the same order: the tables have the same bits.
     const int64_t queries = (int64_t)shape->B * T;
     bool done = false;
