@@ -318,13 +318,15 @@ static bool launch_build_lut_mfma(const lookat_shape *s, int T, const void *q, c
 
 // Which workgroups follow each other: the queries of one subspace, which go to the eight dies in turn so that every die fetches the subspace's rows
 // (d_sub KB), or the subspaces of the same queries: with m*H a multiple of eight a subspace's rows are then fetched by one die and found there by
-// the next queries.  Else, with rows so short that the tables (a KB a query) are what counts, the first order is up to 4% faster.  us per call, first /
+// the next queries.  With rows below 12 coordinates the tables (a KB a query) are what counts: the first order is up to 4% faster where m*H is no
+// multiple, and with many queries the attention that reads the tables is faster behind it (append, tables and attention of 32 x 32 heads, 300 keys,
+// 8 subspaces of 8, 21.6 / 22.3 us; of 16 x 25 heads 18.8 / 17.7): there up to 16 queries only.  us per table call, first /
 // second: 256 (head, subspace) x 4 queries, d_sub 4 2.5 / 2.5, 8 2.8 / 2.5, 12 4.9 / 3.9, 16 4.7 / 3.0, 20 6.1 / 4.2, 32 7.6 / 5.7; x 32, 4 4.7 / 4.6,
 // 8 5.5 / 4.8, 16 7.2 / 5.9, 32 10.7 / 10.0; x 240, 8 18.3 / 17.2, 16 22.8 / 22.3, 32 39.6 / 38.5; 64 x 128, 40 52.5 / 35.8; 100 x 32, 8 3.3 / 3.4,
 // 16 5.1 / 4.2.  (The grid's last dimension ends at 65535.)
-static bool lut_rows_together(const lookat_shape *s, int64_t blocks)
+static bool lut_rows_together(const lookat_shape *s, int64_t nq, int64_t blocks)
 {
-    return blocks <= 65535 && (s->m * s->H % 8 == 0 || s->d_k / s->m >= 12);
+    return blocks <= 65535 && (s->d_k / s->m >= 12 || ((int64_t)s->m * s->H % 8 == 0 && nq <= 16));
 }
 
 template <typename QT>
@@ -338,7 +340,7 @@ static void launch_build_lut(const lookat_shape *s, int T, const void *q, const 
     while (QB < 16 && (nq / (QB * 2)) * s->m * s->H >= 1024)
         QB *= 2;
     const int64_t blocks = (nq + QB - 1) / QB;
-    const bool together = lut_rows_together(s, blocks);
+    const bool together = lut_rows_together(s, nq, blocks);
     const dim3 grid = row_grid(s, blocks, together);
     dim3 block(kLutThreads);
     const QT *qp = static_cast<const QT *>(q);
