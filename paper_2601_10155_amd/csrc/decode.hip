@@ -151,36 +151,73 @@ __device__ __forceinline__ float uniform_elem<__half>(UniformWords p, int idx)
     return __half2float(__ushort_as_half((unsigned short)((idx & 1) ? (w >> 16) : (w & 0xffffu))));
 }
 
+// ---- the rule ----
 // Squared distance of the encoder (paper Sec. 3.4 "Encoding"), exactly as lookat_encode_keys evaluates it: fp64, ascending coordinates, one
-// rounding per subtract, multiply and add.  x: the sub-vector of a dense row (8-byte aligned), y: the centroid.
-template <typename FT, int DSUB>
-__device__ __forceinline__ double step_exact_distance(const FT *x, const float *y)
+// rounding per subtract, multiply and add.  A row lies over G neighbouring lanes, P coordinates each.  Differences and squares need no order; the
+// additions are one chain, which is handed from lane to lane: after G rounds the last lane has added all of it, and every lane of the G gets that.
+__device__ __forceinline__ double rule_square(float x, float y)
 {
 #pragma clang fp contract(off)
-    constexpr int JB = DSUB < 8 || DSUB == 8 ? 4 : 8;
-    double acc = 0.0;
-#pragma unroll 1
-    for (int j0 = 0; j0 < DSUB; j0 += JB) {
-        float yj[JB];
-        FT xj[JB];
-        __builtin_memcpy(yj, __builtin_assume_aligned(y + j0, 16), sizeof(yj));
-        __builtin_memcpy(xj, __builtin_assume_aligned(x + j0, 8), sizeof(xj));
-#pragma unroll
-        for (int j = 0; j < JB; ++j) {
-            const double diff = (double)step_f32<FT>(xj[j]) - (double)yj[j];
-            const double sq = diff * diff;
-            acc = acc + sq;
-        }
+    const double diff = (double)x - (double)y;
+    return diff * diff;
+}
+// (Values that only a rarely taken branch uses: without this the compiler widens them ahead of the branch and keeps both in registers.)
+__device__ __forceinline__ v4f only_here(v4f v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+template <int G, int J>
+__device__ __forceinline__ double group_broadcast64(double x)      // as group_broadcast, G up to 16
+{
+    if constexpr (G == 1)
+        return x;
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    float lo = __uint_as_float((uint32_t)u), hi = __uint_as_float((uint32_t)(u >> 32));
+    if constexpr (G == 2) {
+        constexpr int kOf = J | J << 2 | (2 + J) << 4 | (2 + J) << 6;
+        lo = dpp_mov<kOf>(lo, lo);
+        hi = dpp_mov<kOf>(hi, hi);
+    } else if constexpr (G > 2) {
+        lo = group_broadcast<G, J>(lo);
+        hi = group_broadcast<G, J>(hi);
     }
-    return acc;
+    return __longlong_as_double((long long)((uint64_t)__float_as_uint(hi) << 32 | __float_as_uint(lo)));
+}
+__device__ __forceinline__ void rule_add(double &acc, const v4f &x, const v4f &y)      // four coordinates more
+{
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        acc = acc + rule_square(x[t], y[t]);
+}
+template <int G, int P>
+__device__ __forceinline__ double rule_sum(const double (&sq)[P], int lane)
+{
+#pragma clang fp contract(off)
+    double acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+        acc = acc + sq[j];
+#pragma unroll 1
+    for (int n = 1; n < G; ++n) {
+        const uint64_t u = (uint64_t)__double_as_longlong(acc);
+        const float lo = __uint_as_float((uint32_t)u), hi = __uint_as_float((uint32_t)(u >> 32));
+        const uint64_t left = (uint64_t)__float_as_uint(dpp_mov<0x111>(hi, hi)) << 32 | __float_as_uint(dpp_mov<0x111>(lo, lo));   // row_shr:1
+        acc = lane % G ? __longlong_as_double((long long)left) : 0.0;
+#pragma unroll
+        for (int j = 0; j < P; ++j)
+            acc = acc + sq[j];
+    }
+    return group_broadcast64<G, G - 1>(acc);
 }
 
 // Encoding the new key, in two steps.  In fp32 a squared distance is off by at most (d_sub + 2) 2^-24 of itself, in whatever order its terms are
 // added (each difference is rounded once, each multiply-add and addition once, all terms are positive), so a centroid whose fp32 distance
 // exceeds the smallest by more than twice that cannot be the argmin.  A wavefront of 64 centroids with one left has its candidate without the
-// fp64 rule, which takes two and a half times the instructions; near and exact ties and NaN (whatever is not provably beyond the limit) are
-// evaluated by the rule.  The four candidates of a subspace are compared the same way after the barrier by the wavefront that scores the new
-// key, one lane each.
+// fp64 rule, which takes two and a half times the instructions; of those that are not provably beyond the limit (near and exact ties, NaN) the
+// repeats of the lowest go, and what is left is evaluated by the rule.  The four candidates of a subspace are compared the same way after the
+// barrier by the wavefront that scores the new key, one lane each.
 // The largest fp32 distance that a centroid may have to be the argmin when the smallest is `least` (twice the error bound, rounded up; the last
 // term for squares below the normal range).  NaN if least is.
 template <int DSUB>
@@ -232,10 +269,15 @@ __device__ __forceinline__ void wave_minima(const float (&x)[N], float (&least)[
     }
 }
 // This wavefront's candidates for subspaces i0 .. i0+GS-1: dist[s] is the lane's fp32 distance to centroid c; all four wavefronts of a subspace
-// hold ascending ranges of centroids, `quarter` says which.
-template <typename FT, int DSUB, int M, int GS>
-__device__ __forceinline__ void step_candidates(const float (&dist)[GS], int i0, int c, int quarter, int lane, const float *cb_head,
-                                                const FT *k_row, uint2 *near_s)
+// hold ascending ranges of centroids, `quarter` says which.  distinct(s, among) drops lanes of `among` whose row repeats the lowest one's, and
+// exact(s, among) gives the rest their distances by the rule, both from the rows in registers: a key that meets ties may meet them in every subspace
+// and every step (zeros, say, where unused centroids kept an initial duplicate), and all wavefronts wait for the table.  us, keys that meet no
+// tie / nine copies of the nearest centroid over the four wavefronts in every subspace / that with the rows read again, subspace after subspace:
+// 32 (b,h) x 600 keys, d_k = 128, m = 16 7.2 / 9.9 / 16.2, m = 2 6.9 / 8.0 / 14.5; 640, d_k = 64, m = 8 13.3 / 17.9 / 26.9; two query heads, 64
+// (b,h), d_k = 64, m = 16 8.4 / 10.9 / 18.5.  (The branch is laid out behind the rest: in line it cost groups of 4 and 8, d_k = 128, m = 2 3%.)
+template <int DSUB, int GS, typename Distinct, typename Exact>
+__device__ __forceinline__ void step_candidates(const float (&dist)[GS], int i0, int c, int quarter, int lane, uint2 *near_s, Distinct distinct,
+                                                Exact exact)
 {
     float least[GS];
     wave_minima<GS>(dist, least, lane);
@@ -245,29 +287,54 @@ __device__ __forceinline__ void step_candidates(const float (&dist)[GS], int i0,
         among[s] = __ballot(!(dist[s] > step_limit<DSUB>(least[s])));
         several |= among[s] & (among[s] - 1);
     }
-    if (several) {                           // the rule, lowest centroid on ties
+    if (__builtin_expect(several != 0, 0)) {       // the rule, lowest centroid on ties
 #pragma unroll
         for (int s = 0; s < GS; ++s)
             if (among[s] & (among[s] - 1)) {
+                among[s] = distinct(s, among[s]);
+                if (!(among[s] & (among[s] - 1)))
+                    continue;
                 const bool mine = among[s] >> lane & 1;
-                double dv[1] = {(double)INFINITY};
-                if (mine)
-                    dv[0] = argmin_value(step_exact_distance<FT, DSUB>(k_row + (i0 + s) * DSUB, cb_head + ((i0 + s) * kCentroids + c) * DSUB), c);
-                const double own = dv[0];
-                dmin_wave<1>(dv);
-                int lowest = mine && own == dv[0] ? c : kCentroids;
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) {
-                    const int other = __shfl_xor(lowest, o);
-                    lowest = other < lowest ? other : lowest;
+                const double by_rule = exact(s, among[s]);
+                const double own = mine ? argmin_value(by_rule, c) : (double)INFINITY;
+                if (__popcll(among[s]) == 2) {
+                    const int a = __builtin_ctzll(among[s]), b = 63 - __builtin_clzll(among[s]);
+                    const uint64_t u = (uint64_t)__double_as_longlong(own);
+                    auto of = [&](int from) {
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, from);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), from);
+                        return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+                    };
+                    const double da = of(a), db = of(b);
+                    const bool first = da < db || (da == db && __builtin_amdgcn_readlane(c, a) < __builtin_amdgcn_readlane(c, b));
+                    among[s] = 1ull << (first ? a : b);
+                } else {
+                    double dv[1] = {own};
+                    dmin_wave<1>(dv);
+                    const bool holds = mine && own == dv[0];
+                    among[s] = __ballot(holds);
+                    if (among[s] & (among[s] - 1)) {
+                        const float lowest = wave_max(holds ? -(float)c : -INFINITY);
+                        among[s] = __ballot(holds && -(float)c == lowest);
+                    }
                 }
-                among[s] = __ballot(lowest == c);
             }
     }
 #pragma unroll
     for (int s = 0; s < GS; ++s)
         if (among[s] >> lane & 1)
             near_s[(i0 + s) * kNearest + quarter] = make_uint2(__float_as_uint(dist[s]), (uint32_t)c);
+}
+// `among` without the lanes whose row repeats that of the lowest of them (a row per lane).
+template <int DSUB>
+__device__ __forceinline__ uint64_t rows_without_repeats(const float (&row)[DSUB], uint64_t among)
+{
+    const int lead = __builtin_ctzll(among);
+    bool same = true;
+#pragma unroll
+    for (int j = 0; j < DSUB; ++j)
+        same &= __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row[j]), lead)) == row[j];
+    return (among & ~__ballot(same)) | 1ull << lead;
 }
 // The new key's codes (four to a word; uniform) after the barrier, for the wavefront that scores position L-1: lane (i, w) holds the candidate of
 // subspace i among centroids 64w .. 64w+63.  They go to the cache and, in the lane that scores that key, in the place of the cached row, which
@@ -288,11 +355,42 @@ __device__ __forceinline__ void step_new_codes(uint32_t (&fresh)[code_words(M)],
     left &= kLanes;
     // (one each: then no subspace has fewer, and all have M together)
     if (__popcll(left) != M) {
-        double dv = (double)INFINITY;
-        if (left >> lane & 1) {
-            const int i = at / kNearest;
-            dv = argmin_value(step_exact_distance<FT, DSUB>(k_row + i * DSUB, cb_head + (i * kCentroids + c) * DSUB), c);
+        // (a candidate's row lies over 16 / M lanes: one round trip for all of it)
+        constexpr int G = kWave / (M * kNearest), P = DSUB / G;
+        const int slot = lane / G;
+        const FT *x = k_row + slot / kNearest * DSUB + lane % G * P;
+        const float *y = cb_head + (slot / kNearest * kCentroids + (int)near_s[slot].y) * DSUB + lane % G * P;
+        auto four = [&](int j, v4f &xj, v4f &yj) {
+            FT e[4];
+            __builtin_memcpy(e, __builtin_assume_aligned(x + j, 8), sizeof(e));
+            xj = v4f{step_f32<FT>(e[0]), step_f32<FT>(e[1]), step_f32<FT>(e[2]), step_f32<FT>(e[3])};
+            yj = *reinterpret_cast<const v4f *>(y + j);
+        };
+        double dv = 0.0;
+        if constexpr (G == 1) {                  // (80 registers: four coordinates at a time)
+            if (left >> lane & 1) {
+#pragma unroll 1
+                for (int j = 0; j < P; j += 4) {
+                    v4f xj, yj;
+                    four(j, xj, yj);
+                    rule_add(dv, xj, yj);
+                }
+            }
+        } else {
+            double sq[P] = {};
+            if (left >> slot & 1) {
+#pragma unroll
+                for (int j = 0; j < P; j += 4) {
+                    v4f xj, yj;
+                    four(j, xj, yj);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        sq[j + t] = rule_square(xj[t], yj[t]);
+                }
+            }
+            dv = __shfl(rule_sum<G, P>(sq, lane), lane % (M * kNearest) * G);
         }
+        dv = left >> lane & 1 ? argmin_value(dv, c) : (double)INFINITY;
         double dm = dmin_dpp<0xB1>(dv);
         dm = dmin_dpp<0x4E>(dm);
         left &= __ballot(dv == dm);
@@ -413,9 +511,51 @@ struct StepTable {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
+    static constexpr uint64_t kFirst = LPW == 1 ? ~0ull : ~0ull / ((1ull << LPW) - 1);      // lanes that hold a row's first coordinates
+    // `among` (a row's bit is that of the lane that has its distance) without the rows that repeat the lowest of them.
+    __device__ __forceinline__ uint64_t without_repeats(int s, uint64_t among, int lane) const
+    {
+        uint64_t keep = 0;
+        v4f lowest = {};
+#pragma unroll
+        for (int u = 0; u < LPW; ++u) {
+            const uint64_t rows = among & kFirst << u;
+            if (rows) {
+                const v4f y = only_here(x[s][u]);
+                uint64_t lead = 0;
+                if (!keep) {
+                    lead = rows & -rows;
+                    const int from = 4 * (__builtin_ctzll(rows) / LPW * LPW + lane % LPW);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        lowest[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(y[t])));
+                }
+                uint64_t same = __ballot(y.x == lowest.x && y.y == lowest.y && y.z == lowest.z && y.w == lowest.w);
+#pragma unroll
+                for (int n = LPW / 2; n >= 1; n /= 2)          // (of all of a row's lanes)
+                    same &= same >> n;
+                keep |= lead | (rows & ~((same & kFirst) << u));
+            }
+        }
+        return keep;
+    }
+    // Distances by the rule of the rows in `among`, in the lanes that have their bits; k: the lane's four coordinates of the new key.
+    __device__ __forceinline__ double exact(const v4f &k, int s, uint64_t among, int lane) const
+    {
+        double d = 0.0;
+#pragma unroll
+        for (int u = 0; u < LPW; ++u)
+            if (among & kFirst << u) {
+                const v4f y = only_here(x[s][u]);
+                const double sq[4] = {rule_square(k.x, y.x), rule_square(k.y, y.y), rule_square(k.z, y.z), rule_square(k.w, y.w)};
+                const double sum = rule_sum<LPW, 4>(sq, lane);
+                d = lane % LPW == u ? sum : d;
+            }
+        return d;
+    }
     // Table entries and, if encode, candidates of the group of subspaces i .. i+GS-1 (g0 = i - i0) for batch entry nb.
     __device__ __forceinline__ void group(const float *stage, int nb, int g0, int i, int quarter, int lane, float *lut_s, uint2 *near_s,
-                                          const float *cb_head, const FT *k_row, bool encode) const
+                                          bool encode) const
     {
         const int c = quarter * kWave + lane % LPW * (kWave / LPW) + lane / LPW;
         const float *mine = stage + 2 * nb * kSlice + g0 * DSUB + 4 * (lane % LPW);
@@ -441,7 +581,11 @@ struct StepTable {
                 }
                 dist[s] = sum_rows<LPW>(p, lane);
             }
-            step_candidates<FT, DSUB, M, GS>(dist, i, c, quarter, lane, cb_head, k_row, near_s);
+            step_candidates<DSUB, GS>(
+                dist, i, c, quarter, lane, near_s, [&](int s, uint64_t among) { return without_repeats(s, among, lane); },
+                [&](int s, uint64_t among) {
+                    return exact(only_here(*reinterpret_cast<const v4f *>(mine + kSlice + s * DSUB)), s, among, lane);
+                });
         }
     }
 };
@@ -689,8 +833,7 @@ __device__ __forceinline__ void step_prologue(const DecodeArgs &a, int bh, int p
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
             table.group(stage, nb, g0, ibase + g0, wave, lane, reinterpret_cast<float *>(reinterpret_cast<char *>(lut_s) + nb * lds_stride),
-                        reinterpret_cast<uint2 *>(reinterpret_cast<char *>(near_s) + nb * lds_stride), cb_head,
-                        k_new + ((int64_t)bh + nb * a.H) * DK, encode);
+                        reinterpret_cast<uint2 *>(reinterpret_cast<char *>(near_s) + nb * lds_stride), encode);
     }
 }
 
@@ -786,7 +929,16 @@ __device__ __forceinline__ void step_prologue_grouped(const DecodeArgs &a, int b
                     }
                 }
             }
-            step_candidates<FT, DSUB, M, GS>(dist, i0, tid, wave, lane, cb_head, k_row, near_s);
+            step_candidates<DSUB, GS>(dist, i0, tid, wave, lane, near_s, [&](int g, uint64_t among) { return rows_without_repeats(frow[g], among); },
+                                      [&](int g, uint64_t) {
+                double d = 0.0;
+#pragma unroll
+                for (int j = 0; j < DSUB; j += 4) {
+                    const v4f k = *reinterpret_cast<const v4f *>(stage + G * kRow + (i0 + g) * DSUB + j);
+                    rule_add(d, only_here(k), only_here(v4f{frow[g][j], frow[g][j + 1], frow[g][j + 2], frow[g][j + 3]}));
+                }
+                return d;
+            });
         }
     }
 }
@@ -836,7 +988,21 @@ __device__ __forceinline__ void step_prologue_heads(const DecodeArgs &a, int bh,
             }
         }
         if (encode)
-            step_candidates<FT, DSUB, M, GS>(dist, i0, tid, wave, lane, cb_head, k_row, near_s);
+            step_candidates<DSUB, GS>(dist, i0, tid, wave, lane, near_s, [&](int g, uint64_t among) { return rows_without_repeats(frow[g], among); },
+                                      [&](int g, uint64_t) {
+                UniformWords key = kg;
+                asm volatile("" : "+s"(key));        // (as only_here: the key is fetched again)
+                double d = 0.0;
+#pragma unroll
+                for (int j = 0; j < DSUB; j += 4) {
+                    v4f k;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        k[t] = uniform_elem<FT>(key, (i0 + g) * DSUB + j + t);
+                    rule_add(d, only_here(k), only_here(v4f{frow[g][j], frow[g][j + 1], frow[g][j + 2], frow[g][j + 3]}));
+                }
+                return d;
+            });
     }
 }
 
@@ -1340,7 +1506,7 @@ __global__ __launch_bounds__(4 * kDecThreads, 4) void decode_step_lone_kernel(co
         table.request_rows(cb_head, i0, quarter, lane);
         __builtin_amdgcn_sched_barrier(0);
         table.stage_words(stage, lane);
-        table.group(stage, 0, 0, i0, quarter, lane, lut_s, near_s, cb_head, p_k_new + (int64_t)bh * DK, k1 == p_L);
+        table.group(stage, 0, 0, i0, quarter, lane, lut_s, near_s, k1 == p_L);
         __syncthreads();
         return;
     }
