@@ -232,12 +232,13 @@ __device__ __forceinline__ int ef_exact_code(const KT *key_sub, const float *cb,
 }
 
 // Squared distance by the exact rule: fp64, one rounding per subtract, multiply and add, coordinates ascending.  (32 of them requested at once: with
-// 16, fills of 32 and 64 coordinates took 1 to 10% longer, with 64 registers spill.  Four lanes to a key with two candidates each instead of
-// eight: 5 to 20% slower from 16 coordinates on, the chain of additions counts and not the round trip.)
+// 16, fills of 32 and 64 coordinates took 1 to 10% longer, with 64 registers spill.  Lengths of 33 to 63 take 16, as the last round also requests what
+// is not there, 64 coordinates for 40 with 32 a round: 250 undecided fp32 keys of 40 18.5 / 13.5 us.  Four lanes to a key with two candidates
+// each instead of eight: 5 to 20% slower from 16 coordinates on, the chain of additions counts and not the round trip.)
 template <typename KT, int DP, bool FULL>
 __device__ __forceinline__ double ef_exact_distance(const KT *key_sub, const float *row, int d_sub)
 {
-    constexpr int JB = DP < 32 ? DP : 32;
+    constexpr int JB = DP < 32 ? DP : (DP == 64 && !FULL ? 16 : 32);
     double acc = 0.0;
     const float *rows[1] = {row};
 #pragma unroll 1
@@ -459,6 +460,10 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                 ef_load_tail(sub, piece(l), d_sub, dst[l]);
         }
     };
+    // The first pair's keys are requested behind the codebook's rows, which everything waits for and L2 holds.  Padded lengths from 17 coordinates on
+    // take the keys first: their rows are more requests than they need, which the keys would wait for.  Rows first / keys first, a few hundred keys
+    // a workgroup: fp32 28 coordinates 1.03 of the time, 40 1.03, 48 1.04, 56 1.00; fp16 24 1.03, 40 1.01; of 5 to 14 0.96 to 1.02.
+    constexpr bool kRowsFirst = FULL || DP <= 16;
     Where here[2] = {}, ahead[2] = {};
     auto fetch_pair = [&](int pair) {
         const uint32_t kb = 2u * (uint32_t)(first + pair);
@@ -468,6 +473,10 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
         fetch_keys(ahead[1], raw[1]);
     };
     int p = wave, pn = wave + kEfWaves;     // this wavefront's pair, and the next one
+    if constexpr (!kRowsFirst) {
+        if (p < mine)
+            fetch_pair(p);
+    }
     if (tid == 0)
         next_s = 2 * kEfWaves;
 
@@ -501,10 +510,12 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                 v[j] = j < d_sub ? row[j] : 0.f;
         }
     }
-    // (the first pair's keys behind the rows, which everything waits for and L2 holds; without a branch, so that the rows can be waited for alone)
-    __builtin_amdgcn_sched_barrier(0);
-    fetch_pair(p < mine ? p : mine - 1);
-    __builtin_amdgcn_sched_barrier(0);
+    // (without a branch, so that the rows can be waited for alone)
+    if constexpr (kRowsFirst) {
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_pair(p < mine ? p : mine - 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     if (owner) {
 #pragma unroll
         for (int j = 0; j < DP; ++j) {

@@ -86,3 +86,24 @@ def test_a_repeated_key_that_is_never_decided(lk, d_sub, dtype, value):
     print(f"d_sub {d_sub} {dtype} {value}: {a:.2f} us decided, {b:.2f} us with one key repeated")
     assert not codes[:, :, N // 2:].any() and torch.equal(codes[:, :, :N // 2].long(), pick[:, :, :N // 2])
     assert b < 2 * a, (a, b)
+
+
+def test_undecided_keys_of_40_coordinates_against_32(lk):
+    """What 250 fp32 keys with two equally near centroids add to a fill: 40 coordinates 2.0 times what 32 add, two rounds of the exact rule with 16
+    requests in the last; 2.8 where the last round requested 32."""
+    H, m, N = 4, 4, 1000
+    added = []
+    for d_sub in (40, 32):
+        g = torch.Generator(device="cuda").manual_seed(d_sub)
+        cb = torch.randn((H, m, 256, d_sub), generator=g, device="cuda").half().float()
+        cb[:, :, 1] = cb[:, :, 0]
+        pick = torch.randint(2, 256, (H, N, m), generator=g, device="cuda")
+        plain = cb[torch.arange(H, device="cuda")[:, None, None], torch.arange(m, device="cuda"), pick].reshape(1, H, N, m * d_sub).contiguous()
+        tied = plain.clone()
+        tied[0, 0, :250, :d_sub] = cb[0, 0, 0] + 0.05 * torch.randn((250, d_sub), generator=g, device="cuda")
+        codes = torch.empty((1, H, N, m), dtype=torch.uint8, device="cuda")
+        a, b = best_us(lambda: lk.lookat_encode_keys(plain, cb, codes_out=codes), lambda: lk.lookat_encode_keys(tied, cb, codes_out=codes))
+        assert not codes[0, 0, :250, 0].any()
+        added.append(b - a)
+    print(f"{added[0]:.2f} us more with 40 coordinates, {added[1]:.2f} us with 32")
+    assert added[0] < 2.35 * added[1], added
