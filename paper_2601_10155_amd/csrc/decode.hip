@@ -1053,52 +1053,48 @@ __device__ __forceinline__ void fold_rows(float (&acc)[8], float *mine, int lane
     }
 }
 
-// Merge of the workgroup's partial results red_s[WAVES][DK + 2] (coordinates, reference, sum of weights): WAVES neighbouring lanes take one
-// wavefront's share each and add across lanes, which is one LDS round trip and a dozen lane moves where a thread per coordinate read 3 WAVES
-// words in turn.  write(j, sum, reference, sum of weights) is called once per coordinate.  With fold_rows, us before / now: 12 fused steps of
-// 12 heads x 1024 keys, d_k = 64, m = 2 79.7 / 77.7, of 32 x 12 x 1024, m = 4 130.5 / 129.4; 32 heads x 8003 keys in ranges, d_k = 128 16.7 / 16.4.
-// (Grouped queries keep a thread per coordinate: they have as many coordinates as threads, or twice as many.)
-template <int W>
-__device__ __forceinline__ float sum_neighbours(float v)
+// Merge of the workgroup's partial results of[WAVES], `stride` words apart (coordinates, reference, sum of weights; DK + 2 words each), by a thread
+// per coordinate.  write(sum, reference, sum of weights)
+template <int DK, int WAVES, typename Write>
+__device__ __forceinline__ void merge_coordinate(const float *of, int stride, int j, Write write)
+{
+    float mx = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w)
+        mx = fmaxf(mx, of[w * stride + DK]);
+    const float m_use = (mx == -INFINITY) ? 0.f : mx;
+    float o = 0.f, zz = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const float wgt = fast_exp2(of[w * stride + DK] - m_use);
+        o = fmaf(wgt, of[w * stride + j], o);
+        zz = fmaf(wgt, of[w * stride + DK + 1], zz);
+    }
+    write(o, mx, zz);
+}
+// The same for the fused steps of 64 coordinates, whose kernels give the same bits: eight neighbouring lanes take one wavefront's share each and add
+// across lanes, one LDS round trip and a dozen lane moves.  12 steps of 12 heads x 1024 keys, m = 2 0.994 of the time; of more than 256 (b,h)
+// 1.01.  (Everywhere else the lane moves cost more than the reads: fused steps of 128 coordinates 1.02 of the time, tables given 1.02 to 1.03, at
+// d_k = 256 and short contexts 1.05.)
+__device__ __forceinline__ float sum_octet(float v)
 {
     v += dpp_mov<0xB1>(v, v);
     v += dpp_mov<0x4E>(v, v);
-    if constexpr (W >= 8)
-        v += dpp_mov<0x141>(v, v);
-    if constexpr (W >= 16)
-        v += dpp_mov<0x140>(v, v);
-    return v;
+    return v + dpp_mov<0x141>(v, v);
 }
-template <int DK, int WAVES, typename Write>
-__device__ __forceinline__ void merge_waves(const float *red_s, int tid, Write write)
+template <typename Write>
+__device__ __forceinline__ void merge_octets(const float *red_s, int tid, Write write)
 {
-    static_assert(WAVES == 4 || WAVES == 8 || WAVES == 16, "a wavefront's share per lane of a quad, an octet or a row");
-    const int w = tid % WAVES;
-    const float *of = red_s + w * (DK + 2);
-    const float mw = of[DK], zw = of[DK + 1];
-    constexpr int kRounds = (DK + kWave - 1) / kWave;     // 64 coordinates at a time
-    float o[kRounds];
-#pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const int j = r * kWave + tid / WAVES;
-        o[r] = of[j < DK ? j : 0];
-    }
-    float mx = mw;
-    mx = fmaxf(mx, dpp_mov<0xB1>(mx, mx));
+    constexpr int kRow = 64 + 2;
+    const float *of = red_s + tid % 8 * kRow;
+    const float mw = of[64], zw = of[65], o = of[tid / 8];
+    float mx = fmaxf(mw, dpp_mov<0xB1>(mw, mw));
     mx = fmaxf(mx, dpp_mov<0x4E>(mx, mx));
-    if constexpr (WAVES >= 8)
-        mx = fmaxf(mx, dpp_mov<0x141>(mx, mx));
-    if constexpr (WAVES >= 16)
-        mx = fmaxf(mx, dpp_mov<0x140>(mx, mx));
+    mx = fmaxf(mx, dpp_mov<0x141>(mx, mx));
     const float wgt = fast_exp2(mw - ((mx == -INFINITY) ? 0.f : mx));
-    const float zz = sum_neighbours<WAVES>(wgt * zw);
-#pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const int j = r * kWave + tid / WAVES;
-        const float sum = sum_neighbours<WAVES>(wgt * o[r]);
-        if (w == 0 && j < DK)
-            write(j, sum, mx, zz);
-    }
+    const float zz = sum_octet(wgt * zw), sum = sum_octet(wgt * o);
+    if (tid % 8 == 0)
+        write(sum, mx, zz);
 }
 
 // FT = void: the table comes from memory (lookat_attend_decode).  FT = __half / float: fused
@@ -1384,47 +1380,28 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     }
     __syncthreads();
 
-    if constexpr (G == 1) {
-        merge_waves<DK, WAVES>(red_s, tid, [&](int j, float o, float mx, float zz) {
-            if (PAD && j >= dk)
-                return;
+    auto write_to = [&](int g, int j) {   // query head of the group, output coordinate
+        return [&, g, j](float o, float mx, float zz) {
             if (a.splits == 1) {
-                a.out[(int64_t)bh * dk + j] = o / zz;
+                a.out[((int64_t)bh * G + g) * dk + j] = o / zz;
             } else {
-                float *dst = a.part + ((int64_t)bh * a.splits + split) * (dk + 2);
+                float *dst = a.part + (((int64_t)bh * G + g) * a.splits + split) * (dk + 2);
                 dst[j] = o;
                 if (j == 0) {
                     dst[dk] = mx;
                     dst[dk + 1] = zz;
                 }
             }
-        });
+        };
+    };
+    if constexpr (FUSED && G == 1 && DK == 64) {
+        merge_octets(red_s, tid, write_to(0, tid / 8));
         return;
     }
-    auto finish = [&](int x) {   // x = (query head of the group, output coordinate)
+    auto finish = [&](int x) {
         const int g = x / DK, j = x % DK;
-        float mx = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w)
-            mx = fmaxf(mx, red_s[(w * G + g) * (DK + 2) + DK]);
-        const float m_use = (mx == -INFINITY) ? 0.f : mx;
-        float o = 0.f, zz = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            const float wgt = fast_exp2(red_s[(w * G + g) * (DK + 2) + DK] - m_use);
-            o = fmaf(wgt, red_s[(w * G + g) * (DK + 2) + j], o);
-            zz = fmaf(wgt, red_s[(w * G + g) * (DK + 2) + DK + 1], zz);
-        }
-        if (a.splits == 1) {
-            a.out[((int64_t)bh * G + g) * dk + j] = o / zz;
-        } else {
-            float *dst = a.part + (((int64_t)bh * G + g) * a.splits + split) * (dk + 2);
-            dst[j] = o;
-            if (j == 0) {
-                dst[dk] = mx;
-                dst[dk + 1] = zz;
-            }
-        }
+        if (!PAD || j < dk)
+            merge_coordinate<DK, WAVES>(red_s + g * (DK + 2), G * (DK + 2), j, write_to(g, j));
     };
     if constexpr (G * DK <= NT) {
         if (tid < G * DK)
@@ -1602,18 +1579,24 @@ __global__ __launch_bounds__(4 * kDecThreads, 4) void decode_step_lone_kernel(co
         mine[DK + 1] = st.z[0];
     }
     __syncthreads();
-    merge_waves<DK, WAVES>(red_s, tid, [&](int j, float o, float mx, float zz) {
-        if (a.splits == 1) {
-            late.out[(int64_t)bh * DK + j] = o / zz;
-        } else {
-            float *dst = late.part + ((int64_t)bh * a.splits + split) * (DK + 2);
-            dst[j] = o;
-            if (j == 0) {
-                dst[DK] = mx;
-                dst[DK + 1] = zz;
+    auto write_to = [&](int j) {
+        return [&, j](float o, float mx, float zz) {
+            if (a.splits == 1) {
+                late.out[(int64_t)bh * DK + j] = o / zz;
+            } else {
+                float *dst = late.part + ((int64_t)bh * a.splits + split) * (DK + 2);
+                dst[j] = o;
+                if (j == 0) {
+                    dst[DK] = mx;
+                    dst[DK + 1] = zz;
+                }
             }
-        }
-    });
+        };
+    };
+    if constexpr (DK == 64)
+        merge_octets(red_s, tid, write_to(tid / 8));
+    else if (tid < DK)
+        merge_coordinate<DK, WAVES>(red_s, DK + 2, tid, write_to(tid));
 }
 
 // Merge of the split ranges: M* = max_s M_s, out = sum_s 2^(M_s-M*) o_s / sum_s 2^(M_s-M*) Z_s.
