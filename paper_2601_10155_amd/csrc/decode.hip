@@ -1283,7 +1283,9 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
     uint32_t fresh_early[code_words(M)] = {};
     const uint32_t first_tile = kb;
     const bool scores_new = FUSED && G > 1 && k1 == (uint32_t)a.L && k0 < k1 && (k1 - 1 - k0) / kTile % WAVES == (uint32_t)wave;
-    constexpr bool kAfterFirst = G >= 4 || DK == 64;      // (two heads at d_k = 128 have no registers left for it)
+    // (Two heads at d_k = 128 have no registers left for that; four at d_k = 64 would take 132, and 128 are what two workgroups share on a compute
+    // unit: 8 x 57 key/value heads x 419 keys, m = 4 13.7 us so, 10.4 with the codes before the first tile.)
+    constexpr bool kAfterFirst = G == 8 || (G == 4) == (DK == 128);
     if constexpr (FUSED && G > 1) {
         if (scores_new && (!kAfterFirst || k1 - 1 - kb < (uint32_t)kTile))
             new_codes(fresh_early);
