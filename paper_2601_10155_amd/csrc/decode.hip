@@ -946,13 +946,8 @@ __device__ __forceinline__ void step_prologue_grouped(const DecodeArgs &a, int b
 // The same on the vector ALU, a multiply-add chain per head: q and k_new are addressed uniformly over the wavefront and become scalar loads
 // through the constant address space, which stay out of the in-order vector-memory queue.  Taken for two heads, where the matrix instruction
 // has no advantage and two workgroups share a compute unit's memory pipe (8 x 4 key/value heads x 4000 keys, d_k = 128, m = 4: 29.9 us two
-// layers, 31.4 with staged queries), and for four heads of fp16 queries at d_k = 128 with 16 or 32 coordinates, where two coordinates come with a
-// scalar word (geometric mean of six shapes against the kernel with fp64 distances for every centroid: 0.99 and 1.03, 0.97 and 0.99 on the
-// matrix cores; everywhere else the matrix cores are ahead: 16 subspaces at d_k = 128 1.17, 1.07 here).
-constexpr bool step_heads_on_vector_alu(int group, int d_k, int m, bool fp32)
-{
-    return group == 2 || (group == 4 && d_k == 128 && (m == 4 || m == 8) && !fp32);
-}
+// layers, 31.4 with staged queries).  Four and eight heads are ahead on the matrix cores: 340 shapes of four heads of fp16 queries at d_k = 128
+// with 16 or 32 coordinates 0.96 of the time on the geometric mean, long contexts of more than 256 workgroups up to 1.01.
 template <typename FT, int DK, int M, int G>
 __device__ __forceinline__ void step_prologue_heads(const DecodeArgs &a, int bh, int tid, int lane, int wave, float *lut_s, uint2 *near_s,
                                                     bool encode)
@@ -1236,7 +1231,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
                 auto first = [&](auto *p) { return reinterpret_cast<decltype(p)>(reinterpret_cast<char *>(p) - hf * kHalfBytes); };
                 step_prologue<FT, DK, M, NB>(a, bh - hf * a.H, hf, lane, wave, first(lut_s), first(red_s), first(near_s), kHalfBytes,
                                              k1 == (uint32_t)a.L);
-            } else if constexpr (step_heads_on_vector_alu(G, DK, M, sizeof(FT) == 4)) {
+            } else if constexpr (G == 2) {
                 step_prologue_heads<FT, DK, M, G>(a, bh, tid, lane, wave, lut_s, near_s, k1 == (uint32_t)a.L);
             } else {
                 step_prologue_grouped<FT, DK, M, G>(a, bh, tid, lane, wave, lut_s, red_s, near_s, k1 == (uint32_t)a.L);
