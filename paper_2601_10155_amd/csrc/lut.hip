@@ -323,10 +323,15 @@ static bool launch_build_lut_mfma(const lookat_shape *s, int T, const void *q, c
 // 8 subspaces of 8, 21.6 / 22.3 us; of 16 x 25 heads 18.8 / 17.7): there up to 16 queries only.  us per table call, first /
 // second: 256 (head, subspace) x 4 queries, d_sub 4 2.5 / 2.5, 8 2.8 / 2.5, 12 4.9 / 3.9, 16 4.7 / 3.0, 20 6.1 / 4.2, 32 7.6 / 5.7; x 32, 4 4.7 / 4.6,
 // 8 5.5 / 4.8, 16 7.2 / 5.9, 32 10.7 / 10.0; x 240, 8 18.3 / 17.2, 16 22.8 / 22.3, 32 39.6 / 38.5; 64 x 128, 40 52.5 / 35.8; 100 x 32, 8 3.3 / 3.4,
-// 16 5.1 / 4.2.  (The grid's last dimension ends at 65535.)
+// 16 5.1 / 4.2.  Few subspaces whose number is no multiple of eight go round the dies in either order, and up to 28 coordinates the first is faster:
+// 20 x 40, 16 3.2 / 3.4, 20 x 100 4.3 / 4.6, 2 x 200 2.7 / 2.8.  (The grid's last dimension ends at 65535.)
 static bool lut_rows_together(const lookat_shape *s, int64_t nq, int64_t blocks)
 {
-    return blocks <= 65535 && (s->d_k / s->m >= 12 || ((int64_t)s->m * s->H % 8 == 0 && nq <= 16));
+    const int d_sub = s->d_k / s->m;
+    const int64_t tables = (int64_t)s->m * s->H;
+    if (blocks > 65535)
+        return false;
+    return d_sub >= 32 || (tables % 8 == 0 ? d_sub >= 12 || nq <= 16 : d_sub >= 12 && tables >= 96);
 }
 
 template <typename QT>

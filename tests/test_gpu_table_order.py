@@ -9,14 +9,15 @@ pytestmark = pytest.mark.gpu
 # (head, subspace) pairs in multiples of eight and not, sub-vectors of 4, 8, 10, 12, 16, 20, 32 and 64 coordinates; one query a workgroup and more;
 # and more workgroups than a grid's last dimension takes
 @pytest.mark.parametrize("d_k,m,H", [(8, 2, 3), (16, 4, 4), (8, 1, 5), (64, 8, 32), (80, 8, 5), (40, 4, 3), (24, 2, 4), (48, 4, 25), (48, 3, 3), (80, 4, 16),
-                                     (160, 8, 32), (32, 1, 7), (128, 4, 32), (64, 1, 3), (128, 2, 4)])
+                                     (160, 8, 32), (64, 4, 25), (80, 4, 25), (48, 3, 31), (32, 1, 7), (128, 4, 32), (64, 1, 3), (128, 2, 4)])
 @pytest.mark.parametrize("B,T", [(1, 1), (5, 1), (3, 11), (255, 1)])
 def test_either_order(d_k, m, H, B, T):
     check(d_k, m, H, B, T)
 
 
-def test_more_workgroups_than_the_last_dimension_takes():
-    check(24, 1, 1, 1, 65536 * 16 + 5)
+@pytest.mark.parametrize("d_sub", [24, 40])
+def test_more_workgroups_than_the_last_dimension_takes(d_sub):
+    check(d_sub, 1, 1, 1, 65536 * 16 + 5)
 
 
 def check(d_k, m, H, B, T):
