@@ -50,7 +50,7 @@ constexpr float kPsLoScale = 2048.f;
     const float *__restrict__ p_codebooks /* [H, m, 256, d_sub] */,                                                       \
         const uint8_t *__restrict__ p_codes /* (bh, l, i) at bh*code_stride + l*m + i */, int64_t p_code_stride, int64_t p_L, \
         int p_H, uint32_t p_per_head /* workgroups */, uint32_t p_shares /* per (head, query tile) */,                    \
-        uint32_t p_blocks /* of a wavefront */, uint32_t p_rest /* blocks left over: see blk0 */,                                   \
+        uint32_t p_blocks /* of a wavefront */, uint32_t p_rest /* the first so many have one more */,                    \
         uint32_t p_blocks_per_bh /* 32-key blocks */, const PrefillShortLate late
 struct PrefillShortLate {
     const void *q;            // [BH, T, d_k] fp16 or fp32
@@ -174,13 +174,11 @@ __global__ __launch_bounds__(kPsThreads, 4) void score_prefill_short_kernel(LOOK
     const int n = lane & 15, kg = lane >> 4;
 
     // ---- this wavefront's blocks, and the codes of the next one (key n of each half, in every lane group) ----
-    // Blocks that do not come out go to the first wavefronts of every workgroup, as many in each and one more in the first workgroups: a compute
-    // unit's wavefronts take turns at its LDS, and a workgroup of those with one more is what the launch waits for (to the first wavefronts
-    // of the launch instead: 1 x 16 heads x 18 queries x 2085 keys, d_k = 128, m = 16 13.4 / 15.2 us).
-    const uint32_t most = p_rest % kPsWaves, over = p_rest / kPsWaves, longer = most + (share < over ? 1u : 0u);
-    const int blk0 = (int)((share * kPsWaves + (uint32_t)wave) * p_blocks + share * most + (share < over ? share : over) +
-                           ((uint32_t)wave < longer ? (uint32_t)wave : longer));
-    const int blk1 = blk0 + (int)(p_blocks + ((uint32_t)wave < longer ? 1u : 0u));
+    // Wavefront by wavefront over the workgroups of a head, so that the blocks that do not come out, which go to the first parts, are as many in every
+    // workgroup and one more in the first: a compute unit's wavefronts take turns at its LDS, and a workgroup of those with one more is what the
+    // launch waits for (workgroup by workgroup: 1 x 16 heads x 18 queries x 2085 keys, d_k = 128, m = 16 13.4 / 15.2 us).
+    const uint32_t part = (uint32_t)wave * p_shares + share;
+    const int blk0 = (int)(part * p_blocks + (part < p_rest ? part : p_rest)), blk1 = blk0 + (int)(p_blocks + (part < p_rest ? 1u : 0u));
     int b = (int)((uint32_t)blk0 / p_blocks_per_bh), lb = blk0 - b * (int)p_blocks_per_bh;       // the block's batch entry and number within it
     constexpr int kCodeWords = (M + 3) / 4;
     uint32_t ahead[2][kCodeWords];
@@ -579,8 +577,7 @@ bool launch_prefill_short(const lookat_shape *s, int T, int64_t L, const void *q
     a.blocks_per_bh = (uint32_t)o.blocks_per_bh;
     const int64_t wavefronts = o.shares * kPsWaves;
     a.blocks = (uint32_t)(s->B * o.blocks_per_bh / wavefronts);
-    const int64_t rest = s->B * o.blocks_per_bh % wavefronts;
-    a.rest = (uint32_t)(rest / o.shares + rest % o.shares * kPsWaves);
+    a.rest = (uint32_t)(s->B * o.blocks_per_bh % wavefronts);
 #define LOOKAT_PS_CASE(DK_, M_)                                                                              \
     if (s->d_k == DK_ && s->m == M_) {                                                                       \
         if constexpr (DK_ == 128) {                                                                          \
