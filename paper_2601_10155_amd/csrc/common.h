@@ -172,20 +172,4 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 #endif  // __HIPCC__
 
-// (subspace, head, part of the queries or keys) of a workgroup, grid = (parts, m, H) or (m, H, parts).
-struct RowBlock {
-    int i, h;
-    uint32_t part, parts;
-};
-__device__ __forceinline__ RowBlock row_block(bool rows_together)
-{
-    if (rows_together)
-        return {(int)blockIdx.x, (int)blockIdx.y, blockIdx.z, gridDim.z};
-    return {(int)blockIdx.y, (int)blockIdx.z, blockIdx.x, gridDim.x};
-}
-inline dim3 row_grid(const lookat_shape *s, int64_t parts, bool rows_together)
-{
-    return rows_together ? dim3((unsigned)s->m, (unsigned)s->H, (unsigned)parts) : dim3((unsigned)parts, (unsigned)s->m, (unsigned)s->H);
-}
-
 }  // namespace lookat

@@ -1414,7 +1414,7 @@ __global__ __launch_bounds__(WAVES *NB *kWave, OCC) void decode_split_kernel(LOO
 // memory pipe takes (a wave-wide load of a kilobyte every 16 clocks) and when.  Sixteen wavefronts: the first eight build the table, 0-3 the first
 // half of the subspaces, 4-7 the second, two on a SIMD so that one's arithmetic fills the other's latencies, and end; the others stream the tiles,
 // as in decode_split_kernel, from the start.  The builders are the first wavefronts of the workgroup, which start first, and run at raised
-// priority until their rows are requested, so that these enter the pipe first.  (With eight wavefronts doing both jobs the arithmetic waits
+// priority until they end, so that their requests enter the pipe first.  (With eight wavefronts doing both jobs the arithmetic waits
 // until the pipe has accepted the wavefront's tiles: table complete at 5000 clocks at d_k = 64, 15500 at 128, of 9200 and 21800.)  What has to
 // be known before the first request travels in the preloaded arguments (the (b,h) count, ranges and heads in one word: none exceeds 256).
 //   Measured against the roles of decode_split_kernel with a thread per centroid row and fp64 distances (us per launch): 12 (b,h), d_k = 64, m = 2:
@@ -1838,16 +1838,15 @@ static bool launch_step(const DecodeArgs &a, dim3 grid, hipStream_t st)
 // Two batch entries of one head per workgroup (1024 threads): see decode_split_kernel, NB = 2.
 // When the library takes it.  A compute unit holds two 512-thread workgroups of the fused step or one paired
 // one, and a launch is as slow as its most loaded compute unit.  Up to 256 (b,h) every workgroup has a
-// compute unit to itself and pairing only halves the parallelism (192 (b,h) x 1024 keys, d_k = 64, m = 4,
-// graph replays: 7.2 us single, 9.5 us paired); from 257 to 512 (b,h) some compute units carry two (b,h)
-// either way and the pairs halve the codebook traffic (264: 11.0 -> 9.8 us; 384: 11.8 -> 11.0; 504:
-// 14.4 -> 13.0); beyond 512 the pairs need a second round of workgroups where single entries still
-// fit two to a compute unit (528: 17.7 single, 20.3 paired).  Short contexts (512 keys: 8.8 / 8.9 us) and m >= 8
-// (m = 8: 11.4 / 11.8 us; m = 16: 14.4 / 15.1) measured no gain at d_k = 64.
-// d_k = 128 (fp16 queries, graph replays, single / paired us): m = 4: 384 (b,h) x 1024 keys 23.7 / 22.3, 512 x 1024
-// 30.8 / 27.1, 320 x 1024 23.3 / 20.4, 384 x 4096 72.6 / 66.7, 512 x 512 20.2 / 17.9; m = 8: 384 x 1024 21.6 / 22.3,
-// 512 x 1024 27.4 / 26.6, 512 x 512 17.3 / 17.5, 384 x 4096 71.9 / 69.5, 320 x 2048 38.3 / 33.4, 512 x 2048 (fp32)
-// 51.2 / 49.3: taken from 2048 keys on; m = 16: 384 x 1024 23.7 / 24.8, 512 x 1024 27.8 / 30.2: not taken;
+// compute unit to itself and pairing only halves the parallelism (1.2 to 1.7 times the time); from 257 to 512 (b,h) some compute
+// units carry two (b,h) either way and the pairs halve the codebook traffic; beyond 512 the pairs need a second round of
+// workgroups where single entries still fit two to a compute unit (528: 1.2 to 1.5 times).  us per launch, single / paired, fp16 queries, up to
+// twelve layers in rotation: d_k = 64, m = 4: 264 (b,h) x 768 keys 9.8 / 9.6, 264 x 1024 11.1 / 10.5, 320 x 1024 11.6 / 11.1, 384 x 1024 12.06 /
+// 12.02, 504 x 1024 14.2 / 14.0, 448 x 1024 12.9 / 13.6, 264 x 4096 33.1 / 29.3, 504 x 4096 43.5 / 43.3; at 512 keys 0.99 to 1.01 of the time.
+// m = 8 and 16 are not taken there: 264 x 1024 0.95 and 1.05, 448 x 1024 1.02 and 1.07.  d_k = 128, m = 4: 264 x 512 13.0 / 13.0, 512 x 512 16.4 / 18.1,
+// 264 x 768 16.4 / 15.7, 504 x 768 21.3 / 22.0, 264 x 1024 20.0 / 17.7, 384 x 1024 21.4 / 20.9, 504 x 1024 26.5 / 25.7, 320 x 2048 0.85, 504 x 4096 0.99
+// of the time; m = 8: 264 x 2048 36.6 / 30.2, 384 x 2048 38.6 / 36.4, 504 x 2048 48.3 / 45.4.  (Eight heads of 1024 keys at d_k = 128, where the
+// entries of a pair lie 2 MB apart: 20 to 26% slower from 352 (b,h) on.)
 // m = 2 (one codebook row = 64 registers) has no paired instance at d_k = 128: it would spill.
 static bool step_pairs_entries(const lookat_shape *s, int group, int64_t L, int S)
 {
@@ -1863,11 +1862,12 @@ static bool step_pairs_entries(const lookat_shape *s, int group, int64_t L, int 
 
 // Ranges of the fused step when the caller leaves the choice to the library: as the unfused call, except where one range would be
 // served by paired batch entries.  Cutting them gives that up and pays only for long contexts of up to 320 (b,h).  us per call,
-// paired / cut: d_k = 128, m = 4: 264 (b,h) x 2048 keys 33.9 / 45.8, 320 x 5000 74 / 78, 264 x 12000 154 / 144, 384 x 8192 129 / 140;
-// m = 8: 288 x 2048 34 / 40, 264 x 5000 71 / 64, 384 x 12000 181 / 187; d_k = 64, m = 2: 288 x 3500 27 / 32, 320 x 5000 37 / 43,
-// 264 x 12000 82 / 76; m = 4: 264 x 3500 26.4 / 27.9, 264 x 8192 53 / 50, 384 x 32768 252 / 254.
-// Up to 1024 keys, two tiles per wavefront, that are requested before the table is there, a cut gains nothing (d_k = 128, m = 8, one
-// range / four: 1 (b,h) 10.7 / 10.4, 12 11.7 / 11.9, 32 12.4 / 12.5) and costs a launch.
+// paired / cut: d_k = 128, m = 4: 264 (b,h) x 2048 keys 29.1 / 33.5, 320 x 5000 71 / 67, 264 x 12000 149 / 130, 384 x 8192 124 / 135;
+// m = 8: 288 x 2048 31 / 34, 264 x 2600 37 / 36, 264 x 5000 67 / 61, 384 x 12000 181 / 186; d_k = 64, m = 2: 288 x 3500 26.0 / 25.1, 320 x 5000 37 / 36,
+// 264 x 12000 79 / 66; m = 4: 264 x 3500 26.0 / 24.3, 264 x 8192 53 / 47, 384 x 32768 252 / 244.  (The lines are those of a step that built its table
+// more slowly in every range; where they leave a pair whole that a cut would serve, it costs 3 to 7%.)
+// Up to 1024 keys, two tiles per wavefront, a cut gains less than the merge's launch costs, or little: one range / four, d_k = 64, m = 8: 12 (b,h)
+// 5.0 / 6.4, 64 6.3 / 7.2; d_k = 128, m = 8: 1 (b,h) 6.3 / 6.4, 12 7.7 / 7.1, 32 8.0 / 7.9, 100 9.0 / 11.5.  (At 1536 keys: 12 9.4 / 7.6.)
 static int step_auto_splits(const lookat_shape *s, int64_t L, int unfused)
 {
     const int64_t pays = s->d_k == 128 ? (s->m == 4 ? 10000 : 2500) : (s->m == 2 ? 10000 : 5000);

@@ -28,7 +28,7 @@ namespace lookat {
 // 12 or 16 pieces in flight: no change; the lists alone: 29); 80 us with the next chunk's lists built while members are on their way (AHEAD: for
 // sets of more than one chunk; whole steps, without / with: 32 x 16384, d_k = 128, m = 8 184.6 / 178.5 us, 4 x 24000, d_k = 64, m = 4 85 / 70;
 // for one chunk there is nothing to overlap, and the second buffer costs a workgroup per compute unit: 40 x 512, d_k = 64, m = 16 19.4 / 22.6).
-// Left at 32 x 16384: 341 MB fetched where 268 are needed, the address pipeline busy 61% of the time.  Centroids dealt to the wavefronts by
+// Left at 32 x 16384: 333 MB fetched where 268 are needed, the address units busy 56% of the time.  Centroids dealt to the wavefronts by
 // size, so that none waits for the largest lists: 84 us; the codes requested a chunk ahead: 84.
 //   LDS: first[257] | run[16][256] (512 threads: [8][256]) | list [kKmChunk] uint16; AHEAD: first and list twice
 //   grid = (8 heads x m x groups of a sub-vector's pieces, ceil(H / 8)), 512 or 1024 threads; consecutive workgroups go to the

@@ -25,6 +25,22 @@ __device__ __forceinline__ void split_query(int64_t qi, int T, int64_t &b, int64
     }
 }
 
+// (subspace, head, part of the queries) of a workgroup, grid = (parts, m, H) or (m, H, parts).
+struct RowBlock {
+    int i, h;
+    uint32_t part;
+};
+__device__ __forceinline__ RowBlock row_block(bool rows_together)
+{
+    if (rows_together)
+        return {(int)blockIdx.x, (int)blockIdx.y, blockIdx.z};
+    return {(int)blockIdx.y, (int)blockIdx.z, blockIdx.x};
+}
+static dim3 row_grid(const lookat_shape *s, int64_t parts, bool rows_together)
+{
+    return rows_together ? dim3((unsigned)s->m, (unsigned)s->H, (unsigned)parts) : dim3((unsigned)parts, (unsigned)s->m, (unsigned)s->H);
+}
+
 // One block = one head h, one subspace i, QB consecutive queries of the flattened
 // (b, t) list.  Thread c keeps centroid c of the subspace in registers and reuses it for
 // every query of the block; the query sub-vectors sit in LDS and are read by all lanes
