@@ -460,10 +460,11 @@ __global__ __launch_bounds__(THREADS, (DP == 4 ? 3 : FINE && DP == 64 ? 1 : 2)) 
                 ef_load_tail(sub, piece(l), d_sub, dst[l]);
         }
     };
-    // The first pair's keys are requested behind the codebook's rows, which everything waits for and L2 holds.  Padded lengths from 17 coordinates on
-    // take the keys first: their rows are more requests than they need, which the keys would wait for.  Rows first / keys first, a few hundred keys
-    // a workgroup: fp32 28 coordinates 1.03 of the time, 40 1.03, 48 1.04, 56 1.00; fp16 24 1.03, 40 1.01; of 5 to 14 0.96 to 1.02.
-    constexpr bool kRowsFirst = FULL || DP <= 16;
+    // The first pair's keys are requested behind the codebook's rows, which everything waits for and L2 holds.  Padded lengths take the keys first:
+    // their rows are more requests than they need (whole pieces past the end, or coordinate by coordinate), which the keys would wait for.  1800
+    // drawn fills of nine padded lengths, rows first / keys first against one order for all: geometric means 0.98 / 0.98, at worst 1.14 (640 (head,
+    // subspace) pairs x 76 fp32 keys of 6) / 1.04; 40 and 48 coordinates, fp32, 1.04 / 1.00.
+    constexpr bool kRowsFirst = FULL;
     Where here[2] = {}, ahead[2] = {};
     auto fetch_pair = [&](int pair) {
         const uint32_t kb = 2u * (uint32_t)(first + pair);
